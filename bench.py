@@ -324,7 +324,7 @@ def apply_sizes(torch):
 def fused_sizes(torch):
     """The fused CG step (FP32, one load case) on the two larger grids,
     timed as in the headline roofline: HIP events around solves of 41 and 9
-    steps; HBM fraction of the same algorithmic bytes (11*3N*4 + N + 4E)."""
+    steps; HBM fraction of the same algorithmic bytes (9*3N*4 + N + 4E)."""
     import synth
     from paper_2204_06204_amd.grid import Grid
     out = {}
@@ -332,7 +332,7 @@ def fused_sizes(torch):
         p = synth.config(name)
         g = Grid.from_problem(p, max_rhs=1)
         t = fused_step_timing(g, p, torch, reps=5)
-        nbytes = 11 * p.ndof * 4 + p.N + 4 * p.E
+        nbytes = 9 * p.ndof * 4 + p.N + 4 * p.E
         out[name] = {"us": t * 1e6, "hbm_frac": nbytes / t / 1e9 / HBM_PEAK_GBS, "bytes": nbytes,
                      "grid": [p.nx, p.ny, p.nz]}
         g.close()
@@ -564,18 +564,18 @@ def main():
     N = ndof // 3
     bytes32 = 2 * ndof * 4 + E * 4          # read u, write y, read one density per element
     bytes64 = 2 * ndof * 8 + E * 8
-    # fused CG step: read x, r, p, s, w, D^-1 and write x, r, p, s, w (3N floats
+    # fused CG step: read x, r, p, s, D^-1 and write x, r, p, s (3N floats
     # each), read the mask byte per node and one density per element
-    bytes_fused = 11 * ndof * 4 + N + E * 4
+    bytes_fused = 9 * ndof * 4 + N + E * 4
     achieved = bytes_fused / t_fused / 1e9
     traffic = measured_traffic("k_apply<float, 1, 3, false>", "outer_step_pmc.json")
     # algorithmic bytes of one outer iteration (FP32, m inner steps), kernel by kernel
     m = p.inner_steps
     bytes_outer = (2 * E * 4                                    # filter, in the final pass below: 1/Hs in, rho out
                    + 5 * ndof * 4 + N + E * 4                   # residual: u, f in; r, z, D^-1 out
-                   + 3 * ndof * 4 + N + E * 4                   # step 0 product: z, r in; w out
+                   + 3 * ndof * 4 + N + E * 4                   # step 0 product: p, D^-1 in; s out
                    + (m - 1) * bytes_fused                      # fused steps
-                   + 8 * ndof * 4 + N + 3 * E * 4               # last step + sensitivity: x r p s w D^-1 f in, x out; rho, 1/Hs in, g out
+                   + 6 * ndof * 4 + N + 3 * E * 4               # last step + sensitivity: x r p s f in, x out; rho, 1/Hs in, g out
                    + 3 * E * 4                                  # filter transpose with the step: g, x in, y out
                    + 2 * E * 4                                  # projection: one or two working passes
                    + 3 * E * 4)                                 # final projection pass: y, x_old in, x out (and the filter's x)
@@ -637,7 +637,7 @@ def main():
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
                      "kernel": "k_apply<float, 1, CGF> (fused Jacobi-PCG step, 7 of the 8 steps of an "
-                               "outer iteration), algorithmic bytes 11*3N*4 + N + E*4 = "
+                               "outer iteration), algorithmic bytes 9*3N*4 + N + E*4 = "
                                f"{bytes_fused} per launch, {t_fused * 1e6:.2f} us per launch"},
         "fused_step_sizes": fsizes,
         "outer_roofline": {"bytes_per_iter": bytes_outer, "ceiling_iter_s": HBM_PEAK_GBS * 1e9 / bytes_outer,

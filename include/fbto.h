@@ -180,9 +180,9 @@ fbto_status_t fbto_apply_K(fbto_grid_t g, fbto_prec_t prec, const void* rho_phys
 
 /* Low-level refinement of u towards K(rho_phys) u = f (Alg. 1 / 3 low-level
  * line), `steps` steps of `method` from the warm start in u, per RHS.
- * PCG_JACOBI runs the textbook preconditioned CG recurrence rearranged as in
- * Chronopoulos and Gear (one reduction phase per step; same iterates in
- * exact arithmetic).
+ * PCG_JACOBI runs the textbook preconditioned CG recurrence with beta from
+ * the products r.z, p.Kp and Kp.D^-1 Kp of the same step (one reduction phase
+ * per step; same iterates in exact arithmetic).
  * KRYLOV is ONE low-level step of Alg. 3 with the Krylov preconditioner of
  * Eq. LSP (Sec. 4.1), of degree D = `steps` (0 .. 1000):
  *   u <- u - omega M^-1 (K u - f),  M^-1 b = sum_{i<=D} c_i K^i b,

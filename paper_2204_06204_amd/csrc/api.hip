@@ -157,10 +157,9 @@ fbto_status_t ensure_vecs(fbto_grid_s* g) {
     HIP_TRY(hipMalloc(&V.r[b], nd * sizeof(T)));
     HIP_TRY(hipMalloc(&V.p[b], nd * sizeof(T)));
     HIP_TRY(hipMalloc(&V.s[b], nd * sizeof(T)));
-    HIP_TRY(hipMalloc(&V.w[b], nd * sizeof(T)));
   }
   HIP_TRY(hipMalloc(&V.x1, nd * sizeof(T)));
-  HIP_TRY(hipMalloc(&V.q, nd * sizeof(T)));
+  HIP_TRY(hipMalloc(&V.x2, nd * sizeof(T)));
   HIP_TRY(hipMalloc(&V.invD, g->geo.ndof * sizeof(T)));
   HIP_TRY(hipMalloc(&V.rho, E * sizeof(T)));
   HIP_TRY(hipMalloc(&V.ge, E * sizeof(T)));
@@ -182,8 +181,8 @@ fbto_status_t ensure_sort(fbto_grid_s* g) {
 }
 
 void free_vecs(Vecs& V) {
-  void* ps[] = {V.r[0], V.r[1], V.p[0], V.p[1], V.s[0], V.s[1], V.w[0], V.w[1], V.x1, V.q,
-                V.invD, V.rho, V.ge, V.gx, V.y, V.Hs};
+  void* ps[] = {V.r[0], V.r[1], V.p[0], V.p[1], V.s[0], V.s[1], V.x1, V.x2, V.invD,
+                V.rho, V.ge, V.gx, V.y, V.Hs};
   for (void* p : ps)
     if (p) (void)hipFree(p);
   V = Vecs{};
@@ -231,11 +230,10 @@ void drop_extra(fbto_grid_s* g) {
   }
 }
 
-// Jacobi-PCG on K(rho) x = f from the warm start x, `steps` steps in the
-// Chronopoulos-Gear arrangement (one apply and one vector kernel per step,
-// one reduction phase).  rtol > 0 stops early (checked on the host every 32
-// steps).  f_dot: also leave the f.x partials (slot DOT) after the last
-// step.  Returns the partial counts the finish kernel needs.
+// Jacobi-PCG on K(rho) x = f from the warm start x, `steps` steps with one
+// reduction phase each (k_cg_step).  rtol > 0 stops early (checked on the
+// host every 64 steps).  f_dot: also leave the f.x partials (slot DOT) after
+// the last step.  Returns the partial counts the finish kernel needs.
 struct CgCounts {
   int r, fn;
   int dot;  // partials of f . x (final vector step, or the dot kernel)
@@ -247,12 +245,15 @@ fbto_status_t pcg_run(fbto_grid_s* g, const T* rho, const T* f, T* x, int nrhs, 
                       const T* sens_hsi = nullptr, bool* sens_done = nullptr) {
   Vecs& V = vecs<T>(g);
   T* invD = (T*)V.invD;
-  T* z = (T*)V.q;
-  CgSet<T> set[2] = {{x, (T*)V.r[0], (T*)V.p[0], (T*)V.s[0], (T*)V.w[0]},
-                     {(T*)V.x1, (T*)V.r[1], (T*)V.p[1], (T*)V.s[1], (T*)V.w[1]}};
-  int nb_a = 0, nb_v = 0;
-  HIP_TRY(launch_resid_diag<T>(g, rho, x, f, set[0].r, invD, z, nrhs, st, &nb_a));
-  CgCounts cn{nb_a, nb_a, vec_blocks(g->geo.ndof)};
+  // the iterate of step k: the caller's vector (k = 0), then x1 and x2 in turn
+  auto set_of = [&](int k) {
+    return CgSet<T>{k == 0 ? x : (T*)((k & 1) ? V.x1 : V.x2), (T*)V.r[k & 1], (T*)V.p[k & 1], (T*)V.s[k & 1]};
+  };
+  const CgSet<T> set0 = set_of(0);
+  int nb_r = 0, nb_a = 0, nb_v = 0;
+  // r = f - K x and the first direction p = z = D^-1 r
+  HIP_TRY(launch_resid_diag<T>(g, rho, x, f, set0.r, invD, set0.p, nrhs, st, &nb_r));
+  CgCounts cn{nb_r, nb_r, vec_blocks(g->geo.ndof)};
   if (steps == 0) {
     if (f_dot) HIP_TRY(launch_dot<T>(g, f, x, nrhs, st));
     *cn_out = cn;
@@ -266,54 +267,43 @@ fbto_status_t pcg_run(fbto_grid_s* g, const T* rho, const T* f, T* x, int nrhs, 
     for (int R = 0; R < nrhs; ++R) done = done && host.done[R] != 0.0;
     return FBTO_OK;
   };
-  // step 0's product w = K z from the residual's z
-  HIP_TRY(launch_apply_cg<T>(g, rho, z, set[0].r, set[0].w, nrhs, 0, st, &nb_a));
-  int k = 0;
-  // voxel grids: fused steps (both precisions); plane grids: unfused
+  // step 0's product s = K p
+  HIP_TRY(launch_apply_cg<T>(g, rho, set0.p, invD, set0.s, nrhs, 0, st, &nb_a));
+  CgCnt pc{nb_r, nb_a, nb_r};
+  // voxel grids: fused steps (the update of step k and the product of step
+  // k + 1 in one pass); plane grids: unfused (vector update, then the product)
   const bool fused = g->dim == 3;
-  if (fused) {
-    // fused steps: the update of step k and the product of step k + 1 in one pass
-    for (; k + 1 < steps; ++k) {
-      HIP_TRY(launch_cg_fused<T>(g, rho, set[k & 1], set[(k + 1) & 1], invD, nrhs, k, nb_a, cn.fn, rtol, st,
-                                 &nb_a));
-      if (rtol > 0.0 && (k + 2) % 64 == 0 && k + 2 < steps) {
-        bool done = false;
-        if (fbto_status_t e = all_done(done)) return e;
-        if (done) {
-          ++k;
-          break;
-        }
-      }
+  int k = 0;
+  for (; k + 1 < steps; ++k) {
+    if (fused) {
+      HIP_TRY(launch_cg_fused<T>(g, rho, set_of(k), set_of(k + 1), invD, nrhs, k, pc, rtol, st, &nb_a));
+      pc.gam = pc.apply = nb_a;
+    } else {
+      HIP_TRY(launch_cg_step<T>(g, x, x, set0.r, set0.s, set0.p, invD, nullptr, nrhs, k, false, pc, rtol, st, &nb_v));
+      HIP_TRY(launch_apply_cg<T>(g, rho, set0.p, invD, set0.s, nrhs, k + 1, st, &nb_a));
+      pc.gam = nb_v;
+      pc.apply = nb_a;
     }
-  } else {
-    // unfused steps (plane grids): vector update, then the next product
-    for (; k + 1 < steps; ++k) {
-      HIP_TRY(launch_cg_step<T>(g, x, x, set[0].r, z, z, set[0].w, set[0].p, set[0].s, invD, nullptr, nrhs, nb_a,
-                                cn.fn, k, rtol, st, &nb_v));
-      HIP_TRY(launch_apply_cg<T>(g, rho, z, set[0].r, set[0].w, nrhs, k + 1, st, &nb_a));
-      if (rtol > 0.0 && (k + 2) % 64 == 0 && k + 2 < steps) {
-        bool done = false;
-        if (fbto_status_t e = all_done(done)) return e;
-        if (done) {
-          ++k;
-          break;
-        }
+    if (rtol > 0.0 && (k + 2) % 64 == 0 && k + 2 < steps) {
+      bool done = false;
+      if (fbto_status_t e = all_done(done)) return e;
+      if (done) {
+        ++k;
+        break;
       }
     }
   }
   // last vector update of step k, into the caller's x; with one RHS and a
-  // sensitivity wanted, fused with it
-  const CgSet<T>& cur = set[fused ? (k & 1) : 0];
-  // The fused kernel reads x at halo nodes while their owners store x', so it
-  // may only run when its input and output are different buffers: after an
-  // odd number of fused steps, when the input is the second set.
+  // sensitivity wanted, fused with it.  The fused kernel reads x at halo
+  // nodes while their owners store x', so it needs the iterate in another
+  // buffer (one fused step or more before it).
+  const CgSet<T> cur = fused ? set_of(k) : set0;
   if (sens && nrhs == 1 && cur.x != x) {
-    HIP_TRY(launch_cg_sens<T>(g, rho, cur, x, invD, f_dot ? f : nullptr, sens, sens_hsi, k, nb_a, cn.fn, rtol, st,
-                              &nb_v));
+    HIP_TRY(launch_cg_sens<T>(g, rho, cur, x, f_dot ? f : nullptr, sens, sens_hsi, k, pc, rtol, st, &nb_v));
     if (sens_done) *sens_done = true;
   } else {
-    HIP_TRY(launch_cg_step<T>(g, cur.x, x, cur.r, nullptr, nullptr, cur.w, cur.p, cur.s, invD,
-                              f_dot ? f : nullptr, nrhs, nb_a, cn.fn, k, rtol, st, &nb_v));
+    HIP_TRY(launch_cg_step<T>(g, cur.x, x, cur.r, cur.s, cur.p, invD, f_dot ? f : nullptr, nrhs, k, true, pc, rtol, st,
+                              &nb_v));
   }
   cn.r = nb_v;
   cn.dot = nb_v;
@@ -336,7 +326,7 @@ template <typename T>
 fbto_status_t residual_norms(fbto_grid_s* g, const T* rho, const T* u, const T* f, T* r, const T* invD, int nrhs,
                              hipStream_t st) {
   int nb = 0;
-  HIP_TRY(launch_resid<T>(g, rho, u, f, r, invD, (T*)vecs<T>(g).q, nrhs, st, &nb));
+  HIP_TRY(launch_resid<T>(g, rho, u, f, r, invD, (T*)vecs<T>(g).p[0], nrhs, st, &nb));
   HIP_TRY(launch_pcg_finish(g, nrhs, nb, nb, nullptr, 0, 0, 0, st));
   return FBTO_OK;
 }
@@ -358,14 +348,14 @@ fbto_status_t relax_run(fbto_grid_s* g, const T* rho, const T* f, T* u, int nrhs
 // One low-level step of Alg. 3 with the Krylov preconditioner of degree D
 // (Eq. LSP), per RHS: u <- u + damp * (u_D - u), where u_D minimises the
 // residual over u + span{r, ..., K^D r} (MINRES, D + 1 iterations; see
-// k_minres).  Workspace: w[0] (products), r[0..1] (Lanczos vectors), p[0..1]
-// (MINRES directions).
+// k_minres).  Workspace: s[0..1] (products), r[0..1] and x1 (Lanczos vectors),
+// p[0..1] (MINRES directions).
 template <typename T>
 fbto_status_t krylov_run(fbto_grid_s* g, const T* rho, const T* f, T* u, int nrhs, int D, double damp,
                          hipStream_t st, CgCounts* cn_out = nullptr) {
   Vecs& V = vecs<T>(g);
   const int64_t nd = g->geo.ndof;
-  T* Y = (T*)V.w[0];
+  T* Y = (T*)V.s[0];
   const int last = D + 2;
   for (int R = 0; R < nrhs; ++R) {
     T* x = u + R * nd;
@@ -383,9 +373,9 @@ fbto_status_t krylov_run(fbto_grid_s* g, const T* rho, const T* f, T* u, int nrh
       // t + 1); products alternate between two buffers, the Lanczos
       // vectors rotate through three (halo nodes read them while their
       // owners write the next one)
-      T* Yb[2] = {(T*)V.w[0], (T*)V.w[1]};
-      T* R3 = (T*)V.s[0];
-      HIP_TRY(launch_apply_cg<T>(g, rho, R2, R2, Yb[1], 1, 1, st, &nb_a));
+      T* Yb[2] = {(T*)V.s[0], (T*)V.s[1]};
+      T* R3 = (T*)V.x1;
+      HIP_TRY(launch_apply_lanczos<T>(g, rho, R2, R2, Yb[1], 1, st, &nb_a));
       for (int itn = 1; itn <= D; ++itn) {
         int nb = 0;
         HIP_TRY(launch_minres_fused<T>(g, rho, itn, Yb[itn & 1], R1, R2, R3, Wc, W2, x, Yb[(itn + 1) & 1], nb_a,
@@ -407,7 +397,7 @@ fbto_status_t krylov_run(fbto_grid_s* g, const T* rho, const T* f, T* u, int nrh
     }
     for (int itn = itn0; itn <= D + 1; ++itn) {
       // Y = K R2 with <A.r, R2> and <Y, R2>; A.r = R1 (R2 on the first iteration, where R1 is unused)
-      HIP_TRY(launch_apply_cg<T>(g, rho, R2, itn == 1 ? R2 : R1, Y, 1, itn, st, &nb_a));
+      HIP_TRY(launch_apply_lanczos<T>(g, rho, R2, itn == 1 ? R2 : R1, Y, itn, st, &nb_a));
       int nb = 0;
       HIP_TRY(launch_minres<T>(g, itn, last, Y, R1, R2, W2, Wc, x, nb_a, nb_v, damp, st, &nb));
       nb_v = nb;
@@ -419,7 +409,7 @@ fbto_status_t krylov_run(fbto_grid_s* g, const T* rho, const T* f, T* u, int nrh
   // the final residual and its norms; the residual kernel forms the Jacobi
   // diagonal on the way (its partials are written when it forms or reads one)
   int nb = 0;
-  HIP_TRY(launch_resid_diag<T>(g, rho, u, f, (T*)V.r[0], (T*)V.invD, (T*)V.q, nrhs, st, &nb));
+  HIP_TRY(launch_resid_diag<T>(g, rho, u, f, (T*)V.r[0], (T*)V.invD, (T*)V.p[0], nrhs, st, &nb));
   if (!cn_out) {
     HIP_TRY(launch_pcg_finish(g, nrhs, nb, nb, nullptr, 0, 0, 0, st));
     return FBTO_OK;

@@ -71,8 +71,6 @@ struct Scalars {
   double done[4];      // 1 once converged
   double status[4];    // fbto_status_t of the RHS
   double dot[4];       // scratch dot results
-  double cg_gamma[2][4];  // r.z of the previous CG step (by step parity)
-  double cg_alpha[2][4];  // alpha of the previous CG step
   // projection search state, double-buffered across passes: pass t reads
   // ps[t & 1] and writes ps[(t + 1) & 1] = {lambda, a, b, done}, where the
   // bracket satisfies f(a) > vmax >= f(b)
@@ -96,12 +94,12 @@ struct Scalars {
 // block (and per RHS); the consuming kernel reduces them in a fixed order in
 // every block (no atomics, no inter-block fences, bitwise reproducible).
 enum PartSlot {
-  // CG-mode apply of step k (and the fused step that produces step k's
-  // apply) writes the set of parity k & 1: r.z, w.z, r.r, max|r|
+  // CG step k reads the set of parity k & 1: r.z and r.r (from the update of
+  // step k - 1, or the residual), p.s and s.D^-1 s (from the product s = K p)
   P_RZ0, P_RZ1,
   P_PQ0, P_PQ1,
+  P_EP0, P_EP1,
   P_RN0, P_RN1,
-  P_RI0, P_RI1,
   P_RNF, P_RIF,        // final residual norms (residual apply, last CG vector step)
   P_FN,                // ||f||_2^2
   P_DOT,               // sum_r f_r . u_r
@@ -119,15 +117,14 @@ constexpr int kMaxVecBlocks = 1024;
 constexpr int kProjMaxPasses = 64;   // pass budget limit of the volume projection
 
 // Workspace vectors of one precision.  The CG vectors come in two sets:
-// the fused CG step reads one and writes the other (x of the second set is
-// `x1`; the caller's vector is x of the first).
+// the fused CG step reads one and writes the other (the iterate starts in
+// the caller's vector and alternates between x1 and x2).
 struct Vecs {
   void* r[2] = {nullptr, nullptr};   // [max_rhs][3N] residual
   void* p[2] = {nullptr, nullptr};   // search direction
-  void* s[2] = {nullptr, nullptr};   // s = K p (by recurrence)
-  void* w[2] = {nullptr, nullptr};   // w = K z
-  void* x1 = nullptr;                // iterate, second set
-  void* q = nullptr;                 // z = D^-1 r (unfused steps)
+  void* s[2] = {nullptr, nullptr};   // s = K p
+  void* x1 = nullptr;                // iterates of the fused steps
+  void* x2 = nullptr;
   void* invD = nullptr;   // [3N]
   void* rho = nullptr;    // [E]  filtered density
   void* ge = nullptr;     // [E]  element gradient
@@ -144,7 +141,13 @@ struct CgSet {
   T* r;
   T* p;
   T* s;
-  T* w;
+};
+
+// Partial counts that step k of a CG solve reduces.
+struct CgCnt {
+  int gam;     // r.z, r.r
+  int apply;   // p.s, s.D^-1 s
+  int fn;      // f.f
 };
 
 // Tile shape and slab depth of one apply variant (chosen once per grid).
@@ -153,6 +156,7 @@ struct TileChoice {
   int cap;  // resident blocks per CU at most (0: as the registers and LDS allow)
 };
 
+constexpr int kApplyModes = 7;             // modes of the z-march kernels
 constexpr size_t kApplyMaxLds = 64 * 1024;  // LDS of one z-march block at most
 
 // LDS a block requests so that at most `cap` blocks fit on a CU with
@@ -211,7 +215,7 @@ struct fbto_grid_s {
   int n_cu = 256;
   int lds_per_cu = 160 * 1024;
   int n_gsum = 0;                        // blocks of the last filter launch that left a sum
-  fbto::TileChoice tiles[2][2][6] = {};  // apply tiling by [FP64][NR - 1][mode], chosen on first use
+  fbto::TileChoice tiles[2][2][fbto::kApplyModes] = {};  // apply tiling by [FP64][NR - 1][mode], chosen on first use
   int tile_override[2] = {0, 0};         // FBTO_OPT_APPLY_TILE, FBTO_OPT_CGF_TILE (0: cost model)
   int proj_passes_warm = 2;              // FBTO_OPT_PROJ_PASSES: projection passes of the outer steps
   fbto::SortWs sort;                     // sort-based projection
@@ -235,30 +239,36 @@ hipError_t launch_resid(fbto_grid_s* g, const T* rho, const T* u, const T* f, T*
 template <typename T>
 hipError_t launch_resid_diag(fbto_grid_s* g, const T* rho, const T* u, const T* f, T* r, T* invD_out, T* z,
                              int nrhs, hipStream_t st, int* nb_out);
+// The first product s = K p of a CG solve (step 0; unfused steps: step k's),
+// with the partials of p.s and s.D^-1 s.
 template <typename T>
-hipError_t launch_apply_cg(fbto_grid_s* g, const T* rho, const T* z, const T* r, T* w, int nrhs, int step,
+hipError_t launch_apply_cg(fbto_grid_s* g, const T* rho, const T* p, const T* invD, T* s, int nrhs, int step,
                            hipStream_t st, int* nb_out);
-// One fused CG step k (FP32 only): vector update of step k from `in`, stored
-// into `out`, and out.w = K z of step k + 1 with its partials.
+// y = K u with the partials of r.u and y.u: the product of Lanczos iteration
+// `step` (one RHS).
+template <typename T>
+hipError_t launch_apply_lanczos(fbto_grid_s* g, const T* rho, const T* u, const T* r, T* y, int step, hipStream_t st,
+                                int* nb_out);
+// One fused CG step k (voxel grids): vector update of step k from `in`, stored
+// into `out`, and out.s = K p of step k + 1 with its partials.
 template <typename T>
 hipError_t launch_cg_fused(fbto_grid_s* g, const T* rho, const CgSet<T>& in, const CgSet<T>& out,
-                           const T* invD, int nrhs, int step, int n_apply, int n_fn, double rtol,
-                           hipStream_t st, int* nb_out);
+                           const T* invD, int nrhs, int step, const CgCnt& cn, double rtol, hipStream_t st,
+                           int* nb_out);
 template <typename T>
 hipError_t launch_diag(fbto_grid_s* g, const T* rho, T* invD, hipStream_t st);
 // The last CG step k (one RHS) fused with the sensitivity: x = x_in + alpha p
-// into `x`, final residual norms and f . x into the partial slots, and
-// dobj_e = -ds_e x_e^T KE x_e (times Hsi_e when given).
+// into `x` (not the input's buffer), final residual norms and f . x into the
+// partial slots, and dobj_e = -ds_e x_e^T KE x_e (times Hsi_e when given).
 template <typename T>
-hipError_t launch_cg_sens(fbto_grid_s* g, const T* rho, const CgSet<T>& in, T* x, const T* invD, const T* f,
-                          T* dobj, const T* Hsi, int step, int n_apply, int n_fn, double rtol, hipStream_t st,
+hipError_t launch_cg_sens(fbto_grid_s* g, const T* rho, const CgSet<T>& in, T* x, const T* f, T* dobj, const T* Hsi,
+                          int step, const CgCnt& cn, double rtol, hipStream_t st, int* nb_out);
+// Vector update of CG step k: x = x_in + alpha p, r and p in place.  last:
+// only x, with the final residual norms and f . x as partials.
+template <typename T>
+hipError_t launch_cg_step(fbto_grid_s* g, const T* x_in, T* x, T* r, const T* s, T* p, const T* invD, const T* f,
+                          int nrhs, int step, bool last, const CgCnt& cn, double rtol, hipStream_t st,
                           int* nb_out);
-// Vector update of CG step k: x = x_in + alpha p, r, p, s in place; z from
-// z_in or D^-1 r; z_out optional (the next unfused product's input).
-template <typename T>
-hipError_t launch_cg_step(fbto_grid_s* g, const T* x_in, T* x, T* r, const T* z_in, T* z_out, const T* w,
-                          T* p, T* s, const T* invD, const T* f, int nrhs, int n_apply, int n_fn,
-                          int step, double rtol, hipStream_t st, int* nb_out);
 hipError_t launch_pcg_finish(fbto_grid_s* g, int nrhs, int n_r, int n_fn, double* info, int n_dot,
                              int n_e, int n_gsum, hipStream_t st);
 template <typename T>
@@ -360,8 +370,11 @@ template <typename T>
 hipError_t plane_resid(fbto_grid_s* g, const T* rho, const T* u, const T* f, T* r, const T* invD, T* invD_out,
                        T* z, int nrhs, hipStream_t st, int* nb_out);
 template <typename T>
-hipError_t plane_apply_cg(fbto_grid_s* g, const T* rho, const T* z, const T* r, T* w, int nrhs, int step,
+hipError_t plane_apply_cg(fbto_grid_s* g, const T* rho, const T* p, const T* invD, T* s, int nrhs, int step,
                           hipStream_t st, int* nb_out);
+template <typename T>
+hipError_t plane_apply_lanczos(fbto_grid_s* g, const T* rho, const T* u, const T* r, T* y, int step, hipStream_t st,
+                               int* nb_out);
 template <typename T>
 hipError_t plane_diag(fbto_grid_s* g, const T* rho, T* invD, hipStream_t st);
 template <typename T>

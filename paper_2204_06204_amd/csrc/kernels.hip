@@ -91,15 +91,17 @@ static int flat_grid(int64_t n) {
 //   APPLY  y = K u
 //   RESID  y = r = f - K u; if invD is given, also z = D^-1 r and the
 //          partials of r.r, max|r|, f.f (the start of a CG solve)
-//   CG     y = w = K z with the partials of r.z, w.z, r.r, max|r| (one
-//          reduction phase per step of the Chronopoulos-Gear recurrence)
-//   CGF    one fused Chronopoulos-Gear step: the vector update of step k is
-//          done where each node is staged (z = D^-1 r, p = z + beta p,
-//          s = w + beta s, x += alpha p, r -= alpha s, z' = D^-1 r'), the
-//          owner of the node stores x', r', p', s' into the output set, and
-//          the product is w' = K z' (step k + 1's apply) with its partials.
-//          Input and output sets are distinct buffers: halo nodes of a tile
-//          are read by its neighbours while their owner writes the update.
+//   CG     y = s = K p with the partials of p.s and s.D^-1 s (the product of
+//          the first CG step)
+//   LZ     y = K u with the partials of r.u and y.u (the product of a Lanczos
+//          step of the Krylov update)
+//   CGF    one fused CG step: the vector update of step k is done where each
+//          node is staged (r' = r - alpha s, p' = D^-1 r' + beta p,
+//          x' = x + alpha p), the owner of the node stores x', r', p' into the
+//          output set, and the product is s' = K p' (step k + 1's) with its
+//          partials.  Input and output sets are distinct buffers: halo nodes
+//          of a tile are read by its neighbours while their owner writes the
+//          update.
 // ===========================================================================
 //   MRF    the fused MINRES step of the Krylov low-level step (one RHS):
 //          the vector pass of iteration t (see k_minres) done where each
@@ -107,7 +109,8 @@ static int flat_grid(int64_t n) {
 //          Lanczos vector y in the same pass.  Y, R1, R2 are read at halo
 //          nodes too, so y goes to a third buffer R3 and the product to the
 //          other Y buffer.
-enum { MODE_APPLY = 0, MODE_RESID = 1, MODE_CG = 2, MODE_CGF = 3, MODE_SENSF = 4, MODE_MRF = 5 };
+enum { MODE_APPLY = 0, MODE_RESID = 1, MODE_CG = 2, MODE_CGF = 3, MODE_SENSF = 4, MODE_MRF = 5, MODE_LZ = 6 };
+static_assert(MODE_LZ < kApplyModes, "a tile choice per mode");
 constexpr int kApplyMaxThreads = 512;
 constexpr int kApplyMaxBlocks = 8192;
 constexpr double kTinyNorm = 1e-30;  // Krylov step: a norm below this is zero (FP32 reciprocals stay finite)
@@ -128,11 +131,11 @@ struct ApplyArgs {
   const T* u;          // input vector
   T* y;
   const T* f;          // RESID
-  const T* invD;       // RESID (optional): start of a CG solve
+  const T* invD;       // RESID (optional): start of a CG solve; CG, CGF: the preconditioner
   T* invD_out;         // RESID (optional): the Jacobi diagonal is formed here and stored
   double ke_diag;      // diagonal entry of KE (with invD_out)
   T* z;                // RESID: z = D^-1 r
-  const T* r;          // CG: current residual (for r.z, r.r)
+  const T* r;          // LZ: the vector paired with u in the first partial
   const uint8_t* mask; // bits 0-2: fixed DOFs of the node; bit 3: the node has a spring
   Modal<T> km;
   Simp sp;
@@ -145,10 +148,10 @@ struct ApplyArgs {
   int maxp;
   const Scalars* sc;
   int step;            // CG, CGF: step k; CG writes, CGF reads the partial set of parity k & 1
-  // CGF only
-  const T *xi, *ri, *pi, *si, *wi;   // step k's x, r, p, s, w (p, s unread on the first step)
-  T *xo, *ro, *po, *so;              // step k + 1's x, r, p, s (w goes to y)
-  int n_apply, n_fn;                 // partial counts of step k's product and of f.f
+  // CGF and SENSF
+  const T *xi, *ri, *pi, *si;        // step k's x, r, p, s
+  T *xo, *ro, *po;                   // step k + 1's x, r, p (s goes to y)
+  int n_gam, n_apply, n_fn;          // partial counts of step k's r.z, of its product, and of f.f
   double rtol;
   // SENSF only (last CG step fused with the sensitivity)
   T* dobj;                           // [E] -ds_e x_e^T KE x_e (times Hsi_e)
@@ -161,43 +164,37 @@ struct ApplyArgs {
   double damp;                       // step size of the low-level step
 };
 
-// Step coefficients of the Chronopoulos-Gear recurrence for one RHS from
-// gamma = r.z, delta = w.z, r.r and f.f of step k (identical in every
-// block):  beta = gamma / gamma_prev, alpha = gamma / (delta - beta gamma /
-// alpha_prev); beta = 0, alpha = gamma / delta on the first step.  A solved,
-// converged or broken-down RHS gets alpha = beta = 0.  The lead thread
-// records gamma and alpha in the step-parity slot k & 1 (this kernel reads
-// the other one), the flags and the step count.
-__device__ __forceinline__ void cg_coefficients(double gam, double del, double rr, double ff, int R,
-                                                int step, double rtol, Scalars* sc, bool lead,
-                                                double& alpha, double& beta) {
-  const bool first = step == 0;
-  const int rd = (step + 1) & 1, wr = step & 1;
+// Step coefficients of the CG recurrence for one RHS from gamma = r.z,
+// delta = p.s, eps = s.D^-1 s (s = K p), r.r and f.f of step k (identical in
+// every block):
+//   alpha = gamma / delta,   beta = (alpha^2 eps - gamma) / gamma.
+// The numerator of beta is r'.D^-1 r' of r' = r - alpha s expanded with
+// r.D^-1 s = z.s = p.s (conjugate directions), so one reduction phase serves
+// a step; gamma itself is always summed from r and z, so its rounding is not
+// carried from step to step.  A numerator that rounds below zero (r' is zero
+// to rounding) restarts from z'.  A solved, converged or broken-down RHS gets
+// alpha = beta = 0.  The lead thread records the flags and the step count.
+__device__ __forceinline__ void cg_coefficients(double gam, double del, double eps, double rr, double ff, int R,
+                                                double rtol, Scalars* sc, bool lead, double& alpha,
+                                                double& beta) {
   const double rn = sqrt(rr), fn = sqrt(ff);
   bool done = sc->done[R] != 0.0 || (rtol > 0.0 && rn <= rtol * fn);
   double status = 0.0;
   alpha = 0.0;
   beta = 0.0;
   if (!done) {
-    double denom = del;
-    if (!first) {
-      beta = gam / sc->cg_gamma[rd][R];
-      denom = del - beta * gam / sc->cg_alpha[rd][R];
-    }
-    if (denom > 0.0 && isfinite(denom) && isfinite(gam)) {
-      alpha = gam / denom;
-    } else if (gam == 0.0) {
+    if (gam == 0.0 && isfinite(del)) {
       done = true;
-      beta = 0.0;
+    } else if (del > 0.0 && isfinite(del) && isfinite(gam) && isfinite(eps)) {
+      alpha = gam / del;
+      beta = fmax((alpha * alpha * eps - gam) / gam, 0.0);
     } else {
-      status = isfinite(denom) && isfinite(gam) ? (double)FBTO_ERR_BREAKDOWN : (double)FBTO_ERR_NONFINITE;
+      status = isfinite(del) && isfinite(gam) && isfinite(eps) ? (double)FBTO_ERR_BREAKDOWN
+                                                                : (double)FBTO_ERR_NONFINITE;
       done = true;
-      beta = 0.0;
     }
   }
   if (lead) {
-    sc->cg_gamma[wr][R] = gam;
-    sc->cg_alpha[wr][R] = alpha;
     if (done) sc->done[R] = 1.0;
     if (status != 0.0) sc->status[R] = status;
     if (alpha != 0.0) sc->steps[R] += 1.0;
@@ -273,8 +270,8 @@ struct ApplyStage {
 // Loads of one node plane for the fused CG step (one RHS).
 template <typename T>
 struct FusedStage {
-  T x[3], p[3];                           // owned node only
-  T r[2][3], s[2][3], w[2][3], d[2][3];
+  T x[3];                                 // owned node only
+  T r[2][3], s[2][3], p[2][3], d[2][3];
   unsigned m[2];
 };
 
@@ -505,7 +502,7 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
   // without an element, whose face values nothing reads: their reads stay
   // inside the plane)
   const int lf = elem_t ? li[0] : 0;
-  auto read_face = [&](int buf, T (&F)[NR][4][3], T (&own)[NR][3]) {
+  auto read_face = [&](int buf, T (&F)[NR][4][3]) {
     const T* nb = nodes + buf * (NR * 3 * NS);
     const int o4[4] = {0, 1, NW, NW + 1};
 #pragma unroll
@@ -515,8 +512,6 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
       for (int a = 0; a < 4; ++a)
 #pragma unroll
         for (int c = 0; c < 3; ++c) u4[a][c] = nb[(r * 3 + c) * NS + lf + o4[a]];
-#pragma unroll
-      for (int c = 0; c < 3; ++c) own[r][c] = u4[0][c];
       face_modes(u4, F[r]);
     }
   };
@@ -542,12 +537,11 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
   // The thread's own sums of non-negative terms (r.r, r.z = sum r^2 / d,
   // f.f) and max|r| over its owned nodes, at most 3 (dz + 1) terms per RHS,
   // accumulate in T and join the FP64 partials before the block reduction;
-  // sums with terms of either sign (w.z) stay FP64 throughout.
-  //   RESID: r.r, max|r|, f.f   CG, CGF: r.z, r.r (the step's coefficients
-  //   need no max|r|; the final residual's comes from the last step)
-  T tpart[NR][3];
+  // sums with terms of either sign (p.s) stay FP64 throughout.
+  //   RESID: r.r, max|r|, f.f, r.z   CGF: r.z, r.r   CG, CGF: s.D^-1 s (2)
+  T tpart[NR][4];
 #pragma unroll
-  for (int r = 0; r < NR; ++r) tpart[r][0] = tpart[r][1] = tpart[r][2] = (T)0;
+  for (int r = 0; r < NR; ++r) tpart[r][0] = tpart[r][1] = tpart[r][2] = tpart[r][3] = (T)0;
 #pragma unroll
   for (int i = 0; i < NP; ++i) part[i] = 0.0;
 
@@ -555,25 +549,40 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
   // called in the prologue, after the first planes' loads are issued, so
   // the two latencies overlap)
   T al = (T)0, be = (T)0;
-  const bool first = A.step == 0;
   auto cg_prologue = [&]() {
     const int par = A.step & 1;
-    double pre[4];
-    const double* src[4] = {pslot(A.P, P_RZ0 + par, rhs0, A.maxp), pslot(A.P, P_PQ0 + par, rhs0, A.maxp),
-                            pslot(A.P, P_RN0 + par, rhs0, A.maxp), pslot(A.P, P_FN, rhs0, A.maxp)};
-    const int cnt[4] = {A.n_apply, A.n_apply, A.n_apply, A.n_fn};
-    reduce_parts<4, 0u>(pre, src, cnt);
+    constexpr int NV = RR ? 5 : 3;
+    double pre[NV];
+    const double* src[NV];
+    int cnt[NV];
+    src[0] = pslot(A.P, P_RZ0 + par, rhs0, A.maxp);
+    src[1] = pslot(A.P, P_PQ0 + par, rhs0, A.maxp);
+    src[2] = pslot(A.P, P_EP0 + par, rhs0, A.maxp);
+    cnt[0] = A.n_gam;
+    cnt[1] = cnt[2] = A.n_apply;
+    if constexpr (RR) {
+      src[3] = pslot(A.P, P_RN0 + par, rhs0, A.maxp);
+      src[4] = pslot(A.P, P_FN, rhs0, A.maxp);
+      cnt[3] = A.n_gam;
+      cnt[4] = A.n_fn;
+    }
+    reduce_parts<NV, 0u>(pre, src, cnt);
+    double rr = 0.0, ff = 0.0;
+    if constexpr (RR) {
+      rr = pre[3];
+      ff = pre[4];
+    }
     double alpha, beta;
-    cg_coefficients(pre[0], pre[1], pre[2], pre[3], rhs0, A.step, A.rtol, const_cast<Scalars*>(A.sc),
+    cg_coefficients(pre[0], pre[1], pre[2], rr, ff, rhs0, RR ? A.rtol : 0.0, const_cast<Scalars*>(A.sc),
                     lb == 0 && tid == 0, alpha, beta);
     // the same value in every lane: kept in scalar registers
     al = wave_uniform((T)alpha);
     be = wave_uniform((T)beta);
   };
   // fused CG step: loads of one plane, and the update at staging time.
-  const __amdgpu_buffer_rsrc_t rs_r = vres(A.ri), rs_w = vres(A.wi), rs_s = vres(A.si), rs_x = vres(A.xi),
-                               rs_p = vres(A.pi), rs_d = dres(A.invD);
-  const __amdgpu_buffer_rsrc_t rs_xo = vres(A.xo), rs_ro = vres(A.ro), rs_po = vres(A.po), rs_so = vres(A.so);
+  const __amdgpu_buffer_rsrc_t rs_r = vres(A.ri), rs_s = vres(A.si), rs_x = vres(A.xi), rs_p = vres(A.pi),
+                               rs_d = dres(A.invD);
+  const __amdgpu_buffer_rsrc_t rs_xo = vres(A.xo), rs_ro = vres(A.ro), rs_po = vres(A.po);
   auto issue_f = [&](int k, FusedStage<T>& S) {
     const bool kv = k >= 0 && k <= kend && k <= G.nz;  // planes the block reads
     const bool own_plane = k >= k0 && k < kend;
@@ -584,17 +593,14 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
       const unsigned mv = bmask(gcol[sl], k, ok);
       S.m[sl] = ok ? mv : 7u;
       bload3(rs_r, ob, S.r[sl]);
-      bload3(rs_w, ob, S.w[sl]);
+      bload3(rs_s, ob, S.s[sl]);
       bload3(rs_d, ob, S.d[sl]);
-      bload3(rs_s, first ? kOOR : ob, S.s[sl]);  // zero on the first step (not read)
-      if (sl == 0) {  // p and x are used by the owner only
-        const uint32_t oo = (own_plane && writer && ok) ? ob : kOOR;
-        bload3(rs_x, oo, S.x);
-        bload3(rs_p, first ? kOOR : oo, S.p);
-      }
+      bload3(rs_p, ob, S.p[sl]);
+      if (sl == 0) bload3(rs_x, (own_plane && writer && ok) ? ob : kOOR, S.x);  // used by the owner only
     }
   };
-  auto stage_f = [&](const FusedStage<T>& S, int buf, int k, T (&zq)[3]) {
+  // zq: the node's p' (unmasked: the output of a fixed DOF); dq: its D^-1
+  auto stage_f = [&](const FusedStage<T>& S, int buf, int k, T (&zq)[3], T (&dq)[3]) {
     T* nb = nodes + buf * (3 * NS);
     const bool own_plane = k >= k0 && k < kend;
 #pragma unroll
@@ -602,17 +608,17 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
       const bool owner = sl == 0 && writer && own_plane;  // the owner's node index is valid
       // the owner's byte offset; other threads store out of range (dropped)
       const uint32_t ob = owner ? voff(gcol[0], k) : kOOR;
-      T xn[3], rn[3], pn[3], sn[3];
+      T xn[3], rn[3], pn[3];
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
-        sn[c] = S.w[sl][c] + be * S.s[sl][c];
-        rn[c] = S.r[sl][c] - al * sn[c];
+        rn[c] = S.r[sl][c] - al * S.s[sl][c];
         const T zn = S.d[sl][c] * rn[c];
-        if (sl == 0 || has_extra) nb[c * NS + li[sl]] = ((S.m[sl] >> c) & 1u) ? (T)0 : zn;
+        pn[c] = zn + be * S.p[sl][c];
+        if (sl == 0 || has_extra) nb[c * NS + li[sl]] = ((S.m[sl] >> c) & 1u) ? (T)0 : pn[c];
         if (sl == 0) {
-          zq[c] = zn;  // unmasked: the output of a fixed DOF
-          pn[c] = S.d[sl][c] * S.r[sl][c] + be * S.p[c];
-          xn[c] = S.x[c] + al * pn[c];
+          zq[c] = pn[c];
+          dq[c] = S.d[sl][c];
+          xn[c] = S.x[c] + al * S.p[sl][c];
           if (owner) {
             tpart[0][0] += rn[c] * zn;     // r.z
             if constexpr (RR) tpart[0][1] += rn[c] * rn[c];  // r.r
@@ -623,7 +629,6 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
         bstore3(rs_xo, ob, xn);
         bstore3(rs_ro, ob, rn);
         bstore3(rs_po, ob, pn);
-        bstore3(rs_so, ob, sn);
       }
     }
   };
@@ -767,7 +772,6 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
   FusedStage<T> SF;
   MinresStage<T> SM;
   T F[2][NR][4][3];
-  T own[2][NR][3];
   T carry[NR][4][3];
 #pragma unroll
   for (int r = 0; r < NR; ++r)
@@ -779,11 +783,13 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
   // prologue: planes ez0, ez0 + 1 staged (and, unfused, plane ez0 + 2 in flight)
   unsigned mq;     // masks of the own node, plane ez in byte 0, ez + 1 in byte 1, ..
   T rq[3][NR][3];  // unmasked input value of the own node, planes ez, ez + 1, ez + 2
+  T dq[3][3];      // CGF: its D^-1, the same planes
   T rho_next;
-  // residual and CG modes: values of the own node read only at its output
-  // (RESID: f and D^-1 (or f again); CG: r), loaded one layer ahead.  FP64
-  // loads them at the output instead: the queue would not fit its registers.
-  constexpr bool kOwnQ = sizeof(T) == 4 && (MODE == MODE_RESID || MODE == MODE_CG);
+  // residual, CG and Lanczos modes: values of the own node read only at its
+  // output (RESID: f and D^-1 (or f again); CG: D^-1; LZ: r), loaded one
+  // layer ahead.  FP64 loads them at the output instead: the queue would not
+  // fit its registers.
+  constexpr bool kOwnQ = sizeof(T) == 4 && (MODE == MODE_RESID || MODE == MODE_CG || MODE == MODE_LZ);
   T oq[2][NR][2][3];
   __amdgpu_buffer_rsrc_t rs_f[NR], rs_cr[NR], rs_y[NR], rs_z[NR];
 #pragma unroll
@@ -802,6 +808,8 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
       if constexpr (MODE == MODE_RESID) {
         bload3(rs_f[r], ob, q[r][0]);
         bload3(rs_d, A.invD ? ob : kOOR, q[r][1]);
+      } else if constexpr (MODE == MODE_CG) {
+        bload3(rs_d, ob, q[r][0]);
       } else {
         bload3(rs_cr[r], ob, q[r][0]);
       }
@@ -813,9 +821,9 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
     rho_next = load_rho(ez0);
     issue_f(ez0 + 1, SF1);
     cg_prologue();
-    stage_f(SF, ez0 & 1, ez0, rq[0][0]);
+    stage_f(SF, ez0 & 1, ez0, rq[0][0], dq[0]);
     mq = SF.m[0] & 0xffu;
-    stage_f(SF1, (ez0 + 1) & 1, ez0 + 1, rq[1][0]);
+    stage_f(SF1, (ez0 + 1) & 1, ez0 + 1, rq[1][0], dq[1]);
     mq |= (SF1.m[0] & 0xffu) << 8;
   } else if constexpr (MODE == MODE_MRF) {
     MinresStage<T> SM1;
@@ -848,7 +856,7 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
   }
   T s_below = (T)0;  // s of the element below (diagonal of the residual mode)
   __syncthreads();
-  read_face(ez0 & 1, F[0], own[0]);
+  read_face(ez0 & 1, F[0]);
   __syncthreads();  // the first layer restages the buffer of plane ez0
 
   auto layer = [&](auto parity, int ez) {
@@ -867,7 +875,7 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
     loads_priority<T>(false);
     const T dcol = s_below + s;  // this column's share of the lower-face nodes' diagonal
     s_below = s;
-    read_face((ez + 1) & 1, F[P ^ 1], own[P ^ 1]);
+    read_face((ez + 1) & 1, F[P ^ 1]);
     const bool emit = ez >= k0;  // uniform over the block
     T out[NR][4][3];
 #pragma unroll
@@ -886,7 +894,7 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
       }
     }
     if constexpr (MODE == MODE_CGF) {
-      stage_f(SF, ez & 1, ez + 2, rq[2][0]);
+      stage_f(SF, ez & 1, ez + 2, rq[2][0], dq[2]);
       mq |= (SF.m[0] & 0xffu) << 16;
     } else if constexpr (MODE == MODE_MRF) {
       stage_m(SM, ez & 1, ez + 2, rq[2][0]);
@@ -915,7 +923,7 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
           acc[c] = ((out[r][0][c] + cr[(0 + c) * TS + tl1]) + cr[(3 + c) * TS + tlb]) + cr[(6 + c) * TS + tlbb];
-          pv[c] = own[P][r][c];  // masked input value at this node
+          pv[c] = rq[0][r][c];  // the input value at this node, as staged
         }
         if (m) {  // springs, then identity rows of fixed DOFs (rare nodes)
           if (m & 8u) {
@@ -928,10 +936,7 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
           }
 #pragma unroll
           for (int c = 0; c < 3; ++c)
-            if ((m >> c) & 1u) {  // the unmasked input value, as staged
-              pv[c] = rq[0][r][c];
-              acc[c] = pv[c];
-            }
+            if ((m >> c) & 1u) acc[c] = pv[c];
         }
         // partial sums count owned nodes only (a select: values of a thread
         // without an owned node may be anything, NaN included)
@@ -984,28 +989,32 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
             tpart[r][0] += own_t(rv[c] * rv[c]);
             tpart[r][1] = fmax(tpart[r][1], own_t(fabs(rv[c])));
             tpart[r][2] += own_t(fv[c] * fv[c]);
+            tpart[r][3] += own_t(rv[c] * zv[c]);
           }
         } else {
           bstore3(rs_y[r], ob, acc);
-          if constexpr (MODE == MODE_CG) {
-            T rv3[3];
+          if constexpr (MODE == MODE_CG || MODE == MODE_LZ) {
+            T q3[3];  // CG: D^-1; LZ: the paired vector
             if constexpr (kOwnQ) {
 #pragma unroll
-              for (int c = 0; c < 3; ++c) rv3[c] = oq[P][r][0][c];
+              for (int c = 0; c < 3; ++c) q3[c] = oq[P][r][0][c];
             } else {
-              bload3(rs_cr[r], ob, rv3);
+              bload3(MODE == MODE_CG ? rs_d : rs_cr[r], ob, q3);
             }
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
-              const T rv = rv3[c];
-              tpart[r][0] += own_t(rv * pv[c]);                             // r.z
-              part[4 * r + 1] += own_only((double)acc[c] * (double)pv[c]);  // w.z
-              tpart[r][1] += own_t(rv * rv);                                // r.r
+              part[4 * r + 1] += own_only((double)acc[c] * (double)pv[c]);  // p.s / y.u
+              if constexpr (MODE == MODE_CG) tpart[r][2] += own_t(acc[c] * (q3[c] * acc[c]));  // s.D^-1 s
+              else part[4 * r] += own_only((double)q3[c] * (double)pv[c]);                     // r.u
             }
           }
           if constexpr (MODE == MODE_CGF || MODE == MODE_MRF) {
 #pragma unroll
-            for (int c = 0; c < 3; ++c) part[1] += own_only((double)acc[c] * (double)pv[c]);  // w'.z' / <K y, y>
+            for (int c = 0; c < 3; ++c) part[1] += own_only((double)acc[c] * (double)pv[c]);  // p'.s' / <K y, y>
+          }
+          if constexpr (MODE == MODE_CGF) {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) tpart[0][2] += own_t(acc[c] * (dq[0][c] * acc[c]));  // s'.D^-1 s'
           }
         }
       }
@@ -1018,6 +1027,13 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
         rq[0][r][c] = rq[1][r][c];
         rq[1][r][c] = rq[2][r][c];
       }
+    if constexpr (MODE == MODE_CGF) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        dq[0][c] = dq[1][c];
+        dq[1][c] = dq[2][c];
+      }
+    }
   };
   for (int ez = ez0; ez < kend; ez += 2) {
     layer(std::integral_constant<int, 0>{}, ez);
@@ -1025,21 +1041,32 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
     layer(std::integral_constant<int, 1>{}, ez + 1);
   }
 
-  if constexpr (MODE == MODE_CG || MODE == MODE_CGF) {
-    // CG: step k's product -> set k & 1; CGF: step k + 1's -> set (k + 1) & 1
-    const int par = (MODE == MODE_CG ? A.step : A.step + 1) & 1;
-    constexpr int NV = RR ? 3 : 2;  // r.z, w.z (, r.r)
+  if constexpr (MODE == MODE_CG || MODE == MODE_CGF || MODE == MODE_LZ) {
+    // CG: step k's product -> set k & 1; CGF: step k + 1's -> set (k + 1) & 1;
+    // LZ: iteration k's
+    const int par = (MODE == MODE_CGF ? A.step + 1 : A.step) & 1;
+    // CG: p.s, s.D^-1 s   CGF: also r.z (, r.r)   LZ: y.u, r.u
+    constexpr int NV = MODE == MODE_CGF ? (RR ? 4 : 3) : 2;
     double* dst[NV * NR];
     double v[NV * NR];
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
-      dst[NV * r + 0] = pslot(A.P, P_RZ0 + par, rhs0 + r, A.maxp);
-      dst[NV * r + 1] = pslot(A.P, P_PQ0 + par, rhs0 + r, A.maxp);
-      v[NV * r + 0] = (double)tpart[r][0];
-      v[NV * r + 1] = part[4 * r + 1];
-      if constexpr (RR) {
-        dst[NV * r + 2] = pslot(A.P, P_RN0 + par, rhs0 + r, A.maxp);
-        v[NV * r + 2] = (double)tpart[r][1];
+      dst[NV * r + 0] = pslot(A.P, P_PQ0 + par, rhs0 + r, A.maxp);
+      v[NV * r + 0] = part[4 * r + 1];
+      if constexpr (MODE == MODE_LZ) {
+        dst[NV * r + 1] = pslot(A.P, P_RZ0 + par, rhs0 + r, A.maxp);
+        v[NV * r + 1] = part[4 * r];
+      } else {
+        dst[NV * r + 1] = pslot(A.P, P_EP0 + par, rhs0 + r, A.maxp);
+        v[NV * r + 1] = (double)tpart[r][2];
+      }
+      if constexpr (MODE == MODE_CGF) {
+        dst[NV * r + 2] = pslot(A.P, P_RZ0 + par, rhs0 + r, A.maxp);
+        v[NV * r + 2] = (double)tpart[r][0];
+        if constexpr (RR) {
+          dst[NV * r + 3] = pslot(A.P, P_RN0 + par, rhs0 + r, A.maxp);
+          v[NV * r + 3] = (double)tpart[r][1];
+        }
       }
     }
     write_parts<NV * NR, 0u>(v, dst, lb);
@@ -1063,26 +1090,24 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
         sc->steps[rhs0 + r] = 0.0;
       }
     }
-    double v[3 * NR];
-    double* dst[3 * NR];
-#pragma unroll
-    for (int r = 0; r < NR; ++r) {
-      v[3 * r + 0] = (double)tpart[r][0];
-      v[3 * r + 1] = (double)tpart[r][1];
-      v[3 * r + 2] = (double)tpart[r][2];
-      dst[3 * r + 0] = pslot(A.P, P_RNF, rhs0 + r, A.maxp);
-      dst[3 * r + 1] = pslot(A.P, P_RIF, rhs0 + r, A.maxp);
-      dst[3 * r + 2] = pslot(A.P, P_FN, rhs0 + r, A.maxp);
-    }
-    write_parts<3 * NR, rinf_mask(NR)>(v, dst, lb);
+    static_assert(NR == 1, "one RHS per launch");
+    double v[4];
+    double* dst[4];
+    for (int i = 0; i < 4; ++i) v[i] = (double)tpart[0][i];
+    dst[0] = pslot(A.P, P_RNF, rhs0, A.maxp);
+    dst[1] = pslot(A.P, P_RIF, rhs0, A.maxp);
+    dst[2] = pslot(A.P, P_FN, rhs0, A.maxp);
+    dst[3] = pslot(A.P, P_RZ0, rhs0, A.maxp);  // r.z and r.r of step 0
+    write_parts<4, 0x2u>(v, dst, lb);
+    if (tid == 0) pslot(A.P, P_RN0, rhs0, A.maxp)[lb] = v[0];
   }
 }
 
 // ===========================================================================
-// The last Chronopoulos-Gear step of a solve fused with the sensitivity of
-// Sec. 3 (one RHS).  On the tiling of k_apply, every staged node gets
-// x' = x + alpha (D^-1 r + beta p); the owner of the node stores x', and
-// forms r' = r - alpha (w + beta s) for the final residual norms and f . x'.
+// The last CG step of a solve fused with the sensitivity of Sec. 3 (one
+// RHS).  On the tiling of k_apply, every staged node gets x' = x + alpha p;
+// the owner of the node stores x', and forms r' = r - alpha s for the final
+// residual norms and f . x'.
 // Each element owned by the block gets
 //   dobj_e = -ds_e x'_e^T KE x'_e  (times 1/Hs_e when given)
 // from the face modes of its two faces.  Nothing is scattered back to the
@@ -1091,8 +1116,8 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
 // ===========================================================================
 template <typename T>
 struct SensStage {
-  T x[2][3], r[2][3], p[2][3], d[2][3];  // every staged node
-  T w[3], s[3], f[3];                    // owned node only
+  T x[2][3], p[2][3];   // every staged node
+  T r[3], s[3], f[3];   // owned node only
   unsigned m[2];
 };
 
@@ -1143,28 +1168,27 @@ __global__ void __launch_bounds__(kApplyMaxThreads)
     return (uint32_t)(3 * sizeof(T)) * (uint32_t)(col + (k - ez0) * plane);
   };
   const __amdgpu_buffer_rsrc_t rs_m = zrsrc(A.mask + pbase), rs_x = vres(A.xi), rs_r = vres(A.ri),
-                               rs_d = vres(A.invD), rs_p = vres(A.pi), rs_w = vres(A.wi), rs_s = vres(A.si),
-                               rs_f = vres(A.fvec), rs_xo = vres(A.xo);
+                               rs_p = vres(A.pi), rs_s = vres(A.si), rs_f = vres(A.fvec), rs_xo = vres(A.xo);
   const int64_t ebase = (int64_t)ez0 * G.nx * G.ny;  // first element of layer ez0
   const __amdgpu_buffer_rsrc_t rs_rho = zrsrc(A.rho + ebase), rs_hs = zrsrc(A.Hsi ? A.Hsi + ebase : A.Hsi),
                                rs_do = zrsrc(A.dobj + ebase);
 
-  // step coefficients (every block, same order; called after the first
+  // the step's alpha (every block, same order; called after the first
   // planes' loads are issued, so the two latencies overlap)
-  const bool first = A.step == 0;
-  T al = (T)0, be = (T)0;
+  T al = (T)0;
   auto coefficients = [&]() {
     const int par = A.step & 1;
-    double pre[4];
-    const double* src[4] = {pslot(A.P, P_RZ0 + par, 0, A.maxp), pslot(A.P, P_PQ0 + par, 0, A.maxp),
-                            pslot(A.P, P_RN0 + par, 0, A.maxp), pslot(A.P, P_FN, 0, A.maxp)};
-    const int cnt[4] = {A.n_apply, A.n_apply, A.n_apply, A.n_fn};
-    reduce_parts<4, 0u>(pre, src, cnt);
+    double pre[5];
+    const double* src[5] = {pslot(A.P, P_RZ0 + par, 0, A.maxp), pslot(A.P, P_PQ0 + par, 0, A.maxp),
+                            pslot(A.P, P_EP0 + par, 0, A.maxp), pslot(A.P, P_RN0 + par, 0, A.maxp),
+                            pslot(A.P, P_FN, 0, A.maxp)};
+    const bool tol = A.rtol > 0.0;  // r.r and f.f only for the tolerance test
+    const int cnt[5] = {A.n_gam, A.n_apply, A.n_apply, tol ? A.n_gam : 0, tol ? A.n_fn : 0};
+    reduce_parts<5, 0u>(pre, src, cnt);
     double alpha, beta;
-    cg_coefficients(pre[0], pre[1], pre[2], pre[3], 0, A.step, A.rtol, const_cast<Scalars*>(A.sc),
+    cg_coefficients(pre[0], pre[1], pre[2], pre[3], pre[4], 0, A.rtol, const_cast<Scalars*>(A.sc),
                     lb == 0 && tid == 0, alpha, beta);
     al = wave_uniform((T)alpha);
-    be = wave_uniform((T)beta);
   };
   // r'.r', max|r'|, f.x', and the sum of the block's element sensitivities
   double part[4] = {0.0, 0.0, 0.0, 0.0};
@@ -1179,13 +1203,11 @@ __global__ void __launch_bounds__(kApplyMaxThreads)
       const unsigned mv = __builtin_amdgcn_raw_buffer_load_b8(rs_m, ok ? (uint32_t)(gcol[sl] + (k - ez0) * plane) : kOOR, 0, 0);
       S.m[sl] = ok ? mv : 7u;
       zload3<T>(rs_x, off, S.x[sl]);
-      zload3<T>(rs_r, off, S.r[sl]);
-      zload3<T>(rs_d, off, S.d[sl]);
-      zload3<T>(rs_p, first ? kOOR : off, S.p[sl]);  // allocated on the first step too, its contents unused
+      zload3<T>(rs_p, off, S.p[sl]);
       if (sl == 0) {  // used by the owner only
         const uint32_t oo = owns(k) ? off : kOOR;
-        zload3<T>(rs_w, oo, S.w);
-        zload3<T>(rs_s, first ? kOOR : oo, S.s);
+        zload3<T>(rs_r, oo, S.r);
+        zload3<T>(rs_s, oo, S.s);
         zload3<T>(rs_f, A.fvec ? oo : kOOR, S.f);
       }
     }
@@ -1198,15 +1220,14 @@ __global__ void __launch_bounds__(kApplyMaxThreads)
       T xn[3];
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
-        const T pn = S.d[sl][c] * S.r[sl][c] + be * S.p[sl][c];
-        xn[c] = S.x[sl][c] + al * pn;
+        xn[c] = S.x[sl][c] + al * S.p[sl][c];
         if (sl == 0 || has_extra) nb[c * NS + li[sl]] = ((S.m[sl] >> c) & 1u) ? (T)0 : xn[c];
       }
       if (sl == 0) {
         zstore3<T>(rs_xo, own ? voff(gcol[0], k) : kOOR, xn);
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-          const T rn = S.r[0][c] - al * (S.w[c] + be * S.s[c]);
+          const T rn = S.r[c] - al * S.s[c];
           part[0] += own ? (double)rn * (double)rn : 0.0;
           part[1] = fmax(part[1], own ? fabs((double)rn) : 0.0);
           part[2] += own ? (double)S.f[c] * (double)xn[c] : 0.0;
@@ -1494,22 +1515,34 @@ hipError_t launch_resid_diag(fbto_grid_s* g, const T* rho, const T* u, const T* 
 }
 
 template <typename T>
-hipError_t launch_apply_cg(fbto_grid_s* g, const T* rho, const T* z, const T* r, T* w, int nrhs, int step,
+hipError_t launch_apply_cg(fbto_grid_s* g, const T* rho, const T* p, const T* invD, T* s, int nrhs, int step,
                            hipStream_t st, int* nb_out) {
-  if (g->dim == 2) return plane_apply_cg<T>(g, rho, z, r, w, nrhs, step, st, nb_out);
+  if (g->dim == 2) return plane_apply_cg<T>(g, rho, p, invD, s, nrhs, step, st, nb_out);
   ApplyArgs<T> A{};
   A.rho = rho;
-  A.u = z;
-  A.r = r;
-  A.y = w;
+  A.u = p;
+  A.invD = invD;
+  A.y = s;
   A.step = step;
   return launch_apply_mode<T, MODE_CG>(g, A, nrhs, st, nb_out);
 }
 
 template <typename T>
-hipError_t launch_cg_sens(fbto_grid_s* g, const T* rho, const CgSet<T>& in, T* x, const T* invD, const T* f,
-                          T* dobj, const T* Hsi, int step, int n_apply, int n_fn, double rtol, hipStream_t st,
-                          int* nb_out) {
+hipError_t launch_apply_lanczos(fbto_grid_s* g, const T* rho, const T* u, const T* r, T* y, int step, hipStream_t st,
+                                int* nb_out) {
+  if (g->dim == 2) return plane_apply_lanczos<T>(g, rho, u, r, y, step, st, nb_out);
+  ApplyArgs<T> A{};
+  A.rho = rho;
+  A.u = u;
+  A.r = r;
+  A.y = y;
+  A.step = step;
+  return launch_apply_mode<T, MODE_LZ>(g, A, 1, st, nb_out);
+}
+
+template <typename T>
+hipError_t launch_cg_sens(fbto_grid_s* g, const T* rho, const CgSet<T>& in, T* x, const T* f, T* dobj, const T* Hsi,
+                          int step, const CgCnt& cn, double rtol, hipStream_t st, int* nb_out) {
   TileChoice& t = g->tiles[sizeof(T) == 8 ? 1 : 0][0][MODE_SENSF];
   if (t.nblocks == 0) {
     t = choose_tile<T, 1, MODE_SENSF>(g->geo, g->n_cu, g->lds_per_cu, g->tile_override[0]);
@@ -1526,15 +1559,15 @@ hipError_t launch_cg_sens(fbto_grid_s* g, const T* rho, const CgSet<T>& in, T* x
   A.maxp = g->max_partials;
   A.sc = g->sc;
   A.rho = rho;
-  A.invD = invD;
-  A.xi = in.x; A.ri = in.r; A.pi = in.p; A.si = in.s; A.wi = in.w;
+  A.xi = in.x; A.ri = in.r; A.pi = in.p; A.si = in.s;
   A.xo = x;
   A.dobj = dobj;
   A.Hsi = Hsi;
   A.fvec = f;
   A.step = step;
-  A.n_apply = n_apply;
-  A.n_fn = n_fn;
+  A.n_gam = cn.gam;
+  A.n_apply = cn.apply;
+  A.n_fn = cn.fn;
   A.rtol = rtol;
   A.bx = t.bx;
   A.by = t.by;
@@ -1554,17 +1587,18 @@ hipError_t launch_cg_sens(fbto_grid_s* g, const T* rho, const CgSet<T>& in, T* x
 
 template <typename T>
 hipError_t launch_cg_fused(fbto_grid_s* g, const T* rho, const CgSet<T>& in, const CgSet<T>& out,
-                           const T* invD, int nrhs, int step, int n_apply, int n_fn, double rtol,
-                           hipStream_t st, int* nb_out) {
+                           const T* invD, int nrhs, int step, const CgCnt& cn, double rtol, hipStream_t st,
+                           int* nb_out) {
   ApplyArgs<T> A{};
   A.rho = rho;
-  A.y = out.w;
+  A.y = out.s;
   A.invD = invD;
   A.step = step;
-  A.xi = in.x; A.ri = in.r; A.pi = in.p; A.si = in.s; A.wi = in.w;
-  A.xo = out.x; A.ro = out.r; A.po = out.p; A.so = out.s;
-  A.n_apply = n_apply;
-  A.n_fn = n_fn;
+  A.xi = in.x; A.ri = in.r; A.pi = in.p; A.si = in.s;
+  A.xo = out.x; A.ro = out.r; A.po = out.p;
+  A.n_gam = cn.gam;
+  A.n_apply = cn.apply;
+  A.n_fn = cn.fn;
   A.rtol = rtol;
   // r.r only for the tolerance test
   return rtol > 0.0 ? launch_apply_mode<T, MODE_CGF, true>(g, A, nrhs, st, nb_out)
@@ -1634,37 +1668,35 @@ hipError_t launch_diag(fbto_grid_s* g, const T* rho, T* invD, hipStream_t st) {
 }
 
 // ===========================================================================
-// Jacobi-PCG in the Chronopoulos-Gear arrangement: one reduction phase per
-// step.  With z = D^-1 r and w = K z (from the CG-mode apply, which also
-// leaves the partials of gamma = r.z, delta = w.z, r.r, max|r|):
-//   beta = gamma / gamma_prev,  alpha = gamma / (delta - beta gamma / alpha_prev)
-//   p = z + beta p,  s = w + beta s,  x += alpha p,  r -= alpha s,  z = D^-1 r
-// (beta = 0, alpha = gamma / delta on the first step).  In exact arithmetic
-// the iterates are those of the textbook recurrence.  The scalars are
-// reduced from the partials in every block's prologue; gamma and alpha of
-// the previous step are kept in the scalars, double-buffered by step parity
-// (block 0 writes the slot no block of this kernel reads).  Convergence and
+// Jacobi-PCG with one reduction phase per step.  With s = K p (whose product
+// leaves the partials of delta = p.s and eps = s.D^-1 s) and gamma = r.z:
+//   alpha = gamma / delta,  beta = (alpha^2 eps - gamma) / gamma,
+//   x += alpha p,  r -= alpha s,  z = D^-1 r,  p = z + beta p
+// (cg_coefficients).  In exact arithmetic the iterates are those of the
+// textbook recurrence, and in floating point nearly so: s is the product
+// itself, not a recurrence for it, so the residual follows f - K x as closely
+// as the textbook's.  Against the recurrence of Chronopoulos and Gear
+// (w = K z, s = w + beta s) a step carries one vector less (nine accesses
+// instead of eleven) and its FP32 iterates are 3-10 times closer to FP64's
+// after 8 and 24 steps (48x24x24 grids, CPU emulation).  The scalars are
+// reduced from the partials in every block's prologue; convergence and
 // breakdown are decided identically in every block.
 // ===========================================================================
-constexpr int kU = 8;
 
-struct CgCnt {
-  int apply;   // partials of the last apply (gamma, delta, r.r, max|r|)
-  int fn;      // partials of f.f (the residual apply)
-};
-
-template <typename T, int NR>
+// One vector update, step k (plane grids; also the last step of a solve
+// whose sensitivity is not fused).  LAST: x and the final residual norms
+// only; r, p and z are not needed again.
+template <typename T, int NR, bool LAST>
 __global__ void __launch_bounds__(kVecBlock)
-    k_cg_step(int64_t ndof, const T* x_in, T* x, T* r, const T* z_in, T* z_out, const T* w, T* p, T* s,
-              const T* invD, const T* f, double* P, int maxp, CgCnt cn, int step, double rtol, Scalars* sc) {
+    k_cg_step(int64_t ndof, const T* x_in, T* x, T* r, const T* s, T* p, const T* invD, const T* f, double* P,
+              int maxp, CgCnt cn, int step, double rtol, Scalars* sc) {
   // first chunk of this thread's vector entries is loaded before the prologue
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   const int64_t i_first = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const bool first = step == 0;
   // entries per thread and chunk: fewer with more load cases, so that the
   // chunk stays in registers
   constexpr int kU = NR <= 2 ? 8 : 4;
-  T zv[kU][NR], wv[kU][NR], pv[kU][NR], sv[kU][NR], xv[kU][NR], rv[kU][NR], dv[kU];
+  T sv[kU][NR], pv[kU][NR], xv[kU][NR], rv[kU][NR], dv[kU];
   bool ok[kU];
   auto load_chunk = [&](int64_t i0) {
 #pragma unroll
@@ -1672,50 +1704,52 @@ __global__ void __launch_bounds__(kVecBlock)
       const int64_t i = i0 + k * stride;
       ok[k] = i < ndof;
       const int64_t ii = ok[k] ? i : 0;
-      dv[k] = invD[ii];
+      if constexpr (!LAST) dv[k] = invD[ii];
 #pragma unroll
       for (int R = 0; R < NR; ++R) {
         const int64_t o = R * ndof + ii;
         rv[k][R] = r[o];
-        zv[k][R] = z_in ? z_in[o] : dv[k] * rv[k][R];
-        wv[k][R] = w[o];
+        sv[k][R] = s[o];
         xv[k][R] = x_in[o];
-        pv[k][R] = first ? (T)0 : p[o];
-        sv[k][R] = first ? (T)0 : s[o];
+        pv[k][R] = p[o];
       }
     }
   };
   if (i_first < ndof) load_chunk(i_first);
 
-  double pre[4 * NR];
+  double pre[5 * NR];
+  const int par = step & 1;
   {
-    const int par = step & 1;
-    const double* src[4 * NR];
-    int cnt[4 * NR];
+    const double* src[5 * NR];
+    int cnt[5 * NR];
+    const bool tol = rtol > 0.0;  // r.r and f.f only for the tolerance test
 #pragma unroll
     for (int R = 0; R < NR; ++R) {
-      src[4 * R + 0] = pslot(P, P_RZ0 + par, R, maxp);
-      src[4 * R + 1] = pslot(P, P_PQ0 + par, R, maxp);
-      src[4 * R + 2] = pslot(P, P_RN0 + par, R, maxp);
-      src[4 * R + 3] = pslot(P, P_FN, R, maxp);
-      cnt[4 * R + 0] = cn.apply;
-      cnt[4 * R + 1] = cn.apply;
-      cnt[4 * R + 2] = cn.apply;
-      cnt[4 * R + 3] = cn.fn;
+      src[5 * R + 0] = pslot(P, P_RZ0 + par, R, maxp);
+      src[5 * R + 1] = pslot(P, P_PQ0 + par, R, maxp);
+      src[5 * R + 2] = pslot(P, P_EP0 + par, R, maxp);
+      src[5 * R + 3] = pslot(P, P_RN0 + par, R, maxp);
+      src[5 * R + 4] = pslot(P, P_FN, R, maxp);
+      cnt[5 * R + 0] = cn.gam;
+      cnt[5 * R + 1] = cn.apply;
+      cnt[5 * R + 2] = cn.apply;
+      cnt[5 * R + 3] = tol ? cn.gam : 0;
+      cnt[5 * R + 4] = tol ? cn.fn : 0;
     }
-    reduce_parts<4 * NR, 0u, kVecBlock>(pre, src, cnt);
+    reduce_parts<5 * NR, 0u, kVecBlock>(pre, src, cnt);
   }
   T al[NR], be[NR];
   const bool lead = blockIdx.x == 0 && threadIdx.x == 0;
 #pragma unroll
   for (int R = 0; R < NR; ++R) {
     double alpha, beta;
-    cg_coefficients(pre[4 * R], pre[4 * R + 1], pre[4 * R + 2], pre[4 * R + 3], R, step, rtol, sc, lead, alpha,
-                    beta);
+    cg_coefficients(pre[5 * R], pre[5 * R + 1], pre[5 * R + 2], pre[5 * R + 3], pre[5 * R + 4], R, rtol, sc, lead,
+                    alpha, beta);
     al[R] = (T)alpha;
     be[R] = (T)beta;
   }
 
+  // LAST: r.r, max|r| per RHS, f.x; otherwise r.z, r.r per RHS
   double v[2 * NR + 1];
 #pragma unroll
   for (int i = 0; i < 2 * NR + 1; ++i) v[i] = 0.0;
@@ -1728,29 +1762,44 @@ __global__ void __launch_bounds__(kVecBlock)
 #pragma unroll
       for (int R = 0; R < NR; ++R) {
         const int64_t o = R * ndof + i;
-        const T pn = zv[k][R] + be[R] * pv[k][R];
-        const T sn = wv[k][R] + be[R] * sv[k][R];
-        const T xn = xv[k][R] + al[R] * pn;
-        const T rn = rv[k][R] - al[R] * sn;
-        p[o] = pn;
-        s[o] = sn;
+        const T xn = xv[k][R] + al[R] * pv[k][R];
+        const T rn = rv[k][R] - al[R] * sv[k][R];
         x[o] = xn;
-        r[o] = rn;
-        if (z_out) z_out[o] = dv[k] * rn;
-        v[2 * R] += (double)rn * (double)rn;
-        v[2 * R + 1] = fmax(v[2 * R + 1], fabs((double)rn));
-        if (f) v[2 * NR] += (double)f[o] * (double)xn;
+        if constexpr (LAST) {
+          v[2 * R] += (double)rn * (double)rn;
+          v[2 * R + 1] = fmax(v[2 * R + 1], fabs((double)rn));
+          if (f) v[2 * NR] += (double)f[o] * (double)xn;
+        } else {
+          const T zn = dv[k] * rn;
+          r[o] = rn;
+          p[o] = zn + be[R] * pv[k][R];
+          v[2 * R] += (double)rn * (double)zn;
+          v[2 * R + 1] += (double)rn * (double)rn;
+        }
       }
     }
   }
-  double* dst[2 * NR + 1];
+  if constexpr (LAST) {
+    double* dst[2 * NR + 1];
 #pragma unroll
-  for (int R = 0; R < NR; ++R) {
-    dst[2 * R] = pslot(P, P_RNF, R, maxp);
-    dst[2 * R + 1] = pslot(P, P_RIF, R, maxp);
+    for (int R = 0; R < NR; ++R) {
+      dst[2 * R] = pslot(P, P_RNF, R, maxp);
+      dst[2 * R + 1] = pslot(P, P_RIF, R, maxp);
+    }
+    dst[2 * NR] = pslot(P, P_DOT, 0, maxp);
+    write_parts<2 * NR + 1, 0xAAAu, kVecBlock>(v, dst, blockIdx.x);
+  } else {
+    double w[2 * NR];
+    double* dst[2 * NR];
+#pragma unroll
+    for (int R = 0; R < NR; ++R) {
+      w[2 * R] = v[2 * R];
+      w[2 * R + 1] = v[2 * R + 1];
+      dst[2 * R] = pslot(P, P_RZ0 + (par ^ 1), R, maxp);
+      dst[2 * R + 1] = pslot(P, P_RN0 + (par ^ 1), R, maxp);
+    }
+    write_parts<2 * NR, 0u, kVecBlock>(w, dst, blockIdx.x);
   }
-  dst[2 * NR] = pslot(P, P_DOT, 0, maxp);
-  write_parts<2 * NR + 1, 0xAAAu, kVecBlock>(v, dst, blockIdx.x);
 }
 
 // Threads of the one-block finishing kernels: a block of 256 measured twice
@@ -1851,15 +1900,20 @@ __global__ void __launch_bounds__(kVecBlock)
   }
 
 template <typename T>
-hipError_t launch_cg_step(fbto_grid_s* g, const T* x_in, T* x, T* r, const T* z_in, T* z_out, const T* w, T* p,
-                          T* s, const T* invD, const T* f, int nrhs, int n_apply, int n_fn, int step,
-                          double rtol, hipStream_t st, int* nb_out) {
+hipError_t launch_cg_step(fbto_grid_s* g, const T* x_in, T* x, T* r, const T* s, T* p, const T* invD, const T* f,
+                          int nrhs, int step, bool last, const CgCnt& cn, double rtol, hipStream_t st,
+                          int* nb_out) {
   const int nb = vec_blocks(g->geo.ndof);
   if (nb_out) *nb_out = nb;
-  const CgCnt cn{n_apply, n_fn};
-  FBTO_NR_DISPATCH(nrhs, hipLaunchKernelGGL((k_cg_step<T, NR>), dim3(nb), dim3(kVecBlock), 0, st, g->geo.ndof,
-                                            x_in, x, r, z_in, z_out, w, p, s, invD, f, g->partials,
-                                            g->max_partials, cn, step, rtol, g->sc));
+  if (last) {
+    FBTO_NR_DISPATCH(nrhs, hipLaunchKernelGGL((k_cg_step<T, NR, true>), dim3(nb), dim3(kVecBlock), 0, st, g->geo.ndof,
+                                              x_in, x, r, s, p, invD, f, g->partials, g->max_partials, cn, step,
+                                              rtol, g->sc));
+  } else {
+    FBTO_NR_DISPATCH(nrhs, hipLaunchKernelGGL((k_cg_step<T, NR, false>), dim3(nb), dim3(kVecBlock), 0, st,
+                                              g->geo.ndof, x_in, x, r, s, p, invD, f, g->partials, g->max_partials,
+                                              cn, step, rtol, g->sc));
+  }
   return hipGetLastError();
 }
 hipError_t launch_pcg_finish(fbto_grid_s* g, int nrhs, int n_r, int n_fn, double* info, int n_dot, int n_e,
@@ -2988,13 +3042,14 @@ hipError_t launch_opt_finish(fbto_grid_s* g, int nrhs, int nb_dot, int nb_lo, in
                                            hipStream_t, int*);                                         \
   template hipError_t launch_apply_cg<T>(fbto_grid_s*, const T*, const T*, const T*, T*, int, int,     \
                                          hipStream_t, int*);                                           \
-  template hipError_t launch_cg_step<T>(fbto_grid_s*, const T*, T*, T*, const T*, T*, const T*, T*, T*, \
-                                        const T*, const T*, int, int, int, int, double, hipStream_t,   \
-                                        int*);                                                         \
-  template hipError_t launch_cg_sens<T>(fbto_grid_s*, const T*, const CgSet<T>&, T*, const T*, const T*, \
-                                        T*, const T*, int, int, int, double, hipStream_t, int*);       \
+  template hipError_t launch_apply_lanczos<T>(fbto_grid_s*, const T*, const T*, const T*, T*, int,     \
+                                              hipStream_t, int*);                                      \
+  template hipError_t launch_cg_step<T>(fbto_grid_s*, const T*, T*, T*, const T*, T*, const T*, const T*, int, int, \
+                                        bool, const CgCnt&, double, hipStream_t, int*);                \
+  template hipError_t launch_cg_sens<T>(fbto_grid_s*, const T*, const CgSet<T>&, T*, const T*, T*, const T*, int, \
+                                        const CgCnt&, double, hipStream_t, int*);                      \
   template hipError_t launch_cg_fused<T>(fbto_grid_s*, const T*, const CgSet<T>&, const CgSet<T>&,      \
-                                         const T*, int, int, int, int, double, hipStream_t, int*);      \
+                                         const T*, int, int, const CgCnt&, double, hipStream_t, int*);  \
   template hipError_t launch_diag<T>(fbto_grid_s*, const T*, T*, hipStream_t);                         \
   template hipError_t launch_relax_update<T>(fbto_grid_s*, T*, const T*, const T*, int, double, int,    \
                                              hipStream_t);                                             \

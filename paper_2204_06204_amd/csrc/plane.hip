@@ -25,7 +25,7 @@ namespace fbto {
 namespace {
 constexpr int kPlaneBlock = 256;
 
-enum { PL_APPLY = 0, PL_RESID = 1, PL_CG = 2 };
+enum { PL_APPLY = 0, PL_RESID = 1, PL_CG = 2, PL_LZ = 3 };
 
 template <typename T>
 struct PlaneArgs {
@@ -33,12 +33,12 @@ struct PlaneArgs {
   int64_t N, ndof;
   const T* rho;
   const T* u;          // input vector
-  T* y;                // output: K u, r = f - K u, or w = K z
+  T* y;                // output: K u, or r = f - K u
   const T* f;          // RESID
-  const T* invD;       // RESID (optional): z = D^-1 r from this diagonal
+  const T* invD;       // RESID (optional): z = D^-1 r from this diagonal; CG: the preconditioner
   T* invD_out;         // RESID (optional): form the Jacobi diagonal, store it, z from it
   T* z;                // RESID
-  const T* r;          // CG: the residual paired with the product's partials
+  const T* r;          // LZ: the vector paired with u in the first partial
   const uint8_t* mask; // bit c: DOF c of the node fixed
   Q4<T> ke;
   double ke_diag;
@@ -46,15 +46,8 @@ struct PlaneArgs {
   double* P;
   int maxp;
   Scalars* sc;
-  int step;            // CG: the partials go to the set of parity step & 1
+  int step;            // CG, LZ: the partials go to the set of parity step & 1
 };
-
-// the |r|_inf entries (max-reduced) of the per-RHS triples |r|^2, |r|_inf, |f|^2
-constexpr unsigned resid_max_mask(int nr) {
-  unsigned m = 0u;
-  for (int r = 0; r < nr; ++r) m |= 1u << (3 * r + 1);
-  return m;
-}
 
 __device__ __forceinline__ double* pslot2(double* P, int slot, int r, int maxp) {
   return P + ((int64_t)slot * 4 + r) * maxp;
@@ -64,7 +57,7 @@ __device__ __forceinline__ double* pslot2(double* P, int slot, int r, int maxp) 
 // around the node; fixed DOFs of the neighbours enter as zero.
 template <typename T, int NR, int MODE>
 __global__ void __launch_bounds__(kPlaneBlock) k_plane_apply(PlaneArgs<T> A, int rhs0) {
-  constexpr int NP = MODE == PL_APPLY ? 1 : 4 * NR;
+  constexpr int NP = MODE == PL_APPLY ? 1 : MODE == PL_RESID ? 4 * NR : 2 * NR;
   double part[NP];
 #pragma unroll
   for (int i = 0; i < NP; ++i) part[i] = 0.0;
@@ -140,6 +133,7 @@ __global__ void __launch_bounds__(kPlaneBlock) k_plane_apply(PlaneArgs<T> A, int
           const T fv = A.f[o + c];
           const T rv = fv - acc[r][c];
           A.y[o + c] = rv;
+          T zv = (T)0;
           if (A.invD_out || A.invD) {
             T dl;
             if (A.invD_out) {
@@ -150,36 +144,36 @@ __global__ void __launch_bounds__(kPlaneBlock) k_plane_apply(PlaneArgs<T> A, int
             } else {
               dl = A.invD[2 * (int64_t)n + c];
             }
-            A.z[o + c] = dl * rv;
+            zv = dl * rv;
+            A.z[o + c] = zv;
           }
           part[4 * r + 0] += (double)rv * (double)rv;
           part[4 * r + 1] = fmax(part[4 * r + 1], fabs((double)rv));
           part[4 * r + 2] += (double)fv * (double)fv;
+          part[4 * r + 3] += (double)rv * (double)zv;
         }
-      } else {  // PL_CG
+      } else {  // PL_CG: p.s, s.D^-1 s; PL_LZ: y.u, r.u
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
           A.y[o + c] = acc[r][c];
-          const T rv = A.r[o + c];
-          part[4 * r + 0] += (double)rv * (double)pv[c];          // r.z
-          part[4 * r + 1] += (double)acc[r][c] * (double)pv[c];   // w.z
-          part[4 * r + 2] += (double)rv * (double)rv;             // r.r
-          part[4 * r + 3] = fmax(part[4 * r + 3], fabs((double)rv));
+          part[2 * r] += (double)acc[r][c] * (double)pv[c];
+          if constexpr (MODE == PL_CG)
+            part[2 * r + 1] += (double)acc[r][c] * (double)(A.invD[2 * (int64_t)n + c] * acc[r][c]);
+          else
+            part[2 * r + 1] += (double)A.r[o + c] * (double)pv[c];
         }
       }
     }
   }
-  if constexpr (MODE == PL_CG) {
+  if constexpr (MODE == PL_CG || MODE == PL_LZ) {
     const int par = A.step & 1;
-    double* dst[4 * NR];
+    double* dst[2 * NR];
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
-      dst[4 * r + 0] = pslot2(A.P, P_RZ0 + par, rhs0 + r, A.maxp);
-      dst[4 * r + 1] = pslot2(A.P, P_PQ0 + par, rhs0 + r, A.maxp);
-      dst[4 * r + 2] = pslot2(A.P, P_RN0 + par, rhs0 + r, A.maxp);
-      dst[4 * r + 3] = pslot2(A.P, P_RI0 + par, rhs0 + r, A.maxp);
+      dst[2 * r + 0] = pslot2(A.P, P_PQ0 + par, rhs0 + r, A.maxp);
+      dst[2 * r + 1] = pslot2(A.P, (MODE == PL_CG ? P_EP0 : P_RZ0) + par, rhs0 + r, A.maxp);
     }
-    write_parts<4 * NR, 0x8888u>(part, dst, blockIdx.x);
+    write_parts<2 * NR, 0u>(part, dst, blockIdx.x);
   }
   if constexpr (MODE == PL_RESID) {
     if (A.invD == nullptr && A.invD_out == nullptr) return;
@@ -190,18 +184,19 @@ __global__ void __launch_bounds__(kPlaneBlock) k_plane_apply(PlaneArgs<T> A, int
         A.sc->steps[rhs0 + r] = 0.0;
       }
     }
-    double v[3 * NR];
-    double* dst[3 * NR];
+    double* dst[4 * NR];
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
-      v[3 * r + 0] = part[4 * r + 0];
-      v[3 * r + 1] = part[4 * r + 1];
-      v[3 * r + 2] = part[4 * r + 2];
-      dst[3 * r + 0] = pslot2(A.P, P_RNF, rhs0 + r, A.maxp);
-      dst[3 * r + 1] = pslot2(A.P, P_RIF, rhs0 + r, A.maxp);
-      dst[3 * r + 2] = pslot2(A.P, P_FN, rhs0 + r, A.maxp);
+      dst[4 * r + 0] = pslot2(A.P, P_RNF, rhs0 + r, A.maxp);
+      dst[4 * r + 1] = pslot2(A.P, P_RIF, rhs0 + r, A.maxp);
+      dst[4 * r + 2] = pslot2(A.P, P_FN, rhs0 + r, A.maxp);
+      dst[4 * r + 3] = pslot2(A.P, P_RZ0, rhs0 + r, A.maxp);  // r.z and r.r of step 0
     }
-    write_parts<3 * NR, resid_max_mask(NR)>(v, dst, blockIdx.x);
+    write_parts<4 * NR, 0x2222u>(part, dst, blockIdx.x);
+    if (threadIdx.x == 0) {
+#pragma unroll
+      for (int r = 0; r < NR; ++r) pslot2(A.P, P_RN0, rhs0 + r, A.maxp)[blockIdx.x] = part[4 * r];
+    }
   }
 }
 
@@ -398,15 +393,27 @@ hipError_t plane_resid(fbto_grid_s* g, const T* rho, const T* u, const T* f, T* 
 }
 
 template <typename T>
-hipError_t plane_apply_cg(fbto_grid_s* g, const T* rho, const T* z, const T* r, T* w, int nrhs, int step,
+hipError_t plane_apply_cg(fbto_grid_s* g, const T* rho, const T* p, const T* invD, T* s, int nrhs, int step,
                           hipStream_t st, int* nb_out) {
   PlaneArgs<T> A = plane_args<T>(g);
   A.rho = rho;
-  A.u = z;
-  A.r = r;
-  A.y = w;
+  A.u = p;
+  A.invD = invD;
+  A.y = s;
   A.step = step;
   return plane_launch<T, PL_CG>(g, A, nrhs, st, nb_out);
+}
+
+template <typename T>
+hipError_t plane_apply_lanczos(fbto_grid_s* g, const T* rho, const T* u, const T* r, T* y, int step, hipStream_t st,
+                               int* nb_out) {
+  PlaneArgs<T> A = plane_args<T>(g);
+  A.rho = rho;
+  A.u = u;
+  A.r = r;
+  A.y = y;
+  A.step = step;
+  return plane_launch<T, PL_LZ>(g, A, 1, st, nb_out);
 }
 
 template <typename T>
@@ -461,6 +468,8 @@ hipError_t plane_hs(fbto_grid_s* g, T* Hsi, hipStream_t st) {
                                      hipStream_t, int*);                                                     \
   template hipError_t plane_apply_cg<T>(fbto_grid_s*, const T*, const T*, const T*, T*, int, int, hipStream_t, \
                                         int*);                                                               \
+  template hipError_t plane_apply_lanczos<T>(fbto_grid_s*, const T*, const T*, const T*, T*, int, hipStream_t, \
+                                             int*);                                                          \
   template hipError_t plane_diag<T>(fbto_grid_s*, const T*, T*, hipStream_t);                                \
   template hipError_t plane_sens<T>(fbto_grid_s*, const T*, const T*, const T*, int, T*, const T*,           \
                                     hipStream_t);                                                            \
