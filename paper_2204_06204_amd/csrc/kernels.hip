@@ -2402,6 +2402,106 @@ __global__ void __launch_bounds__(kFiltBX * kFiltBY)
   }
 }
 
+// Density filter for R = 2 (radius 2 to 3) by z-march: a block owns a BX x
+// (256 / BX) tile of element columns and a slab of layers.  Each plane the slab
+// reads is staged in LDS once, with the tile's halo of two columns on every
+// side (its loads issued one plane ahead), and a thread adds the plane's
+// 21 or 25 neighbours of its column to the five outputs they reach, so a value
+// is read from memory (BX + 4) (BY + 4) / 256 (dz + 4) / dz times instead of
+// 125 times through the L1, which bound the gather.  The taps with
+// |offset|^2 >= 9 have no weight at any radius up to 3 and are left out; the
+// others are taken in the gather's order (dz, dy, dx).  Bound by its 93 FMAs
+// per element on large grids (68 us at 384x192x192 FP32, 170 MB at 2.5 TB/s)
+// and by the latency of its planes on small ones.  Gather -> this, FP32
+// forward / transpose: 384x192x192 1158 / 2641 -> 68 / 90 us, 256x128x128
+// 354 / 769 -> 29 / 43 us, 97x53x41 26 / 41 -> 9.0 / 9.4 us; FP64 at
+// 384x192x192 2344 / 4674 -> 123 / 170 us.
+constexpr int kFilt2Halo = 2;
+template <typename T>
+struct Stencil2 {
+  T w[9];  // weight by squared offset
+};
+
+template <typename T, int BX>
+__global__ void __launch_bounds__(kVecBlock)
+    k_filter_r2(Geo G, int kind, const T* in, T* out, const T* Hsi, Stencil2<T> W, int want_sum, double* P, int maxp,
+                int tiles_x, int tiles_y, int dz, int nwork) {
+  constexpr int H = kFilt2Halo, BY = kVecBlock / BX;
+  constexpr int LX = BX + 2 * H, LY = BY + 2 * H, LN = LX * LY;
+  constexpr int NL = (LN + kVecBlock - 1) / kVecBlock;  // values a thread stages per plane
+  __shared__ T sh[2][LN];
+  const int tid = threadIdx.x, tx = tid % BX, ty = tid / BX;
+  const int plane = G.nx * G.ny;
+  double v[1] = {0.0};
+  for (int wk = blockIdx.x; wk < nwork; wk += gridDim.x) {
+    const int bx = wk % tiles_x, t2 = wk / tiles_x, by = t2 % tiles_y, bz = t2 / tiles_y;
+    const int x0 = bx * BX, y0 = by * BY, z0 = bz * dz, z1 = min(z0 + dz, G.nz);
+    int col[NL];  // offset of each staged column in its plane, -1 outside the grid
+#pragma unroll
+    for (int k = 0; k < NL; ++k) {
+      const int i = tid + k * kVecBlock;
+      const int gx = x0 + i % LX - H, gy = y0 + i / LX - H;
+      col[k] = (i < LN && gx >= 0 && gx < G.nx && gy >= 0 && gy < G.ny) ? gx + G.nx * gy : -1;
+    }
+    auto load = [&](int z, T (&q)[NL]) {
+      const bool zok = z >= 0 && z < G.nz && z < z1 + H;
+#pragma unroll
+      for (int k = 0; k < NL; ++k) {
+        const bool ok = zok && col[k] >= 0;
+        const int64_t j = ok ? col[k] + (int64_t)z * plane : 0;
+        T x = in[j];
+        if (kind == FILT_TRANS) x *= Hsi[j];
+        q[k] = ok ? x : (T)0;
+      }
+    };
+    const bool own = x0 + tx < G.nx && y0 + ty < G.ny;
+    const int ecol = x0 + tx + G.nx * (y0 + ty);
+    T acc[2 * H + 1];  // outputs z - 2 .. z + 2 of the current plane z
+#pragma unroll
+    for (int i = 0; i < 2 * H + 1; ++i) acc[i] = (T)0;
+    T q[NL];
+    load(z0 - H, q);
+    for (int z = z0 - H; z < z1 + H; ++z) {
+      T* const b = sh[z & 1];
+#pragma unroll
+      for (int k = 0; k < NL; ++k)
+        if (tid + k * kVecBlock < LN) b[tid + k * kVecBlock] = q[k];
+      load(z + 1, q);
+      T hs = (T)1;
+      const int zo = z - H;  // the output this plane completes
+      const bool emit = own && zo >= z0;
+      const int64_t e = emit ? ecol + (int64_t)zo * plane : 0;
+      if (kind == FILT_FWD) hs = Hsi[e];
+      __syncthreads();
+#pragma unroll
+      for (int dy = -H; dy <= H; ++dy)
+#pragma unroll
+        for (int dx = -H; dx <= H; ++dx) {
+          const T x = b[(ty + H + dy) * LX + tx + H + dx];
+#pragma unroll
+          for (int d = -H; d <= H; ++d) {
+            constexpr int kMax = 8;
+            const int d2 = dx * dx + dy * dy + d * d;
+            if (d2 <= kMax) acc[H - d] += W.w[d2] * x;
+          }
+        }
+      if (emit) {
+        const T res = kind == FILT_FWD ? acc[0] * hs : acc[0];
+        out[e] = res;
+        v[0] += (double)res;
+      }
+#pragma unroll
+      for (int i = 0; i < 2 * H; ++i) acc[i] = acc[i + 1];
+      acc[2 * H] = (T)0;
+    }
+    __syncthreads();  // the next tile restages the buffers
+  }
+  if (want_sum) {
+    double* dst[1] = {pslot(P, P_GSUM, 0, maxp)};
+    write_parts<1, 0u, kVecBlock>(v, dst, blockIdx.x);
+  }
+}
+
 // Generic gather for wide stencils (R > 2): offsets and weights from memory.
 template <typename T>
 __global__ void __launch_bounds__(kVecBlock)
@@ -2486,13 +2586,33 @@ hipError_t launch_filter(fbto_grid_s* g, int kind, const T* in, T* out, int want
                          FiltStep<T>{});
     return hipGetLastError();
   }
+  if (R == 2) {
+    // tiles of 32 x 8 columns (16 x 16 where the rows are that short); slabs
+    // of 4 to 32 layers, so that a small grid still gives 2 blocks per CU
+    // (halo planes cost 4 / dz more) and a large one reads its halo seldom
+    Stencil2<T> W{};
+    for (int d2 = 0; d2 <= 8; ++d2) W.w[d2] = (T)std::max(0.0, r - std::sqrt((double)d2));
+    const int bx = G.nx <= 16 ? 16 : 32, by = kVecBlock / bx;
+    const int tx = (G.nx + bx - 1) / bx, ty = (G.ny + by - 1) / by;
+    const int64_t tiles = (int64_t)tx * ty;
+    const int64_t want = std::max<int64_t>(1, 2 * (int64_t)g->n_cu / tiles);  // slabs
+    const int dz = (int)std::min<int64_t>(32, std::max<int64_t>(4, (G.nz + want - 1) / want));
+    const int64_t nwork = tiles * ((G.nz + dz - 1) / dz);
+    if (nwork > INT32_MAX) return hipErrorInvalidValue;
+    const int grid = (int)std::min<int64_t>(nwork, g->max_partials);
+    if (want_sum) g->n_gsum = grid;
+    if (bx == 16)
+      hipLaunchKernelGGL((k_filter_r2<T, 16>), dim3(grid), dim3(kVecBlock), 0, st, G, kind, in, out, Hsi, W, want_sum,
+                         g->partials, g->max_partials, tx, ty, dz, (int)nwork);
+    else
+      hipLaunchKernelGGL((k_filter_r2<T, 32>), dim3(grid), dim3(kVecBlock), 0, st, G, kind, in, out, Hsi, W, want_sum,
+                         g->partials, g->max_partials, tx, ty, dz, (int)nwork);
+    return hipGetLastError();
+  }
   if (want_sum) g->n_gsum = nb;
   if (R <= 1)
     hipLaunchKernelGGL((k_filter<T, 1>), dim3(nb), dim3(kVecBlock), 0, st, g->geo, kind, in, out, Hsi,
                        stencil_weights<T, 1>(r), want_sum, g->partials, g->max_partials);
-  else if (R == 2)
-    hipLaunchKernelGGL((k_filter<T, 2>), dim3(nb), dim3(kVecBlock), 0, st, g->geo, kind, in, out, Hsi,
-                       stencil_weights<T, 2>(r), want_sum, g->partials, g->max_partials);
   else
     hipLaunchKernelGGL((k_filter_wide<T>), dim3(nb), dim3(kVecBlock), 0, st, g->geo, kind, in, out, Hsi,
                        g->n_stencil, (const int*)g->stencil_off, stencil_w_of<T>(g), want_sum, g->partials,
