@@ -270,17 +270,17 @@ struct ApplyStage {
 // Loads of one node plane for the fused CG step (one RHS).
 template <typename T>
 struct FusedStage {
-  T x[3];                                 // owned node only
-  T r[2][3], s[2][3], p[2][3], d[2][3];
-  unsigned m[2];
+  T x[3];                       // owned node only
+  T r[3], s[3], p[3], d[3];
+  unsigned m;
 };
 
 // Loads of one node plane for the fused MINRES step.
 template <typename T>
 struct MinresStage {
-  T w[3], w2[3], x[3];                    // owned node only
-  T y[2][3], r1[2][3], r2[2][3];
-  unsigned m[2];
+  T w[3], w2[3], x[3];          // owned node only
+  T y[3], r1[3], r2[3];
+  unsigned m;
 };
 
 // Buffer access of the z-march kernels.  A resource spans 2^31 - 1 bytes
@@ -309,41 +309,63 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t zrsrc(const void* p) {
 typedef float zf3 __attribute__((ext_vector_type(3)));
 typedef unsigned zu3 __attribute__((ext_vector_type(3)));
 typedef unsigned zu2 __attribute__((ext_vector_type(2)));
+typedef unsigned zu4 __attribute__((ext_vector_type(4)));
+typedef double zd2 __attribute__((ext_vector_type(2)));
+// voff: the lane's byte offset (a node or element column, or kOOR); soff: the
+// plane's, the same for the block, added by the load itself.  Stores add it in
+// a vector register: with a scalar offset the compiler takes a store of three
+// or four words to be safe from the next instruction's write to its data
+// registers, and single nodes of the FP32 residual were then stored wrong now
+// and then.
 template <typename T>
-__device__ __forceinline__ void zload3(__amdgpu_buffer_rsrc_t rs, uint32_t off, T (&v)[3]) {
+__device__ __forceinline__ void zload3(__amdgpu_buffer_rsrc_t rs, uint32_t voff, uint32_t soff, T (&v)[3]) {
   if constexpr (sizeof(T) == 4) {
-    const zf3 t = __builtin_bit_cast(zf3, __builtin_amdgcn_raw_buffer_load_b96(rs, off, 0, 0));
+    const zf3 t = __builtin_bit_cast(zf3, __builtin_amdgcn_raw_buffer_load_b96(rs, voff, soff, 0));
     v[0] = t.x;
     v[1] = t.y;
     v[2] = t.z;
   } else {
-#pragma unroll
-    for (int c = 0; c < 3; ++c) v[c] = __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(rs, off + 8u * c, 0, 0));
+    const zd2 t = __builtin_bit_cast(zd2, __builtin_amdgcn_raw_buffer_load_b128(rs, voff, soff, 0));
+    v[0] = t.x;
+    v[1] = t.y;
+    v[2] = __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(rs, voff + 16u, soff, 0));
   }
 }
 template <typename T>
-__device__ __forceinline__ void zstore3(__amdgpu_buffer_rsrc_t rs, uint32_t off, const T (&v)[3]) {
+__device__ __forceinline__ void zstore3(__amdgpu_buffer_rsrc_t rs, uint32_t voff, uint32_t soff, const T (&v)[3]) {
   if constexpr (sizeof(T) == 4) {
     zu3 t;
     t.x = __builtin_bit_cast(unsigned, v[0]);
     t.y = __builtin_bit_cast(unsigned, v[1]);
     t.z = __builtin_bit_cast(unsigned, v[2]);
-    __builtin_amdgcn_raw_buffer_store_b96(t, rs, off, 0, 0);
+    __builtin_amdgcn_raw_buffer_store_b96(t, rs, voff + soff, 0, 0);
   } else {
-#pragma unroll
-    for (int c = 0; c < 3; ++c)
-      __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(zu2, v[c]), rs, off + 8u * c, 0, 0);
+    const zd2 t = {v[0], v[1]};
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(zu4, t), rs, voff + soff, 0, 0);
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(zu2, v[2]), rs, voff + soff + 16u, 0, 0);
   }
 }
 template <typename T>
-__device__ __forceinline__ T zload1(__amdgpu_buffer_rsrc_t rs, uint32_t off) {
-  if constexpr (sizeof(T) == 4) return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(rs, off, 0, 0));
-  else return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(rs, off, 0, 0));
+__device__ __forceinline__ T zload1(__amdgpu_buffer_rsrc_t rs, uint32_t voff, uint32_t soff) {
+  if constexpr (sizeof(T) == 4) return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(rs, voff, soff, 0));
+  else return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(rs, voff, soff, 0));
 }
 template <typename T>
-__device__ __forceinline__ void zstore1(__amdgpu_buffer_rsrc_t rs, uint32_t off, T v) {
-  if constexpr (sizeof(T) == 4) __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), rs, off, 0, 0);
-  else __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(zu2, v), rs, off, 0, 0);
+__device__ __forceinline__ void zstore1(__amdgpu_buffer_rsrc_t rs, uint32_t voff, uint32_t soff, T v) {
+  if constexpr (sizeof(T) == 4)
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), rs, voff + soff, 0, 0);
+  else __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(zu2, v), rs, voff + soff, 0, 0);
+}
+// v, or 0 where bit c of the mask byte m is set, by bit operations (two per
+// 32 bits; a compare and a select take three).
+template <typename T>
+__device__ __forceinline__ T zmasked(unsigned m, int c, T v) {
+  const int keep = __builtin_amdgcn_sbfe((int)~m, c, 1);  // all ones where the bit is clear
+  if constexpr (sizeof(T) == 4) {
+    return __builtin_bit_cast(T, __builtin_bit_cast(int, v) & keep);
+  } else {
+    return __hiloint2double(__double2hiint(v) & keep, __double2loint(v) & keep);
+  }
 }
 
 // A value that is the same in every lane of the wave, kept in a scalar
@@ -392,8 +414,11 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
   const int NS = NW * (BY + 1);   // LDS nodes per plane
   const int TW = NL ? NW : BX;    // threads per tile row
   const int TS = NL ? NS : BX * BY;  // threads with a node (node layout) or an element (element layout)
-  T* nodes = reinterpret_cast<T*>(apply_smem);   // [2][NR][3][NS]
-  T* corners = nodes + 2 * NR * 3 * NS;         // [2][NR][9][TS]
+  // a node's three values and a thread's nine corner values lie together:
+  // odd strides of 3 and 9 values (no bank conflicts), few wide LDS
+  // instructions, and immediate offsets instead of an address each
+  T* nodes = reinterpret_cast<T*>(apply_smem);   // [2][NR][NS][3]
+  T* corners = nodes + 2 * NR * 3 * NS;         // [2][NR][TS][9]
   T* dcorn = corners + 2 * NR * 9 * TS;          // [2][TS] density sums of the diagonal
 
   // Thread (tx, ty) of the tile computes element column (x0 + tx, y0 + ty)
@@ -457,16 +482,28 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
   auto rsrc = [](const void* p) { return zrsrc(p); };
   auto vres = [&](const T* v, int r = 0) { return rsrc(v ? v + vbase + (int64_t)r * G.ndof : v); };  // [nrhs][3N]
   auto dres = [&](const T* v) { return rsrc(v ? v + 3 * pbase : v); };  // [3N], one set
-  // byte offset of the first value of node column `col` in plane k (k >= ez0)
-  auto voff = [&](int col, int k) -> uint32_t {
-    return (uint32_t)(3 * sizeof(T)) * (uint32_t)(col + (k - ez0) * plane);
-  };
+  // An access takes the byte offset of the lane's node column in its plane
+  // (computed once; kOOR where the lane has none) and the plane's byte offset
+  // in a scalar register: no vector arithmetic per access.
+  // The small grids are bound by the instructions they issue: with this, the
+  // node and corner layouts above and one select per partial a layer of K u
+  // takes 240 vector instructions instead of 280 (160 of them the product)
+  // and the FP32 fused step 260 instead of 320, in 129 registers instead of
+  // 156.  K u at 256x128x128 51.5 -> 49.0 us; FP32 outer iteration 208 -> 199
+  // us at 128x64x64 and 120 -> 116 us at 64x32x32; FP64 336 -> 325 us.
+  const uint32_t vc1 = gcol[0] >= 0 ? (uint32_t)gcol[0] : kOOR;  // mask bytes
+  const uint32_t vc3 = gcol[0] >= 0 ? (uint32_t)(3 * sizeof(T)) * (uint32_t)gcol[0] : kOOR;
+  const uint32_t vx1 = has_extra && gcol[1] >= 0 ? (uint32_t)gcol[1] : kOOR;  // the far node
+  const uint32_t vx3 = has_extra && gcol[1] >= 0 ? (uint32_t)(3 * sizeof(T)) * (uint32_t)gcol[1] : kOOR;
+  const uint32_t vw3 = writer ? vc3 : kOOR;  // the node a thread owns
+  auto splane = [&](int k) -> uint32_t { return (uint32_t)(k - ez0) * (uint32_t)plane; };
+  auto s3 = [&](int k) -> uint32_t { return (uint32_t)(3 * sizeof(T)) * splane(k); };
   const __amdgpu_buffer_rsrc_t rs_m = rsrc(A.mask + pbase);
-  auto bload3 = [](__amdgpu_buffer_rsrc_t rs, uint32_t off, T (&v)[3]) { zload3<T>(rs, off, v); };
-  auto bstore3 = [](__amdgpu_buffer_rsrc_t rs, uint32_t off, const T (&v)[3]) { zstore3<T>(rs, off, v); };
-  // the mask byte of a node (kOOR: 0)
-  auto bmask = [&](int col, int k, bool ok) -> unsigned {
-    return __builtin_amdgcn_raw_buffer_load_b8(rs_m, ok ? (uint32_t)(col + (k - ez0) * plane) : kOOR, 0, 0);
+  auto bload3 = [](__amdgpu_buffer_rsrc_t rs, uint32_t vo, uint32_t so, T (&v)[3]) { zload3<T>(rs, vo, so, v); };
+  auto bstore3 = [](__amdgpu_buffer_rsrc_t rs, uint32_t vo, uint32_t so, const T (&v)[3]) { zstore3<T>(rs, vo, so, v); };
+  // the mask byte of a node (0 out of range, where the values load as 0 too)
+  auto bmask = [&](uint32_t vo, uint32_t so) -> unsigned {
+    return __builtin_amdgcn_raw_buffer_load_b8(rs_m, vo, so, 0);
   };
 
   // Planes past the slab's last one (kend) are staged but never read; their
@@ -476,14 +513,13 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
   for (int r = 0; r < NR; ++r) rs_u[r] = vres(A.u, r);
   auto issue = [&](int k, ApplyStage<T, NR>& S) {
     const bool kv = k >= 0 && k <= kend && k <= G.nz;  // planes the block reads
+    const uint32_t so1 = kv ? splane(k) : 0u, so3 = (uint32_t)(3 * sizeof(T)) * so1;
 #pragma unroll
     for (int sl = 0; sl < kSlots; ++sl) {
-      const bool ok = kv && gcol[sl] >= 0 && (sl == 0 || has_extra);
-      const uint32_t ob = ok ? voff(gcol[sl], k) : kOOR;
-      const unsigned mv = bmask(gcol[sl], k, ok);
-      S.m[sl] = ok ? mv : 7u;
+      const uint32_t o1 = kv ? (sl ? vx1 : vc1) : kOOR, o3 = kv ? (sl ? vx3 : vc3) : kOOR;
+      S.m[sl] = bmask(o1, so1);
 #pragma unroll
-      for (int r = 0; r < NR; ++r) bload3(rs_u[r], ob, S.v[sl][r]);
+      for (int r = 0; r < NR; ++r) bload3(rs_u[r], o3, so3, S.v[sl][r]);
     }
   };
   auto stage = [&](const ApplyStage<T, NR>& S, int buf) {
@@ -494,24 +530,22 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
 #pragma unroll
       for (int r = 0; r < NR; ++r)
 #pragma unroll
-        for (int c = 0; c < 3; ++c)
-          nb[(r * 3 + c) * NS + li[sl]] = ((S.m[sl] >> c) & 1u) ? (T)0 : S.v[sl][r][c];
+        for (int c = 0; c < 3; ++c) nb[(r * NS + li[sl]) * 3 + c] = zmasked(S.m[sl], c, S.v[sl][r][c]);
     }
   };
   // the lower-left node of the thread's element (node 0's for threads
   // without an element, whose face values nothing reads: their reads stay
   // inside the plane)
-  const int lf = elem_t ? li[0] : 0;
+  const int lf = 3 * (elem_t ? li[0] : 0);
   auto read_face = [&](int buf, T (&F)[NR][4][3]) {
-    const T* nb = nodes + buf * (NR * 3 * NS);
-    const int o4[4] = {0, 1, NW, NW + 1};
+    const T* nb = nodes + buf * (NR * 3 * NS) + lf;
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
       T u4[4][3];
 #pragma unroll
       for (int a = 0; a < 4; ++a)
 #pragma unroll
-        for (int c = 0; c < 3; ++c) u4[a][c] = nb[(r * 3 + c) * NS + lf + o4[a]];
+        for (int c = 0; c < 3; ++c) u4[a][c] = nb[3 * (r * NS + (a >> 1) * NW) + 3 * (a & 1) + c];
       face_modes(u4, F[r]);
     }
   };
@@ -520,10 +554,11 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
   // the wave wait for every load issued before it (the counter is in order),
   // including the node planes prefetched for the next layers.
   const __amdgpu_buffer_rsrc_t rs_rho = rsrc(A.rho + (int64_t)G.nx * G.ny * ez0);
+  const uint32_t ve = col_elem ? (uint32_t)sizeof(T) * (uint32_t)(ex + G.nx * ey) : kOOR;
   auto load_rho = [&](int ez) -> T {
-    const bool el = col_elem && ez >= 0 && ez < G.nz && ez < kend;  // element layers of this block
-    const uint32_t off = el ? (uint32_t)sizeof(T) * (uint32_t)(ex + G.nx * (ey + G.ny * (ez - ez0))) : kOOR;
-    return zload1<T>(rs_rho, off);
+    const bool el = ez >= 0 && ez < G.nz && ez < kend;  // element layers of this block
+    const uint32_t so = el ? (uint32_t)sizeof(T) * (uint32_t)((ez - ez0) * (G.nx * G.ny)) : 0u;
+    return zload1<T>(rs_rho, el ? ve : kOOR, so);
   };
   auto scale_of = [&](int ez, T rv) -> T {
     const bool el = col_elem && ez >= 0 && ez < G.nz;
@@ -586,51 +621,40 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
   auto issue_f = [&](int k, FusedStage<T>& S) {
     const bool kv = k >= 0 && k <= kend && k <= G.nz;  // planes the block reads
     const bool own_plane = k >= k0 && k < kend;
-#pragma unroll
-    for (int sl = 0; sl < kSlots; ++sl) {
-      const bool ok = kv && gcol[sl] >= 0 && (sl == 0 || has_extra);
-      const uint32_t ob = ok ? voff(gcol[sl], k) : kOOR;
-      const unsigned mv = bmask(gcol[sl], k, ok);
-      S.m[sl] = ok ? mv : 7u;
-      bload3(rs_r, ob, S.r[sl]);
-      bload3(rs_s, ob, S.s[sl]);
-      bload3(rs_d, ob, S.d[sl]);
-      bload3(rs_p, ob, S.p[sl]);
-      if (sl == 0) bload3(rs_x, (own_plane && writer && ok) ? ob : kOOR, S.x);  // used by the owner only
-    }
+    const uint32_t so1 = kv ? splane(k) : 0u, so3 = (uint32_t)(3 * sizeof(T)) * so1;
+    const uint32_t o3 = kv ? vc3 : kOOR;
+    S.m = bmask(kv ? vc1 : kOOR, so1);
+    bload3(rs_r, o3, so3, S.r);
+    bload3(rs_s, o3, so3, S.s);
+    bload3(rs_d, o3, so3, S.d);
+    bload3(rs_p, o3, so3, S.p);
+    bload3(rs_x, kv && own_plane ? vw3 : kOOR, so3, S.x);  // used by the owner only
   };
   // zq: the node's p' (unmasked: the output of a fixed DOF); dq: its D^-1
   auto stage_f = [&](const FusedStage<T>& S, int buf, int k, T (&zq)[3], T (&dq)[3]) {
-    T* nb = nodes + buf * (3 * NS);
+    T* nb = nodes + buf * (3 * NS) + 3 * li[0];
     const bool own_plane = k >= k0 && k < kend;
+    // the owner's byte offset; other threads store out of range (dropped)
+    const uint32_t o3 = own_plane ? vw3 : kOOR, so3 = own_plane ? s3(k) : 0u;
+    T xn[3], rn[3], pn[3], rz = (T)0, rr = (T)0;
 #pragma unroll
-    for (int sl = 0; sl < kSlots; ++sl) {
-      const bool owner = sl == 0 && writer && own_plane;  // the owner's node index is valid
-      // the owner's byte offset; other threads store out of range (dropped)
-      const uint32_t ob = owner ? voff(gcol[0], k) : kOOR;
-      T xn[3], rn[3], pn[3];
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        rn[c] = S.r[sl][c] - al * S.s[sl][c];
-        const T zn = S.d[sl][c] * rn[c];
-        pn[c] = zn + be * S.p[sl][c];
-        if (sl == 0 || has_extra) nb[c * NS + li[sl]] = ((S.m[sl] >> c) & 1u) ? (T)0 : pn[c];
-        if (sl == 0) {
-          zq[c] = pn[c];
-          dq[c] = S.d[sl][c];
-          xn[c] = S.x[c] + al * S.p[sl][c];
-          if (owner) {
-            tpart[0][0] += rn[c] * zn;     // r.z
-            if constexpr (RR) tpart[0][1] += rn[c] * rn[c];  // r.r
-          }
-        }
-      }
-      if (sl == 0) {
-        bstore3(rs_xo, ob, xn);
-        bstore3(rs_ro, ob, rn);
-        bstore3(rs_po, ob, pn);
-      }
+    for (int c = 0; c < 3; ++c) {
+      rn[c] = S.r[c] - al * S.s[c];
+      const T zn = S.d[c] * rn[c];
+      pn[c] = zn + be * S.p[c];
+      nb[c] = zmasked(S.m, c, pn[c]);
+      zq[c] = pn[c];
+      dq[c] = S.d[c];
+      xn[c] = S.x[c] + al * S.p[c];
+      rz += rn[c] * zn;
+      if constexpr (RR) rr += rn[c] * rn[c];
     }
+    const bool owner = writer && own_plane;
+    tpart[0][0] += owner ? rz : (T)0;                    // r.z
+    if constexpr (RR) tpart[0][1] += owner ? rr : (T)0;  // r.r
+    bstore3(rs_xo, o3, so3, xn);
+    bstore3(rs_ro, o3, so3, rn);
+    bstore3(rs_po, o3, so3, pn);
   };
 
   // fused MINRES step: the scalar recurrence of iteration t (every block,
@@ -698,59 +722,44 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
   auto issue_m = [&](int k, MinresStage<T>& S) {
     const bool kv = k >= 0 && k <= kend && k <= G.nz;  // planes the block reads
     const bool own_plane = k >= k0 && k < kend;
-#pragma unroll
-    for (int sl = 0; sl < kSlots; ++sl) {
-      const bool ok = kv && gcol[sl] >= 0 && (sl == 0 || has_extra);
-      const uint32_t ob = ok ? voff(gcol[sl], k) : kOOR;
-      const unsigned mv = bmask(gcol[sl], k, ok);
-      S.m[sl] = ok ? mv : 7u;
-      bload3(rs_mY, ob, S.y[sl]);
-      bload3(rs_mR1, ob, S.r1[sl]);
-      bload3(rs_mR2, ob, S.r2[sl]);
-      if (sl == 0) {  // the iterate and the directions: owner only
-        const uint32_t oo = (own_plane && writer && ok) ? ob : kOOR;
-        bload3(rs_mW, oo, S.w);
-        bload3(rs_mW2, oo, S.w2);
-        bload3(rs_mx, oo, S.x);
-      }
-    }
+    const uint32_t so1 = kv ? splane(k) : 0u, so3 = (uint32_t)(3 * sizeof(T)) * so1;
+    const uint32_t o3 = kv ? vc3 : kOOR, oo = kv && own_plane ? vw3 : kOOR;
+    S.m = bmask(kv ? vc1 : kOOR, so1);
+    bload3(rs_mY, o3, so3, S.y);
+    bload3(rs_mR1, o3, so3, S.r1);
+    bload3(rs_mR2, o3, so3, S.r2);
+    bload3(rs_mW, oo, so3, S.w);  // the iterate and the directions: owner only
+    bload3(rs_mW2, oo, so3, S.w2);
+    bload3(rs_mx, oo, so3, S.x);
   };
   auto stage_m = [&](const MinresStage<T>& S, int buf, int k, T (&zq)[3]) {
-    T* nb = nodes + buf * (3 * NS);
+    T* nb = nodes + buf * (3 * NS) + 3 * li[0];
     const bool own_plane = k >= k0 && k < kend;
     const int itn = A.step;
+    T yn[3], wn[3], xn[3];
+    double yy = 0.0, ry = 0.0;
 #pragma unroll
-    for (int sl = 0; sl < kSlots; ++sl) {
-      T yn[3];
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        const T r1m = itn >= 2 ? S.r1[sl][c] : (T)0;  // R1 holds no vector yet on the first iteration
-        yn[c] = ms * S.y[sl][c] - mc1 * r1m - mas * S.r2[sl][c];
-        if (sl == 0 || has_extra) nb[c * NS + li[sl]] = ((S.m[sl] >> c) & 1u) ? (T)0 : yn[c];
-      }
-      if (sl == 0) {
-        const bool owner = writer && own_plane;
-        const uint32_t ob = owner ? voff(gcol[0], k) : kOOR;
-        T wn[3], xn[3];
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-          zq[c] = yn[c];  // unmasked: the output of a fixed DOF
-          const T wm = itn >= 3 ? S.w[c] : (T)0, w2m = itn >= 4 ? S.w2[c] : (T)0;
-          wn[c] = (S.r1[0][c] * minvb - mwc1 * w2m - mwc2 * wm) * minvg;
-          xn[c] = S.x[c] + mstep * wn[c];
-          if constexpr (NP >= 3) {
-            if (owner) {
-              part[0] += (double)yn[c] * (double)yn[c];        // ||y||^2
-              part[2] += (double)S.r2[0][c] * (double)yn[c];   // <R2, y>: R1.R2 of iteration t + 1
-            }
-          }
-        }
-        bstore3(rs_mR3, ob, yn);
-        if (itn >= 2) {  // finishes iteration t - 1 (uniform)
-          bstore3(rs_mW2, ob, wn);
-          bstore3(rs_mx, ob, xn);
-        }
-      }
+    for (int c = 0; c < 3; ++c) {
+      const T r1m = itn >= 2 ? S.r1[c] : (T)0;  // R1 holds no vector yet on the first iteration
+      yn[c] = ms * S.y[c] - mc1 * r1m - mas * S.r2[c];
+      nb[c] = zmasked(S.m, c, yn[c]);
+      zq[c] = yn[c];  // unmasked: the output of a fixed DOF
+      const T wm = itn >= 3 ? S.w[c] : (T)0, w2m = itn >= 4 ? S.w2[c] : (T)0;
+      wn[c] = (S.r1[c] * minvb - mwc1 * w2m - mwc2 * wm) * minvg;
+      xn[c] = S.x[c] + mstep * wn[c];
+      yy += (double)yn[c] * (double)yn[c];
+      ry += (double)S.r2[c] * (double)yn[c];
+    }
+    const bool owner = writer && own_plane;
+    if constexpr (NP >= 3) {
+      part[0] += owner ? yy : 0.0;  // ||y||^2
+      part[2] += owner ? ry : 0.0;  // <R2, y>: R1.R2 of iteration t + 1
+    }
+    const uint32_t oo = own_plane ? vw3 : kOOR, so3 = own_plane ? s3(k) : 0u;
+    bstore3(rs_mR3, oo, so3, yn);
+    if (itn >= 2) {  // finishes iteration t - 1 (uniform)
+      bstore3(rs_mW2, oo, so3, wn);
+      bstore3(rs_mx, oo, so3, xn);
     }
   };
 
@@ -781,9 +790,9 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
       for (int c = 0; c < 3; ++c) carry[r][q][c] = (T)0;
 
   // prologue: planes ez0, ez0 + 1 staged (and, unfused, plane ez0 + 2 in flight)
-  unsigned mq;     // masks of the own node, plane ez in byte 0, ez + 1 in byte 1, ..
-  T rq[3][NR][3];  // unmasked input value of the own node, planes ez, ez + 1, ez + 2
-  T dq[3][3];      // CGF: its D^-1, the same planes
+  unsigned mq[2];  // mask of the own node, by parity of the plane from ez0
+  T rq[2][NR][3];  // its unmasked input value
+  T dq[2][3];      // CGF: its D^-1
   T rho_next;
   // residual, CG and Lanczos modes: values of the own node read only at its
   // output (RESID: f and D^-1 (or f again); CG: D^-1; LZ: r), loaded one
@@ -801,17 +810,17 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
   }
   const __amdgpu_buffer_rsrc_t rs_do = dres(A.invD_out);
   auto load_own = [&](int k, T (&q)[NR][2][3]) {
-    const bool ok = gcol[0] >= 0 && k < kend;  // planes this block outputs
-    const uint32_t ob = ok ? voff(gcol[0], k) : kOOR;
+    const bool ok = k >= k0 && k < kend;  // planes this block outputs
+    const uint32_t o3 = ok ? vw3 : kOOR, so3 = ok ? s3(k) : 0u;
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
       if constexpr (MODE == MODE_RESID) {
-        bload3(rs_f[r], ob, q[r][0]);
-        bload3(rs_d, A.invD ? ob : kOOR, q[r][1]);
+        bload3(rs_f[r], o3, so3, q[r][0]);
+        bload3(rs_d, A.invD ? o3 : kOOR, so3, q[r][1]);
       } else if constexpr (MODE == MODE_CG) {
-        bload3(rs_d, ob, q[r][0]);
+        bload3(rs_d, o3, so3, q[r][0]);
       } else {
-        bload3(rs_cr[r], ob, q[r][0]);
+        bload3(rs_cr[r], o3, so3, q[r][0]);
       }
     }
   };
@@ -822,9 +831,9 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
     issue_f(ez0 + 1, SF1);
     cg_prologue();
     stage_f(SF, ez0 & 1, ez0, rq[0][0], dq[0]);
-    mq = SF.m[0] & 0xffu;
+    mq[0] = SF.m;
     stage_f(SF1, (ez0 + 1) & 1, ez0 + 1, rq[1][0], dq[1]);
-    mq |= (SF1.m[0] & 0xffu) << 8;
+    mq[1] = SF1.m;
   } else if constexpr (MODE == MODE_MRF) {
     MinresStage<T> SM1;
     issue_m(ez0, SM);
@@ -832,15 +841,16 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
     issue_m(ez0 + 1, SM1);
     mrf_prologue();
     stage_m(SM, ez0 & 1, ez0, rq[0][0]);
-    mq = SM.m[0] & 0xffu;
+    mq[0] = SM.m;
     stage_m(SM1, (ez0 + 1) & 1, ez0 + 1, rq[1][0]);
-    mq |= (SM1.m[0] & 0xffu) << 8;
+    mq[1] = SM1.m;
   } else {
     issue(ez0, S[0]);
     issue(ez0 + 1, S[1]);
     stage(S[0], ez0 & 1);
     stage(S[1], (ez0 + 1) & 1);
-    mq = (S[0].m[0] & 0xffu) | ((S[1].m[0] & 0xffu) << 8);
+    mq[0] = S[0].m[0];
+    mq[1] = S[1].m[0];
 #pragma unroll
     for (int r = 0; r < NR; ++r)
 #pragma unroll
@@ -854,6 +864,10 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
     if constexpr (kOwnQ) load_own(ez0, oq[0]);
     issue(ez0 + 2, S[0]);
   }
+  // the three corner values of the neighbouring columns around the own node
+  // (a thread that owns none reads its own slot)
+  const int tl1 = writer ? tid - 1 : tl, tlb = writer ? tid - TW : tl, tlbb = writer ? tid - TW - 1 : tl;
+  const int cr1 = 9 * tl1, crb = 9 * tlb + 3, crbb = 9 * tlbb + 6;
   T s_below = (T)0;  // s of the element below (diagonal of the residual mode)
   __syncthreads();
   read_face(ez0 & 1, F[0]);
@@ -888,44 +902,47 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
         for (int a = 1; a < 4; ++a)
 #pragma unroll
           for (int c = 0; c < 3; ++c)
-            corners[((cb * NR + r) * 9 + (a - 1) * 3 + c) * TS + tid] = out[r][a][c];
+            corners[((cb * NR + r) * TS + tid) * 9 + (a - 1) * 3 + c] = out[r][a][c];
       if constexpr (MODE == MODE_RESID) {
         if (A.invD_out) dcorn[cb * TS + tid] = dcol;
       }
     }
+    // the staged plane's values of the own node: into the slot that this
+    // layer's output leaves
+    T nq[NR][3], nd[3];
+    unsigned nm;
     if constexpr (MODE == MODE_CGF) {
-      stage_f(SF, ez & 1, ez + 2, rq[2][0], dq[2]);
-      mq |= (SF.m[0] & 0xffu) << 16;
+      stage_f(SF, ez & 1, ez + 2, nq[0], nd);
+      nm = SF.m;
     } else if constexpr (MODE == MODE_MRF) {
-      stage_m(SM, ez & 1, ez + 2, rq[2][0]);
-      mq |= (SM.m[0] & 0xffu) << 16;
+      stage_m(SM, ez & 1, ez + 2, nq[0]);
+      nm = SM.m;
     } else {
       stage(S[P], ez & 1);
-      mq |= (S[P].m[0] & 0xffu) << 16;
+      nm = S[P].m[0];
 #pragma unroll
       for (int r = 0; r < NR; ++r)
 #pragma unroll
-        for (int c = 0; c < 3; ++c) rq[2][r][c] = S[P].v[0][r][c];
+        for (int c = 0; c < 3; ++c) nq[r][c] = S[P].v[0][r][c];
     }
     __syncthreads();
     {
       // every thread runs the output code; a thread that owns no output node
       // reads its own LDS slots, loads and stores out of range
       const bool wr = emit && writer;
-      const int n = wr ? gcol[0] + ez * plane : 0;
-      const uint32_t ob = wr ? voff(gcol[0], ez) : kOOR;
-      const unsigned m = wr ? (mq & 0xffu) : 0u;
-      const int tl1 = wr ? tid - 1 : tl, tlb = wr ? tid - TW : tl, tlbb = wr ? tid - TW - 1 : tl;
+      const uint32_t o3 = emit ? vw3 : kOOR, so3 = emit ? s3(ez) : 0u;
+      const unsigned m = wr ? mq[P] : 0u;
 #pragma unroll
       for (int r = 0; r < NR; ++r) {
         const T* cr = corners + (cb * NR + r) * 9 * TS;
         T acc[3], pv[3];
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-          acc[c] = ((out[r][0][c] + cr[(0 + c) * TS + tl1]) + cr[(3 + c) * TS + tlb]) + cr[(6 + c) * TS + tlbb];
-          pv[c] = rq[0][r][c];  // the input value at this node, as staged
+          acc[c] = ((out[r][0][c] + cr[cr1 + c]) + cr[crb + c]) + cr[crbb + c];
+          pv[c] = rq[P][r][c];  // the input value at this node, as staged
         }
         if (m) {  // springs, then identity rows of fixed DOFs (rare nodes)
+          const int n = gcol[0] + ez * plane;
           if (m & 8u) {
             for (int sI = 0; sI < A.nspring; ++sI) {
               const int64_t d = A.sdof[sI] - (int64_t)3 * n;
@@ -952,8 +969,8 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
               dl[c] = oq[P][r][1][c];
             }
           } else {
-            bload3(rs_f[r], ob, fv);
-            bload3(rs_d, A.invD ? ob : kOOR, dl);
+            bload3(rs_f[r], o3, so3, fv);
+            bload3(rs_d, A.invD ? o3 : kOOR, so3, dl);
           }
           const T D = ((dcol + dcorn[cb * TS + tl1]) + dcorn[cb * TS + tlb]) + dcorn[cb * TS + tlbb];
           // Jacobi diagonal: ke_diag * sum of s over the node's 8 elements,
@@ -971,7 +988,7 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
                 T d = d0;
                 if (m & 8u)
                   for (int sI = 0; sI < A.nspring; ++sI)
-                    if (A.sdof[sI] == (int64_t)(3 * n + c)) d += A.sk[sI];
+                    if (A.sdof[sI] == (int64_t)(3 * (gcol[0] + ez * plane) + c)) d += A.sk[sI];
                 if ((m >> c) & 1u) d = (T)1;
                 di = d > (T)0 ? (T)1 / d : (T)0;
               }
@@ -981,58 +998,64 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
             }
             zv[c] = dv[c] * rv[c];
           }
-          bstore3(rs_y[r], ob, rv);
-          bstore3(rs_z[r], zout ? ob : kOOR, zv);
-          if (A.invD_out) bstore3(rs_do, ob, dv);
+          bstore3(rs_y[r], o3, so3, rv);
+          bstore3(rs_z[r], zout ? o3 : kOOR, so3, zv);
+          if (A.invD_out) bstore3(rs_do, o3, so3, dv);
+          T rr = (T)0, rm = (T)0, ff = (T)0, rz = (T)0;
 #pragma unroll
           for (int c = 0; c < 3; ++c) {
-            tpart[r][0] += own_t(rv[c] * rv[c]);
-            tpart[r][1] = fmax(tpart[r][1], own_t(fabs(rv[c])));
-            tpart[r][2] += own_t(fv[c] * fv[c]);
-            tpart[r][3] += own_t(rv[c] * zv[c]);
+            rr += rv[c] * rv[c];
+            rm = fmax(rm, fabs(rv[c]));
+            ff += fv[c] * fv[c];
+            rz += rv[c] * zv[c];
           }
+          tpart[r][0] += own_t(rr);
+          tpart[r][1] = fmax(tpart[r][1], own_t(rm));
+          tpart[r][2] += own_t(ff);
+          tpart[r][3] += own_t(rz);
         } else {
-          bstore3(rs_y[r], ob, acc);
+          bstore3(rs_y[r], o3, so3, acc);
           if constexpr (MODE == MODE_CG || MODE == MODE_LZ) {
             T q3[3];  // CG: D^-1; LZ: the paired vector
             if constexpr (kOwnQ) {
 #pragma unroll
               for (int c = 0; c < 3; ++c) q3[c] = oq[P][r][0][c];
             } else {
-              bload3(MODE == MODE_CG ? rs_d : rs_cr[r], ob, q3);
+              bload3(MODE == MODE_CG ? rs_d : rs_cr[r], o3, so3, q3);
             }
+            double yu = 0.0, ru = 0.0;
+            T ss = (T)0;
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
-              part[4 * r + 1] += own_only((double)acc[c] * (double)pv[c]);  // p.s / y.u
-              if constexpr (MODE == MODE_CG) tpart[r][2] += own_t(acc[c] * (q3[c] * acc[c]));  // s.D^-1 s
-              else part[4 * r] += own_only((double)q3[c] * (double)pv[c]);                     // r.u
+              yu += (double)acc[c] * (double)pv[c];
+              if constexpr (MODE == MODE_CG) ss += acc[c] * (q3[c] * acc[c]);
+              else ru += (double)q3[c] * (double)pv[c];
             }
+            part[4 * r + 1] += own_only(yu);  // p.s / y.u
+            if constexpr (MODE == MODE_CG) tpart[r][2] += own_t(ss);  // s.D^-1 s
+            else part[4 * r] += own_only(ru);                         // r.u
           }
           if constexpr (MODE == MODE_CGF || MODE == MODE_MRF) {
+            double yu = 0.0;
 #pragma unroll
-            for (int c = 0; c < 3; ++c) part[1] += own_only((double)acc[c] * (double)pv[c]);  // p'.s' / <K y, y>
+            for (int c = 0; c < 3; ++c) yu += (double)acc[c] * (double)pv[c];
+            part[1] += own_only(yu);  // p'.s' / <K y, y>
           }
           if constexpr (MODE == MODE_CGF) {
+            T ss = (T)0;
 #pragma unroll
-            for (int c = 0; c < 3; ++c) tpart[0][2] += own_t(acc[c] * (dq[0][c] * acc[c]));  // s'.D^-1 s'
+            for (int c = 0; c < 3; ++c) ss += acc[c] * (dq[P][c] * acc[c]);
+            tpart[0][2] += own_t(ss);  // s'.D^-1 s'
           }
         }
       }
     }
-    mq >>= 8;
+    mq[P] = nm;
 #pragma unroll
-    for (int r = 0; r < NR; ++r)
+    for (int c = 0; c < 3; ++c) {
 #pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        rq[0][r][c] = rq[1][r][c];
-        rq[1][r][c] = rq[2][r][c];
-      }
-    if constexpr (MODE == MODE_CGF) {
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        dq[0][c] = dq[1][c];
-        dq[1][c] = dq[2][c];
-      }
+      for (int r = 0; r < NR; ++r) rq[P][r][c] = nq[r][c];
+      if constexpr (MODE == MODE_CGF) dq[P][c] = nd[c];
     }
   };
   for (int ez = ez0; ez < kend; ez += 2) {
@@ -1116,9 +1139,9 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
 // ===========================================================================
 template <typename T>
 struct SensStage {
-  T x[2][3], p[2][3];   // every staged node
+  T x[3], p[3];         // every staged node
   T r[3], s[3], f[3];   // owned node only
-  unsigned m[2];
+  unsigned m;
 };
 
 template <typename T>
@@ -1132,9 +1155,8 @@ __global__ void __launch_bounds__(kApplyMaxThreads)
   const int BX = A.bx, BY = A.by;
   const int NW = BX + 1;
   const int NS = NW * (BY + 1);
-  T* nodes = reinterpret_cast<T*>(apply_smem);  // [2][3][NS]
+  T* nodes = reinterpret_cast<T*>(apply_smem);  // [2][NS][3]
   // one thread per node column of the tile (the node layout of k_apply)
-  constexpr int kSlots = 1;
   const int tid = threadIdx.x;
   const bool live = tid < NS;
   const int tl = live ? tid : 0;
@@ -1156,17 +1178,15 @@ __global__ void __launch_bounds__(kApplyMaxThreads)
   // at the block's first plane ez0: a plane past the slab or a thread that
   // owns no node gets an out-of-range offset, so its loads return 0 and its
   // stores are dropped, with no branch around them.
-  constexpr bool has_extra = false;
-  int li[2], gcol[2];
-  li[0] = tl;  // padding threads stage thread 0's node again (the same value into the same slot)
-  gcol[0] = (ex >= 0 && ex <= G.nx && ey >= 0 && ey <= G.ny) ? ex + G.nxn * ey : -1;
-  li[1] = li[0];
-  gcol[1] = gcol[0];
+  const int li = 3 * tl;  // padding threads stage thread 0's node again (the same value into the same slot)
+  const bool col = ex >= 0 && ex <= G.nx && ey >= 0 && ey <= G.ny;
+  const uint32_t vc1 = col ? (uint32_t)(ex + G.nxn * ey) : kOOR;
+  const uint32_t vc3 = col ? (uint32_t)(3 * sizeof(T)) * vc1 : kOOR;
+  const uint32_t vw3 = writer ? vc3 : kOOR;  // the node a thread owns
+  const uint32_t ve = elem_owner ? (uint32_t)sizeof(T) * (uint32_t)(ex + G.nx * ey) : kOOR;  // its element
   const int64_t pbase = (int64_t)ez0 * plane;  // first node of plane ez0
   auto vres = [&](const T* v) { return zrsrc(v ? v + 3 * pbase : v); };
-  auto voff = [&](int col, int k) -> uint32_t {
-    return (uint32_t)(3 * sizeof(T)) * (uint32_t)(col + (k - ez0) * plane);
-  };
+  auto splane = [&](int k) -> uint32_t { return (uint32_t)(k - ez0) * (uint32_t)plane; };
   const __amdgpu_buffer_rsrc_t rs_m = zrsrc(A.mask + pbase), rs_x = vres(A.xi), rs_r = vres(A.ri),
                                rs_p = vres(A.pi), rs_s = vres(A.si), rs_f = vres(A.fvec), rs_xo = vres(A.xo);
   const int64_t ebase = (int64_t)ez0 * G.nx * G.ny;  // first element of layer ez0
@@ -1193,72 +1213,60 @@ __global__ void __launch_bounds__(kApplyMaxThreads)
   // r'.r', max|r'|, f.x', and the sum of the block's element sensitivities
   double part[4] = {0.0, 0.0, 0.0, 0.0};
 
-  auto owns = [&](int k) { return k >= 0 && k <= G.nz && writer && k >= k0 && k < kend; };
+  auto owns = [&](int k) { return k >= 0 && k <= G.nz && k >= k0 && k < kend; };  // the block's planes
   auto issue = [&](int k, SensStage<T>& S) {
     const bool kv = k >= 0 && k <= kend && k <= G.nz;  // planes past kend are never read
-#pragma unroll
-    for (int sl = 0; sl < kSlots; ++sl) {
-      const bool ok = kv && gcol[sl] >= 0 && (sl == 0 || has_extra);
-      const uint32_t off = ok ? voff(gcol[sl], k) : kOOR;
-      const unsigned mv = __builtin_amdgcn_raw_buffer_load_b8(rs_m, ok ? (uint32_t)(gcol[sl] + (k - ez0) * plane) : kOOR, 0, 0);
-      S.m[sl] = ok ? mv : 7u;
-      zload3<T>(rs_x, off, S.x[sl]);
-      zload3<T>(rs_p, off, S.p[sl]);
-      if (sl == 0) {  // used by the owner only
-        const uint32_t oo = owns(k) ? off : kOOR;
-        zload3<T>(rs_r, oo, S.r);
-        zload3<T>(rs_s, oo, S.s);
-        zload3<T>(rs_f, A.fvec ? oo : kOOR, S.f);
-      }
-    }
+    const uint32_t so1 = kv ? splane(k) : 0u, so3 = (uint32_t)(3 * sizeof(T)) * so1;
+    const uint32_t o3 = kv ? vc3 : kOOR, oo = owns(k) ? vw3 : kOOR;
+    S.m = __builtin_amdgcn_raw_buffer_load_b8(rs_m, kv ? vc1 : kOOR, so1, 0);
+    zload3<T>(rs_x, o3, so3, S.x);
+    zload3<T>(rs_p, o3, so3, S.p);
+    zload3<T>(rs_r, oo, so3, S.r);  // used by the owner only
+    zload3<T>(rs_s, oo, so3, S.s);
+    zload3<T>(rs_f, A.fvec ? oo : kOOR, so3, S.f);
   };
   auto stage = [&](const SensStage<T>& S, int buf, int k) {
-    T* nb = nodes + buf * (3 * NS);
-    const bool own = owns(k);
+    T* nb = nodes + buf * (3 * NS) + li;
+    const bool ok = owns(k);
+    T xn[3];
+    double rr = 0.0, rm = 0.0, fx = 0.0;
 #pragma unroll
-    for (int sl = 0; sl < kSlots; ++sl) {
-      T xn[3];
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        xn[c] = S.x[sl][c] + al * S.p[sl][c];
-        if (sl == 0 || has_extra) nb[c * NS + li[sl]] = ((S.m[sl] >> c) & 1u) ? (T)0 : xn[c];
-      }
-      if (sl == 0) {
-        zstore3<T>(rs_xo, own ? voff(gcol[0], k) : kOOR, xn);
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-          const T rn = S.r[c] - al * S.s[c];
-          part[0] += own ? (double)rn * (double)rn : 0.0;
-          part[1] = fmax(part[1], own ? fabs((double)rn) : 0.0);
-          part[2] += own ? (double)S.f[c] * (double)xn[c] : 0.0;
-        }
-      }
+    for (int c = 0; c < 3; ++c) {
+      xn[c] = S.x[c] + al * S.p[c];
+      nb[c] = zmasked(S.m, c, xn[c]);
+      const T rn = S.r[c] - al * S.s[c];
+      rr += (double)rn * (double)rn;
+      rm = fmax(rm, fabs((double)rn));
+      fx += (double)S.f[c] * (double)xn[c];
     }
+    zstore3<T>(rs_xo, ok ? vw3 : kOOR, ok ? (uint32_t)(3 * sizeof(T)) * splane(k) : 0u, xn);
+    const bool own = ok && writer;
+    part[0] += own ? rr : 0.0;
+    part[1] = fmax(part[1], own ? rm : 0.0);
+    part[2] += own ? fx : 0.0;
   };
   // the lower-left node of the thread's element (node 0's for threads
   // without an element: their reads stay inside the plane)
-  const int lf = (live && tx < BX && ty < BY) ? li[0] : 0;
+  const int lf = (live && tx < BX && ty < BY) ? li : 0;
   auto read_face = [&](int buf, T (&F)[4][3]) {
-    const T* nb = nodes + buf * (3 * NS);
-    const int o4[4] = {0, 1, NW, NW + 1};
+    const T* nb = nodes + buf * (3 * NS) + lf;
     T u4[4][3];
 #pragma unroll
     for (int a = 0; a < 4; ++a)
 #pragma unroll
-      for (int c = 0; c < 3; ++c) u4[a][c] = nb[c * NS + lf + o4[a]];
+      for (int c = 0; c < 3; ++c) u4[a][c] = nb[3 * (a >> 1) * NW + 3 * (a & 1) + c];
     face_modes(u4, F);
   };
-  // byte offset of the element of layer ez in this thread's column (kOOR if
-  // the element is not this block's)
-  auto eoff = [&](int ez) -> uint32_t {
-    const bool el = elem_owner && ez >= k0 && ez < elem_end;
-    return el ? (uint32_t)sizeof(T) * (uint32_t)(ex + G.nx * (ey + G.ny * (ez - ez0))) : kOOR;
+  // scalar byte offset of an element layer; a layer that is not the block's is out of range
+  auto eown = [&](int ez) { return ez >= k0 && ez < elem_end; };
+  auto eso = [&](int ez) -> uint32_t {
+    return eown(ez) ? (uint32_t)sizeof(T) * (uint32_t)((ez - ez0) * (G.nx * G.ny)) : 0u;
   };
   // density and 1/Hs of the element of a layer, loaded a layer ahead
   auto load_elem = [&](int ez, T (&v)[2]) {
-    const uint32_t off = eoff(ez);
-    v[0] = zload1<T>(rs_rho, off);
-    const T hv = zload1<T>(rs_hs, A.Hsi ? off : kOOR);
+    const uint32_t vo = eown(ez) ? ve : kOOR, so = eso(ez);
+    v[0] = zload1<T>(rs_rho, vo, so);
+    const T hv = zload1<T>(rs_hs, A.Hsi ? vo : kOOR, so);
     v[1] = A.Hsi ? hv : (T)1;
   };
 
@@ -1303,7 +1311,7 @@ __global__ void __launch_bounds__(kApplyMaxThreads)
 #pragma unroll
         for (int q = 1; q < 8; ++q) en += (double)c[i][q] * (double)z[i][q];
       const double dc = -(double)simp_ds<T>(ev[P][0], A.sp) * en;  // d objective / d rho_e
-      zstore1<T>(rs_do, eoff(ez), (T)(dc * (double)ev[P][1]));
+      zstore1<T>(rs_do, eown(ez) ? ve : kOOR, eso(ez), (T)(dc * (double)ev[P][1]));
       // The filter weights are symmetric, so the filtered gradient
       // H^T (dc / Hs) sums to sum_e dc_e: its mean for the step, formed here.
       part[3] += (elem_owner && ez >= k0 && ez < elem_end) ? dc : 0.0;
