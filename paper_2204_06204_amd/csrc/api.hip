@@ -244,7 +244,7 @@ fbto_status_t pcg_run(fbto_grid_s* g, const T* rho, const T* f, T* x, int nrhs, 
                       double rtol, hipStream_t st, bool f_dot, CgCounts* cn_out, T* sens = nullptr,
                       const T* sens_hsi = nullptr, bool* sens_done = nullptr) {
   Vecs& V = vecs<T>(g);
-  T* invD = (T*)V.invD;
+  T* invD = (T*)V.invD;  // (plane grids)
   // the iterate of step k: the caller's vector (k = 0), then x1 and x2 in turn
   auto set_of = [&](int k) {
     return CgSet<T>{k == 0 ? x : (T*)((k & 1) ? V.x1 : V.x2), (T*)V.r[k & 1], (T*)V.p[k & 1], (T*)V.s[k & 1]};
@@ -252,7 +252,7 @@ fbto_status_t pcg_run(fbto_grid_s* g, const T* rho, const T* f, T* x, int nrhs, 
   const CgSet<T> set0 = set_of(0);
   int nb_r = 0, nb_a = 0, nb_v = 0;
   // r = f - K x and the first direction p = z = D^-1 r
-  HIP_TRY(launch_resid_diag<T>(g, rho, x, f, set0.r, invD, set0.p, nrhs, st, &nb_r));
+  HIP_TRY(launch_resid_diag<T>(g, rho, x, f, set0.r, set0.p, nrhs, st, &nb_r));
   CgCounts cn{nb_r, nb_r, vec_blocks(g->geo.ndof)};
   if (steps == 0) {
     if (f_dot) HIP_TRY(launch_dot<T>(g, f, x, nrhs, st));
@@ -268,7 +268,7 @@ fbto_status_t pcg_run(fbto_grid_s* g, const T* rho, const T* f, T* x, int nrhs, 
     return FBTO_OK;
   };
   // step 0's product s = K p
-  HIP_TRY(launch_apply_cg<T>(g, rho, set0.p, invD, set0.s, nrhs, 0, st, &nb_a));
+  HIP_TRY(launch_apply_cg<T>(g, rho, set0.p, set0.s, nrhs, 0, st, &nb_a));
   CgCnt pc{nb_r, nb_a, nb_r};
   // voxel grids: fused steps (the update of step k and the product of step
   // k + 1 in one pass); plane grids: unfused (vector update, then the product)
@@ -276,11 +276,11 @@ fbto_status_t pcg_run(fbto_grid_s* g, const T* rho, const T* f, T* x, int nrhs, 
   int k = 0;
   for (; k + 1 < steps; ++k) {
     if (fused) {
-      HIP_TRY(launch_cg_fused<T>(g, rho, set_of(k), set_of(k + 1), invD, nrhs, k, pc, rtol, st, &nb_a));
+      HIP_TRY(launch_cg_fused<T>(g, rho, set_of(k), set_of(k + 1), nrhs, k, pc, rtol, st, &nb_a));
       pc.gam = pc.apply = nb_a;
     } else {
       HIP_TRY(launch_cg_step<T>(g, x, x, set0.r, set0.s, set0.p, invD, nullptr, nrhs, k, false, pc, rtol, st, &nb_v));
-      HIP_TRY(launch_apply_cg<T>(g, rho, set0.p, invD, set0.s, nrhs, k + 1, st, &nb_a));
+      HIP_TRY(launch_apply_cg<T>(g, rho, set0.p, set0.s, nrhs, k + 1, st, &nb_a));
       pc.gam = nb_v;
       pc.apply = nb_a;
     }
@@ -323,10 +323,9 @@ fbto_status_t pcg_solve(fbto_grid_s* g, const T* rho, const T* f, T* u, int nrhs
 
 // r = f - K u with its norms (into the scalars)
 template <typename T>
-fbto_status_t residual_norms(fbto_grid_s* g, const T* rho, const T* u, const T* f, T* r, const T* invD, int nrhs,
-                             hipStream_t st) {
+fbto_status_t residual_norms(fbto_grid_s* g, const T* rho, const T* u, const T* f, T* r, int nrhs, hipStream_t st) {
   int nb = 0;
-  HIP_TRY(launch_resid<T>(g, rho, u, f, r, invD, (T*)vecs<T>(g).p[0], nrhs, st, &nb));
+  HIP_TRY(launch_resid<T>(g, rho, u, f, r, 1, nrhs, st, &nb));
   HIP_TRY(launch_pcg_finish(g, nrhs, nb, nb, nullptr, 0, 0, 0, st));
   return FBTO_OK;
 }
@@ -339,10 +338,10 @@ fbto_status_t relax_run(fbto_grid_s* g, const T* rho, const T* f, T* u, int nrhs
   T* invD = (T*)V.invD;
   HIP_TRY(launch_diag<T>(g, rho, invD, st));
   for (int s = 0; s < steps; ++s) {
-    HIP_TRY(launch_resid<T>(g, rho, u, f, r, (const T*)nullptr, (T*)nullptr, nrhs, st, nullptr));
+    HIP_TRY(launch_resid<T>(g, rho, u, f, r, 0, nrhs, st, nullptr));
     HIP_TRY(launch_relax_update<T>(g, u, r, invD, nrhs, omega, use_diag, st));
   }
-  return residual_norms<T>(g, rho, u, f, r, invD, nrhs, st);
+  return residual_norms<T>(g, rho, u, f, r, nrhs, st);
 }
 
 // One low-level step of Alg. 3 with the Krylov preconditioner of degree D
@@ -364,7 +363,7 @@ fbto_status_t krylov_run(fbto_grid_s* g, const T* rho, const T* f, T* u, int nrh
     T* R2 = (T*)V.r[0];
     T* Wc = (T*)V.p[0];
     T* W2 = (T*)V.p[1];
-    HIP_TRY(launch_resid<T>(g, rho, x, fr, R2, (const T*)nullptr, (T*)nullptr, 1, st, nullptr));  // R2 = f - K u
+    HIP_TRY(launch_resid<T>(g, rho, x, fr, R2, 0, 1, st, nullptr));  // R2 = f - K u
     int nb_v = 0, nb_a = 0;
     HIP_TRY(launch_minres<T>(g, 0, last, Y, R1, R2, W2, Wc, x, 0, 0, damp, st, &nb_v));
     int itn0 = 1;
@@ -406,10 +405,9 @@ fbto_status_t krylov_run(fbto_grid_s* g, const T* rho, const T* f, T* u, int nrh
     }
     HIP_TRY(launch_minres<T>(g, last, last, Y, R1, R2, W2, Wc, x, 0, nb_v, damp, st, nullptr));
   }
-  // the final residual and its norms; the residual kernel forms the Jacobi
-  // diagonal on the way (its partials are written when it forms or reads one)
+  // the norms of the final residual (itself not needed)
   int nb = 0;
-  HIP_TRY(launch_resid_diag<T>(g, rho, u, f, (T*)V.r[0], (T*)V.invD, (T*)V.p[0], nrhs, st, &nb));
+  HIP_TRY(launch_resid<T>(g, rho, u, f, (T*)nullptr, 1, nrhs, st, &nb));
   if (!cn_out) {
     HIP_TRY(launch_pcg_finish(g, nrhs, nb, nb, nullptr, 0, 0, 0, st));
     return FBTO_OK;
@@ -924,13 +922,12 @@ fbto_status_t fbto_solve_refined(fbto_grid_t g, fbto_prec_t inner_prec, const do
   const int64_t n = g->geo.ndof * nrhs;
   float* rho32 = (float*)g->v32.rho;
   if (inner_prec == FBTO_F32) HIP_TRY(launch_convert<float>(rho_phys, rho32, g->geo.E, 0, st));
-  HIP_TRY(launch_diag<double>(g, rho_phys, (double*)g->v64.invD, st));
   int it = 0;
   double total_inner = 0.0;
   std::vector<double> fn(nrhs, 0.0);
   for (;;) {
     // FP64 residual r = f - K64 u and its norms
-    if ((s = residual_norms<double>(g, rho_phys, u, f, B.r64, (const double*)g->v64.invD, nrhs, st))) return s;
+    if ((s = residual_norms<double>(g, rho_phys, u, f, B.r64, nrhs, st))) return s;
     Scalars h;
     HIP_TRY(hipMemcpyAsync(&h, g->sc, sizeof(Scalars), hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));

@@ -125,7 +125,7 @@ struct Vecs {
   void* s[2] = {nullptr, nullptr};   // s = K p
   void* x1 = nullptr;                // iterates of the fused steps
   void* x2 = nullptr;
-  void* invD = nullptr;   // [3N]
+  void* invD = nullptr;   // [3N] inverse Jacobi diagonal (CG on voxel grids without springs: [N], per node)
   void* rho = nullptr;    // [E]  filtered density
   void* ge = nullptr;     // [E]  element gradient
   void* gx = nullptr;     // [E]  design gradient
@@ -231,19 +231,22 @@ int vec_blocks(int64_t n);
 int apply_max_blocks(const Geo& G, int n_cu);
 template <typename T>
 hipError_t launch_apply(fbto_grid_s* g, const T* rho, const T* u, T* y, int nrhs, hipStream_t st);
+// r = f - K u (r may be NULL).  parts: leave the partials of r.r, max|r| and
+// f.f in the slots of a final residual, and reset the solve's flags.
 template <typename T>
-hipError_t launch_resid(fbto_grid_s* g, const T* rho, const T* u, const T* f, T* r, const T* invD,
-                        T* z, int nrhs, hipStream_t st, int* nb_out);
-// Residual apply that also forms the Jacobi diagonal (stored to invD_out)
-// from the densities it reads, instead of a separate diagonal kernel.
+hipError_t launch_resid(fbto_grid_s* g, const T* rho, const T* u, const T* f, T* r, int parts, int nrhs,
+                        hipStream_t st, int* nb_out);
+// The start of a CG solve: also z = D^-1 r, with the Jacobi diagonal formed
+// from the densities the residual reads and its inverse stored in the
+// workspace for the steps, and the partials of r.z.
 template <typename T>
-hipError_t launch_resid_diag(fbto_grid_s* g, const T* rho, const T* u, const T* f, T* r, T* invD_out, T* z,
-                             int nrhs, hipStream_t st, int* nb_out);
+hipError_t launch_resid_diag(fbto_grid_s* g, const T* rho, const T* u, const T* f, T* r, T* z, int nrhs,
+                             hipStream_t st, int* nb_out);
 // The first product s = K p of a CG solve (step 0; unfused steps: step k's),
 // with the partials of p.s and s.D^-1 s.
 template <typename T>
-hipError_t launch_apply_cg(fbto_grid_s* g, const T* rho, const T* p, const T* invD, T* s, int nrhs, int step,
-                           hipStream_t st, int* nb_out);
+hipError_t launch_apply_cg(fbto_grid_s* g, const T* rho, const T* p, T* s, int nrhs, int step, hipStream_t st,
+                           int* nb_out);
 // y = K u with the partials of r.u and y.u: the product of Lanczos iteration
 // `step` (one RHS).
 template <typename T>
@@ -253,8 +256,7 @@ hipError_t launch_apply_lanczos(fbto_grid_s* g, const T* rho, const T* u, const 
 // into `out`, and out.s = K p of step k + 1 with its partials.
 template <typename T>
 hipError_t launch_cg_fused(fbto_grid_s* g, const T* rho, const CgSet<T>& in, const CgSet<T>& out,
-                           const T* invD, int nrhs, int step, const CgCnt& cn, double rtol, hipStream_t st,
-                           int* nb_out);
+                           int nrhs, int step, const CgCnt& cn, double rtol, hipStream_t st, int* nb_out);
 template <typename T>
 hipError_t launch_diag(fbto_grid_s* g, const T* rho, T* invD, hipStream_t st);
 // The last CG step k (one RHS) fused with the sensitivity: x = x_in + alpha p
@@ -367,8 +369,8 @@ hipError_t launch_opt_finish(fbto_grid_s* g, int nrhs, int nb_dot, int nb_lo, in
 template <typename T>
 hipError_t plane_apply(fbto_grid_s* g, const T* rho, const T* u, T* y, int nrhs, hipStream_t st);
 template <typename T>
-hipError_t plane_resid(fbto_grid_s* g, const T* rho, const T* u, const T* f, T* r, const T* invD, T* invD_out,
-                       T* z, int nrhs, hipStream_t st, int* nb_out);
+hipError_t plane_resid(fbto_grid_s* g, const T* rho, const T* u, const T* f, T* r, T* invD_out, T* z, int parts,
+                       int nrhs, hipStream_t st, int* nb_out);
 template <typename T>
 hipError_t plane_apply_cg(fbto_grid_s* g, const T* rho, const T* p, const T* invD, T* s, int nrhs, int step,
                           hipStream_t st, int* nb_out);

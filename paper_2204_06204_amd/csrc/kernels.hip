@@ -89,8 +89,10 @@ static int flat_grid(int64_t n) {
 //
 // Modes:
 //   APPLY  y = K u
-//   RESID  y = r = f - K u; if invD is given, also z = D^-1 r and the
-//          partials of r.r, max|r|, f.f (the start of a CG solve)
+//   RESID  r = f - K u (to y, if given), with the partials of r.r, max|r|,
+//          f.f on request; the start of a CG solve also forms the Jacobi
+//          diagonal, stores its inverse (one value per node) and z = D^-1 r,
+//          with the partials of r.z
 //   CG     y = s = K p with the partials of p.s and s.D^-1 s (the product of
 //          the first CG step)
 //   LZ     y = K u with the partials of r.u and y.u (the product of a Lanczos
@@ -131,10 +133,16 @@ struct ApplyArgs {
   const T* u;          // input vector
   T* y;
   const T* f;          // RESID
-  const T* invD;       // RESID (optional): start of a CG solve; CG, CGF: the preconditioner
-  T* invD_out;         // RESID (optional): the Jacobi diagonal is formed here and stored
-  double ke_diag;      // diagonal entry of KE (with invD_out)
-  T* z;                // RESID: z = D^-1 r
+  int parts;           // RESID: leave the partials of the residual
+  T* z;                // RESID (optional): z = D^-1 r, with the Jacobi diagonal formed here
+  // The inverse Jacobi diagonal (RESID stores it, CG and CGF read it).  Every
+  // diagonal entry of KE is the same number, so without springs a node has one
+  // value for its DOFs but the fixed ones, whose 1 is seen from the mask (DN =
+  // 1); with springs a value per DOF is kept (DN = 3).
+  T* dinv_out;         // RESID (optional, with z)
+  int dn_out;          // RESID: 1 or 3 values per node
+  double ke_diag;      // diagonal entry of KE (with z)
+  const T* dinv;
   const T* r;          // LZ: the vector paired with u in the first partial
   const uint8_t* mask; // bits 0-2: fixed DOFs of the node; bit 3: the node has a spring
   Modal<T> km;
@@ -268,10 +276,10 @@ struct ApplyStage {
 };
 
 // Loads of one node plane for the fused CG step (one RHS).
-template <typename T>
+template <typename T, int DN>
 struct FusedStage {
   T x[3];                       // owned node only
-  T r[3], s[3], p[3], d[3];
+  T r[3], s[3], p[3], d[DN];
   unsigned m;
 };
 
@@ -399,7 +407,8 @@ constexpr int apply_min_waves() {
 
 // RR (fused CG step): form r.r for the tolerance test; solves of a fixed
 // step count (rtol = 0) read no r.r and run the variant without it.
-template <typename T, int NR, int MODE, bool RR = true>
+// DN (CG, CGF): values of the inverse diagonal per node.
+template <typename T, int NR, int MODE, bool RR = true, int DN = 1>
 __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_per_eu(apply_min_waves<T, NR, MODE>())))
     k_apply(ApplyArgs<T> A, int rhs0) {
   extern __shared__ __align__(16) unsigned char apply_smem[];
@@ -481,7 +490,7 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
   const int64_t vbase = (int64_t)rhs0 * G.ndof + 3 * pbase;  // its first value in RHS rhs0
   auto rsrc = [](const void* p) { return zrsrc(p); };
   auto vres = [&](const T* v, int r = 0) { return rsrc(v ? v + vbase + (int64_t)r * G.ndof : v); };  // [nrhs][3N]
-  auto dres = [&](const T* v) { return rsrc(v ? v + 3 * pbase : v); };  // [3N], one set
+  auto dres = [&](const T* v, int dn) { return rsrc(v ? v + dn * pbase : v); };  // [N][dn]
   // An access takes the byte offset of the lane's node column in its plane
   // (computed once; kOOR where the lane has none) and the plane's byte offset
   // in a scalar register: no vector arithmetic per access.
@@ -496,7 +505,10 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
   const uint32_t vx1 = has_extra && gcol[1] >= 0 ? (uint32_t)gcol[1] : kOOR;  // the far node
   const uint32_t vx3 = has_extra && gcol[1] >= 0 ? (uint32_t)(3 * sizeof(T)) * (uint32_t)gcol[1] : kOOR;
   const uint32_t vw3 = writer ? vc3 : kOOR;  // the node a thread owns
+  const uint32_t vd = gcol[0] >= 0 ? (uint32_t)sizeof(T) * (uint32_t)gcol[0] : kOOR;  // values per node
+  const uint32_t vwd = writer ? vd : kOOR;
   auto splane = [&](int k) -> uint32_t { return (uint32_t)(k - ez0) * (uint32_t)plane; };
+  auto sd = [&](int k) -> uint32_t { return (uint32_t)sizeof(T) * splane(k); };
   auto s3 = [&](int k) -> uint32_t { return (uint32_t)(3 * sizeof(T)) * splane(k); };
   const __amdgpu_buffer_rsrc_t rs_m = rsrc(A.mask + pbase);
   auto bload3 = [](__amdgpu_buffer_rsrc_t rs, uint32_t vo, uint32_t so, T (&v)[3]) { zload3<T>(rs, vo, so, v); };
@@ -616,9 +628,20 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
   };
   // fused CG step: loads of one plane, and the update at staging time.
   const __amdgpu_buffer_rsrc_t rs_r = vres(A.ri), rs_s = vres(A.si), rs_x = vres(A.xi), rs_p = vres(A.pi),
-                               rs_d = dres(A.invD);
+                               rs_d = dres(A.dinv, DN);
+  // loads of the node's inverse diagonal (voffset: per node or per DOF), and
+  // its value at each DOF.  One value per node where the fused step read
+  // three is 8 (FP64: 16) of 108 (212) bytes per node.
+  auto load_d = [&](uint32_t o1, uint32_t so1, uint32_t o3, uint32_t so3, T (&d)[DN]) {
+    if constexpr (DN == 3) bload3(rs_d, o3, so3, d);
+    else d[0] = zload1<T>(rs_d, o1, (uint32_t)sizeof(T) * so1);
+  };
+  auto dof_d = [](const T (&d)[DN], unsigned m, int c) -> T {
+    if constexpr (DN == 3) return d[c];
+    else return ((m >> c) & 1u) ? (T)1 : d[0];
+  };
   const __amdgpu_buffer_rsrc_t rs_xo = vres(A.xo), rs_ro = vres(A.ro), rs_po = vres(A.po);
-  auto issue_f = [&](int k, FusedStage<T>& S) {
+  auto issue_f = [&](int k, FusedStage<T, DN>& S) {
     const bool kv = k >= 0 && k <= kend && k <= G.nz;  // planes the block reads
     const bool own_plane = k >= k0 && k < kend;
     const uint32_t so1 = kv ? splane(k) : 0u, so3 = (uint32_t)(3 * sizeof(T)) * so1;
@@ -626,25 +649,26 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
     S.m = bmask(kv ? vc1 : kOOR, so1);
     bload3(rs_r, o3, so3, S.r);
     bload3(rs_s, o3, so3, S.s);
-    bload3(rs_d, o3, so3, S.d);
+    load_d(kv ? vd : kOOR, so1, o3, so3, S.d);
     bload3(rs_p, o3, so3, S.p);
     bload3(rs_x, kv && own_plane ? vw3 : kOOR, so3, S.x);  // used by the owner only
   };
   // zq: the node's p' (unmasked: the output of a fixed DOF); dq: its D^-1
-  auto stage_f = [&](const FusedStage<T>& S, int buf, int k, T (&zq)[3], T (&dq)[3]) {
+  auto stage_f = [&](const FusedStage<T, DN>& S, int buf, int k, T (&zq)[3], T (&dq)[DN]) {
     T* nb = nodes + buf * (3 * NS) + 3 * li[0];
     const bool own_plane = k >= k0 && k < kend;
     // the owner's byte offset; other threads store out of range (dropped)
     const uint32_t o3 = own_plane ? vw3 : kOOR, so3 = own_plane ? s3(k) : 0u;
     T xn[3], rn[3], pn[3], rz = (T)0, rr = (T)0;
 #pragma unroll
+    for (int c = 0; c < DN; ++c) dq[c] = S.d[c];
+#pragma unroll
     for (int c = 0; c < 3; ++c) {
       rn[c] = S.r[c] - al * S.s[c];
-      const T zn = S.d[c] * rn[c];
+      const T zn = dof_d(S.d, S.m, c) * rn[c];
       pn[c] = zn + be * S.p[c];
       nb[c] = zmasked(S.m, c, pn[c]);
       zq[c] = pn[c];
-      dq[c] = S.d[c];
       xn[c] = S.x[c] + al * S.p[c];
       rz += rn[c] * zn;
       if constexpr (RR) rr += rn[c] * rn[c];
@@ -778,7 +802,7 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
     }
   }
   ApplyStage<T, NR> S[2];
-  FusedStage<T> SF;
+  FusedStage<T, DN> SF;
   MinresStage<T> SM;
   T F[2][NR][4][3];
   T carry[NR][4][3];
@@ -792,14 +816,13 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
   // prologue: planes ez0, ez0 + 1 staged (and, unfused, plane ez0 + 2 in flight)
   unsigned mq[2];  // mask of the own node, by parity of the plane from ez0
   T rq[2][NR][3];  // its unmasked input value
-  T dq[2][3];      // CGF: its D^-1
+  T dq[2][DN];     // CGF: its D^-1
   T rho_next;
   // residual, CG and Lanczos modes: values of the own node read only at its
-  // output (RESID: f and D^-1 (or f again); CG: D^-1; LZ: r), loaded one
-  // layer ahead.  FP64 loads them at the output instead: the queue would not
+  // output (RESID: f; CG: D^-1; LZ: r), loaded one layer ahead.  FP64 loads them at the output instead: the queue would not
   // fit its registers.
   constexpr bool kOwnQ = sizeof(T) == 4 && (MODE == MODE_RESID || MODE == MODE_CG || MODE == MODE_LZ);
-  T oq[2][NR][2][3];
+  T oq[2][NR][3];
   __amdgpu_buffer_rsrc_t rs_f[NR], rs_cr[NR], rs_y[NR], rs_z[NR];
 #pragma unroll
   for (int r = 0; r < NR; ++r) {
@@ -808,24 +831,26 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
     rs_y[r] = vres(A.y, r);
     rs_z[r] = vres(A.z, r);
   }
-  const __amdgpu_buffer_rsrc_t rs_do = dres(A.invD_out);
-  auto load_own = [&](int k, T (&q)[NR][2][3]) {
+  const __amdgpu_buffer_rsrc_t rs_do = dres(A.dinv_out, A.dn_out);
+  auto load_own = [&](int k, T (&q)[NR][3]) {
     const bool ok = k >= k0 && k < kend;  // planes this block outputs
     const uint32_t o3 = ok ? vw3 : kOOR, so3 = ok ? s3(k) : 0u;
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
       if constexpr (MODE == MODE_RESID) {
-        bload3(rs_f[r], o3, so3, q[r][0]);
-        bload3(rs_d, A.invD ? o3 : kOOR, so3, q[r][1]);
+        bload3(rs_f[r], o3, so3, q[r]);
       } else if constexpr (MODE == MODE_CG) {
-        bload3(rs_d, o3, so3, q[r][0]);
+        T d[DN];
+        load_d(ok ? vwd : kOOR, ok ? splane(k) : 0u, o3, so3, d);
+#pragma unroll
+        for (int c = 0; c < DN; ++c) q[r][c] = d[c];
       } else {
-        bload3(rs_cr[r], o3, so3, q[r][0]);
+        bload3(rs_cr[r], o3, so3, q[r]);
       }
     }
   };
   if constexpr (MODE == MODE_CGF) {
-    FusedStage<T> SF1;
+    FusedStage<T, DN> SF1;
     issue_f(ez0, SF);
     rho_next = load_rho(ez0);
     issue_f(ez0 + 1, SF1);
@@ -904,12 +929,12 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
           for (int c = 0; c < 3; ++c)
             corners[((cb * NR + r) * TS + tid) * 9 + (a - 1) * 3 + c] = out[r][a][c];
       if constexpr (MODE == MODE_RESID) {
-        if (A.invD_out) dcorn[cb * TS + tid] = dcol;
+        if (A.z) dcorn[cb * TS + tid] = dcol;
       }
     }
     // the staged plane's values of the own node: into the slot that this
     // layer's output leaves
-    T nq[NR][3], nd[3];
+    T nq[NR][3], nd[DN];
     unsigned nm;
     if constexpr (MODE == MODE_CGF) {
       stage_f(SF, ez & 1, ez + 2, nq[0], nd);
@@ -960,47 +985,41 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
         auto own_only = [wr](double v) { return wr ? v : 0.0; };
         auto own_t = [wr](T v) { return wr ? v : (T)0; };
         if constexpr (MODE == MODE_RESID) {
-          const bool zout = A.invD || A.invD_out;
-          T fv[3], rv[3], dv[3], dl[3], zv[3];
+          T fv[3], rv[3], zv[3] = {(T)0, (T)0, (T)0};
           if constexpr (kOwnQ) {
 #pragma unroll
-            for (int c = 0; c < 3; ++c) {
-              fv[c] = oq[P][r][0][c];
-              dl[c] = oq[P][r][1][c];
-            }
+            for (int c = 0; c < 3; ++c) fv[c] = oq[P][r][c];
           } else {
             bload3(rs_f[r], o3, so3, fv);
-            bload3(rs_d, A.invD ? o3 : kOOR, so3, dl);
           }
-          const T D = ((dcol + dcorn[cb * TS + tl1]) + dcorn[cb * TS + tlb]) + dcorn[cb * TS + tlbb];
-          // Jacobi diagonal: ke_diag * sum of s over the node's 8 elements,
-          // one value (and one division) for the node's three DOFs; springs
-          // and fixed DOFs (nodes with m != 0, rare) set single entries
-          const T d0 = (T)A.ke_diag * D;
-          T dinv0 = (T)0;
-          if (A.invD_out) dinv0 = d0 > (T)0 ? (T)1 / d0 : (T)0;
 #pragma unroll
-          for (int c = 0; c < 3; ++c) {
-            rv[c] = fv[c] - acc[c];
-            if (A.invD_out) {
-              T di = dinv0;
-              if (m) {
-                T d = d0;
+          for (int c = 0; c < 3; ++c) rv[c] = fv[c] - acc[c];
+          if (A.z) {  // the start of a CG solve (uniform)
+            // Jacobi diagonal: ke_diag * sum of s over the node's 8 elements,
+            // one value (and one division) for the node's three DOFs
+            const T d0 = (T)A.ke_diag * (((dcol + dcorn[cb * TS + tl1]) + dcorn[cb * TS + tlb]) + dcorn[cb * TS + tlbb]);
+            const T dinv0 = d0 > (T)0 ? (T)1 / d0 : (T)0;
+            T d[3] = {dinv0, dinv0, dinv0};
+            if (m) {  // springs and fixed DOFs (rare nodes)
+#pragma unroll
+              for (int c = 0; c < 3; ++c) {
+                T dc = d0;
                 if (m & 8u)
                   for (int sI = 0; sI < A.nspring; ++sI)
-                    if (A.sdof[sI] == (int64_t)(3 * (gcol[0] + ez * plane) + c)) d += A.sk[sI];
-                if ((m >> c) & 1u) d = (T)1;
-                di = d > (T)0 ? (T)1 / d : (T)0;
+                    if (A.sdof[sI] == (int64_t)(3 * (gcol[0] + ez * plane) + c)) dc += A.sk[sI];
+                if ((m >> c) & 1u) dc = (T)1;
+                d[c] = dc > (T)0 ? (T)1 / dc : (T)0;
               }
-              dv[c] = di;
-            } else {
-              dv[c] = dl[c];
             }
-            zv[c] = dv[c] * rv[c];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) zv[c] = d[c] * rv[c];
+            bstore3(rs_z[r], o3, so3, zv);
+            if (A.dinv_out) {
+              if (A.dn_out == 1) zstore1<T>(rs_do, emit ? vwd : kOOR, emit ? sd(ez) : 0u, dinv0);
+              else bstore3(rs_do, o3, so3, d);
+            }
           }
-          bstore3(rs_y[r], o3, so3, rv);
-          bstore3(rs_z[r], zout ? o3 : kOOR, so3, zv);
-          if (A.invD_out) bstore3(rs_do, o3, so3, dv);
+          bstore3(rs_y[r], A.y ? o3 : kOOR, so3, rv);
           T rr = (T)0, rm = (T)0, ff = (T)0, rz = (T)0;
 #pragma unroll
           for (int c = 0; c < 3; ++c) {
@@ -1017,11 +1036,21 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
           bstore3(rs_y[r], o3, so3, acc);
           if constexpr (MODE == MODE_CG || MODE == MODE_LZ) {
             T q3[3];  // CG: D^-1; LZ: the paired vector
-            if constexpr (kOwnQ) {
+            if constexpr (MODE == MODE_CG) {
+              T d[DN];
+              if constexpr (kOwnQ) {
 #pragma unroll
-              for (int c = 0; c < 3; ++c) q3[c] = oq[P][r][0][c];
+                for (int c = 0; c < DN; ++c) d[c] = oq[P][r][c];
+              } else {
+                load_d(emit ? vwd : kOOR, emit ? splane(ez) : 0u, o3, so3, d);
+              }
+#pragma unroll
+              for (int c = 0; c < 3; ++c) q3[c] = dof_d(d, m, c);
+            } else if constexpr (kOwnQ) {
+#pragma unroll
+              for (int c = 0; c < 3; ++c) q3[c] = oq[P][r][c];
             } else {
-              bload3(MODE == MODE_CG ? rs_d : rs_cr[r], o3, so3, q3);
+              bload3(rs_cr[r], o3, so3, q3);
             }
             double yu = 0.0, ru = 0.0;
             T ss = (T)0;
@@ -1044,7 +1073,7 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
           if constexpr (MODE == MODE_CGF) {
             T ss = (T)0;
 #pragma unroll
-            for (int c = 0; c < 3; ++c) ss += acc[c] * (dq[P][c] * acc[c]);
+            for (int c = 0; c < 3; ++c) ss += acc[c] * (dof_d(dq[P], m, c) * acc[c]);
             tpart[0][2] += own_t(ss);  // s'.D^-1 s'
           }
         }
@@ -1055,7 +1084,10 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
     for (int c = 0; c < 3; ++c) {
 #pragma unroll
       for (int r = 0; r < NR; ++r) rq[P][r][c] = nq[r][c];
-      if constexpr (MODE == MODE_CGF) dq[P][c] = nd[c];
+    }
+    if constexpr (MODE == MODE_CGF) {
+#pragma unroll
+      for (int c = 0; c < DN; ++c) dq[P][c] = nd[c];
     }
   };
   for (int ez = ez0; ez < kend; ez += 2) {
@@ -1104,7 +1136,7 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
     write_parts<3, 0u>(v, dst, lb);
   }
   if constexpr (MODE == MODE_RESID) {
-    if (A.invD == nullptr && A.invD_out == nullptr) return;
+    if (!A.parts) return;
     if (lb == 0 && tid == 0) {   // a new solve starts from this residual
       Scalars* sc = const_cast<Scalars*>(A.sc);
       for (int r = 0; r < NR; ++r) {
@@ -1435,7 +1467,7 @@ static TileChoice choose_tile(const Geo& G, int n_cu, int lds_per_cu, int overri
   return best;
 }
 
-template <typename T, int NR, int MODE, bool RR = true>
+template <typename T, int NR, int MODE, bool RR = true, int DN = 1>
 static hipError_t launch_apply_t(fbto_grid_s* g, const ApplyArgs<T>& A0, int rhs0, hipStream_t st,
                                  int* nb_out) {
   TileChoice& t = g->tiles[sizeof(T) == 8 ? 1 : 0][NR - 1][MODE];
@@ -1458,11 +1490,11 @@ static hipError_t launch_apply_t(fbto_grid_s* g, const ApplyArgs<T>& A0, int rhs
   size_t lds = apply_lds_bytes<T, NR, MODE>(t.bx, t.by);
   if (t.cap) lds = std::max(lds, (size_t)lds_for_block_cap(g->lds_per_cu, t.cap));
   const int threads = zmarch_threads<MODE>(t.bx, t.by);  // whole waves
-  hipLaunchKernelGGL((k_apply<T, NR, MODE, RR>), dim3(grid), dim3(threads), lds, st, A, rhs0);
+  hipLaunchKernelGGL((k_apply<T, NR, MODE, RR, DN>), dim3(grid), dim3(threads), lds, st, A, rhs0);
   return hipGetLastError();
 }
 
-template <typename T, int MODE, bool RR = true>
+template <typename T, int MODE, bool RR = true, int DN = 1>
 static hipError_t launch_apply_mode(fbto_grid_s* g, ApplyArgs<T> A, int nrhs, hipStream_t st, int* nb_out) {
   A.g = g->geo;
   A.mask = g->mask;
@@ -1477,7 +1509,10 @@ static hipError_t launch_apply_mode(fbto_grid_s* g, ApplyArgs<T> A, int nrhs, hi
   // one RHS per launch: the per-RHS state of the z-march (two face-mode
   // sets, the modal carry, staged loads) fills the register file at NR = 1
   hipError_t e = hipSuccess;
-  for (int r0 = 0; r0 < nrhs && e == hipSuccess; ++r0) e = launch_apply_t<T, 1, MODE, RR>(g, A, r0, st, nb_out);
+  for (int r0 = 0; r0 < nrhs && e == hipSuccess; ++r0) {
+    e = launch_apply_t<T, 1, MODE, RR, DN>(g, A, r0, st, nb_out);
+    A.dinv_out = nullptr;  // the same for every RHS
+  }
   return e;
 }
 
@@ -1494,45 +1529,49 @@ hipError_t launch_apply(fbto_grid_s* g, const T* rho, const T* u, T* y, int nrhs
 }
 
 template <typename T>
-hipError_t launch_resid(fbto_grid_s* g, const T* rho, const T* u, const T* f, T* r, const T* invD, T* z,
-                        int nrhs, hipStream_t st, int* nb_out) {
-  if (g->dim == 2) return plane_resid<T>(g, rho, u, f, r, invD, nullptr, z, nrhs, st, nb_out);
+hipError_t launch_resid(fbto_grid_s* g, const T* rho, const T* u, const T* f, T* r, int parts, int nrhs,
+                        hipStream_t st, int* nb_out) {
+  if (g->dim == 2) return plane_resid<T>(g, rho, u, f, r, nullptr, nullptr, parts, nrhs, st, nb_out);
   ApplyArgs<T> A{};
   A.rho = rho;
   A.u = u;
   A.y = r;
   A.f = f;
-  A.invD = invD;
-  A.z = z;
+  A.parts = parts;
   return launch_apply_mode<T, MODE_RESID>(g, A, nrhs, st, nb_out);
 }
 
 template <typename T>
-hipError_t launch_resid_diag(fbto_grid_s* g, const T* rho, const T* u, const T* f, T* r, T* invD_out, T* z,
-                             int nrhs, hipStream_t st, int* nb_out) {
-  if (g->dim == 2) return plane_resid<T>(g, rho, u, f, r, nullptr, invD_out, z, nrhs, st, nb_out);
+hipError_t launch_resid_diag(fbto_grid_s* g, const T* rho, const T* u, const T* f, T* r, T* z, int nrhs,
+                             hipStream_t st, int* nb_out) {
+  Vecs& V = vecs_of<T>(g);
+  if (g->dim == 2) return plane_resid<T>(g, rho, u, f, r, (T*)V.invD, z, 1, nrhs, st, nb_out);
   ApplyArgs<T> A{};
   A.rho = rho;
   A.u = u;
   A.y = r;
   A.f = f;
-  A.invD_out = invD_out;
+  A.parts = 1;
+  A.dinv_out = (T*)V.invD;
+  A.dn_out = g->n_springs > 0 ? 3 : 1;
   A.ke_diag = g->ke_diag;
   A.z = z;
   return launch_apply_mode<T, MODE_RESID>(g, A, nrhs, st, nb_out);
 }
 
 template <typename T>
-hipError_t launch_apply_cg(fbto_grid_s* g, const T* rho, const T* p, const T* invD, T* s, int nrhs, int step,
-                           hipStream_t st, int* nb_out) {
-  if (g->dim == 2) return plane_apply_cg<T>(g, rho, p, invD, s, nrhs, step, st, nb_out);
+hipError_t launch_apply_cg(fbto_grid_s* g, const T* rho, const T* p, T* s, int nrhs, int step, hipStream_t st,
+                           int* nb_out) {
+  Vecs& V = vecs_of<T>(g);
+  if (g->dim == 2) return plane_apply_cg<T>(g, rho, p, (const T*)V.invD, s, nrhs, step, st, nb_out);
   ApplyArgs<T> A{};
   A.rho = rho;
   A.u = p;
-  A.invD = invD;
+  A.dinv = (const T*)V.invD;
   A.y = s;
   A.step = step;
-  return launch_apply_mode<T, MODE_CG>(g, A, nrhs, st, nb_out);
+  return g->n_springs > 0 ? launch_apply_mode<T, MODE_CG, true, 3>(g, A, nrhs, st, nb_out)
+                          : launch_apply_mode<T, MODE_CG, true, 1>(g, A, nrhs, st, nb_out);
 }
 
 template <typename T>
@@ -1595,12 +1634,12 @@ hipError_t launch_cg_sens(fbto_grid_s* g, const T* rho, const CgSet<T>& in, T* x
 
 template <typename T>
 hipError_t launch_cg_fused(fbto_grid_s* g, const T* rho, const CgSet<T>& in, const CgSet<T>& out,
-                           const T* invD, int nrhs, int step, const CgCnt& cn, double rtol, hipStream_t st,
+                           int nrhs, int step, const CgCnt& cn, double rtol, hipStream_t st,
                            int* nb_out) {
   ApplyArgs<T> A{};
   A.rho = rho;
   A.y = out.s;
-  A.invD = invD;
+  A.dinv = (const T*)vecs_of<T>(g).invD;
   A.step = step;
   A.xi = in.x; A.ri = in.r; A.pi = in.p; A.si = in.s;
   A.xo = out.x; A.ro = out.r; A.po = out.p;
@@ -1609,8 +1648,11 @@ hipError_t launch_cg_fused(fbto_grid_s* g, const T* rho, const CgSet<T>& in, con
   A.n_fn = cn.fn;
   A.rtol = rtol;
   // r.r only for the tolerance test
-  return rtol > 0.0 ? launch_apply_mode<T, MODE_CGF, true>(g, A, nrhs, st, nb_out)
-                    : launch_apply_mode<T, MODE_CGF, false>(g, A, nrhs, st, nb_out);
+  if (g->n_springs > 0)
+    return rtol > 0.0 ? launch_apply_mode<T, MODE_CGF, true, 3>(g, A, nrhs, st, nb_out)
+                      : launch_apply_mode<T, MODE_CGF, false, 3>(g, A, nrhs, st, nb_out);
+  return rtol > 0.0 ? launch_apply_mode<T, MODE_CGF, true, 1>(g, A, nrhs, st, nb_out)
+                    : launch_apply_mode<T, MODE_CGF, false, 1>(g, A, nrhs, st, nb_out);
 }
 
 template <typename T>
@@ -3164,12 +3206,11 @@ hipError_t launch_opt_finish(fbto_grid_s* g, int nrhs, int nb_dot, int nb_lo, in
 // ---- explicit instantiations ----------------------------------------------
 #define FBTO_INST(T)                                                                                   \
   template hipError_t launch_apply<T>(fbto_grid_s*, const T*, const T*, T*, int, hipStream_t);         \
-  template hipError_t launch_resid<T>(fbto_grid_s*, const T*, const T*, const T*, T*, const T*, T*, int, \
-                                      hipStream_t, int*);                                              \
-  template hipError_t launch_resid_diag<T>(fbto_grid_s*, const T*, const T*, const T*, T*, T*, T*, int,  \
+  template hipError_t launch_resid<T>(fbto_grid_s*, const T*, const T*, const T*, T*, int, int, hipStream_t, \
+                                      int*);                                                           \
+  template hipError_t launch_resid_diag<T>(fbto_grid_s*, const T*, const T*, const T*, T*, T*, int,    \
                                            hipStream_t, int*);                                         \
-  template hipError_t launch_apply_cg<T>(fbto_grid_s*, const T*, const T*, const T*, T*, int, int,     \
-                                         hipStream_t, int*);                                           \
+  template hipError_t launch_apply_cg<T>(fbto_grid_s*, const T*, const T*, T*, int, int, hipStream_t, int*); \
   template hipError_t launch_apply_lanczos<T>(fbto_grid_s*, const T*, const T*, const T*, T*, int,     \
                                               hipStream_t, int*);                                      \
   template hipError_t launch_cg_step<T>(fbto_grid_s*, const T*, T*, T*, const T*, T*, const T*, const T*, int, int, \
@@ -3177,7 +3218,7 @@ hipError_t launch_opt_finish(fbto_grid_s* g, int nrhs, int nb_dot, int nb_lo, in
   template hipError_t launch_cg_sens<T>(fbto_grid_s*, const T*, const CgSet<T>&, T*, const T*, T*, const T*, int, \
                                         const CgCnt&, double, hipStream_t, int*);                      \
   template hipError_t launch_cg_fused<T>(fbto_grid_s*, const T*, const CgSet<T>&, const CgSet<T>&,      \
-                                         const T*, int, int, const CgCnt&, double, hipStream_t, int*);  \
+                                         int, int, const CgCnt&, double, hipStream_t, int*);           \
   template hipError_t launch_diag<T>(fbto_grid_s*, const T*, T*, hipStream_t);                         \
   template hipError_t launch_relax_update<T>(fbto_grid_s*, T*, const T*, const T*, int, double, int,    \
                                              hipStream_t);                                             \

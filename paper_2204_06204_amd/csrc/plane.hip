@@ -33,11 +33,12 @@ struct PlaneArgs {
   int64_t N, ndof;
   const T* rho;
   const T* u;          // input vector
-  T* y;                // output: K u, or r = f - K u
+  T* y;                // output: K u, or r = f - K u (RESID: may be NULL)
   const T* f;          // RESID
-  const T* invD;       // RESID (optional): z = D^-1 r from this diagonal; CG: the preconditioner
-  T* invD_out;         // RESID (optional): form the Jacobi diagonal, store it, z from it
-  T* z;                // RESID
+  int parts;           // RESID: leave the partials of the residual
+  const T* invD;       // CG: the preconditioner
+  T* invD_out;         // RESID (optional): form the Jacobi diagonal and store its inverse, and z = D^-1 r
+  T* z;                // RESID, with invD_out
   const T* r;          // LZ: the vector paired with u in the first partial
   const uint8_t* mask; // bit c: DOF c of the node fixed
   Q4<T> ke;
@@ -132,18 +133,13 @@ __global__ void __launch_bounds__(kPlaneBlock) k_plane_apply(PlaneArgs<T> A, int
         for (int c = 0; c < 2; ++c) {
           const T fv = A.f[o + c];
           const T rv = fv - acc[r][c];
-          A.y[o + c] = rv;
+          if (A.y) A.y[o + c] = rv;
           T zv = (T)0;
-          if (A.invD_out || A.invD) {
-            T dl;
-            if (A.invD_out) {
-              T d = (T)A.ke_diag * ssum;
-              if ((m >> c) & 1u) d = (T)1;
-              dl = d > (T)0 ? (T)1 / d : (T)0;
-              if (r == 0) A.invD_out[2 * (int64_t)n + c] = dl;
-            } else {
-              dl = A.invD[2 * (int64_t)n + c];
-            }
+          if (A.invD_out) {
+            T d = (T)A.ke_diag * ssum;
+            if ((m >> c) & 1u) d = (T)1;
+            const T dl = d > (T)0 ? (T)1 / d : (T)0;
+            if (r == 0) A.invD_out[2 * (int64_t)n + c] = dl;
             zv = dl * rv;
             A.z[o + c] = zv;
           }
@@ -176,7 +172,7 @@ __global__ void __launch_bounds__(kPlaneBlock) k_plane_apply(PlaneArgs<T> A, int
     write_parts<2 * NR, 0u>(part, dst, blockIdx.x);
   }
   if constexpr (MODE == PL_RESID) {
-    if (A.invD == nullptr && A.invD_out == nullptr) return;
+    if (!A.parts) return;
     if (blockIdx.x == 0 && threadIdx.x == 0) {  // a new solve starts from this residual
       for (int r = 0; r < NR; ++r) {
         A.sc->done[rhs0 + r] = 0.0;
@@ -379,14 +375,14 @@ hipError_t plane_apply(fbto_grid_s* g, const T* rho, const T* u, T* y, int nrhs,
 }
 
 template <typename T>
-hipError_t plane_resid(fbto_grid_s* g, const T* rho, const T* u, const T* f, T* r, const T* invD, T* invD_out,
-                       T* z, int nrhs, hipStream_t st, int* nb_out) {
+hipError_t plane_resid(fbto_grid_s* g, const T* rho, const T* u, const T* f, T* r, T* invD_out, T* z, int parts,
+                       int nrhs, hipStream_t st, int* nb_out) {
   PlaneArgs<T> A = plane_args<T>(g);
   A.rho = rho;
   A.u = u;
   A.y = r;
   A.f = f;
-  A.invD = invD;
+  A.parts = parts;
   A.invD_out = invD_out;
   A.z = z;
   return plane_launch<T, PL_RESID>(g, A, nrhs, st, nb_out);
@@ -464,7 +460,7 @@ hipError_t plane_hs(fbto_grid_s* g, T* Hsi, hipStream_t st) {
 
 #define FBTO_PLANE_INST(T)                                                                                   \
   template hipError_t plane_apply<T>(fbto_grid_s*, const T*, const T*, T*, int, hipStream_t);                \
-  template hipError_t plane_resid<T>(fbto_grid_s*, const T*, const T*, const T*, T*, const T*, T*, T*, int,  \
+  template hipError_t plane_resid<T>(fbto_grid_s*, const T*, const T*, const T*, T*, T*, T*, int, int,       \
                                      hipStream_t, int*);                                                     \
   template hipError_t plane_apply_cg<T>(fbto_grid_s*, const T*, const T*, const T*, T*, int, int, hipStream_t, \
                                         int*);                                                               \
