@@ -245,11 +245,12 @@ fbto_status_t pcg_run(fbto_grid_s* g, const T* rho, const T* f, T* x, int nrhs, 
                       const T* sens_hsi = nullptr, bool* sens_done = nullptr) {
   Vecs& V = vecs<T>(g);
   T* invD = (T*)V.invD;  // (plane grids)
-  // the iterate of step k: the caller's vector (k = 0), then x1 and x2 in turn
-  auto set_of = [&](int k) {
-    return CgSet<T>{k == 0 ? x : (T*)((k & 1) ? V.x1 : V.x2), (T*)V.r[k & 1], (T*)V.p[k & 1], (T*)V.s[k & 1]};
+  // the vectors of step k: two sets in turn.  The iterate moves apart from
+  // them: the caller's vector, then x1 and x2 in turn.
+  auto set_of = [&](int k, T* xk) {
+    return CgSet<T>{xk, (T*)V.r[k & 1], (T*)V.p[k & 1], (T*)V.s[k & 1]};
   };
-  const CgSet<T> set0 = set_of(0);
+  const CgSet<T> set0 = set_of(0, x);
   int nb_r = 0, nb_a = 0, nb_v = 0;
   // r = f - K x and the first direction p = z = D^-1 r
   HIP_TRY(launch_resid_diag<T>(g, rho, x, f, set0.r, set0.p, nrhs, st, &nb_r));
@@ -274,9 +275,20 @@ fbto_status_t pcg_run(fbto_grid_s* g, const T* rho, const T* f, T* x, int nrhs, 
   // k + 1 in one pass); plane grids: unfused (vector update, then the product)
   const bool fused = g->dim == 3;
   int k = 0;
+  T* xk = x;
+  const bool pairs = fused && cg_pairs_updates(g);
+  bool pend = false;  // the iterate lacks the last fused step's update
   for (; k + 1 < steps; ++k) {
+    const bool check = rtol > 0.0 && (k + 2) % 64 == 0 && k + 2 < steps;
     if (fused) {
-      HIP_TRY(launch_cg_fused<T>(g, rho, set_of(k), set_of(k + 1), nrhs, k, pc, rtol, st, &nb_a));
+      // in pairs: the iterate is updated every second step, and by the last
+      // fused step before it may be read (the end of the loop, a check)
+      const bool up = !pairs || pend || check || k + 2 == steps;
+      T* xo = xk == (T*)V.x1 ? (T*)V.x2 : (T*)V.x1;
+      HIP_TRY(launch_cg_fused<T>(g, rho, set_of(k, xk), set_of(k + 1, xo), nrhs, k, up ? 1 + pend : 0, pc, rtol,
+                                 st, &nb_a));
+      if (up) xk = xo;
+      pend = !up;
       pc.gam = pc.apply = nb_a;
     } else {
       HIP_TRY(launch_cg_step<T>(g, x, x, set0.r, set0.s, set0.p, invD, nullptr, nrhs, k, false, pc, rtol, st, &nb_v));
@@ -284,7 +296,7 @@ fbto_status_t pcg_run(fbto_grid_s* g, const T* rho, const T* f, T* x, int nrhs, 
       pc.gam = nb_v;
       pc.apply = nb_a;
     }
-    if (rtol > 0.0 && (k + 2) % 64 == 0 && k + 2 < steps) {
+    if (check) {
       bool done = false;
       if (fbto_status_t e = all_done(done)) return e;
       if (done) {
@@ -297,7 +309,7 @@ fbto_status_t pcg_run(fbto_grid_s* g, const T* rho, const T* f, T* x, int nrhs, 
   // sensitivity wanted, fused with it.  The fused kernel reads x at halo
   // nodes while their owners store x', so it needs the iterate in another
   // buffer (one fused step or more before it).
-  const CgSet<T> cur = fused ? set_of(k) : set0;
+  const CgSet<T> cur = fused ? set_of(k, xk) : set0;
   if (sens && nrhs == 1 && cur.x != x) {
     HIP_TRY(launch_cg_sens<T>(g, rho, cur, x, f_dot ? f : nullptr, sens, sens_hsi, k, pc, rtol, st, &nb_v));
     if (sens_done) *sens_done = true;

@@ -61,8 +61,7 @@ struct Simp {
 struct Scalars {
   double rz[4];        // r . z of the current CG iterate
   double pq[4];
-  double alpha[4];
-  double beta[4];
+  double alpha[2][4];  // by step parity
   double rnorm2[4];    // ||r||_2
   double rinf[4];      // ||r||_inf
   double fnorm2[4];
@@ -253,10 +252,13 @@ template <typename T>
 hipError_t launch_apply_lanczos(fbto_grid_s* g, const T* rho, const T* u, const T* r, T* y, int step, hipStream_t st,
                                 int* nb_out);
 // One fused CG step k (voxel grids): vector update of step k from `in`, stored
-// into `out`, and out.s = K p of step k + 1 with its partials.
+// into `out`, and out.s = K p of step k + 1 with its partials.  x_updates: 1:
+// out.x = in.x + alpha_k p_k; 0: no x is read or written; 2: in.x lacks step
+// k - 1's update, which is made too (out.p still holds its direction).
 template <typename T>
-hipError_t launch_cg_fused(fbto_grid_s* g, const T* rho, const CgSet<T>& in, const CgSet<T>& out,
-                           int nrhs, int step, const CgCnt& cn, double rtol, hipStream_t st, int* nb_out);
+hipError_t launch_cg_fused(fbto_grid_s* g, const T* rho, const CgSet<T>& in, const CgSet<T>& out, int nrhs, int step,
+                           int x_updates, const CgCnt& cn, double rtol, hipStream_t st, int* nb_out);
+bool cg_pairs_updates(const fbto_grid_s* g);  // whether the steps take x_updates 0 and 2 in turn
 template <typename T>
 hipError_t launch_diag(fbto_grid_s* g, const T* rho, T* invD, hipStream_t st);
 // The last CG step k (one RHS) fused with the sensitivity: x = x_in + alpha p

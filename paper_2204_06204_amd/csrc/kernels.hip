@@ -103,7 +103,8 @@ static int flat_grid(int64_t n) {
 //          output set, and the product is s' = K p' (step k + 1's) with its
 //          partials.  Input and output sets are distinct buffers: halo nodes
 //          of a tile are read by its neighbours while their owner writes the
-//          update.
+//          update.  On large grids the iterate is updated every second step,
+//          by two directions at once (XU).
 // ===========================================================================
 //   MRF    the fused MINRES step of the Krylov low-level step (one RHS):
 //          the vector pass of iteration t (see k_minres) done where each
@@ -183,7 +184,7 @@ struct ApplyArgs {
 // to rounding) restarts from z'.  A solved, converged or broken-down RHS gets
 // alpha = beta = 0.  The lead thread records the flags and the step count.
 __device__ __forceinline__ void cg_coefficients(double gam, double del, double eps, double rr, double ff, int R,
-                                                double rtol, Scalars* sc, bool lead, double& alpha,
+                                                int par, double rtol, Scalars* sc, bool lead, double& alpha,
                                                 double& beta) {
   const double rn = sqrt(rr), fn = sqrt(ff);
   bool done = sc->done[R] != 0.0 || (rtol > 0.0 && rn <= rtol * fn);
@@ -206,8 +207,7 @@ __device__ __forceinline__ void cg_coefficients(double gam, double del, double e
     if (done) sc->done[R] = 1.0;
     if (status != 0.0) sc->status[R] = status;
     if (alpha != 0.0) sc->steps[R] += 1.0;
-    sc->alpha[R] = alpha;
-    sc->beta[R] = beta;
+    sc->alpha[par][R] = alpha;
   }
 }
 
@@ -278,7 +278,7 @@ struct ApplyStage {
 // Loads of one node plane for the fused CG step (one RHS).
 template <typename T, int DN>
 struct FusedStage {
-  T x[3];                       // owned node only
+  T x[3], q[3];                 // owned node only: x, step k - 1's p
   T r[3], s[3], p[3], d[DN];
   unsigned m;
 };
@@ -408,7 +408,19 @@ constexpr int apply_min_waves() {
 // RR (fused CG step): form r.r for the tolerance test; solves of a fixed
 // step count (rtol = 0) read no r.r and run the variant without it.
 // DN (CG, CGF): values of the inverse diagonal per node.
-template <typename T, int NR, int MODE, bool RR = true, int DN = 1>
+// XU (fused CG step): updates of the iterate.  1: x += alpha_k p_k.  0: none, it
+// is left to the next step; 2: x += alpha_{k-1} p_{k-1} + alpha_k p_k, with
+// p_{k-1} read from the buffer that p_{k+1} goes to, before it is stored.  The
+// operations and their order are the same; two steps read x and p_{k-1} and
+// write x once instead of reading and writing x twice, half a vector less per
+// step.
+// DN (CG, CGF): values of the inverse diagonal per node.
+// XUP (fused CG step): update the iterate.  A step without it leaves
+// x += alpha_k p_k to the next one, which reads p_k from the buffer that its own
+// p_{k+2} goes to, before storing it: two steps read x, p_k and write x once,
+// where an update per step reads and writes x twice (the same operations in
+// the same order, half a vector less per step on average).
+template <typename T, int NR, int MODE, bool RR = true, int DN = 1, int XU = 1>
 __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_per_eu(apply_min_waves<T, NR, MODE>())))
     k_apply(ApplyArgs<T> A, int rhs0) {
   extern __shared__ __align__(16) unsigned char apply_smem[];
@@ -595,7 +607,7 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
   // fused CG step: coefficients of step k from its partials (every block;
   // called in the prologue, after the first planes' loads are issued, so
   // the two latencies overlap)
-  T al = (T)0, be = (T)0;
+  T al = (T)0, be = (T)0, alq = (T)0;  // alq: step k - 1's alpha, if its update is pending
   auto cg_prologue = [&]() {
     const int par = A.step & 1;
     constexpr int NV = RR ? 5 : 3;
@@ -613,6 +625,9 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
       cnt[3] = A.n_gam;
       cnt[4] = A.n_fn;
     }
+    // step k - 1's alpha: the lead thread stores step k's beside it, by parity
+    double aq = 0.0;
+    if constexpr (XU == 2) aq = A.sc->alpha[par ^ 1][rhs0];
     reduce_parts<NV, 0u>(pre, src, cnt);
     double rr = 0.0, ff = 0.0;
     if constexpr (RR) {
@@ -620,11 +635,12 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
       ff = pre[4];
     }
     double alpha, beta;
-    cg_coefficients(pre[0], pre[1], pre[2], rr, ff, rhs0, RR ? A.rtol : 0.0, const_cast<Scalars*>(A.sc),
+    cg_coefficients(pre[0], pre[1], pre[2], rr, ff, rhs0, par, RR ? A.rtol : 0.0, const_cast<Scalars*>(A.sc),
                     lb == 0 && tid == 0, alpha, beta);
     // the same value in every lane: kept in scalar registers
     al = wave_uniform((T)alpha);
     be = wave_uniform((T)beta);
+    if constexpr (XU == 2) alq = wave_uniform((T)aq);
   };
   // fused CG step: loads of one plane, and the update at staging time.
   const __amdgpu_buffer_rsrc_t rs_r = vres(A.ri), rs_s = vres(A.si), rs_x = vres(A.xi), rs_p = vres(A.pi),
@@ -651,7 +667,9 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
     bload3(rs_s, o3, so3, S.s);
     load_d(kv ? vd : kOOR, so1, o3, so3, S.d);
     bload3(rs_p, o3, so3, S.p);
-    bload3(rs_x, kv && own_plane ? vw3 : kOOR, so3, S.x);  // used by the owner only
+    const uint32_t oo = kv && own_plane ? vw3 : kOOR;  // used by the owner only
+    if constexpr (XU >= 1) bload3(rs_x, oo, so3, S.x);
+    if constexpr (XU == 2) bload3(rs_po, oo, so3, S.q);
   };
   // zq: the node's p' (unmasked: the output of a fixed DOF); dq: its D^-1
   auto stage_f = [&](const FusedStage<T, DN>& S, int buf, int k, T (&zq)[3], T (&dq)[DN]) {
@@ -669,14 +687,15 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
       pn[c] = zn + be * S.p[c];
       nb[c] = zmasked(S.m, c, pn[c]);
       zq[c] = pn[c];
-      xn[c] = S.x[c] + al * S.p[c];
+      if constexpr (XU == 1) xn[c] = S.x[c] + al * S.p[c];
+      if constexpr (XU == 2) xn[c] = (S.x[c] + alq * S.q[c]) + al * S.p[c];
       rz += rn[c] * zn;
       if constexpr (RR) rr += rn[c] * rn[c];
     }
     const bool owner = writer && own_plane;
     tpart[0][0] += owner ? rz : (T)0;                    // r.z
     if constexpr (RR) tpart[0][1] += owner ? rr : (T)0;  // r.r
-    bstore3(rs_xo, o3, so3, xn);
+    if constexpr (XU >= 1) bstore3(rs_xo, o3, so3, xn);
     bstore3(rs_ro, o3, so3, rn);
     bstore3(rs_po, o3, so3, pn);
   };
@@ -1238,7 +1257,7 @@ __global__ void __launch_bounds__(kApplyMaxThreads)
     const int cnt[5] = {A.n_gam, A.n_apply, A.n_apply, tol ? A.n_gam : 0, tol ? A.n_fn : 0};
     reduce_parts<5, 0u>(pre, src, cnt);
     double alpha, beta;
-    cg_coefficients(pre[0], pre[1], pre[2], pre[3], pre[4], 0, A.rtol, const_cast<Scalars*>(A.sc),
+    cg_coefficients(pre[0], pre[1], pre[2], pre[3], pre[4], 0, par, A.rtol, const_cast<Scalars*>(A.sc),
                     lb == 0 && tid == 0, alpha, beta);
     al = wave_uniform((T)alpha);
   };
@@ -1467,7 +1486,7 @@ static TileChoice choose_tile(const Geo& G, int n_cu, int lds_per_cu, int overri
   return best;
 }
 
-template <typename T, int NR, int MODE, bool RR = true, int DN = 1>
+template <typename T, int NR, int MODE, bool RR = true, int DN = 1, int XU = 1>
 static hipError_t launch_apply_t(fbto_grid_s* g, const ApplyArgs<T>& A0, int rhs0, hipStream_t st,
                                  int* nb_out) {
   TileChoice& t = g->tiles[sizeof(T) == 8 ? 1 : 0][NR - 1][MODE];
@@ -1490,11 +1509,11 @@ static hipError_t launch_apply_t(fbto_grid_s* g, const ApplyArgs<T>& A0, int rhs
   size_t lds = apply_lds_bytes<T, NR, MODE>(t.bx, t.by);
   if (t.cap) lds = std::max(lds, (size_t)lds_for_block_cap(g->lds_per_cu, t.cap));
   const int threads = zmarch_threads<MODE>(t.bx, t.by);  // whole waves
-  hipLaunchKernelGGL((k_apply<T, NR, MODE, RR, DN>), dim3(grid), dim3(threads), lds, st, A, rhs0);
+  hipLaunchKernelGGL((k_apply<T, NR, MODE, RR, DN, XU>), dim3(grid), dim3(threads), lds, st, A, rhs0);
   return hipGetLastError();
 }
 
-template <typename T, int MODE, bool RR = true, int DN = 1>
+template <typename T, int MODE, bool RR = true, int DN = 1, int XU = 1>
 static hipError_t launch_apply_mode(fbto_grid_s* g, ApplyArgs<T> A, int nrhs, hipStream_t st, int* nb_out) {
   A.g = g->geo;
   A.mask = g->mask;
@@ -1510,7 +1529,7 @@ static hipError_t launch_apply_mode(fbto_grid_s* g, ApplyArgs<T> A, int nrhs, hi
   // sets, the modal carry, staged loads) fills the register file at NR = 1
   hipError_t e = hipSuccess;
   for (int r0 = 0; r0 < nrhs && e == hipSuccess; ++r0) {
-    e = launch_apply_t<T, 1, MODE, RR, DN>(g, A, r0, st, nb_out);
+    e = launch_apply_t<T, 1, MODE, RR, DN, XU>(g, A, r0, st, nb_out);
     A.dinv_out = nullptr;  // the same for every RHS
   }
   return e;
@@ -1632,10 +1651,16 @@ hipError_t launch_cg_sens(fbto_grid_s* g, const T* rho, const CgSet<T>& in, T* x
   return hipGetLastError();
 }
 
+// Grids whose iterate is updated every second step: 2^19 elements and more,
+// without springs.  On smaller ones the steps are bound by latency, and two
+// kernels in turn measured slower than one (16x8x8 FP64 iteration 85.8 against
+// 84.0 us); four-load 384x192x192 iteration 13.47 -> 13.19 ms with it,
+// 128x64x64 FP64 308 -> 303 us.
+bool cg_pairs_updates(const fbto_grid_s* g) { return g->geo.E >= ((int64_t)1 << 19) && g->n_springs == 0; }
+
 template <typename T>
-hipError_t launch_cg_fused(fbto_grid_s* g, const T* rho, const CgSet<T>& in, const CgSet<T>& out,
-                           int nrhs, int step, const CgCnt& cn, double rtol, hipStream_t st,
-                           int* nb_out) {
+hipError_t launch_cg_fused(fbto_grid_s* g, const T* rho, const CgSet<T>& in, const CgSet<T>& out, int nrhs, int step,
+                           int x_updates, const CgCnt& cn, double rtol, hipStream_t st, int* nb_out) {
   ApplyArgs<T> A{};
   A.rho = rho;
   A.y = out.s;
@@ -1648,11 +1673,21 @@ hipError_t launch_cg_fused(fbto_grid_s* g, const T* rho, const CgSet<T>& in, con
   A.n_fn = cn.fn;
   A.rtol = rtol;
   // r.r only for the tolerance test
-  if (g->n_springs > 0)
-    return rtol > 0.0 ? launch_apply_mode<T, MODE_CGF, true, 3>(g, A, nrhs, st, nb_out)
-                      : launch_apply_mode<T, MODE_CGF, false, 3>(g, A, nrhs, st, nb_out);
-  return rtol > 0.0 ? launch_apply_mode<T, MODE_CGF, true, 1>(g, A, nrhs, st, nb_out)
-                    : launch_apply_mode<T, MODE_CGF, false, 1>(g, A, nrhs, st, nb_out);
+  if (g->n_springs > 0) {
+    if (x_updates != 1) return hipErrorInvalidValue;
+    return rtol > 0.0 ? launch_apply_mode<T, MODE_CGF, true, 3, 1>(g, A, nrhs, st, nb_out)
+                      : launch_apply_mode<T, MODE_CGF, false, 3, 1>(g, A, nrhs, st, nb_out);
+  }
+  auto run = [&](auto xu) {
+    constexpr int XU = decltype(xu)::value;
+    return rtol > 0.0 ? launch_apply_mode<T, MODE_CGF, true, 1, XU>(g, A, nrhs, st, nb_out)
+                      : launch_apply_mode<T, MODE_CGF, false, 1, XU>(g, A, nrhs, st, nb_out);
+  };
+  switch (x_updates) {
+    case 0: return run(std::integral_constant<int, 0>{});
+    case 1: return run(std::integral_constant<int, 1>{});
+    default: return run(std::integral_constant<int, 2>{});
+  }
 }
 
 template <typename T>
@@ -1793,8 +1828,8 @@ __global__ void __launch_bounds__(kVecBlock)
 #pragma unroll
   for (int R = 0; R < NR; ++R) {
     double alpha, beta;
-    cg_coefficients(pre[5 * R], pre[5 * R + 1], pre[5 * R + 2], pre[5 * R + 3], pre[5 * R + 4], R, rtol, sc, lead,
-                    alpha, beta);
+    cg_coefficients(pre[5 * R], pre[5 * R + 1], pre[5 * R + 2], pre[5 * R + 3], pre[5 * R + 4], R, par, rtol, sc,
+                    lead, alpha, beta);
     al[R] = (T)alpha;
     be[R] = (T)beta;
   }
@@ -3218,7 +3253,7 @@ hipError_t launch_opt_finish(fbto_grid_s* g, int nrhs, int nb_dot, int nb_lo, in
   template hipError_t launch_cg_sens<T>(fbto_grid_s*, const T*, const CgSet<T>&, T*, const T*, T*, const T*, int, \
                                         const CgCnt&, double, hipStream_t, int*);                      \
   template hipError_t launch_cg_fused<T>(fbto_grid_s*, const T*, const CgSet<T>&, const CgSet<T>&,      \
-                                         int, int, const CgCnt&, double, hipStream_t, int*);           \
+                                         int, int, int, const CgCnt&, double, hipStream_t, int*);      \
   template hipError_t launch_diag<T>(fbto_grid_s*, const T*, T*, hipStream_t);                         \
   template hipError_t launch_relax_update<T>(fbto_grid_s*, T*, const T*, const T*, int, double, int,    \
                                              hipStream_t);                                             \
