@@ -366,7 +366,7 @@ fbto_status_t krylov_run(fbto_grid_s* g, const T* rho, const T* f, T* u, int nrh
                          hipStream_t st, CgCounts* cn_out = nullptr) {
   Vecs& V = vecs<T>(g);
   const int64_t nd = g->geo.ndof;
-  T* Y = (T*)V.s[0];
+  T* Yb[2] = {(T*)V.s[0], (T*)V.s[1]};
   const int last = D + 2;
   for (int R = 0; R < nrhs; ++R) {
     T* x = u + R * nd;
@@ -377,45 +377,30 @@ fbto_status_t krylov_run(fbto_grid_s* g, const T* rho, const T* f, T* u, int nrh
     T* W2 = (T*)V.p[1];
     HIP_TRY(launch_resid<T>(g, rho, x, fr, R2, 0, 1, st, nullptr));  // R2 = f - K u
     int nb_v = 0, nb_a = 0;
-    HIP_TRY(launch_minres<T>(g, 0, last, Y, R1, R2, W2, Wc, x, 0, 0, damp, st, &nb_v));
-    int itn0 = 1;
-    if (g->dim == 3) {
-      // voxel grids: iterations 1 .. D fused (vector pass t with the product of
-      // t + 1); products alternate between two buffers, the Lanczos
-      // vectors rotate through three (halo nodes read them while their
-      // owners write the next one)
-      T* Yb[2] = {(T*)V.s[0], (T*)V.s[1]};
-      T* R3 = (T*)V.x1;
-      HIP_TRY(launch_apply_lanczos<T>(g, rho, R2, R2, Yb[1], 1, st, &nb_a));
-      for (int itn = 1; itn <= D; ++itn) {
-        int nb = 0;
-        HIP_TRY(launch_minres_fused<T>(g, rho, itn, Yb[itn & 1], R1, R2, R3, Wc, W2, x, Yb[(itn + 1) & 1], nb_a,
-                                       nb_v, damp, st, &nb));
-        nb_a = nb_v = nb;
-        T* t = R1;
-        R1 = R2;
-        R2 = R3;
-        R3 = t;
-        if (itn >= 2) std::swap(Wc, W2);
-      }
-      // iteration D + 1: the unfused vector pass on the last product
+    HIP_TRY(launch_minres<T>(g, 0, last, Yb[0], R1, R2, W2, Wc, x, 0, 0, damp, st, &nb_v));
+    // iterations 1 .. D fused (vector pass t with the product of t + 1);
+    // products alternate between two buffers, the Lanczos vectors rotate
+    // through three (halo nodes read them while their owners write the next one)
+    T* R3 = (T*)V.x1;
+    HIP_TRY(launch_apply_lanczos<T>(g, rho, R2, R2, Yb[1], 1, st, &nb_a));
+    for (int itn = 1; itn <= D; ++itn) {
       int nb = 0;
-      HIP_TRY(launch_minres<T>(g, D + 1, last, Yb[(D + 1) & 1], R1, R2, W2, Wc, x, nb_a, nb_v, damp, st, &nb));
-      nb_v = nb;
-      std::swap(R1, R2);
-      if (D + 1 >= 2) std::swap(Wc, W2);
-      itn0 = D + 2;
+      HIP_TRY(launch_minres_fused<T>(g, rho, itn, Yb[itn & 1], R1, R2, R3, Wc, W2, x, Yb[(itn + 1) & 1], nb_a, nb_v,
+                                     damp, st, &nb));
+      nb_a = nb_v = nb;
+      T* t = R1;
+      R1 = R2;
+      R2 = R3;
+      R3 = t;
+      if (itn >= 2) std::swap(Wc, W2);
     }
-    for (int itn = itn0; itn <= D + 1; ++itn) {
-      // Y = K R2 with <A.r, R2> and <Y, R2>; A.r = R1 (R2 on the first iteration, where R1 is unused)
-      HIP_TRY(launch_apply_lanczos<T>(g, rho, R2, itn == 1 ? R2 : R1, Y, itn, st, &nb_a));
-      int nb = 0;
-      HIP_TRY(launch_minres<T>(g, itn, last, Y, R1, R2, W2, Wc, x, nb_a, nb_v, damp, st, &nb));
-      nb_v = nb;
-      std::swap(R1, R2);                 // R1 <- R2, R2 <- the new Lanczos vector
-      if (itn >= 2) std::swap(Wc, W2);   // W <- the new direction, W2 <- W
-    }
-    HIP_TRY(launch_minres<T>(g, last, last, Y, R1, R2, W2, Wc, x, 0, nb_v, damp, st, nullptr));
+    // iteration D + 1: the unfused vector pass on the last product
+    int nb = 0;
+    HIP_TRY(launch_minres<T>(g, D + 1, last, Yb[(D + 1) & 1], R1, R2, W2, Wc, x, nb_a, nb_v, damp, st, &nb));
+    nb_v = nb;
+    std::swap(R1, R2);
+    if (D + 1 >= 2) std::swap(Wc, W2);
+    HIP_TRY(launch_minres<T>(g, last, last, Yb[0], R1, R2, W2, Wc, x, 0, nb_v, damp, st, nullptr));
   }
   // the norms of the final residual (itself not needed)
   int nb = 0;

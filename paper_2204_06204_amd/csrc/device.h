@@ -167,6 +167,71 @@ __device__ __forceinline__ void write_parts(double (&v)[NV], double* const (&dst
   }
 }
 
+// Scalar recurrence of MINRES pass itn (see k_minres), from ||R2||^2 and, with
+// `lanczos`, the partials <R1, R2> and <Y, R2> of its product; ks is the state
+// that pass itn - 1 left.  Every block runs it on the same reduced values in
+// the same order; the lead thread stores the next state.
+constexpr double kTinyNorm = 1e-30;  // a norm below this is zero (FP32 reciprocals stay finite)
+struct MinresCoef {
+  double s, c1, as;                        // y = s Y - c1 R1 - as R2
+  double inv_oldb, wc1, wc2, inv_gamma;    // w = (R1 inv_oldb - wc1 W2 - wc2 W) inv_gamma
+  double phi;                              // x += damp phi w
+};
+__device__ __forceinline__ MinresCoef minres_scalars(int itn, bool lanczos, double nrm2, double r12, double yr2,
+                                                     const double (&ks)[7], double* next, bool lead) {
+  MinresCoef q;
+  const double beta = itn >= 1 ? sqrt(fmax(nrm2, 0.0)) : 0.0;
+  double oldb = 0.0, alfa_prev = 0.0, dbar = 0.0, epsln = 0.0, phibar = beta, cs = -1.0, sn = 0.0;
+  if (itn >= 2) {
+    oldb = ks[0];
+    alfa_prev = ks[1];
+    dbar = ks[2];
+    epsln = ks[3];
+    phibar = ks[4];
+    cs = ks[5];
+    sn = ks[6];
+  }
+  // Givens rotation of iteration itn - 1
+  double oldeps = 0.0, delta = 0.0, gamma = 1.0, phi = 0.0;
+  if (itn >= 2) {
+    oldeps = epsln;
+    delta = cs * dbar + sn * alfa_prev;
+    const double gbar = sn * dbar - cs * alfa_prev;
+    epsln = sn * beta;
+    dbar = -cs * beta;
+    gamma = fmax(sqrt(gbar * gbar + beta * beta), 1e-300);
+    cs = gbar / gamma;
+    sn = beta / gamma;
+    phi = cs * phibar;
+    phibar = sn * phibar;
+  }
+  // Lanczos step of iteration itn.  Norms below kTinyNorm mean the Krylov
+  // space is exhausted (the residual is zero to rounding): the reciprocals are
+  // then taken as 0, so every further vector and update is 0 rather than 0 *
+  // inf in FP32.
+  const double s = beta > kTinyNorm ? 1.0 / beta : 0.0;
+  const double c1 = (itn >= 2 && oldb > kTinyNorm) ? beta / oldb : 0.0;
+  const double alfa = lanczos ? s * (s * yr2 - c1 * r12) : 0.0;
+  if (lead && itn >= 1) {
+    next[0] = beta;
+    next[1] = alfa;
+    next[2] = dbar;
+    next[3] = epsln;
+    next[4] = phibar;
+    next[5] = cs;
+    next[6] = sn;
+  }
+  q.s = s;
+  q.c1 = c1;
+  q.as = alfa * s;
+  q.inv_oldb = oldb > kTinyNorm ? 1.0 / oldb : 0.0;
+  q.wc1 = oldeps;
+  q.wc2 = delta;
+  q.inv_gamma = gamma > kTinyNorm ? 1.0 / gamma : 0.0;
+  q.phi = phi;
+  return q;
+}
+
 // q = n / d for 0 <= n < 2^31 with rd = 1.0 / d: the FP64 product is within
 // 2^-21 of n / d, so one correction step makes the quotient exact.
 __device__ __forceinline__ int fdiv(int n, int d, double rd) {

@@ -389,13 +389,18 @@ hipError_t plane_filter(fbto_grid_s* g, int kind, const T* in, T* out, T* tmp, c
                         hipStream_t st);
 template <typename T>
 hipError_t plane_hs(fbto_grid_s* g, T* Hsi, hipStream_t st);
+template <typename T>
+hipError_t plane_minres_fused(fbto_grid_s* g, const T* rho, int itn, const T* Y, const T* R1, const T* R2, T* R3,
+                              const T* W, T* W2, T* x, T* Ynext, int n_apply, int n_kr, double damp, hipStream_t st,
+                              int* nb_out);
 // One vector pass of the Krylov step (MINRES recurrence), iteration `itn`
 // of 0 .. last (see k_minres); returns the block count of its partials.
 template <typename T>
 hipError_t launch_minres(fbto_grid_s* g, int itn, int last, const T* Y, T* R1, const T* R2, T* W2, const T* W,
                          T* x, int n_apply, int n_prev, double damp, hipStream_t st, int* nb_out);
-// FP32: the vector pass of iteration itn (1 .. D) fused with iteration
-// itn + 1's product (k_apply's MRF mode): y -> R3, K y -> Ynext.
+// The vector pass of iteration itn (1 .. D) fused with iteration itn + 1's
+// product (voxel grids: k_apply's MRF mode; plane grids: k_plane_minres):
+// y -> R3, K y -> Ynext.
 template <typename T>
 hipError_t launch_minres_fused(fbto_grid_s* g, const T* rho, int itn, const T* Y, const T* R1, const T* R2, T* R3,
                                const T* W, T* W2, T* x, T* Ynext, int n_apply, int n_kr, double damp,

@@ -116,7 +116,6 @@ enum { MODE_APPLY = 0, MODE_RESID = 1, MODE_CG = 2, MODE_CGF = 3, MODE_SENSF = 4
 static_assert(MODE_LZ < kApplyModes, "a tile choice per mode");
 constexpr int kApplyMaxThreads = 512;
 constexpr int kApplyMaxBlocks = 8192;
-constexpr double kTinyNorm = 1e-30;  // Krylov step: a norm below this is zero (FP32 reciprocals stay finite)
 
 // Bits 3 R + 1 for R < nr: the |r|_inf entries (max-reduced) of the
 // per-RHS triples (sum of squares, |r|_inf, another sum) that the residual
@@ -711,53 +710,19 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
                             pslot(A.P, P_PQ0 + (itn & 1), 0, A.maxp)};
     const int cnt[3] = {A.n_kr, A.n_apply, A.n_apply};
     reduce_parts<3, 0u>(v, src, cnt);
-    const double beta = sqrt(fmax(v[0], 0.0)), r12 = v[1], yr2 = v[2];
-    double oldb = 0.0, alfa_prev = 0.0, dbar = 0.0, epsln = 0.0, phibar = beta, cs = -1.0, sn = 0.0;
     Scalars* sc = const_cast<Scalars*>(A.sc);
-    if (itn >= 2) {
-      const double* k = sc->kr[(itn + 1) & 1];
-      oldb = k[0];
-      alfa_prev = k[1];
-      dbar = k[2];
-      epsln = k[3];
-      phibar = k[4];
-      cs = k[5];
-      sn = k[6];
-    }
-    double oldeps = 0.0, delta = 0.0, gamma = 1.0, phi = 0.0;
-    if (itn >= 2) {
-      oldeps = epsln;
-      delta = cs * dbar + sn * alfa_prev;
-      const double gbar = sn * dbar - cs * alfa_prev;
-      epsln = sn * beta;
-      dbar = -cs * beta;
-      gamma = fmax(sqrt(gbar * gbar + beta * beta), 1e-300);
-      cs = gbar / gamma;
-      sn = beta / gamma;
-      phi = cs * phibar;
-      phibar = sn * phibar;
-    }
-    const double sv = beta > kTinyNorm ? 1.0 / beta : 0.0;  // as in k_minres
-    const double c1 = (itn >= 2 && oldb > kTinyNorm) ? beta / oldb : 0.0;
-    const double alfa = sv * (sv * yr2 - c1 * r12);
-    if (lb == 0 && tid == 0) {
-      double* k = sc->kr[itn & 1];
-      k[0] = beta;
-      k[1] = alfa;
-      k[2] = dbar;
-      k[3] = epsln;
-      k[4] = phibar;
-      k[5] = cs;
-      k[6] = sn;
-    }
-    ms = uniform((T)sv);
-    mc1 = uniform((T)c1);
-    mas = uniform((T)(alfa * sv));
-    minvb = uniform((T)(oldb > kTinyNorm ? 1.0 / oldb : 0.0));
-    mwc1 = uniform((T)oldeps);
-    mwc2 = uniform((T)delta);
-    minvg = uniform((T)(gamma > kTinyNorm ? 1.0 / gamma : 0.0));
-    mstep = uniform((T)(A.damp * phi));
+    double ks[7];
+#pragma unroll
+    for (int i = 0; i < 7; ++i) ks[i] = sc->kr[(itn + 1) & 1][i];
+    const MinresCoef q = minres_scalars(itn, true, v[0], v[1], v[2], ks, sc->kr[itn & 1], lb == 0 && tid == 0);
+    ms = uniform((T)q.s);
+    mc1 = uniform((T)q.c1);
+    mas = uniform((T)q.as);
+    minvb = uniform((T)q.inv_oldb);
+    mwc1 = uniform((T)q.wc1);
+    mwc2 = uniform((T)q.wc2);
+    minvg = uniform((T)q.inv_gamma);
+    mstep = uniform((T)(A.damp * q.phi));
   };
   // fused MINRES step (single vectors, rhs0 = 0): the memory access of the fused CG step
   const __amdgpu_buffer_rsrc_t rs_mY = vres(A.mY), rs_mR1 = vres(A.mR1), rs_mR2 = vres(A.mR2), rs_mW = vres(A.mW),
@@ -1694,6 +1659,8 @@ template <typename T>
 hipError_t launch_minres_fused(fbto_grid_s* g, const T* rho, int itn, const T* Y, const T* R1, const T* R2, T* R3,
                                const T* W, T* W2, T* x, T* Ynext, int n_apply, int n_kr, double damp,
                                hipStream_t st, int* nb_out) {
+  if (g->dim == 2)
+    return plane_minres_fused<T>(g, rho, itn, Y, R1, R2, R3, W, W2, x, Ynext, n_apply, n_kr, damp, st, nb_out);
   ApplyArgs<T> A{};
   A.rho = rho;
   A.y = Ynext;
@@ -2042,13 +2009,13 @@ template <typename T>
 __global__ void __launch_bounds__(kVecBlock)
     k_minres(int64_t n, int itn, int last, const T* Y, T* R1, const T* R2, T* W2, const T* W, T* x,
              double* P, int maxp, int n_apply, int n_prev, Scalars* sc, double damp) {
-  double beta = 0.0;
+  double nrm2 = 0.0;
   if (itn >= 1) {
     double v[1];
     const double* src[1] = {pslot(P, P_KRN0 + ((itn - 1) & 1), 0, maxp)};
     const int cnt[1] = {n_prev};
     reduce_parts<1, 0u>(v, src, cnt);
-    beta = sqrt(fmax(v[0], 0.0));
+    nrm2 = v[0];
   }
   const bool lanczos = itn >= 1 && itn < last;
   const bool finish = itn >= 2;
@@ -2061,54 +2028,16 @@ __global__ void __launch_bounds__(kVecBlock)
     r12 = v[0];
     yr2 = v[1];
   }
-  // state carried from the previous pass
-  double oldb = 0.0, alfa_prev = 0.0, dbar = 0.0, epsln = 0.0, phibar = beta, cs = -1.0, sn = 0.0;
-  if (itn >= 2) {
-    const double* k = sc->kr[(itn + 1) & 1];  // written by pass itn - 1
-    oldb = k[0];
-    alfa_prev = k[1];
-    dbar = k[2];
-    epsln = k[3];
-    phibar = k[4];
-    cs = k[5];
-    sn = k[6];
-  }
-  // Givens rotation of iteration itn - 1
-  double oldeps = 0.0, delta = 0.0, gamma = 1.0, phi = 0.0;
-  if (finish) {
-    oldeps = epsln;
-    delta = cs * dbar + sn * alfa_prev;
-    const double gbar = sn * dbar - cs * alfa_prev;
-    epsln = sn * beta;
-    dbar = -cs * beta;
-    gamma = fmax(sqrt(gbar * gbar + beta * beta), 1e-300);
-    cs = gbar / gamma;
-    sn = beta / gamma;
-    phi = cs * phibar;
-    phibar = sn * phibar;
-  }
-  // Lanczos step of iteration itn.  Norms below kTinyNorm mean the Krylov
-  // space is exhausted (the residual is zero to rounding): the
-  // reciprocals are then taken as 0, so every further vector and update is
-  // 0 rather than 0 * inf in FP32.
-  const double s = beta > kTinyNorm ? 1.0 / beta : 0.0;
-  const double c1 = (itn >= 2 && oldb > kTinyNorm) ? beta / oldb : 0.0;
-  const double alfa = lanczos ? s * (s * yr2 - c1 * r12) : 0.0;
-  if (blockIdx.x == 0 && threadIdx.x == 0 && itn >= 1) {
-    double* k = sc->kr[itn & 1];
-    k[0] = beta;
-    k[1] = alfa;
-    k[2] = dbar;
-    k[3] = epsln;
-    k[4] = phibar;
-    k[5] = cs;
-    k[6] = sn;
-  }
+  double ks[7];  // written by pass itn - 1
+#pragma unroll
+  for (int i = 0; i < 7; ++i) ks[i] = sc->kr[(itn + 1) & 1][i];
+  const MinresCoef q =
+      minres_scalars(itn, lanczos, nrm2, r12, yr2, ks, sc->kr[itn & 1], blockIdx.x == 0 && threadIdx.x == 0);
   const int j = itn - 1;  // the iteration finished here
-  const T inv_oldb = (T)(oldb > kTinyNorm ? 1.0 / oldb : 0.0);
-  const T wc1 = (T)oldeps, wc2 = (T)delta, inv_gamma = (T)(gamma > kTinyNorm ? 1.0 / gamma : 0.0);
-  const T step = (T)(damp * phi);
-  const T ts = (T)s, tc1 = (T)c1, ta = (T)(alfa * s);
+  const T inv_oldb = (T)q.inv_oldb;
+  const T wc1 = (T)q.wc1, wc2 = (T)q.wc2, inv_gamma = (T)q.inv_gamma;
+  const T step = (T)(damp * q.phi);
+  const T ts = (T)q.s, tc1 = (T)q.c1, ta = (T)q.as;
   double acc = 0.0;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
     const T r1 = R1[i];

@@ -10,7 +10,8 @@
 // The plane grids of the paper (at most 192 x 576 elements, 0.9 MB per FP32
 // vector) sit in the L2 and Infinity caches, so these kernels gather
 // directly from global memory: one node (apply) or element (sensitivity)
-// per thread, its 3 x 3 node neighbourhood read through L1/L2.  The
+// per thread, its 3 x 3 node neighbourhood read through L1/L2; the MINRES step
+// (k_plane_minres) stages tiles in LDS.  The
 // reductions use the per-block partial slots of the 3D path, with the same
 // meaning, so the CG, MINRES, projection and finishing kernels serve both.
 #include <hip/hip_runtime.h>
@@ -194,6 +195,189 @@ __global__ void __launch_bounds__(kPlaneBlock) k_plane_apply(PlaneArgs<T> A, int
       for (int r = 0; r < NR; ++r) pslot2(A.P, P_RN0, rhs0 + r, A.maxp)[blockIdx.x] = part[4 * r];
     }
   }
+}
+
+// The fused MINRES step of the Krylov low-level step: the vector pass of
+// iteration t (see k_minres) and iteration t + 1's product K y of its new
+// Lanczos vector y.  A block owns a tile of 32 x 8 nodes, one per thread; y is
+// formed at them and (by the first 84 threads) at the ring of halo nodes around
+// them, and staged in LDS masked; s_e of the tile's 33 x 9 elements is staged
+// beside it.  Y, R1 and R2 are read at halo nodes too, so y goes to a third
+// buffer R3 and the product to the other Y buffer.  As two kernels (vector
+// pass, product) the step was bound by two launches, each waiting for the
+// partials of the one before: 8.0 + 8.2 us at 576 x 192 FP64.  The loads of a
+// block's first tile are issued before its prologue reduces the partials.
+constexpr int kPmX = 32, kPmY = 8, kPmRing = 2 * (kPmX + 2) + 2 * kPmY;
+static_assert(kPmX * kPmY == kPlaneBlock, "one node per thread");
+template <typename T>
+struct Vec2 {
+  T v[2];
+};
+template <typename T>
+struct PlaneMinresArgs {
+  int nx, ny, tiles_x, ntiles;
+  const T* rho;
+  const T *Y, *R1, *R2, *W;
+  T *R3, *W2, *x, *Ynext;
+  const uint8_t* mask;
+  Q4<T> ke;
+  Simp sp;
+  double* P;
+  int maxp;
+  Scalars* sc;
+  int itn, n_apply, n_kr;
+  double damp;
+};
+
+template <typename T>
+__global__ void __launch_bounds__(kPlaneBlock) k_plane_minres(PlaneMinresArgs<T> A) {
+  using V2 = Vec2<T>;
+  constexpr int LX = kPmX + 2, LY = kPmY + 2;   // staged nodes
+  constexpr int SX = kPmX + 1, SY = kPmY + 1;   // staged elements
+  __shared__ T ys[LX * LY][2];
+  __shared__ T ss[SX * SY];
+  const int tid = threadIdx.x, tx = tid % kPmX, ty = tid / kPmX;
+  const int nxn = A.nx + 1, itn = A.itn;
+  // LDS position of the thread's ring node, if it has one, and of its second element
+  const bool has_ring = tid < kPmRing;
+  int rx, ry;
+  if (tid < 2 * LX) {
+    rx = tid < LX ? tid : tid - LX;
+    ry = tid < LX ? 0 : LY - 1;
+  } else {
+    const int t = tid - 2 * LX;
+    rx = t < kPmY ? 0 : LX - 1;
+    ry = 1 + (t < kPmY ? t : t - kPmY);
+  }
+  const bool has_el = tid < kPmX + SY;
+  const int fx = tid < SY ? kPmX : tid - SY, fy = tid < SY ? tid : kPmY;
+
+  struct Node {
+    V2 y, r1, r2;
+    unsigned m;
+    bool ok;
+  };
+  Node own, ring;
+  V2 wv{}, w2v{}, xv{};
+  T re[2];
+  bool oke[2];
+  int n = 0;
+  auto load_node = [&](int i, int j, bool want, Node& q) -> int {
+    q.ok = want && i >= 0 && i <= A.nx && j >= 0 && j <= A.ny;
+    const int k = q.ok ? i + nxn * j : 0;
+    q.y = reinterpret_cast<const V2*>(A.Y)[k];
+    q.r1 = reinterpret_cast<const V2*>(A.R1)[k];
+    q.r2 = reinterpret_cast<const V2*>(A.R2)[k];
+    q.m = A.mask[k];
+    return k;
+  };
+  auto load_elem = [&](int ex, int ey, bool want, T& r, bool& ok) {
+    ok = want && ex >= 0 && ex < A.nx && ey >= 0 && ey < A.ny;
+    r = A.rho[ok ? ex + A.nx * ey : 0];
+  };
+  auto load_tile = [&](int t) {
+    const int x0 = (t % A.tiles_x) * kPmX, y0 = (t / A.tiles_x) * kPmY;
+    n = load_node(x0 + tx, y0 + ty, true, own);
+    load_node(x0 - 1 + rx, y0 - 1 + ry, has_ring, ring);
+    load_elem(x0 - 1 + tx, y0 - 1 + ty, true, re[0], oke[0]);
+    load_elem(x0 - 1 + fx, y0 - 1 + fy, has_el, re[1], oke[1]);
+    wv = reinterpret_cast<const V2*>(A.W)[n];
+    w2v = reinterpret_cast<const V2*>(A.W2)[n];
+    xv = reinterpret_cast<const V2*>(A.x)[n];
+  };
+  load_tile(blockIdx.x);
+
+  double ks[7], pv[3];
+#pragma unroll
+  for (int i = 0; i < 7; ++i) ks[i] = A.sc->kr[(itn + 1) & 1][i];
+  {
+    const double* src[3] = {pslot2(A.P, P_KRN0 + ((itn + 1) & 1), 0, A.maxp), pslot2(A.P, P_RZ0 + (itn & 1), 0, A.maxp),
+                            pslot2(A.P, P_PQ0 + (itn & 1), 0, A.maxp)};
+    const int cnt[3] = {A.n_kr, A.n_apply, A.n_apply};
+    reduce_parts<3, 0u>(pv, src, cnt);
+  }
+  const MinresCoef q =
+      minres_scalars(itn, true, pv[0], pv[1], pv[2], ks, A.sc->kr[itn & 1], blockIdx.x == 0 && tid == 0);
+  const T s = (T)q.s, c1 = (T)q.c1, as = (T)q.as, inv_oldb = (T)q.inv_oldb;
+  const T wc1 = (T)q.wc1, wc2 = (T)q.wc2, inv_gamma = (T)q.inv_gamma, step = (T)(A.damp * q.phi);
+
+  double part[3] = {0.0, 0.0, 0.0};  // ||y||^2, <K y, y>, <R2, y>
+  for (int t = blockIdx.x; t < A.ntiles; t += gridDim.x) {
+    if (t != (int)blockIdx.x) {
+      __syncthreads();  // the last tile's product has read the LDS
+      load_tile(t);
+    }
+    T yo[2];  // the own node's y
+    auto stage = [&](const Node& q, int li, T (&yn)[2]) {
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        const T r1m = itn >= 2 ? q.r1.v[c] : (T)0;  // R1 holds no vector yet on the first iteration
+        yn[c] = s * q.y.v[c] - c1 * r1m - as * q.r2.v[c];
+        ys[li][c] = q.ok && !((q.m >> c) & 1u) ? yn[c] : (T)0;
+      }
+    };
+    stage(own, tx + 1 + LX * (ty + 1), yo);
+    if (has_ring) {
+      T yr[2];
+      stage(ring, rx + LX * ry, yr);
+    }
+    ss[tx + SX * ty] = oke[0] ? simp_s<T>(re[0], A.sp) : (T)0;
+    if (has_el) ss[fx + SX * fy] = oke[1] ? simp_s<T>(re[1], A.sp) : (T)0;
+    if (own.ok) {
+      V2 wn, xn, yn;
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        const T wm = itn >= 3 ? wv.v[c] : (T)0, w2m = itn >= 4 ? w2v.v[c] : (T)0;  // zero before the first
+        wn.v[c] = (own.r1.v[c] * inv_oldb - wc1 * w2m - wc2 * wm) * inv_gamma;
+        xn.v[c] = xv.v[c] + step * wn.v[c];
+        yn.v[c] = yo[c];
+        part[0] += (double)yo[c] * (double)yo[c];
+        part[2] += (double)own.r2.v[c] * (double)yo[c];
+      }
+      reinterpret_cast<V2*>(A.R3)[n] = yn;
+      if (itn >= 2) {  // finishes iteration t - 1
+        reinterpret_cast<V2*>(A.W2)[n] = wn;
+        reinterpret_cast<V2*>(A.x)[n] = xn;
+      }
+    }
+    __syncthreads();
+    // K y at the own node from the four elements around it, in k_plane_apply's order
+    T acc[2] = {(T)0, (T)0};
+#pragma unroll
+    for (int ay = 0; ay < 2; ++ay)
+#pragma unroll
+      for (int ax = 0; ax < 2; ++ax) {
+        const T se = ss[tx + 1 - ax + SX * (ty + 1 - ay)];
+        const int a = ax + 2 * ay;
+        T tc[2] = {(T)0, (T)0};
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+          const int bx = b & 1, by = b >> 1;
+          const int li = tx + 1 + bx - ax + LX * (ty + 1 + by - ay);
+#pragma unroll
+          for (int d = 0; d < 2; ++d) {
+            const T v = ys[li][d];
+#pragma unroll
+            for (int c = 0; c < 2; ++c) tc[c] += A.ke.k[2 * a + c][2 * b + d] * v;
+          }
+        }
+#pragma unroll
+        for (int c = 0; c < 2; ++c) acc[c] += se * tc[c];
+      }
+    if (own.ok) {
+      V2 o;
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        if ((own.m >> c) & 1u) acc[c] = yo[c];  // identity row of a fixed DOF
+        o.v[c] = acc[c];
+        part[1] += (double)acc[c] * (double)yo[c];
+      }
+      reinterpret_cast<V2*>(A.Ynext)[n] = o;
+    }
+  }
+  double* dst[3] = {pslot2(A.P, P_KRN0 + (itn & 1), 0, A.maxp), pslot2(A.P, P_PQ0 + ((itn + 1) & 1), 0, A.maxp),
+                    pslot2(A.P, P_RZ0 + ((itn + 1) & 1), 0, A.maxp)};
+  write_parts<3, 0u>(part, dst, blockIdx.x);
 }
 
 // Jacobi diagonal: ke_diag * (sum of s over the node's elements), 1 at fixed DOFs.
@@ -413,6 +597,36 @@ hipError_t plane_apply_lanczos(fbto_grid_s* g, const T* rho, const T* u, const T
 }
 
 template <typename T>
+hipError_t plane_minres_fused(fbto_grid_s* g, const T* rho, int itn, const T* Y, const T* R1, const T* R2, T* R3,
+                              const T* W, T* W2, T* x, T* Ynext, int n_apply, int n_kr, double damp, hipStream_t st,
+                              int* nb_out) {
+  PlaneMinresArgs<T> A{};
+  A.nx = g->geo.nx;
+  A.ny = g->geo.ny;
+  A.tiles_x = (g->geo.nxn + kPmX - 1) / kPmX;
+  const int64_t ntiles = (int64_t)A.tiles_x * ((g->geo.ny + kPmY) / kPmY);  // ny + 1 rows of nodes
+  if (ntiles > INT32_MAX || n_apply > g->max_partials || n_kr > g->max_partials) return hipErrorInvalidValue;
+  A.ntiles = (int)ntiles;
+  A.rho = rho;
+  A.Y = Y; A.R1 = R1; A.R2 = R2; A.W = W;
+  A.R3 = R3; A.W2 = W2; A.x = x; A.Ynext = Ynext;
+  A.mask = g->mask;
+  A.ke = q4_of<T>(g);
+  A.sp = g->simp;
+  A.P = g->partials;
+  A.maxp = g->max_partials;
+  A.sc = g->sc;
+  A.itn = itn;
+  A.n_apply = n_apply;
+  A.n_kr = n_kr;
+  A.damp = damp;
+  const int nb = (int)(ntiles < g->max_partials ? ntiles : g->max_partials);
+  if (nb_out) *nb_out = nb;
+  hipLaunchKernelGGL((k_plane_minres<T>), dim3(nb), dim3(kPlaneBlock), 0, st, A);
+  return hipGetLastError();
+}
+
+template <typename T>
 hipError_t plane_diag(fbto_grid_s* g, const T* rho, T* invD, hipStream_t st) {
   hipLaunchKernelGGL((k_plane_diag<T>), dim3(plane_blocks(g->geo.N)), dim3(kPlaneBlock), 0, st, g->geo.nx,
                      g->geo.ny, g->geo.N, rho, invD, g->mask, g->simp, g->ke_diag);
@@ -466,6 +680,8 @@ hipError_t plane_hs(fbto_grid_s* g, T* Hsi, hipStream_t st) {
                                         int*);                                                               \
   template hipError_t plane_apply_lanczos<T>(fbto_grid_s*, const T*, const T*, const T*, T*, int, hipStream_t, \
                                              int*);                                                          \
+  template hipError_t plane_minres_fused<T>(fbto_grid_s*, const T*, int, const T*, const T*, const T*, T*,   \
+                                            const T*, T*, T*, T*, int, int, double, hipStream_t, int*);      \
   template hipError_t plane_diag<T>(fbto_grid_s*, const T*, T*, hipStream_t);                                \
   template hipError_t plane_sens<T>(fbto_grid_s*, const T*, const T*, const T*, int, T*, const T*,           \
                                     hipStream_t);                                                            \
