@@ -2215,11 +2215,13 @@ __global__ void __launch_bounds__(kVecBlock)
   }
 }
 
-// Density filter for R <= 1 by z-march: a thread owns element column
-// (ex, ey) of a z-slab and keeps the 2R+1 planes of its (2R+1)^2
-// neighbourhood in registers, so a slab of dz layers reads each input
-// (2R+1)^2 (dz + 2R) / dz times instead of (2R+1)^3.  Out-of-grid
-// neighbours load as 0 (the stencil is truncated at the boundary).
+// Density filter for R <= 1: a block owns 64 x 4 element columns and four
+// layers and stages them with their halo in LDS, every load issued up front
+// (one memory latency per block, 2.3 loads per output); a thread then sums the
+// windows of its column's four outputs.  Read by each thread from memory, the
+// window took 13.5 loads per output (27 transposed, with Hsi), and the final
+// projection pass clamped each of them.  Out-of-grid neighbours are 0 (the
+// stencil is truncated at the boundary).
 // The evaluation of one search pass at lam for one entry: f(lam) and the
 // classification of the entry just right (+) and just left (-) of lam, plus
 // the nearest breakpoints on either side (slots of proj_decide).
@@ -2288,6 +2290,7 @@ struct FiltStep {
 // and kFiltDZ layers; the thread's column (ex, ey) and output layers
 // [z0, z1).
 struct FiltPos {
+  int tx, ty, x0, y0;  // thread in the tile, the tile's first column
   int ex, ey, z0, z1;
   bool col;  // the column lies in the grid
 };
@@ -2296,51 +2299,66 @@ __device__ __forceinline__ FiltPos filt_pos(const Geo& G, int tiles_x, int tiles
   const int tx = threadIdx.x % kFiltBX, ty = threadIdx.x / kFiltBX;
   const int b = blockIdx.x;
   const int bx = b % tiles_x, t2 = b / tiles_x, by = t2 % tiles_y, bz = t2 / tiles_y;
-  q.ex = bx * kFiltBX + tx;
-  q.ey = by * kFiltBY + ty;
+  q.tx = tx;
+  q.ty = ty;
+  q.x0 = bx * kFiltBX;
+  q.y0 = by * kFiltBY;
+  q.ex = q.x0 + tx;
+  q.ey = q.y0 + ty;
   q.z0 = bz * kFiltDZ;
   q.z1 = min(q.z0 + kFiltDZ, G.nz);
   q.col = q.ex < G.nx && q.ey < G.ny;
   return q;
 }
 
-// Every value the thread's outputs read (its kFiltDZ layers and R halo
-// planes on each side, (2R + 1)^2 columns), loaded up front: one memory
-// latency per block.  Values outside the grid are 0.  trans: each value
-// times Hsi.  proj: each value v becomes the design value clamp(v - lam,
-// lo, hi) (in FP64, rounded to T, as the projection's final pass writes it).
+// The values a block stages: its columns and layers with R more on each side,
+// kN of them in threads' turns of one, x fastest.
+template <int R>
+struct FiltStage {
+  static constexpr int LX = kFiltBX + 2 * R, LY = kFiltBY + 2 * R, LZ = kFiltDZ + 2 * R;
+  static constexpr int kThreads = kFiltBX * kFiltBY, kN = LX * LY * LZ, kTurns = (kN + kThreads - 1) / kThreads;
+};
+// Issues the thread's loads (trans: times Hsi); bit t of ok: turn t lies in
+// the grid.  Out-of-grid values are 0.
 template <typename T, int R>
-__device__ __forceinline__ void filt_window(const Geo& G, const FiltPos& q, const T* in, const T* Hsi, bool trans,
-                                            T (&win)[kFiltDZ + 2 * R][2 * R + 1][2 * R + 1], bool proj = false,
-                                            double lam = 0.0, double lo = 0.0, double hi = 0.0) {
-  constexpr int D = 2 * R + 1;
-  const int plane = G.nx * G.ny;
-  bool okxy[D][D];
-  int offxy[D][D];
+__device__ __forceinline__ void filt_load(const Geo& G, const FiltPos& q, const T* in, const T* Hsi, bool trans,
+                                          T (&v)[FiltStage<R>::kTurns], unsigned& ok) {
+  using S = FiltStage<R>;
+  ok = 0u;
 #pragma unroll
-  for (int dy = 0; dy < D; ++dy)
-#pragma unroll
-    for (int dx = 0; dx < D; ++dx) {
-      const int jx = q.ex + dx - R, jy = q.ey + dy - R;
-      okxy[dy][dx] = q.col && jx >= 0 && jx < G.nx && jy >= 0 && jy < G.ny;
-      offxy[dy][dx] = okxy[dy][dx] ? jx + G.nx * jy : 0;
-    }
-#pragma unroll
-  for (int p = 0; p < kFiltDZ + 2 * R; ++p) {
-    const int jz = q.z0 - R + p;
-    const bool zok = jz >= 0 && jz < G.nz;
-#pragma unroll
-    for (int dy = 0; dy < D; ++dy)
-#pragma unroll
-      for (int dx = 0; dx < D; ++dx) {
-        const bool ok = okxy[dy][dx] && zok;
-        const int j = ok ? offxy[dy][dx] + jz * plane : 0;
-        T v = in[j];
-        if (trans) v *= Hsi[j];
-        if (proj) v = (T)fmin(fmax((double)v - lam, lo), hi);
-        win[p][dy][dx] = ok ? v : (T)0;
-      }
+  for (int t = 0; t < S::kTurns; ++t) {
+    const int i = (int)threadIdx.x + t * S::kThreads;
+    const int row = i / S::LX, lz = row / S::LY;
+    const int jx = q.x0 - R + i - row * S::LX, jy = q.y0 - R + row - lz * S::LY, jz = q.z0 - R + lz;
+    const bool in_grid = i < S::kN && jx >= 0 && jx < G.nx && jy >= 0 && jy < G.ny && jz >= 0 && jz < G.nz;
+    const int j = in_grid ? jx + G.nx * (jy + G.ny * jz) : 0;
+    T x = in[j];
+    if (trans) x *= Hsi[j];
+    v[t] = in_grid ? x : (T)0;
+    ok |= in_grid ? 1u << t : 0u;
   }
+}
+template <typename T, int R>
+__device__ __forceinline__ void filt_store(const T (&v)[FiltStage<R>::kTurns], T (&sh)[FiltStage<R>::kN]) {
+  using S = FiltStage<R>;
+#pragma unroll
+  for (int t = 0; t < S::kTurns; ++t) {
+    const int i = (int)threadIdx.x + t * S::kThreads;
+    if (i < S::kN) sh[i] = v[t];
+  }
+}
+// The window of the thread's outputs: kFiltDZ layers and R more on each side
+// of its (2R + 1)^2 columns.
+template <typename T, int R>
+__device__ __forceinline__ void filt_window(const T (&sh)[FiltStage<R>::kN], const FiltPos& q,
+                                            T (&win)[kFiltDZ + 2 * R][2 * R + 1][2 * R + 1]) {
+  using S = FiltStage<R>;
+#pragma unroll
+  for (int p = 0; p < S::LZ; ++p)
+#pragma unroll
+    for (int dy = 0; dy < 2 * R + 1; ++dy)
+#pragma unroll
+      for (int dx = 0; dx < 2 * R + 1; ++dx) win[p][dy][dx] = sh[q.tx + dx + S::LX * (q.ty + dy + S::LY * p)];
 }
 
 // The stencil sum of output layer l of the window.
@@ -2363,8 +2381,10 @@ __global__ void __launch_bounds__(kFiltBX * kFiltBY)
     k_filter_z(Geo G, int kind, const T* in, T* out, const T* Hsi, StencilW<T, R> W, int want_sum,
                double* P, int maxp, int tiles_x, int tiles_y, FiltStep<T> S) {
   const FiltPos q = filt_pos(G, tiles_x, tiles_y);
-  T win[kFiltDZ + 2 * R][2 * R + 1][2 * R + 1];  // [plane][dy][dx]
-  filt_window<T, R>(G, q, in, Hsi, kind == FILT_TRANS, win);
+  __shared__ T sh[FiltStage<R>::kN];
+  T sv[FiltStage<R>::kTurns];
+  unsigned ok;
+  filt_load<T, R>(G, q, in, Hsi, kind == FILT_TRANS, sv, ok);
   // step: the design values of the slab's outputs, and the mean of g
   T xv[kFiltDZ];
   double mean = 0.0, lam_w = 0.0;
@@ -2383,6 +2403,18 @@ __global__ void __launch_bounds__(kFiltBX * kFiltBY)
       mean = v[0] / (double)G.E;
     }
   }
+  T hs[kFiltDZ];  // forward: 1/Hs of the outputs
+  if (!STEP && kind == FILT_FWD) {
+#pragma unroll
+    for (int l = 0; l < kFiltDZ; ++l) {
+      const int ez = q.z0 + l;
+      hs[l] = Hsi[(q.col && ez < q.z1) ? q.ex + G.nx * (q.ey + G.ny * ez) : 0];
+    }
+  }
+  filt_store<T, R>(sv, sh);
+  __syncthreads();
+  T win[kFiltDZ + 2 * R][2 * R + 1][2 * R + 1];  // [plane][dy][dx]
+  filt_window<T, R>(sh, q, win);
   double vs[1] = {0.0};
   double v3[3] = {0.0, -INFINITY, 0.0};  // step: sum clamp(y), max y, #interior
   double ev[11];                         // step: evaluation at lam_w
@@ -2393,7 +2425,7 @@ __global__ void __launch_bounds__(kFiltBX * kFiltBY)
     const T acc = filt_sum<T, R>(W, win, l);
     if (q.col && ez < q.z1) {
       const int e = q.ex + G.nx * (q.ey + G.ny * ez);
-      const T res = kind == FILT_FWD ? acc * Hsi[e] : acc;
+      const T res = !STEP && kind == FILT_FWD ? acc * hs[l] : acc;
       if constexpr (STEP) {
         const T ye = (T)((double)xv[l] - S.half_alpha * ((double)res - mean));
         S.y[e] = ye;
@@ -2951,11 +2983,17 @@ __global__ void __launch_bounds__(kFiltBX * kFiltBY)
                         double vmax, ProjWs W, int nb, int passes, int tiles_x, int tiles_y) {
   constexpr int D = 2 * R + 1;
   const FiltPos q = filt_pos(G, tiles_x, tiles_y);
-  T xo[kFiltDZ];  // the design before the step at the own elements (only their owner reads them)
+  __shared__ T sh[FiltStage<R>::kN];
+  T sv[FiltStage<R>::kTurns];
+  unsigned ok;
+  filt_load<T, R>(G, q, y, nullptr, false, sv, ok);
+  T xo[kFiltDZ], hs[kFiltDZ];  // the design before the step (only its owner reads it) and 1/Hs at the own elements
 #pragma unroll
   for (int l = 0; l < kFiltDZ; ++l) {
     const int ez = q.z0 + l;
-    xo[l] = x[(q.col && ez < q.z1) ? q.ex + G.nx * (q.ey + G.ny * ez) : 0];
+    const int e = (q.col && ez < q.z1) ? q.ex + G.nx * (q.ey + G.ny * ez) : 0;
+    xo[l] = x[e];
+    hs[l] = Hsi[e];
   }
   Scalars* sc = W.sc;
   const double* in = sc->ps[passes & 1];
@@ -2976,9 +3014,14 @@ __global__ void __launch_bounds__(kFiltBX * kFiltBY)
     sc->lam = lam;
     sc->lam_prev = lam;
   }
-  // the window of new design values, from y and the multiplier
+  // the staged values become the new design's (in FP64, rounded to T)
+#pragma unroll
+  for (int t = 0; t < FiltStage<R>::kTurns; ++t)
+    sv[t] = (ok >> t) & 1u ? (T)fmin(fmax((double)sv[t] - lam, lo), hi) : (T)0;
+  filt_store<T, R>(sv, sh);
+  __syncthreads();
   T win[kFiltDZ + 2 * R][D][D];
-  filt_window<T, R>(G, q, y, nullptr, false, win, true, lam, lo, hi);
+  filt_window<T, R>(sh, q, win);
   double v[2] = {0.0, 0.0};
 #pragma unroll
   for (int l = 0; l < kFiltDZ; ++l) {
@@ -2990,7 +3033,7 @@ __global__ void __launch_bounds__(kFiltBX * kFiltBY)
       v[1] = fmax(v[1], fabs((double)xe - (double)xo[l]));
       x[e] = xe;
       v[0] += (double)xe;
-      rho[e] = acc * Hsi[e];
+      rho[e] = acc * hs[l];
     }
   }
   double* dst[2] = {lslot(W, L_VOL), lslot(W, L_DX)};
