@@ -1364,47 +1364,83 @@ bool apply_offsets_fit(const Geo& G, int dz, size_t value_bytes) {
   return (int64_t)(3 * value_bytes) * G.nxn * G.nyn * (dz + 3) < ((int64_t)1 << 31);
 }
 
-// Tile shape and slab depth for one apply variant.  The cost is the work of
-// the busiest CU in wave-layers (each block: its waves x (layers + 1 for the
-// prologue)), with a floor of kMinWaves resident waves per round below which
-// latency, not issue, sets the time.
+// Tile of the fused steps on large grids (2^21 elements and more), where the
+// memory path bounds them: blocks of 240 to 256 threads, two or three per CU.
+// The cost of a choice is its rounds of resident blocks (the last one, partly
+// filled, counts half and half its filling) times the planes that a block
+// reads, times
+//   - 1.55 with three blocks per CU: a round of three measured 1.55 times as
+//     long as one of two (256x128x128 in one round of three 113 us a step,
+//     320x160x160 in three of two 219 and two of three 226 us);
+//   - the partial cache lines of a tile's rows, one line of 64 bytes per row.
+// Against one fixed tile (27 x 8 columns, 33 layers), FP32 CG step: 320x160x160
+// 251 -> 219 us, 230x130x150 140 -> 125 us, 220x115x115 (before: the model
+// below) 88 -> 79 us; FP64 230x130x150 261 -> 245 us; 256x128x128 and
+// 384x192x192 as before within 1%.
+template <typename T, int NR, int MODE>
+static TileChoice choose_large_tile(const Geo& G, int n_cu, int lds_per_cu) {
+  static const int shapes[][2] = {{27, 8}, {31, 7}, {35, 6}, {24, 9}, {20, 11}, {18, 12}};
+  TileChoice best{};
+  double best_cost = 1e300;
+  for (const auto& sh : shapes) {
+    const int bx = sh[0], by = sh[1], threads = zmarch_threads<MODE>(bx, by);
+    const int tiles_x = (G.nxn + bx - 2) / (bx - 1), tiles_y = (G.nyn + by - 2) / (by - 1);
+    const size_t need = apply_lds_bytes<T, NR, MODE>(bx, by);
+    if (need > kApplyMaxLds) continue;
+    for (int cap = 2; cap <= 3; ++cap) {
+      const size_t lds = std::max(need, (size_t)lds_for_block_cap(lds_per_cu, cap));
+      int occ = 0;
+      const hipError_t oe = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_apply<T, NR, MODE>, threads, lds);
+      if (oe != hipSuccess || occ < cap || lds > kApplyMaxLds) continue;
+      for (int dz = std::min(16, G.nzn); dz <= std::min(49, G.nzn); ++dz) {
+        const int slabs = (G.nzn + dz - 1) / dz;
+        const int64_t nb = (int64_t)tiles_x * tiles_y * slabs;
+        if (nb > kApplyMaxBlocks || !apply_offsets_fit(G, dz, sizeof(T))) continue;
+        const double r = (double)nb / ((double)cap * n_cu), full = std::floor(r), part = r - full;
+        const double rounds = full + (part > 0.0 ? 0.5 + 0.5 * part : 0.0);
+        const double cost = rounds * (dz + 3) * (cap == 3 ? 1.55 : 1.0) * (1.0 + 64.0 / (3 * sizeof(T)) / (bx + 1));
+        if (cost < best_cost) {
+          best_cost = cost;
+          best = TileChoice{bx, by, dz, tiles_x, tiles_y, slabs, (int)nb, cap};
+        }
+      }
+    }
+  }
+  return best;
+}
+
+// The time of one layer of a round with w waves per CU, in wave-layers.  K u and
+// the other element-layout kernels: w + 8 (K u at 256x128x128 FP32: 1.07 us per
+// layer with 8 waves, 1.49 with 14, 1.58 with 16).  The fused steps in FP64: w +
+// 3.9 (CG step at 64x32x32: 12.9 us in four layers of 4 waves, 13.9 in three of
+// 8).  In FP32 a layer takes as long with 4 waves as with 8, and from there
+// grows as w: at 97x53x41 five layers of 8 waves 13.8 us, seven of 4 15.2 us.
+template <typename T, int MODE>
+static double layer_cost(double w) {
+  if (!node_layout<MODE>()) return w + 8.0;
+  return sizeof(T) == 8 ? w + 3.9 : std::max(w, 8.0);
+}
+
+// Tile shape and slab depth for one apply variant.  The cost of a choice is the
+// time of a layer (layer_cost) summed over the busiest CU's rounds of resident
+// blocks, times the layers of a block (+ 2 for the prologue).  Rows count a
+// little more the shorter they are (97x53x41, fused CG step with equal blocks:
+// 13.8 us with 35 columns, 14.1 with 16, 14.4 with 10).  Before, a layer cost
+// max(w, 8) in every kernel: K u at 256x128x128 48 -> 39.6 us; FP64 CG step at
+// 64x32x32 13.9 -> 13.1 us, at 180x90x90 87 -> 79 us.
 template <typename T, int NR, int MODE>
 static TileChoice choose_tile(const Geo& G, int n_cu, int lds_per_cu, int override_shape) {
   // fixed fields of a caller's override (FBTO_OPT_APPLY_TILE / _CGF_TILE)
   const int want_bx = override_shape & 0xff, want_by = (override_shape >> 8) & 0xff,
             want_dz = (override_shape >> 16) & 0xff;
-  constexpr double kMinWaves = 8.0;
-  TileChoice best{};
-  double best_cost = 1e300;
-  // The fused steps on large grids (2^22 elements and more): 27 x 8 element
-  // columns (28 x 9 = 252 threads, rows of 28 nodes) in slabs of 33 layers.
-  // Long rows keep the L1 path, which bounds these steps there, on few
-  // partial cache lines.  The CG step runs at most two blocks per CU (the
-  // L1 path then serves fewer waves) unless three per CU (as many as its
-  // registers allow) finish the grid in fewer rounds: a round of three
-  // measured 1.31 times as long as a round of two.  Measured (FP32 CG step):
-  // 155 us at 256x128x128 (one round of three) and 497 us at 384x192x192
-  // (two per CU), against 167 and 527 us for the cost model's choice.
   if constexpr (MODE == MODE_CGF || MODE == MODE_MRF) {
-    if (override_shape == 0 && G.E >= ((int64_t)1 << 22)) {
-      const int bx = 27, by = 8, dz = std::min(33, G.nzn);
-      const int threads = zmarch_threads<MODE>(bx, by);
-      const int tiles_x = (G.nxn + bx - 2) / (bx - 1), tiles_y = (G.nyn + by - 2) / (by - 1);
-      const int slabs = (G.nzn + dz - 1) / dz;
-      const int64_t nb = (int64_t)tiles_x * tiles_y * slabs;
-      int cap = 0;
-      if constexpr (MODE == MODE_CGF) {
-        const int64_t r2 = (nb + 2 * n_cu - 1) / (2 * n_cu), r3 = (nb + 3 * n_cu - 1) / (3 * n_cu);
-        cap = 1.31 * (double)r3 < (double)r2 ? 0 : 2;
-      }
-      const size_t lds = std::max(apply_lds_bytes<T, NR, MODE>(bx, by), cap ? (size_t)lds_for_block_cap(lds_per_cu, cap) : 0);
-      int occ = 0;
-      const hipError_t oe = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_apply<T, NR, MODE>, threads, lds);
-      if (oe == hipSuccess && occ >= 1 && lds <= kApplyMaxLds && nb <= kApplyMaxBlocks &&
-          apply_offsets_fit(G, dz, sizeof(T)))
-        return TileChoice{bx, by, dz, tiles_x, tiles_y, slabs, (int)nb, cap};
+    if (override_shape == 0 && G.E >= ((int64_t)1 << 21)) {
+      const TileChoice t = choose_large_tile<T, NR, MODE>(G, n_cu, lds_per_cu);
+      if (t.nblocks) return t;
     }
   }
+  TileChoice best{};
+  double best_cost = 1e300;
   for (int bx = 8; bx <= 64; ++bx) {
     if (want_bx && bx != want_bx) continue;
     for (int by = 4; by <= 64; ++by) {
@@ -1434,13 +1470,12 @@ static TileChoice choose_tile(const Geo& G, int n_cu, int lds_per_cu, int overri
         if (nb > kApplyMaxBlocks) continue;
         const int64_t per_cu = (nb + n_cu - 1) / n_cu;
         const int64_t full = per_cu / occ, rem = per_cu % occ;
-        const double layers = dz + 2.0;
         // a block's waves go to the CU's four SIMDs; a count that does not
         // spread evenly (3, 5, 6, 7) leaves one SIMD with more work, as if
         // the block had the next multiple of four
         const double w = (waves == 1 || waves == 2 || waves == 4 || waves == 8) ? waves : (waves + 3) / 4 * 4;
-        const double cost = full * std::max((double)occ * w, kMinWaves) * layers +
-                            (rem ? std::max((double)rem * w, kMinWaves) * layers : 0.0);
+        const double cost = (full * layer_cost<T, MODE>(occ * w) + (rem ? layer_cost<T, MODE>(rem * w) : 0.0)) *
+                            (dz + 2.0) * (1.0 + 1.0 / (bx + 1));
         if (cost < best_cost) {
           best_cost = cost;
           best = TileChoice{bx, by, dz, tiles_x, tiles_y, slabs, (int)nb, (override_shape >> 24) & 0xf};
