@@ -116,6 +116,7 @@ enum { MODE_APPLY = 0, MODE_RESID = 1, MODE_CG = 2, MODE_CGF = 3, MODE_SENSF = 4
 static_assert(MODE_LZ < kApplyModes, "a tile choice per mode");
 constexpr int kApplyMaxThreads = 512;
 constexpr int kApplyMaxBlocks = 8192;
+constexpr int kMaxP = kApplyMaxBlocks;  // partials per slot of a voxel grid
 
 // Bits 3 R + 1 for R < nr: the |r|_inf entries (max-reduced) of the
 // per-RHS triples (sum of squares, |r|_inf, another sum) that the residual
@@ -152,8 +153,9 @@ struct ApplyArgs {
   const T* sk;
   int bx, by;          // tile of bx * by element columns (threads = (bx + 1) * (by + 1), one per node column)
   int tiles_x, tiles_y, slabs, dz, nblocks, per_xcd;
-  double* P;           // partial slots
-  int maxp;
+  uint32_t inv_tx, inv_ty;  // floor(2^32 / tiles) + 1 (0: one tile), for div_small
+  float inv_tw;             // 1 / threads per tile row
+  double* P;           // partial slots (of the RHS; kApplyMaxBlocks apart)
   const Scalars* sc;
   int step;            // CG, CGF: step k; CG writes, CGF reads the partial set of parity k & 1
   // CGF and SENSF
@@ -171,6 +173,17 @@ struct ApplyArgs {
   int n_kr;                          // partial count of ||R2||^2
   double damp;                       // step size of the low-level step
 };
+
+// n / d by the multiplicative inverse inv = floor(2^32 / d) + 1 (0 for d = 1):
+// exact while n d < 2^32 (block numbers and tile counts, at most 2^13 each).
+// A kernel's first loads wait for its address arithmetic, 2 of the 9 us of a
+// small grid's step.  With these instead of integer divisions, constant slot
+// strides and the load case's offsets added on the host, an FP32 CG step went
+// from 11.1 to 10.5 us at 64x32x32 and from 19.1 to 18.5 us at 128x64x64, K u
+// there from 11.6 to 11.0 us.
+__device__ __forceinline__ uint32_t div_small(uint32_t n, uint32_t inv) { return inv ? __umulhi(n, inv) : n; }
+static uint32_t inv_small(int d) { return d == 1 ? 0u : (uint32_t)(((uint64_t)1 << 32) / (uint64_t)d + 1); }
+static_assert((int64_t)kApplyMaxBlocks * kApplyMaxBlocks < ((int64_t)1 << 32), "div_small is exact");
 
 // Step coefficients of the CG recurrence for one RHS from gamma = r.z,
 // delta = p.s, eps = s.D^-1 s (s = K p), r.r and f.f of step k (identical in
@@ -452,11 +465,11 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
   const int tid = threadIdx.x;
   const bool live = tid < TS;
   const int tl = live ? tid : 0;
-  const int ty = tl / TW, tx = tl - ty * TW;
-  const int bxi = lb % A.tiles_x;
-  const int t2 = lb / A.tiles_x;
-  const int byi = t2 % A.tiles_y;
-  const int bz = t2 / A.tiles_y;
+  const int ty = (int)((tl + 0.5f) * A.inv_tw), tx = tl - ty * TW;  // exact: tl < 512
+  const int t2 = (int)div_small(lb, A.inv_tx);
+  const int bxi = lb - t2 * A.tiles_x;
+  const int bz = (int)div_small(t2, A.inv_ty);
+  const int byi = t2 - bz * A.tiles_y;
   const int x0 = bxi * (BX - 1) - 1, y0 = byi * (BY - 1) - 1;
   const int ex = x0 + tx, ey = y0 + ty;
   const int k0 = bz * A.dz;
@@ -498,7 +511,7 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
   // offset: its load returns 0 and its store is dropped, without a cache
   // request, while every memory instruction is still issued unconditionally.
   const int64_t pbase = (int64_t)ez0 * plane;               // first node of plane ez0
-  const int64_t vbase = (int64_t)rhs0 * G.ndof + 3 * pbase;  // its first value in RHS rhs0
+  const int64_t vbase = 3 * pbase;                          // its first value (the host adds the RHS's offset)
   auto rsrc = [](const void* p) { return zrsrc(p); };
   auto vres = [&](const T* v, int r = 0) { return rsrc(v ? v + vbase + (int64_t)r * G.ndof : v); };  // [nrhs][3N]
   auto dres = [&](const T* v, int dn) { return rsrc(v ? v + dn * pbase : v); };  // [N][dn]
@@ -613,14 +626,14 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
     double pre[NV];
     const double* src[NV];
     int cnt[NV];
-    src[0] = pslot(A.P, P_RZ0 + par, rhs0, A.maxp);
-    src[1] = pslot(A.P, P_PQ0 + par, rhs0, A.maxp);
-    src[2] = pslot(A.P, P_EP0 + par, rhs0, A.maxp);
+    src[0] = pslot(A.P, P_RZ0 + par, 0, kMaxP);
+    src[1] = pslot(A.P, P_PQ0 + par, 0, kMaxP);
+    src[2] = pslot(A.P, P_EP0 + par, 0, kMaxP);
     cnt[0] = A.n_gam;
     cnt[1] = cnt[2] = A.n_apply;
     if constexpr (RR) {
-      src[3] = pslot(A.P, P_RN0 + par, rhs0, A.maxp);
-      src[4] = pslot(A.P, P_FN, rhs0, A.maxp);
+      src[3] = pslot(A.P, P_RN0 + par, 0, kMaxP);
+      src[4] = pslot(A.P, P_FN, 0, kMaxP);
       cnt[3] = A.n_gam;
       cnt[4] = A.n_fn;
     }
@@ -706,8 +719,8 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
   auto mrf_prologue = [&]() {
     const int itn = A.step;
     double v[3];
-    const double* src[3] = {pslot(A.P, P_KRN0 + ((itn - 1) & 1), 0, A.maxp), pslot(A.P, P_RZ0 + (itn & 1), 0, A.maxp),
-                            pslot(A.P, P_PQ0 + (itn & 1), 0, A.maxp)};
+    const double* src[3] = {pslot(A.P, P_KRN0 + ((itn - 1) & 1), 0, kMaxP), pslot(A.P, P_RZ0 + (itn & 1), 0, kMaxP),
+                            pslot(A.P, P_PQ0 + (itn & 1), 0, kMaxP)};
     const int cnt[3] = {A.n_kr, A.n_apply, A.n_apply};
     reduce_parts<3, 0u>(v, src, cnt);
     Scalars* sc = const_cast<Scalars*>(A.sc);
@@ -1090,20 +1103,20 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
     double v[NV * NR];
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
-      dst[NV * r + 0] = pslot(A.P, P_PQ0 + par, rhs0 + r, A.maxp);
+      dst[NV * r + 0] = pslot(A.P, P_PQ0 + par, r, kMaxP);
       v[NV * r + 0] = part[4 * r + 1];
       if constexpr (MODE == MODE_LZ) {
-        dst[NV * r + 1] = pslot(A.P, P_RZ0 + par, rhs0 + r, A.maxp);
+        dst[NV * r + 1] = pslot(A.P, P_RZ0 + par, r, kMaxP);
         v[NV * r + 1] = part[4 * r];
       } else {
-        dst[NV * r + 1] = pslot(A.P, P_EP0 + par, rhs0 + r, A.maxp);
+        dst[NV * r + 1] = pslot(A.P, P_EP0 + par, r, kMaxP);
         v[NV * r + 1] = (double)tpart[r][2];
       }
       if constexpr (MODE == MODE_CGF) {
-        dst[NV * r + 2] = pslot(A.P, P_RZ0 + par, rhs0 + r, A.maxp);
+        dst[NV * r + 2] = pslot(A.P, P_RZ0 + par, r, kMaxP);
         v[NV * r + 2] = (double)tpart[r][0];
         if constexpr (RR) {
-          dst[NV * r + 3] = pslot(A.P, P_RN0 + par, rhs0 + r, A.maxp);
+          dst[NV * r + 3] = pslot(A.P, P_RN0 + par, r, kMaxP);
           v[NV * r + 3] = (double)tpart[r][1];
         }
       }
@@ -1115,8 +1128,8 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
     // product partials of iteration t + 1
     const int itn = A.step;
     double v[3] = {part[0], part[1], part[2]};
-    double* dst[3] = {pslot(A.P, P_KRN0 + (itn & 1), 0, A.maxp), pslot(A.P, P_PQ0 + ((itn + 1) & 1), 0, A.maxp),
-                      pslot(A.P, P_RZ0 + ((itn + 1) & 1), 0, A.maxp)};
+    double* dst[3] = {pslot(A.P, P_KRN0 + (itn & 1), 0, kMaxP), pslot(A.P, P_PQ0 + ((itn + 1) & 1), 0, kMaxP),
+                      pslot(A.P, P_RZ0 + ((itn + 1) & 1), 0, kMaxP)};
     write_parts<3, 0u>(v, dst, lb);
   }
   if constexpr (MODE == MODE_RESID) {
@@ -1133,12 +1146,12 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
     double v[4];
     double* dst[4];
     for (int i = 0; i < 4; ++i) v[i] = (double)tpart[0][i];
-    dst[0] = pslot(A.P, P_RNF, rhs0, A.maxp);
-    dst[1] = pslot(A.P, P_RIF, rhs0, A.maxp);
-    dst[2] = pslot(A.P, P_FN, rhs0, A.maxp);
-    dst[3] = pslot(A.P, P_RZ0, rhs0, A.maxp);  // r.z and r.r of step 0
+    dst[0] = pslot(A.P, P_RNF, 0, kMaxP);
+    dst[1] = pslot(A.P, P_RIF, 0, kMaxP);
+    dst[2] = pslot(A.P, P_FN, 0, kMaxP);
+    dst[3] = pslot(A.P, P_RZ0, 0, kMaxP);  // r.z and r.r of step 0
     write_parts<4, 0x2u>(v, dst, lb);
-    if (tid == 0) pslot(A.P, P_RN0, rhs0, A.maxp)[lb] = v[0];
+    if (tid == 0) pslot(A.P, P_RN0, 0, kMaxP)[lb] = v[0];
   }
 }
 
@@ -1176,11 +1189,11 @@ __global__ void __launch_bounds__(kApplyMaxThreads)
   const int tid = threadIdx.x;
   const bool live = tid < NS;
   const int tl = live ? tid : 0;
-  const int ty = tl / NW, tx = tl - ty * NW;
-  const int bxi = lb % A.tiles_x;
-  const int t2 = lb / A.tiles_x;
-  const int byi = t2 % A.tiles_y;
-  const int bz = t2 / A.tiles_y;
+  const int ty = (int)((tl + 0.5f) * A.inv_tw), tx = tl - ty * NW;  // exact: tl < 512
+  const int t2 = (int)div_small(lb, A.inv_tx);
+  const int bxi = lb - t2 * A.tiles_x;
+  const int bz = (int)div_small(t2, A.inv_ty);
+  const int byi = t2 - bz * A.tiles_y;
   const int x0 = bxi * (BX - 1) - 1, y0 = byi * (BY - 1) - 1;
   const int ex = x0 + tx, ey = y0 + ty;
   const int k0 = bz * A.dz;
@@ -1215,9 +1228,9 @@ __global__ void __launch_bounds__(kApplyMaxThreads)
   auto coefficients = [&]() {
     const int par = A.step & 1;
     double pre[5];
-    const double* src[5] = {pslot(A.P, P_RZ0 + par, 0, A.maxp), pslot(A.P, P_PQ0 + par, 0, A.maxp),
-                            pslot(A.P, P_EP0 + par, 0, A.maxp), pslot(A.P, P_RN0 + par, 0, A.maxp),
-                            pslot(A.P, P_FN, 0, A.maxp)};
+    const double* src[5] = {pslot(A.P, P_RZ0 + par, 0, kMaxP), pslot(A.P, P_PQ0 + par, 0, kMaxP),
+                            pslot(A.P, P_EP0 + par, 0, kMaxP), pslot(A.P, P_RN0 + par, 0, kMaxP),
+                            pslot(A.P, P_FN, 0, kMaxP)};
     const bool tol = A.rtol > 0.0;  // r.r and f.f only for the tolerance test
     const int cnt[5] = {A.n_gam, A.n_apply, A.n_apply, tol ? A.n_gam : 0, tol ? A.n_fn : 0};
     reduce_parts<5, 0u>(pre, src, cnt);
@@ -1340,8 +1353,8 @@ __global__ void __launch_bounds__(kApplyMaxThreads)
     if (ez + 1 >= kend) break;
     layer(std::integral_constant<int, 1>{}, ez + 1);
   }
-  double* dst[4] = {pslot(A.P, P_RNF, 0, A.maxp), pslot(A.P, P_RIF, 0, A.maxp), pslot(A.P, P_DOT, 0, A.maxp),
-                     pslot(A.P, P_GSUM, 0, A.maxp)};
+  double* dst[4] = {pslot(A.P, P_RNF, 0, kMaxP), pslot(A.P, P_RIF, 0, kMaxP), pslot(A.P, P_DOT, 0, kMaxP),
+                     pslot(A.P, P_GSUM, 0, kMaxP)};
   write_parts<4, 0x2u>(part, dst, lb);
 }
 
@@ -1505,6 +1518,9 @@ static hipError_t launch_apply_t(fbto_grid_s* g, const ApplyArgs<T>& A0, int rhs
   A.dz = t.dz;
   A.nblocks = t.nblocks;
   A.per_xcd = (t.nblocks + 7) / 8;
+  A.inv_tx = inv_small(t.tiles_x);
+  A.inv_ty = inv_small(t.tiles_y);
+  A.inv_tw = 1.0f / (float)(node_layout<MODE>() ? t.bx + 1 : t.bx);
   const int grid = A.per_xcd * 8;
   size_t lds = apply_lds_bytes<T, NR, MODE>(t.bx, t.by);
   if (t.cap) lds = std::max(lds, (size_t)lds_for_block_cap(g->lds_per_cu, t.cap));
@@ -1523,14 +1539,20 @@ static hipError_t launch_apply_mode(fbto_grid_s* g, ApplyArgs<T> A, int nrhs, hi
   A.sdof = g->spring_dof;
   A.sk = spring_k_of<T>(g);
   A.P = g->partials;
-  A.maxp = g->max_partials;
   A.sc = g->sc;
   // one RHS per launch: the per-RHS state of the z-march (two face-mode
   // sets, the modal carry, staged loads) fills the register file at NR = 1
   hipError_t e = hipSuccess;
+  if (g->max_partials != kApplyMaxBlocks) return hipErrorInvalidValue;
   for (int r0 = 0; r0 < nrhs && e == hipSuccess; ++r0) {
     e = launch_apply_t<T, 1, MODE, RR, DN, XU>(g, A, r0, st, nb_out);
     A.dinv_out = nullptr;  // the same for every RHS
+    A.P += kApplyMaxBlocks;
+    auto next = [&](auto*& v) {
+      if (v) v += A.g.ndof;
+    };
+    next(A.u), next(A.y), next(A.f), next(A.z), next(A.r);
+    next(A.xi), next(A.ri), next(A.pi), next(A.si), next(A.xo), next(A.ro), next(A.po);
   }
   return e;
 }
@@ -1614,7 +1636,7 @@ hipError_t launch_cg_sens(fbto_grid_s* g, const T* rho, const CgSet<T>& in, T* x
     t = choose_tile<T, 1, MODE_SENSF>(g->geo, g->n_cu, g->lds_per_cu, g->tile_override[0]);
     if (t.nblocks == 0) return hipErrorInvalidConfiguration;
   }
-  if (t.nblocks > g->max_partials) return hipErrorInvalidValue;
+  if (t.nblocks > g->max_partials || g->max_partials != kApplyMaxBlocks) return hipErrorInvalidValue;
   if (nb_out) *nb_out = t.nblocks;
   ApplyArgs<T> A{};
   A.g = g->geo;
@@ -1622,7 +1644,6 @@ hipError_t launch_cg_sens(fbto_grid_s* g, const T* rho, const CgSet<T>& in, T* x
   A.km = modal_of<T>(g);
   A.sp = g->simp;
   A.P = g->partials;
-  A.maxp = g->max_partials;
   A.sc = g->sc;
   A.rho = rho;
   A.xi = in.x; A.ri = in.r; A.pi = in.p; A.si = in.s;
@@ -1643,6 +1664,9 @@ hipError_t launch_cg_sens(fbto_grid_s* g, const T* rho, const CgSet<T>& in, T* x
   A.dz = t.dz;
   A.nblocks = t.nblocks;
   A.per_xcd = (t.nblocks + 7) / 8;
+  A.inv_tx = inv_small(t.tiles_x);
+  A.inv_ty = inv_small(t.tiles_y);
+  A.inv_tw = 1.0f / (float)(t.bx + 1);
   const int grid = A.per_xcd * 8;
   const int threads = zmarch_threads<MODE_SENSF>(t.bx, t.by);
   size_t lds = sens_lds_bytes<T>(t.bx, t.by);
@@ -2133,13 +2157,12 @@ struct Vec3 {
 template <typename T, bool LAM>
 __global__ void __launch_bounds__(kVecBlock)
     k_sens(Geo G, const T* rho, const T* u, const T* lam, int nrhs, T* dobj, const uint8_t* mask, Modal<T> km,
-           Simp sp, const T* Hsi, int tiles_x, int tiles_y) {
+           Simp sp, const T* Hsi) {
   using V3 = Vec3<T>;
   __shared__ T un[kSensN][3];
   __shared__ T ln[LAM ? kSensN : 1][3];
   const int tid = threadIdx.x, tx = tid % kSensX, ty = tid / kSensX % kSensY, tz = tid / (kSensX * kSensY);
-  const int b = blockIdx.x, bxi = b % tiles_x, t2 = b / tiles_x, byi = t2 % tiles_y;
-  const int x0 = bxi * kSensX, y0 = byi * kSensY, z0 = (t2 / tiles_y) * kSensZ;
+  const int x0 = blockIdx.x * kSensX, y0 = blockIdx.y * kSensY, z0 = blockIdx.z * kSensZ;
   int node[kSensTurns];   // staged nodes of this thread (0 outside the grid: no element of the grid reads those)
   unsigned m[kSensTurns];
 #pragma unroll
@@ -2205,15 +2228,14 @@ hipError_t launch_sens(fbto_grid_s* g, const T* rho, const T* u, const T* lam, i
                        const T* Hsi, hipStream_t st) {
   if (g->dim == 2) return plane_sens<T>(g, rho, u, lam, nrhs, dobj, Hsi, st);
   const Geo& G = g->geo;
-  const int tx = (G.nx + kSensX - 1) / kSensX, ty = (G.ny + kSensY - 1) / kSensY;
-  const int64_t nb = (int64_t)tx * ty * ((G.nz + kSensZ - 1) / kSensZ);
-  if (nb > INT32_MAX) return hipErrorInvalidValue;
+  // axes of at most 65,534 elements: within the limits of a grid
+  const dim3 grid((G.nx + kSensX - 1) / kSensX, (G.ny + kSensY - 1) / kSensY, (G.nz + kSensZ - 1) / kSensZ);
   if (lam)
-    hipLaunchKernelGGL((k_sens<T, true>), dim3((unsigned)nb), dim3(kVecBlock), 0, st, G, rho, u, lam, nrhs, dobj,
-                       g->mask, modal_of<T>(g), g->simp, Hsi, tx, ty);
+    hipLaunchKernelGGL((k_sens<T, true>), grid, dim3(kVecBlock), 0, st, G, rho, u, lam, nrhs, dobj, g->mask,
+                       modal_of<T>(g), g->simp, Hsi);
   else
-    hipLaunchKernelGGL((k_sens<T, false>), dim3((unsigned)nb), dim3(kVecBlock), 0, st, G, rho, u, lam, nrhs, dobj,
-                       g->mask, modal_of<T>(g), g->simp, Hsi, tx, ty);
+    hipLaunchKernelGGL((k_sens<T, false>), grid, dim3(kVecBlock), 0, st, G, rho, u, lam, nrhs, dobj, g->mask,
+                       modal_of<T>(g), g->simp, Hsi);
   return hipGetLastError();
 }
 
@@ -2341,7 +2363,7 @@ __device__ __forceinline__ void proj_eval_init(double (&v)[11]) {
 // at the warm-start multiplier (evaluation set 0, the next 11 slots).
 static_assert(P_YMAX == P_S0 + 1 && P_NACT == P_S0 + 2 && P_E0 == P_S0 + 3, "seed and set 0 are consecutive slots");
 template <int NTHR>
-__device__ __forceinline__ void step_parts(double (&v3)[3], double (&ev)[11], double* P, int maxp) {
+__device__ __forceinline__ void step_parts(double (&v3)[3], double (&ev)[11], double* P, int maxp, int block) {
   double w[14];
   double* dst[14];
 #pragma unroll
@@ -2350,7 +2372,7 @@ __device__ __forceinline__ void step_parts(double (&v3)[3], double (&ev)[11], do
     dst[i] = pslot(P, P_S0 + i, 0, maxp);
   }
   // max-reduced: max y (1) and the nearest breakpoints (3 + 9, 3 + 10)
-  write_parts<14, 0x3002u, NTHR>(w, dst, blockIdx.x);
+  write_parts<14, 0x3002u, NTHR>(w, dst, block);
 }
 
 constexpr int kFiltBX = 64, kFiltBY = 4, kFiltDZ = 4;
@@ -2371,19 +2393,20 @@ struct FiltStep {
   const Scalars* sc;
 };
 
-// Thread geometry of the z-march filter: tile b of 64 x 4 element columns
+// Thread geometry of the filter: a tile of 64 x 4 element columns
 // and kFiltDZ layers; the thread's column (ex, ey) and output layers
 // [z0, z1).
 struct FiltPos {
+  int block;           // number of the block's partials
   int tx, ty, x0, y0;  // thread in the tile, the tile's first column
   int ex, ey, z0, z1;
   bool col;  // the column lies in the grid
 };
-__device__ __forceinline__ FiltPos filt_pos(const Geo& G, int tiles_x, int tiles_y) {
+__device__ __forceinline__ FiltPos filt_pos(const Geo& G) {
   FiltPos q;
   const int tx = threadIdx.x % kFiltBX, ty = threadIdx.x / kFiltBX;
-  const int b = blockIdx.x;
-  const int bx = b % tiles_x, t2 = b / tiles_x, by = t2 % tiles_y, bz = t2 / tiles_y;
+  const int bx = blockIdx.x, by = blockIdx.y, bz = blockIdx.z;
+  q.block = bx + gridDim.x * (by + gridDim.y * bz);
   q.tx = tx;
   q.ty = ty;
   q.x0 = bx * kFiltBX;
@@ -2464,8 +2487,8 @@ __device__ __forceinline__ T filt_sum(const StencilW<T, R>& W, const T (&win)[kF
 template <typename T, int R, bool STEP>
 __global__ void __launch_bounds__(kFiltBX * kFiltBY)
     k_filter_z(Geo G, int kind, const T* in, T* out, const T* Hsi, StencilW<T, R> W, int want_sum,
-               double* P, int maxp, int tiles_x, int tiles_y, FiltStep<T> S) {
-  const FiltPos q = filt_pos(G, tiles_x, tiles_y);
+               double* P, int maxp, FiltStep<T> S) {
+  const FiltPos q = filt_pos(G);
   __shared__ T sh[FiltStage<R>::kN];
   T sv[FiltStage<R>::kTurns];
   unsigned ok;
@@ -2526,10 +2549,10 @@ __global__ void __launch_bounds__(kFiltBX * kFiltBY)
     }
   }
   if constexpr (STEP) {
-    step_parts<kFiltBX * kFiltBY>(v3, ev, P, maxp);
+    step_parts<kFiltBX * kFiltBY>(v3, ev, P, maxp, q.block);
   } else if (want_sum) {
     double* dst[1] = {pslot(P, P_GSUM, 0, maxp)};
-    write_parts<1, 0u>(vs, dst, blockIdx.x);
+    write_parts<1, 0u>(vs, dst, q.block);
   }
 }
 
@@ -2692,6 +2715,14 @@ static StencilW<T, R> stencil_weights(double r) {
   return W;
 }
 
+static dim3 filt_grid(const Geo& G) {
+  return dim3((G.nx + kFiltBX - 1) / kFiltBX, (G.ny + kFiltBY - 1) / kFiltBY, (G.nz + kFiltDZ - 1) / kFiltDZ);
+}
+static int64_t filt_blocks(const Geo& G) {
+  const dim3 d = filt_grid(G);
+  return (int64_t)d.x * d.y * d.z;
+}
+
 template <typename T>
 hipError_t launch_filter(fbto_grid_s* g, int kind, const T* in, T* out, int want_sum, hipStream_t st) {
   Vecs& V = vecs_of<T>(g);
@@ -2703,18 +2734,15 @@ hipError_t launch_filter(fbto_grid_s* g, int kind, const T* in, T* out, int want
   const int R = r > 1.0 ? (int)std::ceil(r) - 1 : 0;
   const T* Hsi = (const T*)V.Hs;
   const Geo& G = g->geo;
-  const int tiles_x = (G.nx + kFiltBX - 1) / kFiltBX, tiles_y = (G.ny + kFiltBY - 1) / kFiltBY;
-  const int64_t nbz = (int64_t)tiles_x * tiles_y * ((G.nz + kFiltDZ - 1) / kFiltDZ);
+  const int64_t nbz = filt_blocks(G);
   if (R <= 1 && nbz <= g->max_partials) {
     if (want_sum) g->n_gsum = (int)nbz;
     if (R == 0)
-      hipLaunchKernelGGL((k_filter_z<T, 0, false>), dim3(nbz), dim3(kFiltBX * kFiltBY), 0, st, G, kind, in, out,
-                         Hsi, stencil_weights<T, 0>(r), want_sum, g->partials, g->max_partials, tiles_x, tiles_y,
-                         FiltStep<T>{});
+      hipLaunchKernelGGL((k_filter_z<T, 0, false>), filt_grid(G), dim3(kFiltBX * kFiltBY), 0, st, G, kind, in,
+                         out, Hsi, stencil_weights<T, 0>(r), want_sum, g->partials, g->max_partials, FiltStep<T>{});
     else
-      hipLaunchKernelGGL((k_filter_z<T, 1, false>), dim3(nbz), dim3(kFiltBX * kFiltBY), 0, st, G, kind, in, out,
-                         Hsi, stencil_weights<T, 1>(r), want_sum, g->partials, g->max_partials, tiles_x, tiles_y,
-                         FiltStep<T>{});
+      hipLaunchKernelGGL((k_filter_z<T, 1, false>), filt_grid(G), dim3(kFiltBX * kFiltBY), 0, st, G, kind, in,
+                         out, Hsi, stencil_weights<T, 1>(r), want_sum, g->partials, g->max_partials, FiltStep<T>{});
     return hipGetLastError();
   }
   if (R == 2) {
@@ -2759,8 +2787,7 @@ bool zmarch_filter(const fbto_grid_s* g) {
   const double r = g->desc.filter_radius;
   const int R = r > 1.0 ? (int)std::ceil(r) - 1 : 0;
   const Geo& G = g->geo;
-  const int64_t tiles_x = (G.nx + kFiltBX - 1) / kFiltBX, tiles_y = (G.ny + kFiltBY - 1) / kFiltBY;
-  const int64_t nbz = tiles_x * tiles_y * ((G.nz + kFiltDZ - 1) / kFiltDZ);
+  const int64_t nbz = filt_blocks(G);
   return R <= 1 && nbz <= g->max_partials;
 }
 
@@ -2772,19 +2799,16 @@ hipError_t launch_filter_step(fbto_grid_s* g, const T* ge, const T* x, T* y, dou
   const double r = g->desc.filter_radius;
   const int R = r > 1.0 ? (int)std::ceil(r) - 1 : 0;
   const Geo& G = g->geo;
-  const int tiles_x = (G.nx + kFiltBX - 1) / kFiltBX, tiles_y = (G.ny + kFiltBY - 1) / kFiltBY;
-  const int64_t nbz = (int64_t)tiles_x * tiles_y * ((G.nz + kFiltDZ - 1) / kFiltDZ);
+  const int64_t nbz = filt_blocks(G);
   if (mean_project && (nb_sum < 1 || nb_sum > g->max_partials)) return hipErrorInvalidValue;
   const FiltStep<T> S{x, y, half_alpha, mean_project, nb_sum, lo, hi, (const Scalars*)g->sc};
   const T* Hsi = (const T*)vecs_of<T>(g).Hs;  // not read by the plain sum
   if (R == 0)
-    hipLaunchKernelGGL((k_filter_z<T, 0, true>), dim3(nbz), dim3(kFiltBX * kFiltBY), 0, st, G, (int)FILT_SUM, ge,
-                       (T*)nullptr, Hsi, stencil_weights<T, 0>(r), 0, g->partials, g->max_partials, tiles_x,
-                       tiles_y, S);
+    hipLaunchKernelGGL((k_filter_z<T, 0, true>), filt_grid(G), dim3(kFiltBX * kFiltBY), 0, st, G, (int)FILT_SUM,
+                       ge, (T*)nullptr, Hsi, stencil_weights<T, 0>(r), 0, g->partials, g->max_partials, S);
   else
-    hipLaunchKernelGGL((k_filter_z<T, 1, true>), dim3(nbz), dim3(kFiltBX * kFiltBY), 0, st, G, (int)FILT_SUM, ge,
-                       (T*)nullptr, Hsi, stencil_weights<T, 1>(r), 0, g->partials, g->max_partials, tiles_x,
-                       tiles_y, S);
+    hipLaunchKernelGGL((k_filter_z<T, 1, true>), filt_grid(G), dim3(kFiltBX * kFiltBY), 0, st, G, (int)FILT_SUM,
+                       ge, (T*)nullptr, Hsi, stencil_weights<T, 1>(r), 0, g->partials, g->max_partials, S);
   *nb_seed = (int)nbz;
   return hipGetLastError();
 }
@@ -2839,7 +2863,7 @@ __global__ void __launch_bounds__(kVecBlock)
     v[2] += (yd > lo && yd < hi) ? 1.0 : 0.0;
     proj_eval(ev, yd, lam_w, lo, hi);
   }
-  step_parts<kVecBlock>(v, ev, P, maxp);
+  step_parts<kVecBlock>(v, ev, P, maxp, blockIdx.x);
 }
 
 __device__ __forceinline__ double* lslot(const ProjWs& W, int i) { return W.base + i * W.stride; }
@@ -3065,9 +3089,9 @@ __global__ void __launch_bounds__(kVecBlock)
 template <typename T, int R>
 __global__ void __launch_bounds__(kFiltBX * kFiltBY)
     k_proj_final_filter(Geo G, const T* y, T* x, T* rho, const T* Hsi, StencilW<T, R> Wf, double lo, double hi,
-                        double vmax, ProjWs W, int nb, int passes, int tiles_x, int tiles_y) {
+                        double vmax, ProjWs W, int nb, int passes) {
   constexpr int D = 2 * R + 1;
-  const FiltPos q = filt_pos(G, tiles_x, tiles_y);
+  const FiltPos q = filt_pos(G);
   __shared__ T sh[FiltStage<R>::kN];
   T sv[FiltStage<R>::kTurns];
   unsigned ok;
@@ -3091,7 +3115,7 @@ __global__ void __launch_bounds__(kFiltBX * kFiltBY)
     bad = d.bad;
     unfinished = !d.done;
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
+  if (q.block == 0 && threadIdx.x == 0) {
     double status = sc->proj_status;  // 0, or FBTO_ERR_NONFINITE from a pass
     if (bad) status = (double)FBTO_ERR_NONFINITE;
     else if (unfinished && status == 0.0) status = (double)FBTO_INEXACT;
@@ -3122,7 +3146,7 @@ __global__ void __launch_bounds__(kFiltBX * kFiltBY)
     }
   }
   double* dst[2] = {lslot(W, L_VOL), lslot(W, L_DX)};
-  write_parts<2, 0x2u, kFiltBX * kFiltBY>(v, dst, blockIdx.x);
+  write_parts<2, 0x2u, kFiltBX * kFiltBY>(v, dst, q.block);
 }
 
 template <typename T>
@@ -3132,17 +3156,16 @@ hipError_t launch_proj_final_filter(fbto_grid_s* g, const ProjWs& W, const T* y,
   const double r = g->desc.filter_radius;
   const int R = r > 1.0 ? (int)std::ceil(r) - 1 : 0;
   const Geo& G = g->geo;
-  const int tiles_x = (G.nx + kFiltBX - 1) / kFiltBX, tiles_y = (G.ny + kFiltBY - 1) / kFiltBY;
-  const int64_t nbz = (int64_t)tiles_x * tiles_y * ((G.nz + kFiltDZ - 1) / kFiltDZ);
+  const int64_t nbz = filt_blocks(G);
   if (nbz > W.maxp) return hipErrorInvalidValue;
   const int nb = vec_blocks(G.E);  // the passes' partials
   const T* Hsi = (const T*)vecs_of<T>(g).Hs;
   if (R == 0)
-    hipLaunchKernelGGL((k_proj_final_filter<T, 0>), dim3(nbz), dim3(kFiltBX * kFiltBY), 0, st, G, y, x, rho, Hsi,
-                       stencil_weights<T, 0>(r), lo, hi, vmax, W, nb, passes, tiles_x, tiles_y);
+    hipLaunchKernelGGL((k_proj_final_filter<T, 0>), filt_grid(G), dim3(kFiltBX * kFiltBY), 0, st, G, y, x, rho,
+                       Hsi, stencil_weights<T, 0>(r), lo, hi, vmax, W, nb, passes);
   else
-    hipLaunchKernelGGL((k_proj_final_filter<T, 1>), dim3(nbz), dim3(kFiltBX * kFiltBY), 0, st, G, y, x, rho, Hsi,
-                       stencil_weights<T, 1>(r), lo, hi, vmax, W, nb, passes, tiles_x, tiles_y);
+    hipLaunchKernelGGL((k_proj_final_filter<T, 1>), filt_grid(G), dim3(kFiltBX * kFiltBY), 0, st, G, y, x, rho,
+                       Hsi, stencil_weights<T, 1>(r), lo, hi, vmax, W, nb, passes);
   *nb_final = (int)nbz;
   return hipGetLastError();
 }
