@@ -92,6 +92,7 @@ struct Scalars {
 // Per-block FP64 partial results.  A producing kernel writes one value per
 // block (and per RHS); the consuming kernel reduces them in a fixed order in
 // every block (no atomics, no inter-block fences, bitwise reproducible).
+constexpr int kProjEval = 7;  // entries of one evaluation of the volume projection
 enum PartSlot {
   // CG step k reads the set of parity k & 1: r.z and r.r (from the update of
   // step k - 1, or the residual), p.s and s.D^-1 s (from the product s = K p)
@@ -104,9 +105,9 @@ enum PartSlot {
   P_DOT,               // sum_r f_r . u_r
   P_GSUM,              // sum of the filtered gradient
   P_S0, P_YMAX, P_NACT,  // projection seed: sum clamp(y), max y, #interior
-  P_E0,                // projection pass: two sets of 11 slots, P_E0 + 11 q .. P_E0 + 11 q + 10;
+  P_E0,                // projection pass: two sets of kProjEval slots, from P_E0 + kProjEval q;
                        // pass t reads set t & 1 (written by pass t - 1) and writes set (t + 1) & 1
-  P_VOL = P_E0 + 22,   // sum x_new
+  P_VOL = P_E0 + 2 * kProjEval,  // sum x_new
   P_DX,                // max |x_new - x_old|
   P_KRN0, P_KRN1,      // Krylov step: ||y||^2 of the new Lanczos vector, by iteration parity
   P_MET0, P_MET1,      // optimality metrics: squared distances (low-level, high-level)
@@ -315,8 +316,8 @@ hipError_t launch_project_sorted(fbto_grid_s* g, const T* y, T* x, double lo, do
 // P_S0 .. P_DX (stride 4 maxp); a caller-free workspace packs them.
 enum ProjSlot {
   L_S0, L_YMAX, L_NACT,   // seed: sum clamp(y), max y, #interior
-  L_E0,                   // evaluation sets: L_E0 + 11 q .. L_E0 + 11 q + 10, q = 0, 1
-  L_VOL = L_E0 + 22,      // sum x_new
+  L_E0,                   // evaluation sets: from L_E0 + kProjEval q, q = 0, 1
+  L_VOL = L_E0 + 2 * kProjEval,  // sum x_new
   L_DX,                   // max |x_new - x_old|
   kProjSlots
 };

@@ -2329,50 +2329,49 @@ __global__ void __launch_bounds__(kVecBlock)
 // window took 13.5 loads per output (27 transposed, with Hsi), and the final
 // projection pass clamped each of them.  Out-of-grid neighbours are 0 (the
 // stencil is truncated at the boundary).
-// The evaluation of one search pass at lam for one entry: f(lam) and the
-// classification of the entry just right (+) and just left (-) of lam, plus
-// the nearest breakpoints on either side (slots of proj_decide).
-// (Written with selects only: branches here let the compiler pick v[9] or
-// v[10] by a dynamic index, which puts the array in scratch memory.)
-__device__ __forceinline__ void proj_eval(double (&v)[11], double yd, double lam, double lo, double hi) {
+// The evaluation of one search pass at lam for one entry: f(lam) and the linear
+// piece of f just right (+) and just left (-) of lam, f(l) = C - l nA (an
+// entry adds its bound to C where it is clamped, else its value to C and one
+// to nA), plus the nearest breakpoints on either side:
+//   v = {f, nA+, C+, nA-, C-, max breakpoint below lam, -(min above)}.
+// (Written with selects only: branches here let the compiler pick the last two
+// by a dynamic index, which puts the array in scratch memory.)
+constexpr int kEval = kProjEval;
+constexpr unsigned kEvalMax = 0x60u;  // the max-reduced entries
+static_assert(kEval == 7, "entries of an evaluation");
+__device__ __forceinline__ void proj_eval(double (&v)[kEval], double yd, double lam, double lo, double hi) {
   const double t = yd - lam;
   v[0] += fmin(fmax(t, lo), hi);
   const bool rU = t > hi, rL = !rU && t <= lo, rA = !rU && !rL;   // just right of lambda
-  v[3] += rU ? 1.0 : 0.0;
-  v[4] += rL ? 1.0 : 0.0;
   v[1] += rA ? 1.0 : 0.0;
-  v[2] += rA ? yd : 0.0;
+  v[2] += rU ? hi : (rL ? lo : yd);
   const bool lU = t >= hi, lL = !lU && t < lo, lA = !lU && !lL;   // just left of lambda
-  v[7] += lU ? 1.0 : 0.0;
-  v[8] += lL ? 1.0 : 0.0;
-  v[5] += lA ? 1.0 : 0.0;
-  v[6] += lA ? yd : 0.0;
+  v[3] += lA ? 1.0 : 0.0;
+  v[4] += lU ? hi : (lL ? lo : yd);
   const double b1 = yd - lo, b2 = yd - hi;
-  v[9] = fmax(v[9], fmax(b1 < lam ? b1 : -INFINITY, b2 < lam ? b2 : -INFINITY));
-  v[10] = fmax(v[10], fmax(b1 > lam ? -b1 : -INFINITY, b2 > lam ? -b2 : -INFINITY));
+  v[5] = fmax(v[5], fmax(b1 < lam ? b1 : -INFINITY, b2 < lam ? b2 : -INFINITY));
+  v[6] = fmax(v[6], fmax(b1 > lam ? -b1 : -INFINITY, b2 > lam ? -b2 : -INFINITY));
 }
-__device__ __forceinline__ void proj_eval_init(double (&v)[11]) {
+__device__ __forceinline__ void proj_eval_init(double (&v)[kEval]) {
 #pragma unroll
-  for (int i = 0; i < 11; ++i) v[i] = 0.0;
-  v[9] = -INFINITY;
-  v[10] = -INFINITY;
+  for (int i = 0; i < kEval; ++i) v[i] = (kEvalMax >> i) & 1u ? -INFINITY : 0.0;
 }
 
 // The step's partials of one block in one reduction: the projection's seed
 // (sum clamp(y), max y, #interior: slots S0, YMAX, NACT) and the evaluation
-// at the warm-start multiplier (evaluation set 0, the next 11 slots).
+// at the warm-start multiplier (evaluation set 0, the next slots).
 static_assert(P_YMAX == P_S0 + 1 && P_NACT == P_S0 + 2 && P_E0 == P_S0 + 3, "seed and set 0 are consecutive slots");
+constexpr unsigned kSeedEvalMax = 0x2u | (kEvalMax << 3);  // max y, and the evaluation's
 template <int NTHR>
-__device__ __forceinline__ void step_parts(double (&v3)[3], double (&ev)[11], double* P, int maxp, int block) {
-  double w[14];
-  double* dst[14];
+__device__ __forceinline__ void step_parts(double (&v3)[3], double (&ev)[kEval], double* P, int maxp, int block) {
+  double w[3 + kEval];
+  double* dst[3 + kEval];
 #pragma unroll
-  for (int i = 0; i < 14; ++i) {
+  for (int i = 0; i < 3 + kEval; ++i) {
     w[i] = i < 3 ? v3[i] : ev[i - 3];
     dst[i] = pslot(P, P_S0 + i, 0, maxp);
   }
-  // max-reduced: max y (1) and the nearest breakpoints (3 + 9, 3 + 10)
-  write_parts<14, 0x3002u, NTHR>(w, dst, block);
+  write_parts<3 + kEval, kSeedEvalMax, NTHR>(w, dst, block);
 }
 
 constexpr int kFiltBX = 64, kFiltBY = 4, kFiltDZ = 4;
@@ -2525,7 +2524,7 @@ __global__ void __launch_bounds__(kFiltBX * kFiltBY)
   filt_window<T, R>(sh, q, win);
   double vs[1] = {0.0};
   double v3[3] = {0.0, -INFINITY, 0.0};  // step: sum clamp(y), max y, #interior
-  double ev[11];                         // step: evaluation at lam_w
+  double ev[kEval];                      // step: evaluation at lam_w
   proj_eval_init(ev);
 #pragma unroll
   for (int l = 0; l < kFiltDZ; ++l) {
@@ -2833,6 +2832,18 @@ template hipError_t launch_hs<float>(fbto_grid_s*, float*, hipStream_t);
 // pass solves that piece exactly; if the solution leaves the piece (beyond
 // the nearest breakpoint) it becomes a Newton step safeguarded by the
 // bracket [a, b] with f(a) > vmax >= f(b), else bisection.
+// The kernels that reduce partials first take a thread's entries four at a time,
+// a grid apart, the first four loaded before that reduction.
+constexpr int kProjChunk = 4;
+template <typename T>
+__device__ __forceinline__ void load_chunk(const T* a, int64_t n, int64_t first, int64_t stride, T (&v)[kProjChunk]) {
+#pragma unroll
+  for (int k = 0; k < kProjChunk; ++k) {
+    const int64_t e = first + k * stride;
+    v[k] = a[e < n ? e : 0];
+  }
+}
+
 // The gradient step y = x - alpha/2 (g - mean g), with the seed of the
 // projection (sum clamp(y), max y, #interior) and its first evaluation, at
 // the multiplier of the previous projection (the warm start), into
@@ -2841,6 +2852,12 @@ template <typename T>
 __global__ void __launch_bounds__(kVecBlock)
     k_step(int64_t E, const T* x, const T* gx, T* y, double half_alpha, int mean_project, double lo,
            double hi, double* P, int maxp, int nb_sum, const Scalars* sc) {
+  // the first entries are loaded before the reduction of the mean
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  const int64_t first = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  T xv[kProjChunk], gv[kProjChunk];
+  load_chunk(x, E, first, stride, xv);
+  load_chunk(gx, E, first, stride, gv);
   const double lam_w = sc->lam_prev;
   double mean = 0.0;
   if (mean_project) {
@@ -2851,17 +2868,25 @@ __global__ void __launch_bounds__(kVecBlock)
     mean = v[0] / (double)E;
   }
   double v[3] = {0.0, -INFINITY, 0.0};
-  double ev[11];
+  double ev[kEval];
   proj_eval_init(ev);
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < E;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    const T ye = (T)((double)x[e] - half_alpha * ((double)gx[e] - mean));
-    y[e] = ye;
-    const double yd = (double)ye;
-    v[0] += fmin(fmax(yd, lo), hi);
-    v[1] = fmax(v[1], yd);
-    v[2] += (yd > lo && yd < hi) ? 1.0 : 0.0;
-    proj_eval(ev, yd, lam_w, lo, hi);
+  for (int64_t e0 = first; e0 < E; e0 += kProjChunk * stride) {
+    if (e0 != first) {
+      load_chunk(x, E, e0, stride, xv);
+      load_chunk(gx, E, e0, stride, gv);
+    }
+#pragma unroll
+    for (int k = 0; k < kProjChunk; ++k) {
+      const int64_t e = e0 + k * stride;
+      if (e >= E) break;
+      const T ye = (T)((double)xv[k] - half_alpha * ((double)gv[k] - mean));
+      y[e] = ye;
+      const double yd = (double)ye;
+      v[0] += fmin(fmax(yd, lo), hi);
+      v[1] = fmax(v[1], yd);
+      v[2] += (yd > lo && yd < hi) ? 1.0 : 0.0;
+      proj_eval(ev, yd, lam_w, lo, hi);
+    }
   }
   step_parts<kVecBlock>(v, ev, P, maxp, blockIdx.x);
 }
@@ -2893,26 +2918,17 @@ struct ProjDecision {
 };
 
 // First slot of the evaluation set q of the projection passes.
-__host__ __device__ constexpr int proj_set(int q) { return L_E0 + 11 * (q & 1); }
-// pass t reads set t and writes set t + 1: two disjoint runs of 11 slots
-static_assert(proj_set(0) + 11 <= proj_set(1) && proj_set(1) + 11 <= L_VOL, "projection slot sets overlap");
+__host__ __device__ constexpr int proj_set(int q) { return L_E0 + kEval * (q & 1); }
+// pass t reads set t and writes set t + 1: two disjoint runs of slots
+static_assert(proj_set(0) + kEval <= proj_set(1) && proj_set(1) + kEval <= L_VOL, "projection slot sets overlap");
 
-// Decision from the evaluation at lam left in evaluation set `set`, with the
-// bracket [a, b] of the root.
-__device__ ProjDecision proj_decide_eval(const ProjWs& W, int nb, int set, double lo, double hi, double vmax,
-                                         double lam, double a, double b) {
+// Decision from an evaluation v (proj_eval) at lam, with the bracket [a, b] of
+// the root.
+__device__ __forceinline__ ProjDecision proj_decide_eval(const double (&v)[kEval], double vmax, double lam, double a,
+                                                         double b) {
   ProjDecision d{};
-  double v[11];
-  const double* src[11];
-  int cnt[11];
-#pragma unroll
-  for (int i = 0; i < 11; ++i) {
-    src[i] = lslot(W, proj_set(set) + i);
-    cnt[i] = nb;
-  }
-  reduce_parts<11, 0x600u, kVecBlock>(v, src, cnt);
   const double F = v[0];
-  const double lb = v[9], ub = -v[10];
+  const double lb = v[5], ub = -v[6];
   double next;
   bool done = false;
   d.bad = !isfinite(F);
@@ -2927,7 +2943,7 @@ __device__ ProjDecision proj_decide_eval(const ProjWs& W, int nb, int set, doubl
     a = lam;
     const double nA = v[1];
     if (nA > 0.0) {
-      const double ls = (hi * v[3] + lo * v[4] + v[2] - vmax) / nA;
+      const double ls = (v[2] - vmax) / nA;
       if (ls <= ub) { next = fmax(ls, lam); done = true; }
       else next = (ls > a && ls < b) ? ls : 0.5 * (a + b);
     } else {
@@ -2935,9 +2951,9 @@ __device__ ProjDecision proj_decide_eval(const ProjWs& W, int nb, int set, doubl
     }
   } else if (F < vmax) {
     b = lam;
-    const double nA = v[5];
+    const double nA = v[3];
     if (nA > 0.0) {
-      const double ls = (hi * v[7] + lo * v[8] + v[6] - vmax) / nA;
+      const double ls = (v[4] - vmax) / nA;
       if (ls >= lb) { next = fmin(ls, lam); done = true; }
       else next = (ls > a && ls < b) ? ls : 0.5 * (a + b);
     } else {
@@ -2962,15 +2978,35 @@ __device__ ProjDecision proj_decide_eval(const ProjWs& W, int nb, int set, doubl
 // the seed (sum clamp(y), max y, #interior), and -- warm_eval -- from the
 // evaluation at the warm start lam_prev in set 0 when lam_prev lies in the
 // bracket; otherwise from the evaluation at `lam` left in set `set`.
-__device__ ProjDecision proj_decide(const ProjWs& W, int nb, bool first, int set, double lo, double hi,
-                                    double vmax, double lam_prev, double lam, double a, double b,
-                                    bool warm_eval = false) {
-  if (!first) return proj_decide_eval(W, nb, set, lo, hi, vmax, lam, a, b);
+__device__ __forceinline__ ProjDecision proj_decide(const ProjWs& W, int nb, bool first, int set, double lo, double hi,
+                                                    double vmax, double lam_prev, double lam, double a, double b,
+                                                    bool warm_eval = false) {
+  double ev[kEval];
+  if (!first) {
+    const double* src[kEval];
+    int cnt[kEval];
+#pragma unroll
+    for (int i = 0; i < kEval; ++i) {
+      src[i] = lslot(W, proj_set(set) + i);
+      cnt[i] = nb;
+    }
+    reduce_parts<kEval, kEvalMax, kVecBlock>(ev, src, cnt);
+    return proj_decide_eval(ev, vmax, lam, a, b);
+  }
+  // the seed and, behind it, the evaluation at the warm start: one reduction
+  static_assert(L_S0 == 0 && L_E0 == 3, "the seed's slots come before set 0");
   ProjDecision d{};
-  double v[3];
-  const double* src[3] = {lslot(W, L_S0), lslot(W, L_YMAX), lslot(W, L_NACT)};
-  const int cnt[3] = {nb, nb, nb};
-  reduce_parts<3, 0x2u, kVecBlock>(v, src, cnt);
+  double v[3 + kEval];
+  {
+    const double* src[3 + kEval];
+    int cnt[3 + kEval];
+#pragma unroll
+    for (int i = 0; i < 3 + kEval; ++i) {
+      src[i] = lslot(W, L_S0 + i);
+      cnt[i] = i < 3 || warm_eval ? nb : 0;
+    }
+    reduce_parts<3 + kEval, kSeedEvalMax, kVecBlock>(v, src, cnt);
+  }
   const double S0 = v[0], ymax = v[1], nact0 = v[2];
   d.bad = !isfinite(S0);
   if (S0 <= vmax || d.bad) {
@@ -2981,8 +3017,11 @@ __device__ ProjDecision proj_decide(const ProjWs& W, int nb, bool first, int set
   }
   d.a = 0.0;
   d.b = ymax - lo;
-  if (warm_eval && lam_prev > d.a && lam_prev < d.b)
-    return proj_decide_eval(W, nb, 0, lo, hi, vmax, lam_prev, d.a, d.b);
+  if (warm_eval && lam_prev > d.a && lam_prev < d.b) {
+#pragma unroll
+    for (int i = 0; i < kEval; ++i) ev[i] = v[3 + i];
+    return proj_decide_eval(ev, vmax, lam_prev, d.a, d.b);
+  }
   double l0;
   if (lam_prev > d.a && lam_prev < d.b) l0 = lam_prev;
   else if (nact0 > 0.0) {
@@ -3014,6 +3053,10 @@ __global__ void __launch_bounds__(kVecBlock)
       for (int i = 0; i < 4; ++i) out[i] = in[i];
     return;
   }
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  const int64_t first = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  T yv[kProjChunk];
+  load_chunk(y, E, first, stride, yv);
   const ProjDecision d =
       proj_decide(W, nb, pass == 0, pass, lo, hi, vmax, sc->lam_prev, in[0], in[1], in[2], warm_eval != 0);
   if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -3026,15 +3069,20 @@ __global__ void __launch_bounds__(kVecBlock)
   }
   if (d.done) return;
   const double lam = d.lam;
-  double v[11];
+  double v[kEval];
   proj_eval_init(v);
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < E;
-       e += (int64_t)gridDim.x * blockDim.x)
-    proj_eval(v, (double)y[e], lam, lo, hi);
-  double* dst[11];
+  for (int64_t e0 = first; e0 < E; e0 += kProjChunk * stride) {
+    if (e0 != first) load_chunk(y, E, e0, stride, yv);
 #pragma unroll
-  for (int i = 0; i < 11; ++i) dst[i] = lslot(W, proj_set(pass + 1) + i);
-  write_parts<11, 0x600u, kVecBlock>(v, dst, blockIdx.x);
+    for (int k = 0; k < kProjChunk; ++k) {
+      if (e0 + k * stride >= E) break;
+      proj_eval(v, (double)yv[k], lam, lo, hi);
+    }
+  }
+  double* dst[kEval];
+#pragma unroll
+  for (int i = 0; i < kEval; ++i) dst[i] = lslot(W, proj_set(pass + 1) + i);
+  write_parts<kEval, kEvalMax, kVecBlock>(v, dst, blockIdx.x);
 }
 
 // x = clamp(y - lambda, lo, hi) after `passes` passes.  A search still open
@@ -3046,6 +3094,11 @@ template <typename T>
 __global__ void __launch_bounds__(kVecBlock)
     k_proj_final(int64_t E, const T* y, T* x, double lo, double hi, double vmax, const T* x_old, ProjWs W, int nb,
                  int passes, double* lam_out, double* status_out) {
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  const int64_t first = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  T yv[kProjChunk], xv[kProjChunk];
+  load_chunk(y, E, first, stride, yv);
+  if (x_old) load_chunk(x_old, E, first, stride, xv);
   Scalars* sc = W.sc;
   const double* in = sc->ps[passes & 1];
   double lam = in[0];
@@ -3068,12 +3121,20 @@ __global__ void __launch_bounds__(kVecBlock)
     if (status_out) *status_out = status;
   }
   double v[2] = {0.0, 0.0};
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < E;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    const T xe = (T)fmin(fmax((double)y[e] - lam, lo), hi);
-    if (x_old) v[1] = fmax(v[1], fabs((double)xe - (double)x_old[e]));
-    x[e] = xe;
-    v[0] += (double)xe;
+  for (int64_t e0 = first; e0 < E; e0 += kProjChunk * stride) {
+    if (e0 != first) {
+      load_chunk(y, E, e0, stride, yv);
+      if (x_old) load_chunk(x_old, E, e0, stride, xv);
+    }
+#pragma unroll
+    for (int k = 0; k < kProjChunk; ++k) {
+      const int64_t e = e0 + k * stride;
+      if (e >= E) break;
+      const T xe = (T)fmin(fmax((double)yv[k] - lam, lo), hi);
+      if (x_old) v[1] = fmax(v[1], fabs((double)xe - (double)xv[k]));
+      x[e] = xe;
+      v[0] += (double)xe;
+    }
   }
   double* dst[2] = {lslot(W, L_VOL), lslot(W, L_DX)};
   write_parts<2, 0x2u, kVecBlock>(v, dst, blockIdx.x);
