@@ -64,33 +64,14 @@ Vecs& vecs<float>(fbto_grid_s* g) { return g->v32; }
 //             W_l(q) = prod_{k != l} M(q_k),
 //   coupling  to component j, mode q ^ (1<<i) ^ (1<<j) when q_i != q_j:
 //             lambda/4 M(q_k) if q_i = d, else mu/4 M(q_k).
-// The diagonal depends on q only through q_i and how many of the other two
-// bits are set (W_l is a product over the other axes), so it is stored as
-// dg[q_i][count] and computed for component 0 at a representative mode.
+// With M(m) = 1/4 and M(d) = 1/12 these are the groups of Modal: for instance
+// (i, {i}) has (lambda + 2 mu) / 16 on the diagonal and lambda / 16 beside it,
+// (i, {j}) mu / 16 in both places, (i, {i, k}) (lambda + 3 mu) / 48 and lambda /
+// 48, the other two axes mu / 24 and mu / 48.
 void modal_coefficients(double young, double poisson, Modal<double>& km, double& ke_diag) {
   const double lam = young * poisson / ((1.0 + poisson) * (1.0 - 2.0 * poisson));
   const double mu = young / (2.0 * (1.0 + poisson));
-  const double M[2] = {0.25, 1.0 / 12.0};
-  for (int qi = 0; qi < 2; ++qi) {
-    for (int cnt = 0; cnt < 3; ++cnt) {
-      const int q = qi | (cnt >= 1 ? 2 : 0) | (cnt >= 2 ? 4 : 0);
-      double W[3];
-      for (int l = 0; l < 3; ++l) {
-        W[l] = 1.0;
-        for (int k = 0; k < 3; ++k)
-          if (k != l) W[l] *= M[(q >> k) & 1];
-      }
-      double d = qi ? (lam + mu) * W[0] : 0.0;
-      for (int l = 0; l < 3; ++l)
-        if ((q >> l) & 1) d += mu * W[l];
-      km.dg[qi][cnt] = d;
-    }
-  }
-  // dg[0][0] is mode 0 (rigid translation): no energy, computed as 0
-  for (int b = 0; b < 2; ++b) {
-    km.lam4[b] = 0.25 * lam * M[b];
-    km.mu4[b] = 0.25 * mu * M[b];
-  }
+  km = Modal<double>{lam / 16.0, lam / 48.0, mu / 8.0, mu / 16.0, mu / 48.0, (lam + 4.0 * mu) / 144.0};
   ke_diag = (lam + 4.0 * mu) / 9.0;
 }
 
@@ -614,12 +595,8 @@ fbto_status_t fbto_setup_grid(const fbto_grid_desc_t* d, const uint8_t* fixed_do
   G.rnxn = 1.0 / G.nxn;
   G.rnyn = 1.0 / G.nyn;
   modal_coefficients(d->young, d->poisson, g->km64, g->ke_diag);
-  for (int a = 0; a < 2; ++a)
-    for (int c = 0; c < 3; ++c) g->km32.dg[a][c] = (float)g->km64.dg[a][c];
-  for (int b = 0; b < 2; ++b) {
-    g->km32.lam4[b] = (float)g->km64.lam4[b];
-    g->km32.mu4[b] = (float)g->km64.mu4[b];
-  }
+  const Modal<double>& km = g->km64;
+  g->km32 = Modal<float>{(float)km.l0, (float)km.l1, (float)km.m8, (float)km.m0, (float)km.m1, (float)km.d3};
   g->simp.penal = d->penal;
   g->simp.rho_min = d->rho_min;
   g->simp.cubic = d->penal == 3.0 ? 1 : 0;

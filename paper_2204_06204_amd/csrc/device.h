@@ -281,7 +281,7 @@ __device__ __forceinline__ T simp_ds(T rho, const Simp& sp) {
 
 // --------------------------------------------------------------------------
 // Element product in the sum/difference basis (45 nonzeros instead of the
-// dense 24 x 24): analysis butterflies, sparse modal KE, synthesis.
+// dense 24 x 24): analysis butterflies, sparse modal KE.
 // --------------------------------------------------------------------------
 template <typename T>
 __device__ __forceinline__ void analysis8(T (&v)[8]) {
@@ -296,66 +296,34 @@ __device__ __forceinline__ void analysis8(T (&v)[8]) {
     }
   }
 }
-template <typename T>
-__device__ __forceinline__ void synthesis8(T (&v)[8]) {
-#pragma unroll
-  for (int bit = 1; bit < 8; bit <<= 1) {
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      if (i & bit) continue;
-      const T lo = v[i], hi = v[i | bit];
-      v[i] = lo - hi;
-      v[i | bit] = lo + hi;
-    }
-  }
-}
-
-// z = KE_modal c  (component-major c[3][8], z[3][8]; mode 0 carries no energy)
+// z = KE_modal c  (component-major c[3][8], z[3][8]; mode 0 carries no energy).
+// The modes fall into groups that couple only within themselves (see Modal):
+// a common term and one product per member, 14 additions and 26 products (as
+// 15 multiply-adds and 11 multiplications), where the matrix entry by entry
+// takes 21 multiplications and 24 multiply-adds.
 template <typename T>
 __device__ __forceinline__ void modal_ke(const T (&c)[3][8], const Modal<T>& km, T (&z)[3][8]) {
+  z[0][0] = z[1][0] = z[2][0] = (T)0;
+  // normal strains, mode i of component i
+  const T tn = km.l0 * ((c[0][1] + c[1][2]) + c[2][4]);
+  // the modes of the other two axes
+  const T tt = km.m1 * ((c[0][6] + c[1][5]) + c[2][3]);
 #pragma unroll
   for (int i = 0; i < 3; ++i) {
-    z[i][0] = (T)0;
-#pragma unroll
-    for (int q = 1; q < 8; ++q) z[i][q] = km.dg[(q >> i) & 1][__builtin_popcount((unsigned)q & ~(1u << i))] * c[i][q];
+    z[i][1 << i] = km.m8 * c[i][1 << i] + tn;
+    z[i][7 ^ (1 << i)] = km.m1 * c[i][7 ^ (1 << i)] + tt;
+    z[i][7] = km.d3 * c[i][7];
   }
 #pragma unroll
-  for (int i = 0; i < 3; ++i) {
-#pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      if (i == j) continue;
-      const int k = 3 - i - j;
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const int qi = (q >> i) & 1, qj = (q >> j) & 1;
-        if (qi == qj) continue;
-        const int qp = q ^ (1 << i) ^ (1 << j);
-        const T w = qi ? km.lam4[(q >> k) & 1] : km.mu4[(q >> k) & 1];
-        z[i][q] += w * c[j][qp];
-      }
-    }
-  }
-}
-
-// ye = s * KE ue   (ue, ye: [local node a][component])
-template <typename T>
-__device__ __forceinline__ void elem_apply(const T (&ue)[8][3], T s, const Modal<T>& km,
-                                           T (&ye)[8][3]) {
-  T c[3][8], z[3][8];
-#pragma unroll
-  for (int i = 0; i < 3; ++i) {
-#pragma unroll
-    for (int a = 0; a < 8; ++a) c[i][a] = ue[a][i];
-    analysis8(c[i]);
-#pragma unroll
-    for (int q = 1; q < 8; ++q) c[i][q] *= s;
-  }
-  modal_ke(c, km, z);
-#pragma unroll
-  for (int i = 0; i < 3; ++i) {
-    synthesis8(z[i]);
-#pragma unroll
-    for (int a = 0; a < 8; ++a) ye[a][i] = z[i][a];
+  for (int k = 0; k < 3; ++k) {
+    const int i = k == 0 ? 1 : 0, j = k == 2 ? 1 : 2;  // the other two axes
+    // shear strain of axes i and j
+    z[i][1 << j] = z[j][1 << i] = km.m0 * (c[i][1 << j] + c[j][1 << i]);
+    // normal strains of i and j varying along k
+    const int qi = (1 << i) | (1 << k), qj = (1 << j) | (1 << k);
+    const T tk = km.l1 * (c[i][qi] + c[j][qj]);
+    z[i][qi] = km.m0 * c[i][qi] + tk;
+    z[j][qj] = km.m0 * c[j][qj] + tk;
   }
 }
 

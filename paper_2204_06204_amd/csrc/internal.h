@@ -19,20 +19,20 @@ struct Geo {
 };
 
 // Element stiffness in the sum/difference ("modal") basis.  Per axis the
-// two nodal values (u0, u1) map to (u0 + u1, u1 - u0); on the unit cube the
-// 24x24 KE becomes a 45-entry sparse matrix:
-//   diagonal  dg[q_i][number of the other two bits of q that are set]
-//             (component i, mode q; by the cube's symmetry six values)
-//   coupling  component i, mode q  <-  component j, mode q ^ (1<<i) ^ (1<<j)
-//             whenever bits i and j of q differ, with weight
-//             lam4[bit k of q] if bit i of q is set, else mu4[bit k of q]
-// (k the third axis).  Mode q has bit b set when it is the difference mode
-// along axis b.  Derived from the 1D integrals of the basis {1/2, t - 1/2}.
+// two nodal values (u0, u1) map to (u0 + u1, u1 - u0), and mode q has bit b set
+// when it is the difference mode along axis b.  On the unit cube the 24x24 KE
+// splits into groups of (component, mode), with the 1D integrals M = 1/4 (sum)
+// and 1/12 (difference mode):
+//   (i, {i}), i = 0, 1, 2        normal strains: m8 c_i + l0 (c_0 + c_1 + c_2)
+//   (i, {j}), (j, {i})           shear strain: m0 (c_i + c_j) for both
+//   (i, {i, k}), (j, {j, k})     normal strains varying along k: m0 c + l1 (c_i + c_j)
+//   (i, the other two axes)      m1 c_i + m1 (c_0 + c_1 + c_2)
+//   (i, all three axes)          d3 c
 template <typename T>
 struct Modal {
-  T dg[2][3];
-  T lam4[2];
-  T mu4[2];
+  T l0, l1;        // lambda / 16, lambda / 48
+  T m8, m0, m1;    // mu / 8, mu / 16, mu / 48
+  T d3;            // (lambda + 4 mu) / 144
 };
 
 // Element stiffness of the unit-square Q4 (plane stress), local DOF 2a + c.

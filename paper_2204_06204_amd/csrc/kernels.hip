@@ -265,18 +265,20 @@ __device__ __forceinline__ void layer_product(const T (&Flo)[4][3], const T (&Fu
     c[i][0] = (T)0;  // the all-sum mode (translation) carries no energy
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      if (q) c[i][q] = s * (Flo[q][i] + Fup[q][i]);
-      c[i][q + 4] = s * (Fup[q][i] - Flo[q][i]);
+      if (q) c[i][q] = Flo[q][i] + Fup[q][i];
+      c[i][q + 4] = Fup[q][i] - Flo[q][i];
     }
   }
   modal_ke(c, km, z);
+  // scaled by s here, where half of the products join an addition
   T lo[4][3];
 #pragma unroll
   for (int q = 0; q < 4; ++q)
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
-      lo[q][i] = (z[i][q] - z[i][q + 4]) + carry[q][i];
-      carry[q][i] = z[i][q] + z[i][q + 4];
+      const T zl = q ? z[i][q] - z[i][q + 4] : -z[i][4], zu = q ? z[i][q] + z[i][q + 4] : z[i][4];
+      lo[q][i] = s * zl + carry[q][i];
+      carry[q][i] = s * zu;
     }
   face_values(lo, out);
 }
