@@ -215,7 +215,7 @@ struct fbto_grid_s {
   int n_cu = 256;
   int lds_per_cu = 160 * 1024;
   int n_gsum = 0;                        // blocks of the last filter launch that left a sum
-  fbto::TileChoice tiles[2][2][fbto::kApplyModes] = {};  // apply tiling by [FP64][NR - 1][mode], chosen on first use
+  fbto::TileChoice tiles[2][4][fbto::kApplyModes] = {};  // apply tiling by [FP64][nrhs - 1][mode], chosen on first use
   int tile_override[2] = {0, 0};         // FBTO_OPT_APPLY_TILE, FBTO_OPT_CGF_TILE (0: cost model)
   int proj_passes_warm = 2;              // FBTO_OPT_PROJ_PASSES: projection passes of the outer steps
   fbto::SortWs sort;                     // sort-based projection

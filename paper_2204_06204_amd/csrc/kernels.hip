@@ -155,7 +155,7 @@ struct ApplyArgs {
   int tiles_x, tiles_y, slabs, dz, nblocks, per_xcd;
   uint32_t inv_tx, inv_ty;  // floor(2^32 / tiles) + 1 (0: one tile), for div_small
   float inv_tw;             // 1 / threads per tile row
-  double* P;           // partial slots (of the RHS; kApplyMaxBlocks apart)
+  double* P;           // partial slots, of kMaxP values per RHS
   const Scalars* sc;
   int step;            // CG, CGF: step k; CG writes, CGF reads the partial set of parity k & 1
   // CGF and SENSF
@@ -177,10 +177,9 @@ struct ApplyArgs {
 // n / d by the multiplicative inverse inv = floor(2^32 / d) + 1 (0 for d = 1):
 // exact while n d < 2^32 (block numbers and tile counts, at most 2^13 each).
 // A kernel's first loads wait for its address arithmetic, 2 of the 9 us of a
-// small grid's step.  With these instead of integer divisions, constant slot
-// strides and the load case's offsets added on the host, an FP32 CG step went
-// from 11.1 to 10.5 us at 64x32x32 and from 19.1 to 18.5 us at 128x64x64, K u
-// there from 11.6 to 11.0 us.
+// small grid's step.  With these instead of integer divisions and constant slot
+// strides an FP32 CG step went from 11.1 to 10.5 us at 64x32x32 and from 19.1
+// to 18.5 us at 128x64x64, K u there from 11.6 to 11.0 us.
 __device__ __forceinline__ uint32_t div_small(uint32_t n, uint32_t inv) { return inv ? __umulhi(n, inv) : n; }
 static uint32_t inv_small(int d) { return d == 1 ? 0u : (uint32_t)(((uint64_t)1 << 32) / (uint64_t)d + 1); }
 static_assert((int64_t)kApplyMaxBlocks * kApplyMaxBlocks < ((int64_t)1 << 32), "div_small is exact");
@@ -436,11 +435,13 @@ constexpr int apply_min_waves() {
 // the same order, half a vector less per step on average).
 template <typename T, int NR, int MODE, bool RR = true, int DN = 1, int XU = 1>
 __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_per_eu(apply_min_waves<T, NR, MODE>())))
-    k_apply(ApplyArgs<T> A, int rhs0) {
+    k_apply(ApplyArgs<T> A) {
   extern __shared__ __align__(16) unsigned char apply_smem[];
   const int b = blockIdx.x;
   const int lb = (b & 7) * A.per_xcd + (b >> 3);  // XCD-aware: neighbours share an L2
   if (lb >= A.nblocks) return;                    // whole block
+  const int rhs0 = blockIdx.y;                    // the load case
+  double* const parts = A.P + rhs0 * kMaxP;       // its partials
   const Geo G = A.g;
   const int BX = A.bx, BY = A.by;
   constexpr bool NL = node_layout<MODE>();
@@ -513,7 +514,7 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
   // offset: its load returns 0 and its store is dropped, without a cache
   // request, while every memory instruction is still issued unconditionally.
   const int64_t pbase = (int64_t)ez0 * plane;               // first node of plane ez0
-  const int64_t vbase = 3 * pbase;                          // its first value (the host adds the RHS's offset)
+  const int64_t vbase = (int64_t)rhs0 * G.ndof + 3 * pbase;  // its first value in RHS rhs0
   auto rsrc = [](const void* p) { return zrsrc(p); };
   auto vres = [&](const T* v, int r = 0) { return rsrc(v ? v + vbase + (int64_t)r * G.ndof : v); };  // [nrhs][3N]
   auto dres = [&](const T* v, int dn) { return rsrc(v ? v + dn * pbase : v); };  // [N][dn]
@@ -628,14 +629,14 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
     double pre[NV];
     const double* src[NV];
     int cnt[NV];
-    src[0] = pslot(A.P, P_RZ0 + par, 0, kMaxP);
-    src[1] = pslot(A.P, P_PQ0 + par, 0, kMaxP);
-    src[2] = pslot(A.P, P_EP0 + par, 0, kMaxP);
+    src[0] = pslot(parts, P_RZ0 + par, 0, kMaxP);
+    src[1] = pslot(parts, P_PQ0 + par, 0, kMaxP);
+    src[2] = pslot(parts, P_EP0 + par, 0, kMaxP);
     cnt[0] = A.n_gam;
     cnt[1] = cnt[2] = A.n_apply;
     if constexpr (RR) {
-      src[3] = pslot(A.P, P_RN0 + par, 0, kMaxP);
-      src[4] = pslot(A.P, P_FN, 0, kMaxP);
+      src[3] = pslot(parts, P_RN0 + par, 0, kMaxP);
+      src[4] = pslot(parts, P_FN, 0, kMaxP);
       cnt[3] = A.n_gam;
       cnt[4] = A.n_fn;
     }
@@ -721,8 +722,8 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
   auto mrf_prologue = [&]() {
     const int itn = A.step;
     double v[3];
-    const double* src[3] = {pslot(A.P, P_KRN0 + ((itn - 1) & 1), 0, kMaxP), pslot(A.P, P_RZ0 + (itn & 1), 0, kMaxP),
-                            pslot(A.P, P_PQ0 + (itn & 1), 0, kMaxP)};
+    const double* src[3] = {pslot(parts, P_KRN0 + ((itn - 1) & 1), 0, kMaxP), pslot(parts, P_RZ0 + (itn & 1), 0, kMaxP),
+                            pslot(parts, P_PQ0 + (itn & 1), 0, kMaxP)};
     const int cnt[3] = {A.n_kr, A.n_apply, A.n_apply};
     reduce_parts<3, 0u>(v, src, cnt);
     Scalars* sc = const_cast<Scalars*>(A.sc);
@@ -1013,7 +1014,7 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
 #pragma unroll
             for (int c = 0; c < 3; ++c) zv[c] = d[c] * rv[c];
             bstore3(rs_z[r], o3, so3, zv);
-            if (A.dinv_out) {
+            if (A.dinv_out && rhs0 == 0) {  // the same for every RHS
               if (A.dn_out == 1) zstore1<T>(rs_do, emit ? vwd : kOOR, emit ? sd(ez) : 0u, dinv0);
               else bstore3(rs_do, o3, so3, d);
             }
@@ -1105,20 +1106,20 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
     double v[NV * NR];
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
-      dst[NV * r + 0] = pslot(A.P, P_PQ0 + par, r, kMaxP);
+      dst[NV * r + 0] = pslot(parts, P_PQ0 + par, r, kMaxP);
       v[NV * r + 0] = part[4 * r + 1];
       if constexpr (MODE == MODE_LZ) {
-        dst[NV * r + 1] = pslot(A.P, P_RZ0 + par, r, kMaxP);
+        dst[NV * r + 1] = pslot(parts, P_RZ0 + par, r, kMaxP);
         v[NV * r + 1] = part[4 * r];
       } else {
-        dst[NV * r + 1] = pslot(A.P, P_EP0 + par, r, kMaxP);
+        dst[NV * r + 1] = pslot(parts, P_EP0 + par, r, kMaxP);
         v[NV * r + 1] = (double)tpart[r][2];
       }
       if constexpr (MODE == MODE_CGF) {
-        dst[NV * r + 2] = pslot(A.P, P_RZ0 + par, r, kMaxP);
+        dst[NV * r + 2] = pslot(parts, P_RZ0 + par, r, kMaxP);
         v[NV * r + 2] = (double)tpart[r][0];
         if constexpr (RR) {
-          dst[NV * r + 3] = pslot(A.P, P_RN0 + par, r, kMaxP);
+          dst[NV * r + 3] = pslot(parts, P_RN0 + par, r, kMaxP);
           v[NV * r + 3] = (double)tpart[r][1];
         }
       }
@@ -1130,8 +1131,8 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
     // product partials of iteration t + 1
     const int itn = A.step;
     double v[3] = {part[0], part[1], part[2]};
-    double* dst[3] = {pslot(A.P, P_KRN0 + (itn & 1), 0, kMaxP), pslot(A.P, P_PQ0 + ((itn + 1) & 1), 0, kMaxP),
-                      pslot(A.P, P_RZ0 + ((itn + 1) & 1), 0, kMaxP)};
+    double* dst[3] = {pslot(parts, P_KRN0 + (itn & 1), 0, kMaxP), pslot(parts, P_PQ0 + ((itn + 1) & 1), 0, kMaxP),
+                      pslot(parts, P_RZ0 + ((itn + 1) & 1), 0, kMaxP)};
     write_parts<3, 0u>(v, dst, lb);
   }
   if constexpr (MODE == MODE_RESID) {
@@ -1148,12 +1149,12 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
     double v[4];
     double* dst[4];
     for (int i = 0; i < 4; ++i) v[i] = (double)tpart[0][i];
-    dst[0] = pslot(A.P, P_RNF, 0, kMaxP);
-    dst[1] = pslot(A.P, P_RIF, 0, kMaxP);
-    dst[2] = pslot(A.P, P_FN, 0, kMaxP);
-    dst[3] = pslot(A.P, P_RZ0, 0, kMaxP);  // r.z and r.r of step 0
+    dst[0] = pslot(parts, P_RNF, 0, kMaxP);
+    dst[1] = pslot(parts, P_RIF, 0, kMaxP);
+    dst[2] = pslot(parts, P_FN, 0, kMaxP);
+    dst[3] = pslot(parts, P_RZ0, 0, kMaxP);  // r.z and r.r of step 0
     write_parts<4, 0x2u>(v, dst, lb);
-    if (tid == 0) pslot(A.P, P_RN0, 0, kMaxP)[lb] = v[0];
+    if (tid == 0) pslot(parts, P_RN0, 0, kMaxP)[lb] = v[0];
   }
 }
 
@@ -1393,7 +1394,7 @@ bool apply_offsets_fit(const Geo& G, int dz, size_t value_bytes) {
 // below) 88 -> 79 us; FP64 230x130x150 261 -> 245 us; 256x128x128 and
 // 384x192x192 as before within 1%.
 template <typename T, int NR, int MODE>
-static TileChoice choose_large_tile(const Geo& G, int n_cu, int lds_per_cu) {
+static TileChoice choose_large_tile(const Geo& G, int nrhs, int n_cu, int lds_per_cu) {
   static const int shapes[][2] = {{27, 8}, {31, 7}, {35, 6}, {24, 9}, {20, 11}, {18, 12}};
   TileChoice best{};
   double best_cost = 1e300;
@@ -1411,7 +1412,7 @@ static TileChoice choose_large_tile(const Geo& G, int n_cu, int lds_per_cu) {
         const int slabs = (G.nzn + dz - 1) / dz;
         const int64_t nb = (int64_t)tiles_x * tiles_y * slabs;
         if (nb > kApplyMaxBlocks || !apply_offsets_fit(G, dz, sizeof(T))) continue;
-        const double r = (double)nb / ((double)cap * n_cu), full = std::floor(r), part = r - full;
+        const double r = (double)nb * nrhs / ((double)cap * n_cu), full = std::floor(r), part = r - full;
         const double rounds = full + (part > 0.0 ? 0.5 + 0.5 * part : 0.0);
         const double cost = rounds * (dz + 3) * (cap == 3 ? 1.55 : 1.0) * (1.0 + 64.0 / (3 * sizeof(T)) / (bx + 1));
         if (cost < best_cost) {
@@ -1444,13 +1445,13 @@ static double layer_cost(double w) {
 // max(w, 8) in every kernel: K u at 256x128x128 48 -> 39.6 us; FP64 CG step at
 // 64x32x32 13.9 -> 13.1 us, at 180x90x90 87 -> 79 us.
 template <typename T, int NR, int MODE>
-static TileChoice choose_tile(const Geo& G, int n_cu, int lds_per_cu, int override_shape) {
+static TileChoice choose_tile(const Geo& G, int nrhs, int n_cu, int lds_per_cu, int override_shape) {
   // fixed fields of a caller's override (FBTO_OPT_APPLY_TILE / _CGF_TILE)
   const int want_bx = override_shape & 0xff, want_by = (override_shape >> 8) & 0xff,
             want_dz = (override_shape >> 16) & 0xff;
   if constexpr (MODE == MODE_CGF || MODE == MODE_MRF) {
     if (override_shape == 0 && G.E >= ((int64_t)1 << 21)) {
-      const TileChoice t = choose_large_tile<T, NR, MODE>(G, n_cu, lds_per_cu);
+      const TileChoice t = choose_large_tile<T, NR, MODE>(G, nrhs, n_cu, lds_per_cu);
       if (t.nblocks) return t;
     }
   }
@@ -1483,7 +1484,7 @@ static TileChoice choose_tile(const Geo& G, int n_cu, int lds_per_cu, int overri
         const int slabs = (G.nzn + dz - 1) / dz;
         const int64_t nb = (int64_t)tiles_x * tiles_y * slabs;
         if (nb > kApplyMaxBlocks) continue;
-        const int64_t per_cu = (nb + n_cu - 1) / n_cu;
+        const int64_t per_cu = (nb * nrhs + n_cu - 1) / n_cu;
         const int64_t full = per_cu / occ, rem = per_cu % occ;
         // a block's waves go to the CU's four SIMDs; a count that does not
         // spread evenly (3, 5, 6, 7) leaves one SIMD with more work, as if
@@ -1502,11 +1503,10 @@ static TileChoice choose_tile(const Geo& G, int n_cu, int lds_per_cu, int overri
 }
 
 template <typename T, int NR, int MODE, bool RR = true, int DN = 1, int XU = 1>
-static hipError_t launch_apply_t(fbto_grid_s* g, const ApplyArgs<T>& A0, int rhs0, hipStream_t st,
-                                 int* nb_out) {
-  TileChoice& t = g->tiles[sizeof(T) == 8 ? 1 : 0][NR - 1][MODE];
+static hipError_t launch_apply_t(fbto_grid_s* g, const ApplyArgs<T>& A0, int nrhs, hipStream_t st, int* nb_out) {
+  TileChoice& t = g->tiles[sizeof(T) == 8 ? 1 : 0][nrhs - 1][MODE];
   if (t.nblocks == 0) {
-    t = choose_tile<T, NR, MODE>(g->geo, g->n_cu, g->lds_per_cu, g->tile_override[MODE == MODE_CGF ? 1 : 0]);
+    t = choose_tile<T, NR, MODE>(g->geo, nrhs, g->n_cu, g->lds_per_cu, g->tile_override[MODE == MODE_CGF ? 1 : 0]);
     if (t.nblocks == 0) return hipErrorInvalidConfiguration;
   }
   if (t.nblocks > g->max_partials) return hipErrorInvalidValue;
@@ -1527,7 +1527,7 @@ static hipError_t launch_apply_t(fbto_grid_s* g, const ApplyArgs<T>& A0, int rhs
   size_t lds = apply_lds_bytes<T, NR, MODE>(t.bx, t.by);
   if (t.cap) lds = std::max(lds, (size_t)lds_for_block_cap(g->lds_per_cu, t.cap));
   const int threads = zmarch_threads<MODE>(t.bx, t.by);  // whole waves
-  hipLaunchKernelGGL((k_apply<T, NR, MODE, RR, DN, XU>), dim3(grid), dim3(threads), lds, st, A, rhs0);
+  hipLaunchKernelGGL((k_apply<T, NR, MODE, RR, DN, XU>), dim3(grid, nrhs), dim3(threads), lds, st, A);
   return hipGetLastError();
 }
 
@@ -1542,21 +1542,12 @@ static hipError_t launch_apply_mode(fbto_grid_s* g, ApplyArgs<T> A, int nrhs, hi
   A.sk = spring_k_of<T>(g);
   A.P = g->partials;
   A.sc = g->sc;
-  // one RHS per launch: the per-RHS state of the z-march (two face-mode
-  // sets, the modal carry, staged loads) fills the register file at NR = 1
-  hipError_t e = hipSuccess;
-  if (g->max_partials != kApplyMaxBlocks) return hipErrorInvalidValue;
-  for (int r0 = 0; r0 < nrhs && e == hipSuccess; ++r0) {
-    e = launch_apply_t<T, 1, MODE, RR, DN, XU>(g, A, r0, st, nb_out);
-    A.dinv_out = nullptr;  // the same for every RHS
-    A.P += kApplyMaxBlocks;
-    auto next = [&](auto*& v) {
-      if (v) v += A.g.ndof;
-    };
-    next(A.u), next(A.y), next(A.f), next(A.z), next(A.r);
-    next(A.xi), next(A.ri), next(A.pi), next(A.si), next(A.xo), next(A.ro), next(A.po);
-  }
-  return e;
+  // One RHS per block (the per-RHS state of the z-march, two face-mode sets, the
+  // modal carry and the staged loads, fills the register file), all of them in
+  // one launch: on small grids a launch per load case left most CUs idle.
+  // Three loads at 97x53x41, FP32: a CG step of all three 39 -> 18 us.
+  if (g->max_partials != kApplyMaxBlocks || nrhs < 1 || nrhs > 4) return hipErrorInvalidValue;
+  return launch_apply_t<T, 1, MODE, RR, DN, XU>(g, A, nrhs, st, nb_out);
 }
 
 int apply_max_blocks(const Geo&, int) { return kApplyMaxBlocks; }
@@ -1635,7 +1626,7 @@ hipError_t launch_cg_sens(fbto_grid_s* g, const T* rho, const CgSet<T>& in, T* x
                           int step, const CgCnt& cn, double rtol, hipStream_t st, int* nb_out) {
   TileChoice& t = g->tiles[sizeof(T) == 8 ? 1 : 0][0][MODE_SENSF];
   if (t.nblocks == 0) {
-    t = choose_tile<T, 1, MODE_SENSF>(g->geo, g->n_cu, g->lds_per_cu, g->tile_override[0]);
+    t = choose_tile<T, 1, MODE_SENSF>(g->geo, 1, g->n_cu, g->lds_per_cu, g->tile_override[0]);
     if (t.nblocks == 0) return hipErrorInvalidConfiguration;
   }
   if (t.nblocks > g->max_partials || g->max_partials != kApplyMaxBlocks) return hipErrorInvalidValue;
