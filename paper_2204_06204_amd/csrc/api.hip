@@ -364,16 +364,20 @@ fbto_status_t krylov_run(fbto_grid_s* g, const T* rho, const T* f, T* u, int nrh
     // through three (halo nodes read them while their owners write the next one)
     T* R3 = (T*)V.x1;
     HIP_TRY(launch_apply_lanczos<T>(g, rho, R2, R2, Yb[1], 1, st, &nb_a));
+    const bool pairs = minres_pairs_updates(g);
+    bool pend = false;  // the last pass left its direction to the next one
     for (int itn = 1; itn <= D; ++itn) {
       int nb = 0;
+      const bool up = !pairs || itn == 1 || pend || itn == D;
       HIP_TRY(launch_minres_fused<T>(g, rho, itn, Yb[itn & 1], R1, R2, R3, Wc, W2, x, Yb[(itn + 1) & 1], nb_a, nb_v,
-                                     damp, st, &nb));
+                                     damp, up ? 1 + pend : 0, st, &nb));
       nb_a = nb_v = nb;
       T* t = R1;
       R1 = R2;
       R2 = R3;
       R3 = t;
-      if (itn >= 2) std::swap(Wc, W2);
+      if (itn >= 2 && up && !pend) std::swap(Wc, W2);
+      pend = !up;
     }
     // iteration D + 1: the unfused vector pass on the last product
     int nb = 0;

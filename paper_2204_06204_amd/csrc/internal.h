@@ -87,6 +87,7 @@ struct Scalars {
   // and the Givens state dbar, epsln, phibar, cs, sn.  Pass t writes
   // kr[t & 1] while its blocks read kr[(t + 1) & 1].
   double kr[2][8];
+  double kr_pend[8];   // coefficients of a direction left to the next pass (fused passes)
 };
 
 // Per-block FP64 partial results.  A producing kernel writes one value per
@@ -401,10 +402,14 @@ hipError_t launch_minres(fbto_grid_s* g, int itn, int last, const T* Y, T* R1, c
                          T* x, int n_apply, int n_prev, double damp, hipStream_t st, int* nb_out);
 // The vector pass of iteration itn (1 .. D) fused with iteration itn + 1's
 // product (voxel grids: k_apply's MRF mode; plane grids: k_plane_minres):
-// y -> R3, K y -> Ynext.
+// y -> R3, K y -> Ynext.  x_updates: 1: iteration itn - 1 is finished (its
+// direction to W2); 0 (voxel grids): left to the next pass; 2: iterations itn -
+// 2 and itn - 1 are (directions to W2 and W), the former's Lanczos vector being
+// still in R3.
 template <typename T>
 hipError_t launch_minres_fused(fbto_grid_s* g, const T* rho, int itn, const T* Y, const T* R1, const T* R2, T* R3,
-                               const T* W, T* W2, T* x, T* Ynext, int n_apply, int n_kr, double damp,
+                               T* W, T* W2, T* x, T* Ynext, int n_apply, int n_kr, double damp, int x_updates,
                                hipStream_t st, int* nb_out);
+bool minres_pairs_updates(const fbto_grid_s* g);  // whether the passes take x_updates 0 and 2 in turn
 
 }  // namespace fbto

@@ -111,7 +111,13 @@ static int flat_grid(int64_t n) {
 //          node is staged, and iteration t + 1's product K y of the new
 //          Lanczos vector y in the same pass.  Y, R1, R2 are read at halo
 //          nodes too, so y goes to a third buffer R3 and the product to the
-//          other Y buffer.
+//          other Y buffer.  On large grids every second pass leaves the
+//          direction and the iterate to the next one, which forms two
+//          directions (XU): the Lanczos vector it lacks is still in the buffer
+//          that R3 goes to, and two passes read W, W2, x and that vector and
+//          write W, W2 and x, where a direction per pass takes ten accesses.
+//          FP32 256x128x128 118 -> 105 us per Krylov degree, 128x64x64 21.5 ->
+//          20.3 us; FP64 233 -> 208 and 31.7 -> 29.5 us.
 enum { MODE_APPLY = 0, MODE_RESID = 1, MODE_CG = 2, MODE_CGF = 3, MODE_SENSF = 4, MODE_MRF = 5, MODE_LZ = 6 };
 static_assert(MODE_LZ < kApplyModes, "a tile choice per mode");
 constexpr int kApplyMaxThreads = 512;
@@ -170,6 +176,7 @@ struct ApplyArgs {
   // MRF only (fused MINRES step; `step` is the iteration t, A.y the product)
   const T *mY, *mR1, *mR2, *mW;      // K R2 of iteration t, Lanczos vectors t - 1 and t, direction t - 2
   T *mR3, *mW2, *mx;                 // new Lanczos vector; direction t - 3 in, t - 1 out; iterate
+  T* mWo;                            // XU 2: mW, written (direction t - 1; mW2 gets t - 2)
   int n_kr;                          // partial count of ||R2||^2
   double damp;                       // step size of the low-level step
 };
@@ -299,7 +306,7 @@ struct FusedStage {
 // Loads of one node plane for the fused MINRES step.
 template <typename T>
 struct MinresStage {
-  T w[3], w2[3], x[3];          // owned node only
+  T w[3], w2[3], x[3], v[3];    // owned node only; v: Lanczos vector t - 2
   T y[3], r1[3], r2[3];
   unsigned m;
 };
@@ -421,7 +428,7 @@ constexpr int apply_min_waves() {
 // RR (fused CG step): form r.r for the tolerance test; solves of a fixed
 // step count (rtol = 0) read no r.r and run the variant without it.
 // DN (CG, CGF): values of the inverse diagonal per node.
-// XU (fused CG step): updates of the iterate.  1: x += alpha_k p_k.  0: none, it
+// XU (fused CG and MINRES steps): updates of the iterate.  1: x += alpha_k p_k.  0: none, it
 // is left to the next step; 2: x += alpha_{k-1} p_{k-1} + alpha_k p_k, with
 // p_{k-1} read from the buffer that p_{k+1} goes to, before it is stored.  The
 // operations and their order are the same; two steps read x and p_{k-1} and
@@ -718,6 +725,7 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
   // fused MINRES step: the scalar recurrence of iteration t (every block,
   // same order; block 0 keeps the state), as in k_minres
   T ms = (T)0, mc1 = (T)0, mas = (T)0, minvb = (T)0, mwc1 = (T)0, mwc2 = (T)0, minvg = (T)0, mstep = (T)0;
+  T pinvb = (T)0, pwc1 = (T)0, pwc2 = (T)0, pinvg = (T)0, pstep = (T)0;  // XU 2: of iteration t - 2
   auto uniform = [](T v) -> T { return wave_uniform(v); };
   auto mrf_prologue = [&]() {
     const int itn = A.step;
@@ -739,10 +747,26 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
     mwc2 = uniform((T)q.wc2);
     minvg = uniform((T)q.inv_gamma);
     mstep = uniform((T)(A.damp * q.phi));
+    if constexpr (XU == 0) {  // left to the next pass
+      if (lb == 0 && tid == 0) {
+        sc->kr_pend[0] = q.inv_oldb;
+        sc->kr_pend[1] = q.wc1;
+        sc->kr_pend[2] = q.wc2;
+        sc->kr_pend[3] = q.inv_gamma;
+        sc->kr_pend[4] = q.phi;
+      }
+    }
+    if constexpr (XU == 2) {
+      pinvb = uniform((T)sc->kr_pend[0]);
+      pwc1 = uniform((T)sc->kr_pend[1]);
+      pwc2 = uniform((T)sc->kr_pend[2]);
+      pinvg = uniform((T)sc->kr_pend[3]);
+      pstep = uniform((T)(A.damp * sc->kr_pend[4]));
+    }
   };
   // fused MINRES step (single vectors, rhs0 = 0): the memory access of the fused CG step
   const __amdgpu_buffer_rsrc_t rs_mY = vres(A.mY), rs_mR1 = vres(A.mR1), rs_mR2 = vres(A.mR2), rs_mW = vres(A.mW),
-                               rs_mW2 = vres(A.mW2), rs_mx = vres(A.mx), rs_mR3 = vres(A.mR3);
+                               rs_mW2 = vres(A.mW2), rs_mx = vres(A.mx), rs_mR3 = vres(A.mR3), rs_mWo = vres(A.mWo);
   auto issue_m = [&](int k, MinresStage<T>& S) {
     const bool kv = k >= 0 && k <= kend && k <= G.nz;  // planes the block reads
     const bool own_plane = k >= k0 && k < kend;
@@ -752,15 +776,18 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
     bload3(rs_mY, o3, so3, S.y);
     bload3(rs_mR1, o3, so3, S.r1);
     bload3(rs_mR2, o3, so3, S.r2);
-    bload3(rs_mW, oo, so3, S.w);  // the iterate and the directions: owner only
-    bload3(rs_mW2, oo, so3, S.w2);
-    bload3(rs_mx, oo, so3, S.x);
+    if constexpr (XU >= 1) {  // the iterate and the directions: owner only
+      bload3(rs_mW, oo, so3, S.w);
+      bload3(rs_mW2, oo, so3, S.w2);
+      bload3(rs_mx, oo, so3, S.x);
+    }
+    if constexpr (XU == 2) bload3(rs_mR3, oo, so3, S.v);
   };
   auto stage_m = [&](const MinresStage<T>& S, int buf, int k, T (&zq)[3]) {
     T* nb = nodes + buf * (3 * NS) + 3 * li[0];
     const bool own_plane = k >= k0 && k < kend;
     const int itn = A.step;
-    T yn[3], wn[3], xn[3];
+    T yn[3], wn[3], wp[3], xn[3];
     double yy = 0.0, ry = 0.0;
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
@@ -768,9 +795,17 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
       yn[c] = ms * S.y[c] - mc1 * r1m - mas * S.r2[c];
       nb[c] = zmasked(S.m, c, yn[c]);
       zq[c] = yn[c];  // unmasked: the output of a fixed DOF
-      const T wm = itn >= 3 ? S.w[c] : (T)0, w2m = itn >= 4 ? S.w2[c] : (T)0;
-      wn[c] = (S.r1[c] * minvb - mwc1 * w2m - mwc2 * wm) * minvg;
-      xn[c] = S.x[c] + mstep * wn[c];
+      if constexpr (XU == 1) {
+        const T wm = itn >= 3 ? S.w[c] : (T)0, w2m = itn >= 4 ? S.w2[c] : (T)0;
+        wn[c] = (S.r1[c] * minvb - mwc1 * w2m - mwc2 * wm) * minvg;
+        xn[c] = S.x[c] + mstep * wn[c];
+      }
+      if constexpr (XU == 2) {  // iterations t - 2 (wp), then t - 1
+        const T wm = itn >= 4 ? S.w[c] : (T)0, w2m = itn >= 5 ? S.w2[c] : (T)0;
+        wp[c] = (S.v[c] * pinvb - pwc1 * w2m - pwc2 * wm) * pinvg;
+        wn[c] = (S.r1[c] * minvb - mwc1 * wm - mwc2 * wp[c]) * minvg;
+        xn[c] = (S.x[c] + pstep * wp[c]) + mstep * wn[c];
+      }
       yy += (double)yn[c] * (double)yn[c];
       ry += (double)S.r2[c] * (double)yn[c];
     }
@@ -781,8 +816,9 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
     }
     const uint32_t oo = own_plane ? vw3 : kOOR, so3 = own_plane ? s3(k) : 0u;
     bstore3(rs_mR3, oo, so3, yn);
-    if (itn >= 2) {  // finishes iteration t - 1 (uniform)
-      bstore3(rs_mW2, oo, so3, wn);
+    if (XU >= 1 && itn >= 2) {  // finishes iteration t - 1 (uniform)
+      bstore3(rs_mW2, oo, so3, XU == 2 ? wp : wn);
+      if constexpr (XU == 2) bstore3(rs_mWo, oo, so3, wn);
       bstore3(rs_mx, oo, so3, xn);
     }
   };
@@ -1673,7 +1709,8 @@ hipError_t launch_cg_sens(fbto_grid_s* g, const T* rho, const CgSet<T>& in, T* x
 // kernels in turn measured slower than one (16x8x8 FP64 iteration 85.8 against
 // 84.0 us); four-load 384x192x192 iteration 13.47 -> 13.19 ms with it,
 // 128x64x64 FP64 308 -> 303 us.
-bool cg_pairs_updates(const fbto_grid_s* g) { return g->geo.E >= ((int64_t)1 << 19) && g->n_springs == 0; }
+bool cg_pairs_updates(const fbto_grid_s* g) { return minres_pairs_updates(g) && g->n_springs == 0; }
+bool minres_pairs_updates(const fbto_grid_s* g) { return g->dim == 3 && g->geo.E >= ((int64_t)1 << 19); }
 
 template <typename T>
 hipError_t launch_cg_fused(fbto_grid_s* g, const T* rho, const CgSet<T>& in, const CgSet<T>& out, int nrhs, int step,
@@ -1709,20 +1746,26 @@ hipError_t launch_cg_fused(fbto_grid_s* g, const T* rho, const CgSet<T>& in, con
 
 template <typename T>
 hipError_t launch_minres_fused(fbto_grid_s* g, const T* rho, int itn, const T* Y, const T* R1, const T* R2, T* R3,
-                               const T* W, T* W2, T* x, T* Ynext, int n_apply, int n_kr, double damp,
+                               T* W, T* W2, T* x, T* Ynext, int n_apply, int n_kr, double damp, int x_updates,
                                hipStream_t st, int* nb_out) {
-  if (g->dim == 2)
+  if (g->dim == 2) {
+    if (x_updates != 1) return hipErrorInvalidValue;
     return plane_minres_fused<T>(g, rho, itn, Y, R1, R2, R3, W, W2, x, Ynext, n_apply, n_kr, damp, st, nb_out);
+  }
   ApplyArgs<T> A{};
   A.rho = rho;
   A.y = Ynext;
   A.step = itn;
   A.mY = Y; A.mR1 = R1; A.mR2 = R2; A.mW = W;
-  A.mR3 = R3; A.mW2 = W2; A.mx = x;
+  A.mR3 = R3; A.mW2 = W2; A.mx = x; A.mWo = W;
   A.n_apply = n_apply;
   A.n_kr = n_kr;
   A.damp = damp;
-  return launch_apply_mode<T, MODE_MRF>(g, A, 1, st, nb_out);
+  switch (x_updates) {
+    case 0: return launch_apply_mode<T, MODE_MRF, true, 1, 0>(g, A, 1, st, nb_out);
+    case 1: return launch_apply_mode<T, MODE_MRF, true, 1, 1>(g, A, 1, st, nb_out);
+    default: return launch_apply_mode<T, MODE_MRF, true, 1, 2>(g, A, 1, st, nb_out);
+  }
 }
 
 // ===========================================================================
@@ -3393,8 +3436,8 @@ hipError_t launch_opt_finish(fbto_grid_s* g, int nrhs, int nb_dot, int nb_lo, in
                                              hipStream_t);                                             \
   template hipError_t launch_minres<T>(fbto_grid_s*, int, int, const T*, T*, const T*, T*, const T*, T*, \
                                        int, int, double, hipStream_t, int*);                          \
-  template hipError_t launch_minres_fused<T>(fbto_grid_s*, const T*, int, const T*, const T*, const T*, T*,  \
-                                             const T*, T*, T*, T*, int, int, double, hipStream_t, int*);  \
+  template hipError_t launch_minres_fused<T>(fbto_grid_s*, const T*, int, const T*, const T*, const T*, T*, T*, T*, \
+                                             T*, T*, int, int, double, int, hipStream_t, int*);        \
   template hipError_t launch_sens<T>(fbto_grid_s*, const T*, const T*, const T*, int, T*, const T*,    \
                                      hipStream_t);                                                     \
   template hipError_t launch_dot<T>(fbto_grid_s*, const T*, const T*, int, hipStream_t);               \
