@@ -409,12 +409,19 @@ fbto_status_t krylov_run(fbto_grid_s* g, const T* rho, const T* f, T* u, int nrh
 // density of x is already in V.rho (left by the previous iteration); on
 // return, whether this iteration left the next one's there.  fuse_next: the
 // final projection pass also filters the new design (another iteration
-// follows in the same call, so x does not change in between).
+// follows in the same call, so x does not change in between).  Where the filter
+// and the step run as one pass, the records of such iterations are written by
+// that pass of their own iteration and of the next (`pending`: the record that
+// still lacks the projection's part), not by a launch of their own.
+struct PendingRec {
+  double* info = nullptr;
+  int n_e = 0;
+};
 template <typename T>
 fbto_status_t outer_run(fbto_grid_s* g, T* x, T* u, const T* f, int nrhs, int k, double alpha0,
                         int inner_steps, int mean_project, double lo, double vmax, double* info,
                         hipStream_t st, int krylov_degree = -1, double beta = 1.0, double inner_rtol = 0.0,
-                        bool* rho_ready = nullptr, bool fuse_next = false) {
+                        bool* rho_ready = nullptr, bool fuse_next = false, PendingRec* pending = nullptr) {
   Vecs& V = vecs<T>(g);
   T* rho = (T*)V.rho;
   if (!(rho_ready && *rho_ready)) HIP_TRY(launch_filter<T>(g, 0, x, rho, 0, st));
@@ -431,12 +438,28 @@ fbto_status_t outer_run(fbto_grid_s* g, T* x, T* u, const T* f, int nrhs, int k,
   const double alpha_k = alpha0 * std::pow((double)k, -0.75);
   int nb_seed = 0;
   hipError_t fe = hipErrorNotSupported;
+  // (both conditions are the same for all iterations of a call, so the next
+  // one completes the record)
+  const bool defer = fuse_next && pending && sens_done && zmarch_filter(g);
   if (sens_done) {
     // the last CG step left the gradient's sum (slot GSUM, cn.dot partials):
     // the filter and the step run as one pass
     g->n_gsum = cn.dot;
-    fe = launch_filter_step<T>(g, (const T*)V.ge, x, (T*)V.y, 0.5 * alpha_k, mean_project, cn.dot, lo, 1.0, st,
-                               &nb_seed);
+    OuterRec rec{};
+    if (pending && pending->info) {
+      rec.prev = pending->info;
+      rec.n_e = pending->n_e;
+      pending->info = nullptr;
+    }
+    if (defer) {
+      rec.solve = 1;
+      rec.info = info;
+      rec.n_r = cn.r;
+      rec.n_fn = cn.fn;
+      rec.n_dot = cn.dot;
+    }
+    fe = launch_filter_step<T>(g, (const T*)V.ge, x, (T*)V.y, 0.5 * alpha_k, mean_project, cn.dot, lo, 1.0,
+                               rec.prev || rec.solve ? &rec : nullptr, st, &nb_seed);
     if (fe != hipSuccess && fe != hipErrorNotSupported) HIP_TRY(fe);
   }
   if (fe == hipErrorNotSupported) {
@@ -456,6 +479,11 @@ fbto_status_t outer_run(fbto_grid_s* g, T* x, T* u, const T* f, int nrhs, int k,
   } else {
     HIP_TRY(launch_project<T>(proj_ws(g), g->geo.E, (const T*)V.y, x, lo, 1.0, vmax, 1, g->proj_passes_warm, x,
                               nullptr, nullptr, st, nb_seed));
+  }
+  if (defer) {
+    pending->info = info;
+    pending->n_e = nbE;
+    return FBTO_OK;
   }
   HIP_TRY(launch_pcg_finish(g, nrhs, cn.r, cn.fn, info, cn.dot, nbE, g->n_gsum, st));
   return FBTO_OK;
@@ -1071,15 +1099,16 @@ fbto_status_t fbto_outer_steps(fbto_grid_t g, fbto_prec_t prec, void* x, void* u
   fbto_status_t s = prec == FBTO_F64 ? ensure_vecs<double>(g) : ensure_vecs<float>(g);
   if (s) return s;
   bool rho_ready = false;  // the first iteration filters the caller's x
+  PendingRec pending;
   for (int32_t i = 0; i < n_steps; ++i) {
     double* inf = info ? info + (int64_t)i * FBTO_OUTER_INFO : nullptr;
     const bool fuse_next = i + 1 < n_steps;
     if (prec == FBTO_F64)
       s = outer_run<double>(g, (double*)x, (double*)u, (const double*)f, nrhs, k + i, alpha0, inner_steps,
-                            mean_project, lo, vmax, inf, st, -1, 1.0, 0.0, &rho_ready, fuse_next);
+                            mean_project, lo, vmax, inf, st, -1, 1.0, 0.0, &rho_ready, fuse_next, &pending);
     else
       s = outer_run<float>(g, (float*)x, (float*)u, (const float*)f, nrhs, k + i, alpha0, inner_steps,
-                           mean_project, lo, vmax, inf, st, -1, 1.0, 0.0, &rho_ready, fuse_next);
+                           mean_project, lo, vmax, inf, st, -1, 1.0, 0.0, &rho_ready, fuse_next, &pending);
     if (s) return s;
   }
   return ok();

@@ -292,16 +292,26 @@ hipError_t launch_filter(fbto_grid_s* g, int kind, const T* in, T* out, int want
 template <typename T>
 hipError_t launch_step(fbto_grid_s* g, const T* x, const T* gx, T* y, double half_alpha,
                        int mean_project, double lo, double hi, hipStream_t st);
+// The outer-iteration records a filter-step launch writes, for the iterations of
+// one call (one load case).  Of its own iteration (solve != 0): the final
+// residual norms into the scalars and, with `info`, the solve's part of the
+// record.  Of the iteration before (prev not null): the projection's part, from
+// n_e partials of its final pass, and the status of both.
+struct OuterRec {
+  double* prev;
+  double* info;
+  int solve, n_r, n_fn, n_dot, n_e;
+};
 // The plain-sum filter of the element gradient ge fused with the design
 // step y = x - half_alpha (H ge - mean), leaving the projection's seed
 // partials (their count in *nb_seed).  The mean comes from nb_sum partials
 // in slot GSUM.  hipErrorNotSupported where the filter is not a z-march
 // (plane grids, stencils wider than 3): the caller then filters and steps
-// apart.
+// apart.  rec (may be null): the parts of outer-iteration records it writes too.
 template <typename T>
 hipError_t launch_filter_step(fbto_grid_s* g, const T* ge, const T* x, T* y, double half_alpha,
-                              int mean_project, int nb_sum, double lo, double hi, hipStream_t st,
-                              int* nb_seed);
+                              int mean_project, int nb_sum, double lo, double hi, const OuterRec* rec,
+                              hipStream_t st, int* nb_seed);
 template <typename T>
 hipError_t launch_hs(fbto_grid_s* g, T* Hs, hipStream_t st);
 // Sort-based projection (project_sort.hip).  sort_ws_layout returns the

@@ -2028,6 +2028,56 @@ __global__ void __launch_bounds__(kFinishThreads)
   }
 }
 
+// The parts of two outer-iteration records that a filter-step launch writes (see
+// OuterRec), by one block of kFinishThreads threads beside the filter's: the same
+// sums as k_pcg_finish, whose launch of one block (4.4 us at the end of an
+// iteration, with nothing beside it) is then left to a call's last iteration.
+// Per iteration of a call of 20, FP32: 183.1 -> 179.6 us at 128x64x64, 112.2 ->
+// 107.9 at 64x32x32, 78.6 -> 71.5 at 16x8x8.
+__device__ __forceinline__ void outer_record(const OuterRec& O, const double* P, int maxp, int n_gsum, Scalars* sc,
+                                             int64_t E) {
+  double v[7];
+  const double* src[7] = {pslot(P, P_RNF, 0, maxp), pslot(P, P_RIF, 0, maxp), pslot(P, P_FN, 0, maxp),
+                          pslot(P, P_DOT, 0, maxp), pslot(P, P_VOL, 0, maxp), pslot(P, P_DX, 0, maxp),
+                          pslot(P, P_GSUM, 0, maxp)};
+  const int ns = O.solve ? 1 : 0, np = O.prev ? O.n_e : 0;
+  const int cnt[7] = {ns * O.n_r, ns * O.n_r, ns * O.n_fn, ns * O.n_dot, np, np, ns * n_gsum};
+  double st = 0.0, proj_status = 0.0, lam = 0.0, status = 0.0;
+  if (threadIdx.x == 0) {
+    st = sc->status[0];
+    proj_status = sc->proj_status;
+    lam = sc->lam;
+    if (O.prev) status = O.prev[FBTO_OI_STATUS];
+  }
+  reduce_parts<7, 0x22u, kFinishThreads>(v, src, cnt);
+  if (threadIdx.x != 0) return;
+  if (O.prev) {
+    if (proj_status > 0.0 && (status == 0.0 || proj_status == (double)FBTO_ERR_NONFINITE)) status = proj_status;
+    O.prev[FBTO_OI_DX_INF] = v[5];
+    O.prev[FBTO_OI_LAMBDA] = lam;
+    O.prev[FBTO_OI_VOLUME] = v[4];
+    O.prev[FBTO_OI_STATUS] = status;
+  }
+  if (O.solve) {
+    const double rn = sqrt(v[0]), fnrm = sqrt(v[2]);
+    sc->rnorm2[0] = rn;
+    sc->rinf[0] = v[1];
+    sc->fnorm2[0] = fnrm;
+    if (!isfinite(v[0]) && st == 0.0) {
+      st = (double)FBTO_ERR_NONFINITE;
+      sc->status[0] = st;
+    }
+    if (O.info) {
+      sc->dot[0] = v[3];
+      O.info[FBTO_OI_COMPLIANCE] = v[3];
+      O.info[FBTO_OI_R_INF] = fmax(0.0, v[1]);
+      O.info[FBTO_OI_RREL] = fmax(0.0, fnrm > 0.0 ? rn / fnrm : rn);
+      O.info[FBTO_OI_STATUS] = st;
+      O.info[FBTO_OI_GRAD_MEAN] = v[6] / (double)E;
+    }
+  }
+}
+
 template <typename T>
 __global__ void __launch_bounds__(kVecBlock)
     k_relax_update(int64_t ndof, int nrhs, T* u, const T* r, const T* invD, T omega, int use_diag) {
@@ -2425,7 +2475,9 @@ struct FiltStep {
   double half_alpha;
   int mean_project, nb_sum;
   double lo, hi;
-  const Scalars* sc;
+  Scalars* sc;
+  int rec_on;  // the first layer of blocks writes `rec`
+  OuterRec rec;
 };
 
 // Thread geometry of the filter: a tile of 64 x 4 element columns
@@ -2437,10 +2489,10 @@ struct FiltPos {
   int ex, ey, z0, z1;
   bool col;  // the column lies in the grid
 };
-__device__ __forceinline__ FiltPos filt_pos(const Geo& G) {
+__device__ __forceinline__ FiltPos filt_pos(const Geo& G, int bz) {
   FiltPos q;
   const int tx = threadIdx.x % kFiltBX, ty = threadIdx.x / kFiltBX;
-  const int bx = blockIdx.x, by = blockIdx.y, bz = blockIdx.z;
+  const int bx = blockIdx.x, by = blockIdx.y;
   q.block = bx + gridDim.x * (by + gridDim.y * bz);
   q.tx = tx;
   q.ty = ty;
@@ -2523,7 +2575,17 @@ template <typename T, int R, bool STEP>
 __global__ void __launch_bounds__(kFiltBX * kFiltBY)
     k_filter_z(Geo G, int kind, const T* in, T* out, const T* Hsi, StencilW<T, R> W, int want_sum,
                double* P, int maxp, FiltStep<T> S) {
-  const FiltPos q = filt_pos(G);
+  int bz = blockIdx.z;
+  if constexpr (STEP) {
+    if (S.rec_on) {
+      if (bz == 0) {
+        if (blockIdx.x == 0 && blockIdx.y == 0) outer_record(S.rec, P, maxp, S.nb_sum, S.sc, G.E);
+        return;
+      }
+      --bz;
+    }
+  }
+  const FiltPos q = filt_pos(G, bz);
   __shared__ T sh[FiltStage<R>::kN];
   T sv[FiltStage<R>::kTurns];
   unsigned ok;
@@ -2828,21 +2890,24 @@ bool zmarch_filter(const fbto_grid_s* g) {
 
 template <typename T>
 hipError_t launch_filter_step(fbto_grid_s* g, const T* ge, const T* x, T* y, double half_alpha,
-                              int mean_project, int nb_sum, double lo, double hi, hipStream_t st,
-                              int* nb_seed) {
+                              int mean_project, int nb_sum, double lo, double hi, const OuterRec* rec,
+                              hipStream_t st, int* nb_seed) {
   if (!zmarch_filter(g)) return hipErrorNotSupported;
   const double r = g->desc.filter_radius;
   const int R = r > 1.0 ? (int)std::ceil(r) - 1 : 0;
   const Geo& G = g->geo;
   const int64_t nbz = filt_blocks(G);
   if (mean_project && (nb_sum < 1 || nb_sum > g->max_partials)) return hipErrorInvalidValue;
-  const FiltStep<T> S{x, y, half_alpha, mean_project, nb_sum, lo, hi, (const Scalars*)g->sc};
+  static_assert(kFinishThreads == kFiltBX * kFiltBY, "the record's block is one of the filter's");
+  const FiltStep<T> S{x, y, half_alpha, mean_project, nb_sum, lo, hi, g->sc, rec ? 1 : 0, rec ? *rec : OuterRec{}};
+  dim3 grid = filt_grid(G);
+  if (rec) ++grid.z;
   const T* Hsi = (const T*)vecs_of<T>(g).Hs;  // not read by the plain sum
   if (R == 0)
-    hipLaunchKernelGGL((k_filter_z<T, 0, true>), filt_grid(G), dim3(kFiltBX * kFiltBY), 0, st, G, (int)FILT_SUM,
+    hipLaunchKernelGGL((k_filter_z<T, 0, true>), grid, dim3(kFiltBX * kFiltBY), 0, st, G, (int)FILT_SUM,
                        ge, (T*)nullptr, Hsi, stencil_weights<T, 0>(r), 0, g->partials, g->max_partials, S);
   else
-    hipLaunchKernelGGL((k_filter_z<T, 1, true>), filt_grid(G), dim3(kFiltBX * kFiltBY), 0, st, G, (int)FILT_SUM,
+    hipLaunchKernelGGL((k_filter_z<T, 1, true>), grid, dim3(kFiltBX * kFiltBY), 0, st, G, (int)FILT_SUM,
                        ge, (T*)nullptr, Hsi, stencil_weights<T, 1>(r), 0, g->partials, g->max_partials, S);
   *nb_seed = (int)nbz;
   return hipGetLastError();
@@ -3188,7 +3253,7 @@ __global__ void __launch_bounds__(kFiltBX * kFiltBY)
     k_proj_final_filter(Geo G, const T* y, T* x, T* rho, const T* Hsi, StencilW<T, R> Wf, double lo, double hi,
                         double vmax, ProjWs W, int nb, int passes) {
   constexpr int D = 2 * R + 1;
-  const FiltPos q = filt_pos(G);
+  const FiltPos q = filt_pos(G, blockIdx.z);
   __shared__ T sh[FiltStage<R>::kN];
   T sv[FiltStage<R>::kTurns];
   unsigned ok;
@@ -3450,7 +3515,7 @@ hipError_t launch_opt_finish(fbto_grid_s* g, int nrhs, int nb_dot, int nb_lo, in
   template hipError_t launch_proj_final_filter<T>(fbto_grid_s*, const ProjWs&, const T*, T*, T*, double, \
                                                   double, double, int, hipStream_t, int*);               \
   template hipError_t launch_filter_step<T>(fbto_grid_s*, const T*, const T*, T*, double, int, int, double, \
-                                            double, hipStream_t, int*);
+                                            double, const OuterRec*, hipStream_t, int*);
 
 FBTO_INST(double)
 FBTO_INST(float)
