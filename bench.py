@@ -49,8 +49,8 @@ def kernel_hash() -> str:
     return h.hexdigest()[:16]
 
 
-def measured_traffic(kernel_key: str, summary: str = "apply_K_pmc.json"):
-    """HBM bytes (fetch + write) per launch of the named kernel from the
+def measured_traffic(kernel_keys, summary: str = "apply_K_pmc.json"):
+    """HBM bytes (fetch + write) per launch, averaged over the named kernels, from the
     committed rocprofv3 PMC summary, scaled by the calibration copy, if it
     was taken on the current kernel sources; else None."""
     path = os.path.join(ROOT, "profiles", summary)
@@ -62,10 +62,10 @@ def measured_traffic(kernel_key: str, summary: str = "apply_K_pmc.json"):
         return None
     if d.get("kernel_hash") != kernel_hash():
         return None
-    for name, v in d.get("kernels", {}).items():
-        if kernel_key in name and v.get("fetch_bytes") is not None and v.get("write_bytes") is not None:
-            return v["fetch_bytes"] + v["write_bytes"]
-    return None
+    found = [v["fetch_bytes"] + v["write_bytes"] for name, v in d.get("kernels", {}).items()
+             if any(key in name for key in kernel_keys)
+             and v.get("fetch_bytes") is not None and v.get("write_bytes") is not None]
+    return sum(found) / len(found) if len(found) == len(kernel_keys) else None
 
 
 def parse():
@@ -321,10 +321,20 @@ def apply_sizes(torch):
     return out
 
 
+def fused_step_bytes(ndof, E):
+    """Algorithmic bytes of one fused FP32 CG step on a grid of 2^19 elements or
+    more (averaged over a pair of steps, which update the iterate once): read r,
+    p, s and write r, p, s (3N floats each), read and write x and read the older
+    p every second step, read D^-1 (a float) and the mask byte per node, and one
+    density per element."""
+    N = ndof // 3
+    return int(7.5 * ndof * 4) + 4 * N + N + 4 * E
+
+
 def fused_sizes(torch):
     """The fused CG step (FP32, one load case) on the two larger grids,
     timed as in the headline roofline: HIP events around solves of 41 and 9
-    steps; HBM fraction of the same algorithmic bytes (9*3N*4 + N + 4E)."""
+    steps; HBM fraction of the same algorithmic bytes (fused_step_bytes)."""
     import synth
     from paper_2204_06204_amd.grid import Grid
     out = {}
@@ -332,7 +342,7 @@ def fused_sizes(torch):
         p = synth.config(name)
         g = Grid.from_problem(p, max_rhs=1)
         t = fused_step_timing(g, p, torch, reps=5)
-        nbytes = 9 * p.ndof * 4 + p.N + 4 * p.E
+        nbytes = fused_step_bytes(p.ndof, p.E)
         out[name] = {"us": t * 1e6, "hbm_frac": nbytes / t / 1e9 / HBM_PEAK_GBS, "bytes": nbytes,
                      "grid": [p.nx, p.ny, p.nz]}
         g.close()
@@ -564,16 +574,15 @@ def main():
     N = ndof // 3
     bytes32 = 2 * ndof * 4 + E * 4          # read u, write y, read one density per element
     bytes64 = 2 * ndof * 8 + E * 8
-    # fused CG step: read x, r, p, s, D^-1 and write x, r, p, s (3N floats
-    # each), read the mask byte per node and one density per element
-    bytes_fused = 9 * ndof * 4 + N + E * 4
+    bytes_fused = fused_step_bytes(ndof, E)
     achieved = bytes_fused / t_fused / 1e9
-    traffic = measured_traffic("k_apply<float, 1, 3, false>", "outer_step_pmc.json")
+    traffic = measured_traffic(("k_apply<float, 1, 3, false, 1, 0>", "k_apply<float, 1, 3, false, 1, 2>"),
+                               "outer_step_pmc.json")
     # algorithmic bytes of one outer iteration (FP32, m inner steps), kernel by kernel
     m = p.inner_steps
     bytes_outer = (2 * E * 4                                    # filter, in the final pass below: 1/Hs in, rho out
-                   + 5 * ndof * 4 + N + E * 4                   # residual: u, f in; r, z, D^-1 out
-                   + 3 * ndof * 4 + N + E * 4                   # step 0 product: p, D^-1 in; s out
+                   + 4 * ndof * 4 + 5 * N + E * 4               # residual: u, f in; r, p, D^-1 (per node) out
+                   + 2 * ndof * 4 + 5 * N + E * 4               # step 0 product: p, D^-1 in; s out
                    + (m - 1) * bytes_fused                      # fused steps
                    + 6 * ndof * 4 + N + 3 * E * 4               # last step + sensitivity: x r p s f in, x out; rho, 1/Hs in, g out
                    + 3 * E * 4                                  # filter transpose with the step: g, x in, y out
@@ -637,7 +646,7 @@ def main():
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
                      "kernel": "k_apply<float, 1, CGF> (fused Jacobi-PCG step, 7 of the 8 steps of an "
-                               "outer iteration), algorithmic bytes 9*3N*4 + N + E*4 = "
+                               "outer iteration), algorithmic bytes 7.5*3N*4 + 5N + E*4 = "
                                f"{bytes_fused} per launch, {t_fused * 1e6:.2f} us per launch"},
         "fused_step_sizes": fsizes,
         "outer_roofline": {"bytes_per_iter": bytes_outer, "ceiling_iter_s": HBM_PEAK_GBS * 1e9 / bytes_outer,
