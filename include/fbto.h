@@ -363,7 +363,7 @@ fbto_status_t fbto_optimality(fbto_grid_t g, fbto_prec_t prec, const void* x, co
  * harnesses that forbid hipMalloc.  No grid handle: n_elem is the length
  * of y and x.  It calls no hipMalloc, hipFree or allocating routine.
  * Its workspace -- the per-block FP64 partials of the passes and the search
- * state, 222,016 bytes -- is a static device array that each GPU the
+ * state, 156,416 bytes -- is a static device array that each GPU the
  * library runs on holds until the process ends; the first call on a device
  * looks up its address there.  Every call on one GPU shares that GPU's
  * array: calls that overlap on one GPU (two streams, or two threads) race
