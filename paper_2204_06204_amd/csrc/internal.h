@@ -397,8 +397,7 @@ template <typename T>
 hipError_t plane_sens(fbto_grid_s* g, const T* rho, const T* u, const T* lam, int nrhs, T* dobj, const T* Hsi,
                       hipStream_t st);
 template <typename T>
-hipError_t plane_filter(fbto_grid_s* g, int kind, const T* in, T* out, T* tmp, const T* Hsi, int want_sum,
-                        hipStream_t st);
+hipError_t plane_filter(fbto_grid_s* g, int kind, const T* in, T* out, const T* Hsi, int want_sum, hipStream_t st);
 template <typename T>
 hipError_t plane_hs(fbto_grid_s* g, T* Hsi, hipStream_t st);
 template <typename T>

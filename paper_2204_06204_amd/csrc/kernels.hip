@@ -2823,8 +2823,7 @@ static int64_t filt_blocks(const Geo& G) {
 template <typename T>
 hipError_t launch_filter(fbto_grid_s* g, int kind, const T* in, T* out, int want_sum, hipStream_t st) {
   Vecs& V = vecs_of<T>(g);
-  if (g->dim == 2)  // separable Gaussian: two passes through the step buffer y (unused while filtering)
-    return plane_filter<T>(g, kind, in, out, (T*)V.y, (const T*)V.Hs, want_sum, st);
+  if (g->dim == 2) return plane_filter<T>(g, kind, in, out, (const T*)V.Hs, want_sum, st);
   // with a sum, the grid is capped so that its partials stay few
   const int nb = want_sum ? vec_blocks(g->geo.E) : flat_grid(g->geo.E);
   const double r = g->desc.filter_radius;
