@@ -358,12 +358,12 @@ fbto_status_t krylov_run(fbto_grid_s* g, const T* rho, const T* f, T* u, int nrh
     T* W2 = (T*)V.p[1];
     HIP_TRY(launch_resid<T>(g, rho, x, fr, R2, 0, 1, st, nullptr));  // R2 = f - K u
     int nb_v = 0, nb_a = 0;
-    HIP_TRY(launch_minres<T>(g, 0, last, Yb[0], R1, R2, W2, Wc, x, 0, 0, damp, st, &nb_v));
     // iterations 1 .. D fused (vector pass t with the product of t + 1);
     // products alternate between two buffers, the Lanczos vectors rotate
     // through three (halo nodes read them while their owners write the next one)
     T* R3 = (T*)V.x1;
     HIP_TRY(launch_apply_lanczos<T>(g, rho, R2, R2, Yb[1], 1, st, &nb_a));
+    nb_v = nb_a;  // the product leaves ||R2||^2 too
     const bool pairs = minres_pairs_updates(g);
     bool pend = false;  // the last pass left its direction to the next one
     for (int itn = 1; itn <= D; ++itn) {

@@ -249,7 +249,8 @@ template <typename T>
 hipError_t launch_apply_cg(fbto_grid_s* g, const T* rho, const T* p, T* s, int nrhs, int step, hipStream_t st,
                            int* nb_out);
 // y = K u with the partials of r.u and y.u: the product of Lanczos iteration
-// `step` (one RHS).
+// `step` (one RHS).  r is u itself: r.u is also left as the norm of iteration
+// step - 1.
 template <typename T>
 hipError_t launch_apply_lanczos(fbto_grid_s* g, const T* rho, const T* u, const T* r, T* y, int step, hipStream_t st,
                                 int* nb_out);

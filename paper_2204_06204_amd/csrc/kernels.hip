@@ -1161,6 +1161,11 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
       }
     }
     write_parts<NV * NR, 0u>(v, dst, lb);
+    // LZ: the paired vector is u itself, so r.u is its norm's square too (which
+    // had a launch of its own: Alg. 3 iteration at 128x64x64 FP32 469.9 -> 464.8 us,
+    // plane 576x192 FP64 280.6 -> 276.6 us)
+    if constexpr (MODE == MODE_LZ)
+      if (tid == 0) pslot(parts, P_KRN0 + (par ^ 1), 0, kMaxP)[lb] = v[1];
   }
   if constexpr (MODE == MODE_MRF) {
     // ||y||^2 -> the norm slot of iteration t; <K y, y> and <R2, y> -> the
@@ -2143,8 +2148,8 @@ hipError_t launch_relax_update(fbto_grid_s* g, T* u, const T* r, const T* invD, 
 //     v' = R1 / oldb is that iteration's Lanczos vector;
 //   - forms the next Lanczos vector y = K v - (beta/oldb) R1 - (alpha/beta) R2
 //     into R1's buffer and leaves ||y||^2 as partials.
-// Pass 0 only leaves ||R2||^2 (R2 = f - K u); pass D + 2 only finishes
-// iteration D + 1.  Every block runs the scalar recurrence on the same
+// The first product (LZ mode) leaves ||R2||^2 of R2 = f - K u; pass D + 2 only
+// finishes iteration D + 1.  Every block runs the scalar recurrence on the same
 // reduced values in the same order; block 0 keeps its state for the next
 // pass.  The caller rotates the buffers: R1 <- R2, R2 <- the buffer y went
 // to, W <- the buffer w went to (W2), W2 <- W.  `damp` scales the step
@@ -2154,15 +2159,14 @@ template <typename T>
 __global__ void __launch_bounds__(kVecBlock)
     k_minres(int64_t n, int itn, int last, const T* Y, T* R1, const T* R2, T* W2, const T* W, T* x,
              double* P, int maxp, int n_apply, int n_prev, Scalars* sc, double damp) {
-  double nrm2 = 0.0;
-  if (itn >= 1) {
-    double v[1];
+  double nv[1];
+  {
     const double* src[1] = {pslot(P, P_KRN0 + ((itn - 1) & 1), 0, maxp)};
     const int cnt[1] = {n_prev};
-    reduce_parts<1, 0u>(v, src, cnt);
-    nrm2 = v[0];
+    reduce_parts<1, 0u>(nv, src, cnt);
   }
-  const bool lanczos = itn >= 1 && itn < last;
+  const double nrm2 = nv[0];
+  const bool lanczos = itn < last;
   const bool finish = itn >= 2;
   double yr2 = 0.0, r12 = 0.0;
   if (lanczos) {
@@ -2193,17 +2197,14 @@ __global__ void __launch_bounds__(kVecBlock)
       W2[i] = wn;
       x[i] += step * wn;
     }
-    if (itn == 0) {
-      const T r2 = R2[i];
-      acc += (double)r2 * (double)r2;
-    } else if (lanczos) {
+    if (lanczos) {
       const T r1m = itn >= 2 ? r1 : (T)0;  // R1 holds no vector yet on the first iteration
       const T yn = ts * Y[i] - tc1 * r1m - ta * R2[i];
       R1[i] = yn;
       acc += (double)yn * (double)yn;
     }
   }
-  if (itn == 0 || lanczos) {
+  if (lanczos) {
     double v[1] = {acc};
     double* dst[1] = {pslot(P, P_KRN0 + (itn & 1), 0, maxp)};
     write_parts<1, 0u>(v, dst, blockIdx.x);

@@ -171,6 +171,9 @@ __global__ void __launch_bounds__(kPlaneBlock) k_plane_apply(PlaneArgs<T> A, int
       dst[2 * r + 1] = pslot2(A.P, (MODE == PL_CG ? P_EP0 : P_RZ0) + par, rhs0 + r, A.maxp);
     }
     write_parts<2 * NR, 0u>(part, dst, blockIdx.x);
+    // LZ: the paired vector is u itself, so r.u is its norm's square too
+    if constexpr (MODE == PL_LZ)
+      if (threadIdx.x == 0) pslot2(A.P, P_KRN0 + (par ^ 1), 0, A.maxp)[blockIdx.x] = part[1];
   }
   if constexpr (MODE == PL_RESID) {
     if (!A.parts) return;
