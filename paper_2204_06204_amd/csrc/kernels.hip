@@ -2310,19 +2310,76 @@ __global__ void __launch_bounds__(kVecBlock)
   dobj[e] = (T)val;
 }
 
+// The same for grids that fill few of the tiles' elements (see sens_staged): one
+// element per thread in the order of their numbers, its eight nodes gathered
+// through the caches.  No thread is idle on any grid, but a node is read eight
+// times.  Same operations in the same order as k_sens.
+template <typename T, bool LAM>
+__global__ void __launch_bounds__(kVecBlock)
+    k_sens_gather(Geo G, const T* rho, const T* u, const T* lam, int nrhs, T* dobj, const uint8_t* mask, Modal<T> km,
+                  Simp sp, const T* Hsi) {
+  const int e = blockIdx.x * kVecBlock + threadIdx.x;
+  if (e >= (int)G.E) return;
+  const int row = fdiv(e, G.nx, G.rnx);
+  const int ex = e - row * G.nx;
+  const int ez = fdiv(row, G.ny, G.rny);
+  const int ey = row - ez * G.ny;
+  double acc = 0.0;
+  for (int R = 0; R < nrhs; ++R) {
+    T ue[8][3], le[8][3];
+#pragma unroll
+    for (int a = 0; a < 8; ++a) {
+      const int n = ex + (a & 1) + G.nxn * (ey + ((a >> 1) & 1) + G.nyn * (ez + (a >> 2)));
+      const unsigned m = mask[n];
+      const int64_t o = R * G.ndof + 3 * (int64_t)n;
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        ue[a][c] = zmasked(m, c, u[o + c]);
+        if constexpr (LAM) le[a][c] = zmasked(m, c, lam[o + c]);
+      }
+    }
+    if constexpr (LAM) acc += elem_bilinear<T>(le, ue, km);
+    else acc += elem_bilinear<T>(ue, ue, km);
+  }
+  double val = -(double)simp_ds<T>(rho[e], sp) * acc;
+  if (Hsi) val *= (double)Hsi[e];
+  dobj[e] = (T)val;
+}
+
+// Share of the LDS tiles that a grid's elements have to fill for the staged
+// kernel to be chosen: below it, its idle threads cost more than the repeated
+// reads.  Staged against gathered, 2.2M elements: with all of the tile filled
+// (1024x1024x2) 0.83 of the time in FP32 and 0.61 in FP64, with lam 0.65 and
+// 0.54; with 0.87 to 0.93 of it (56, 60 x 195^2, 30x270x270) 1.05-0.97, 0.86-
+// 0.74, 0.79-0.74, 0.78-0.66; with 0.69 to 0.74 (22, 24, 48 x N^2) 1.22-1.16,
+// 0.93-0.90, 0.94-0.88, 0.86-0.83; with 0.56 (18, 36 x N^2) 1.46, 1.11, 1.12,
+// 1.03; with 1/32 (1x1483x1483) 19, 14, 16, 13.
+template <typename T, bool LAM>
+static bool sens_staged(const Geo& G, const dim3& grid) {
+  constexpr double min_fill = sizeof(T) == 4 ? (LAM ? 0.72 : 0.9) : (LAM ? 0.56 : 0.72);
+  return (double)G.E >= min_fill * kVecBlock * ((double)grid.x * grid.y * grid.z);
+}
+
+template <typename T, bool LAM>
+static void run_sens(fbto_grid_s* g, const T* rho, const T* u, const T* lam, int nrhs, T* dobj, const T* Hsi,
+                     hipStream_t st) {
+  const Geo& G = g->geo;
+  // axes of at most 65,534 elements: within the limits of a grid
+  const dim3 grid((G.nx + kSensX - 1) / kSensX, (G.ny + kSensY - 1) / kSensY, (G.nz + kSensZ - 1) / kSensZ);
+  if (sens_staged<T, LAM>(G, grid))
+    hipLaunchKernelGGL((k_sens<T, LAM>), grid, dim3(kVecBlock), 0, st, G, rho, u, lam, nrhs, dobj, g->mask,
+                       modal_of<T>(g), g->simp, Hsi);
+  else
+    hipLaunchKernelGGL((k_sens_gather<T, LAM>), dim3((G.E + kVecBlock - 1) / kVecBlock), dim3(kVecBlock), 0, st, G,
+                       rho, u, lam, nrhs, dobj, g->mask, modal_of<T>(g), g->simp, Hsi);
+}
+
 template <typename T>
 hipError_t launch_sens(fbto_grid_s* g, const T* rho, const T* u, const T* lam, int nrhs, T* dobj,
                        const T* Hsi, hipStream_t st) {
   if (g->dim == 2) return plane_sens<T>(g, rho, u, lam, nrhs, dobj, Hsi, st);
-  const Geo& G = g->geo;
-  // axes of at most 65,534 elements: within the limits of a grid
-  const dim3 grid((G.nx + kSensX - 1) / kSensX, (G.ny + kSensY - 1) / kSensY, (G.nz + kSensZ - 1) / kSensZ);
-  if (lam)
-    hipLaunchKernelGGL((k_sens<T, true>), grid, dim3(kVecBlock), 0, st, G, rho, u, lam, nrhs, dobj, g->mask,
-                       modal_of<T>(g), g->simp, Hsi);
-  else
-    hipLaunchKernelGGL((k_sens<T, false>), grid, dim3(kVecBlock), 0, st, G, rho, u, lam, nrhs, dobj, g->mask,
-                       modal_of<T>(g), g->simp, Hsi);
+  if (lam) run_sens<T, true>(g, rho, u, lam, nrhs, dobj, Hsi, st);
+  else run_sens<T, false>(g, rho, u, lam, nrhs, dobj, Hsi, st);
   return hipGetLastError();
 }
 
