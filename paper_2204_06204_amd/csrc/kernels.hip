@@ -1434,10 +1434,18 @@ bool apply_offsets_fit(const Geo& G, int dz, size_t value_bytes) {
 // 251 -> 219 us, 230x130x150 140 -> 125 us, 220x115x115 (before: the model
 // below) 88 -> 79 us; FP64 230x130x150 261 -> 245 us; 256x128x128 and
 // 384x192x192 as before within 1%.
+// No choice (the model below then takes the grid) where the shapes do not fit.
+// Planes that fill less than half of their threads, FP32 CG step, these shapes
+// against the model's: 1x1483x1483 519 and 192 us, 8x524x524 76 and 57 (0.40
+// filled), 12x428x428 54 and 56 (0.58), 469x10x469 60 and 58 (0.75).  And fewer
+// planes than the thinnest slab: 1048x1050x2 165 and 125 us, 396x397x14 53 and
+// 48.
 template <typename T, int NR, int MODE>
 static TileChoice choose_large_tile(const Geo& G, int nrhs, int n_cu, int lds_per_cu) {
+  constexpr int kMinDz = 16;
   static const int shapes[][2] = {{27, 8}, {31, 7}, {35, 6}, {24, 9}, {20, 11}, {18, 12}};
   TileChoice best{};
+  if (G.nzn < kMinDz) return best;
   double best_cost = 1e300;
   for (const auto& sh : shapes) {
     const int bx = sh[0], by = sh[1], threads = zmarch_threads<MODE>(bx, by);
@@ -1449,7 +1457,7 @@ static TileChoice choose_large_tile(const Geo& G, int nrhs, int n_cu, int lds_pe
       int occ = 0;
       const hipError_t oe = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_apply<T, NR, MODE>, threads, lds);
       if (oe != hipSuccess || occ < cap || lds > kApplyMaxLds) continue;
-      for (int dz = std::min(16, G.nzn); dz <= std::min(49, G.nzn); ++dz) {
+      for (int dz = kMinDz; dz <= std::min(49, G.nzn); ++dz) {
         const int slabs = (G.nzn + dz - 1) / dz;
         const int64_t nb = (int64_t)tiles_x * tiles_y * slabs;
         if (nb > kApplyMaxBlocks || !apply_offsets_fit(G, dz, sizeof(T))) continue;
@@ -1463,7 +1471,8 @@ static TileChoice choose_large_tile(const Geo& G, int nrhs, int n_cu, int lds_pe
       }
     }
   }
-  return best;
+  const double threads = (double)best.tiles_x * best.tiles_y * (best.bx + 1) * (best.by + 1);
+  return (double)G.nxn * G.nyn >= 0.5 * threads ? best : TileChoice{};
 }
 
 // The time of one layer of a round with w waves per CU, in wave-layers.  K u and
@@ -1482,7 +1491,8 @@ static double layer_cost(double w) {
 // time of a layer (layer_cost) summed over the busiest CU's rounds of resident
 // blocks, times the layers of a block (+ 2 for the prologue).  Rows count a
 // little more the shorter they are (97x53x41, fused CG step with equal blocks:
-// 13.8 us with 35 columns, 14.1 with 16, 14.4 with 10).  Before, a layer cost
+// 13.8 us with 35 columns, 14.1 with 16, 14.4 with 10), up to the grid's own
+// width (8x8x65000, FP32 MINRES pass: 195 us with 22 columns, 170 with 10).  Before, a layer cost
 // max(w, 8) in every kernel: K u at 256x128x128 48 -> 39.6 us; FP64 CG step at
 // 64x32x32 13.9 -> 13.1 us, at 180x90x90 87 -> 79 us.
 template <typename T, int NR, int MODE>
@@ -1532,7 +1542,7 @@ static TileChoice choose_tile(const Geo& G, int nrhs, int n_cu, int lds_per_cu, 
         // the block had the next multiple of four
         const double w = (waves == 1 || waves == 2 || waves == 4 || waves == 8) ? waves : (waves + 3) / 4 * 4;
         const double cost = (full * layer_cost<T, MODE>(occ * w) + (rem ? layer_cost<T, MODE>(rem * w) : 0.0)) *
-                            (dz + 2.0) * (1.0 + 1.0 / (bx + 1));
+                            (dz + 2.0) * (1.0 + 1.0 / std::min(bx + 1, G.nxn + 1));
         if (cost < best_cost) {
           best_cost = cost;
           best = TileChoice{bx, by, dz, tiles_x, tiles_y, slabs, (int)nb, (override_shape >> 24) & 0xf};
