@@ -81,24 +81,28 @@ __device__ __forceinline__ void block_reduce(double (&v)[NV]) {
 // block's entries each and a row-wise DPP butterfly joins the 16 lanes.
 // Every thread does about NV + NTHR / 16 operations, against some 20 per
 // value and wave for the DPP reduction of every value above.  The order of
-// operations is fixed.
+// operations is fixed.  lds: reduce_lds_words values of LDS.  A kernel that
+// reduces more than once can hand every call the same ones (an array declared
+// in here would be a further one for each), with a barrier before a call if
+// other threads may still read what lies there.
+template <int NV, int NTHR>
+__host__ __device__ constexpr int reduce_lds_words() { return NV * (NTHR + 1); }
 template <int NV, unsigned MAXMASK, int NTHR>
-__device__ __forceinline__ void block_reduce_lds(double (&v)[NV]) {
+__device__ __forceinline__ void block_reduce_lds(double (&v)[NV], double* lds) {
   static_assert(NTHR % 64 == 0 && NTHR <= 1024, "whole waves");
   constexpr int SEG = NTHR / 16;
-  __shared__ double sh[NV][NTHR];
-  __shared__ double res[NV];
+  double* const res = lds + NV * NTHR;
   const int tid = threadIdx.x;
 #pragma unroll
-  for (int i = 0; i < NV; ++i) sh[i][tid] = v[i];
+  for (int i = 0; i < NV; ++i) lds[i * NTHR + tid] = v[i];
   __syncthreads();
   for (int t = tid; t < NV * 16; t += NTHR) {  // rows of 16 lanes: one value each
     const int i = t >> 4, l = t & 15;
     const bool is_max = (MAXMASK >> i) & 1u;
-    double acc = sh[i][l];
+    double acc = lds[i * NTHR + l];
 #pragma unroll
     for (int j = 1; j < SEG; ++j) {
-      const double x = sh[i][l + 16 * j];
+      const double x = lds[i * NTHR + l + 16 * j];
       acc = is_max ? fmax(acc, x) : acc + x;
     }
     const double a1 = dpp_move<0xB1, 0xf>(acc);   // quad_perm [1,0,3,2]
@@ -115,6 +119,11 @@ __device__ __forceinline__ void block_reduce_lds(double (&v)[NV]) {
 #pragma unroll
   for (int i = 0; i < NV; ++i) v[i] = res[i];
 }
+template <int NV, unsigned MAXMASK, int NTHR>
+__device__ __forceinline__ void block_reduce_lds(double (&v)[NV]) {
+  __shared__ double lds[reduce_lds_words<NV, NTHR>()];
+  block_reduce_lds<NV, MAXMASK, NTHR>(v, lds);
+}
 
 // Reduce NV arrays of per-block partials (entry i: n[i] values at src[i];
 // sum, or max where bit i of MAXMASK is set).  Every block computes the same
@@ -122,9 +131,8 @@ __device__ __forceinline__ void block_reduce_lds(double (&v)[NV]) {
 // loads see its stores.  Each round loads two entries per thread of every
 // array before folding any, so that the arrays cost one memory latency per
 // round, not one each.
-template <int NV, unsigned MAXMASK, int NTHR = 0>
-__device__ __forceinline__ void reduce_parts(double (&v)[NV], const double* const (&src)[NV],
-                                             const int (&n)[NV]) {
+template <int NV, unsigned MAXMASK>
+__device__ __forceinline__ void fold_parts(double (&v)[NV], const double* const (&src)[NV], const int (&n)[NV]) {
   const int tid = threadIdx.x + blockDim.x * (threadIdx.y + blockDim.y * threadIdx.z);
   const int nthr = blockDim.x * blockDim.y * blockDim.z;
   int nmax = 0;
@@ -149,22 +157,42 @@ __device__ __forceinline__ void reduce_parts(double (&v)[NV], const double* cons
 #pragma unroll
       for (int u = 0; u < 2; ++u) v[i] = ((MAXMASK >> i) & 1u) ? fmax(v[i], x[i][u]) : v[i] + x[i][u];
   }
+}
+template <int NV, unsigned MAXMASK, int NTHR = 0>
+__device__ __forceinline__ void reduce_parts(double (&v)[NV], const double* const (&src)[NV],
+                                             const int (&n)[NV]) {
+  fold_parts<NV, MAXMASK>(v, src, n);
   if constexpr (NTHR > 0) block_reduce_lds<NV, MAXMASK, NTHR>(v);
   else block_reduce<NV, MAXMASK>(v);
+}
+template <int NV, unsigned MAXMASK, int NTHR>
+__device__ __forceinline__ void reduce_parts(double (&v)[NV], const double* const (&src)[NV], const int (&n)[NV],
+                                             double* lds) {
+  fold_parts<NV, MAXMASK>(v, src, n);
+  block_reduce_lds<NV, MAXMASK, NTHR>(v, lds);
 }
 
 // Block-reduce NV values and let thread 0 store them as this block's
 // partials: entry i goes to dst[i][block].  NTHR > 0: the block has NTHR
 // threads, reduced through LDS.
-template <int NV, unsigned MAXMASK, int NTHR = 0>
-__device__ __forceinline__ void write_parts(double (&v)[NV], double* const (&dst)[NV], int block) {
-  if constexpr (NTHR > 0) block_reduce_lds<NV, MAXMASK, NTHR>(v);
-  else block_reduce<NV, MAXMASK>(v);
+template <int NV>
+__device__ __forceinline__ void store_parts(const double (&v)[NV], double* const (&dst)[NV], int block) {
   const int tid = threadIdx.x + blockDim.x * (threadIdx.y + blockDim.y * threadIdx.z);
   if (tid == 0) {
 #pragma unroll
     for (int i = 0; i < NV; ++i) dst[i][block] = v[i];
   }
+}
+template <int NV, unsigned MAXMASK, int NTHR = 0>
+__device__ __forceinline__ void write_parts(double (&v)[NV], double* const (&dst)[NV], int block) {
+  if constexpr (NTHR > 0) block_reduce_lds<NV, MAXMASK, NTHR>(v);
+  else block_reduce<NV, MAXMASK>(v);
+  store_parts(v, dst, block);
+}
+template <int NV, unsigned MAXMASK, int NTHR>
+__device__ __forceinline__ void write_parts(double (&v)[NV], double* const (&dst)[NV], int block, double* lds) {
+  block_reduce_lds<NV, MAXMASK, NTHR>(v, lds);
+  store_parts(v, dst, block);
 }
 
 // Scalar recurrence of MINRES pass itn (see k_minres), from ||R2||^2 and, with

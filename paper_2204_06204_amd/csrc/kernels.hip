@@ -2049,14 +2049,15 @@ __global__ void __launch_bounds__(kFinishThreads)
 // iteration, with nothing beside it) is then left to a call's last iteration.
 // Per iteration of a call of 20, FP32: 183.1 -> 179.6 us at 128x64x64, 112.2 ->
 // 107.9 at 64x32x32, 78.6 -> 71.5 at 16x8x8.
+constexpr int kRecVals = 7;
 __device__ __forceinline__ void outer_record(const OuterRec& O, const double* P, int maxp, int n_gsum, Scalars* sc,
-                                             int64_t E) {
-  double v[7];
-  const double* src[7] = {pslot(P, P_RNF, 0, maxp), pslot(P, P_RIF, 0, maxp), pslot(P, P_FN, 0, maxp),
+                                             int64_t E, double* lds) {
+  double v[kRecVals];
+  const double* src[kRecVals] = {pslot(P, P_RNF, 0, maxp), pslot(P, P_RIF, 0, maxp), pslot(P, P_FN, 0, maxp),
                           pslot(P, P_DOT, 0, maxp), pslot(P, P_VOL, 0, maxp), pslot(P, P_DX, 0, maxp),
                           pslot(P, P_GSUM, 0, maxp)};
   const int ns = O.solve ? 1 : 0, np = O.prev ? O.n_e : 0;
-  const int cnt[7] = {ns * O.n_r, ns * O.n_r, ns * O.n_fn, ns * O.n_dot, np, np, ns * n_gsum};
+  const int cnt[kRecVals] = {ns * O.n_r, ns * O.n_r, ns * O.n_fn, ns * O.n_dot, np, np, ns * n_gsum};
   double st = 0.0, proj_status = 0.0, lam = 0.0, status = 0.0;
   if (threadIdx.x == 0) {
     st = sc->status[0];
@@ -2064,7 +2065,7 @@ __device__ __forceinline__ void outer_record(const OuterRec& O, const double* P,
     lam = sc->lam;
     if (O.prev) status = O.prev[FBTO_OI_STATUS];
   }
-  reduce_parts<7, 0x22u, kFinishThreads>(v, src, cnt);
+  reduce_parts<kRecVals, 0x22u, kFinishThreads>(v, src, cnt, lds);
   if (threadIdx.x != 0) return;
   if (O.prev) {
     if (proj_status > 0.0 && (status == 0.0 || proj_status == (double)FBTO_ERR_NONFINITE)) status = proj_status;
@@ -2517,7 +2518,8 @@ __device__ __forceinline__ void proj_eval_init(double (&v)[kEval]) {
 static_assert(P_YMAX == P_S0 + 1 && P_NACT == P_S0 + 2 && P_E0 == P_S0 + 3, "seed and set 0 are consecutive slots");
 constexpr unsigned kSeedEvalMax = 0x2u | (kEvalMax << 3);  // max y, and the evaluation's
 template <int NTHR>
-__device__ __forceinline__ void step_parts(double (&v3)[3], double (&ev)[kEval], double* P, int maxp, int block) {
+__device__ __forceinline__ void step_parts(double (&v3)[3], double (&ev)[kEval], double* P, int maxp, int block,
+                                           double* lds) {
   double w[3 + kEval];
   double* dst[3 + kEval];
 #pragma unroll
@@ -2525,7 +2527,7 @@ __device__ __forceinline__ void step_parts(double (&v3)[3], double (&ev)[kEval],
     w[i] = i < 3 ? v3[i] : ev[i - 3];
     dst[i] = pslot(P, P_S0 + i, 0, maxp);
   }
-  write_parts<3 + kEval, kSeedEvalMax, NTHR>(w, dst, block);
+  write_parts<3 + kEval, kSeedEvalMax, NTHR>(w, dst, block, lds);
 }
 
 constexpr int kFiltBX = 64, kFiltBY = 4, kFiltDZ = 4;
@@ -2629,8 +2631,7 @@ __device__ __forceinline__ void filt_load(const Geo& G, const FiltPos& q, const 
 // 1000x2000x1 FP64, transposed 16.3 instead of 11.3, and 17.3 instead of 15.8 at
 // 256x128x128.
 template <typename T, int R>
-__device__ __forceinline__ void filt_window(const T (&v)[FiltStage<R>::kTurns], T (&sh)[FiltStage<R>::kLds],
-                                            const FiltPos& q,
+__device__ __forceinline__ void filt_window(const T (&v)[FiltStage<R>::kTurns], T* sh, const FiltPos& q,
                                             T (&win)[kFiltDZ + 2 * R][2 * R + 1][2 * R + 1]) {
   using S = FiltStage<R>;
   if constexpr (R == 0) {
@@ -2671,18 +2672,31 @@ template <typename T, int R, bool STEP>
 __global__ void __launch_bounds__(kFiltBX * kFiltBY)
     k_filter_z(Geo G, int kind, const T* in, T* out, const T* Hsi, StencilW<T, R> W, int want_sum,
                double* P, int maxp, FiltStep<T> S) {
+  // The staged values and, in the step, every reduction share one LDS array:
+  // the record's block uses nothing else, the mean's reduction lies behind the
+  // staged values, the final one on top of both after a barrier.  With an array
+  // each the step took 46.5 KB (FP32; FP64 56.0) where it now takes 20.6 (21.1),
+  // and a SIMD held 3 (2) of its waves instead of 5 (3): at 256x128x128 41.0
+  // (56.7) us instead of 34.7 (47.0), also in calls without records.
+  constexpr int kThreads = kFiltBX * kFiltBY;
+  constexpr int kStaged = (int)((FiltStage<R>::kLds * sizeof(T) + sizeof(double) - 1) / sizeof(double));
+  constexpr int kMean = reduce_lds_words<1, kThreads>();
+  constexpr int kWords = STEP ? std::max({kStaged + kMean, reduce_lds_words<3 + kEval, kThreads>(),
+                                          reduce_lds_words<kRecVals, kThreads>()})
+                              : kStaged;
+  __shared__ double lds[kWords];
   int bz = blockIdx.z;
   if constexpr (STEP) {
     if (S.rec_on) {
       if (bz == 0) {
-        if (blockIdx.x == 0 && blockIdx.y == 0) outer_record(S.rec, P, maxp, S.nb_sum, S.sc, G.E);
+        if (blockIdx.x == 0 && blockIdx.y == 0) outer_record(S.rec, P, maxp, S.nb_sum, S.sc, G.E, lds);
         return;
       }
       --bz;
     }
   }
   const FiltPos q = filt_pos(G, bz);
-  __shared__ T sh[FiltStage<R>::kLds];
+  T* const sh = reinterpret_cast<T*>(lds);
   T sv[FiltStage<R>::kTurns];
   unsigned ok;
   filt_load<T, R>(G, q, in, Hsi, kind == FILT_TRANS, sv, ok);
@@ -2700,7 +2714,7 @@ __global__ void __launch_bounds__(kFiltBX * kFiltBY)
       double v[1];
       const double* src[1] = {pslot(P, P_GSUM, 0, maxp)};
       const int cnt[1] = {S.nb_sum};
-      reduce_parts<1, 0u, kFiltBX * kFiltBY>(v, src, cnt);
+      reduce_parts<1, 0u, kThreads>(v, src, cnt, lds + kStaged);
       mean = v[0] / (double)G.E;
     }
   }
@@ -2740,7 +2754,8 @@ __global__ void __launch_bounds__(kFiltBX * kFiltBY)
     }
   }
   if constexpr (STEP) {
-    step_parts<kFiltBX * kFiltBY>(v3, ev, P, maxp, q.block);
+    __syncthreads();  // every window is read
+    step_parts<kThreads>(v3, ev, P, maxp, q.block, lds);
   } else if (want_sum) {
     double* dst[1] = {pslot(P, P_GSUM, 0, maxp)};
     write_parts<1, 0u>(vs, dst, q.block);
@@ -3082,7 +3097,8 @@ __global__ void __launch_bounds__(kVecBlock)
       proj_eval(ev, yd, lam_w, lo, hi);
     }
   }
-  step_parts<kVecBlock>(v, ev, P, maxp, blockIdx.x);
+  __shared__ double lds[reduce_lds_words<3 + kEval, kVecBlock>()];
+  step_parts<kVecBlock>(v, ev, P, maxp, blockIdx.x, lds);
 }
 
 __device__ __forceinline__ double* lslot(const ProjWs& W, int i) { return W.base + i * W.stride; }

@@ -47,3 +47,11 @@ def test_identity_filter_stages_nothing(lds, t):
     """A filter without neighbours has its values in registers: beside the sum's
     few words (16 waves' values) it needs no LDS."""
     assert _kernel(lds, "k_filter_z", f"{t}Li0ELb0E") <= 16 * 8 + 16
+
+
+@pytest.mark.parametrize("radius", [0, 1])
+@pytest.mark.parametrize("t", ["f", "d"])
+def test_filter_step_lds(lds, t, radius):
+    """The fused filter and step: no more LDS than before it also wrote records
+    (30,840 bytes: five blocks of four waves on a CU)."""
+    assert _kernel(lds, "k_filter_z", f"{t}Li{radius}ELb1E") <= 30840
