@@ -362,7 +362,7 @@ fbto_status_t krylov_run(fbto_grid_s* g, const T* rho, const T* f, T* u, int nrh
     // products alternate between two buffers, the Lanczos vectors rotate
     // through three (halo nodes read them while their owners write the next one)
     T* R3 = (T*)V.x1;
-    HIP_TRY(launch_apply_lanczos<T>(g, rho, R2, R2, Yb[1], 1, st, &nb_a));
+    HIP_TRY(launch_apply_lanczos<T>(g, rho, R2, Yb[1], 1, st, &nb_a));
     nb_v = nb_a;  // the product leaves ||R2||^2 too
     const bool pairs = minres_pairs_updates(g);
     bool pend = false;  // the last pass left its direction to the next one

@@ -195,7 +195,7 @@ __device__ __forceinline__ void write_parts(double (&v)[NV], double* const (&dst
   store_parts(v, dst, block);
 }
 
-// Scalar recurrence of MINRES pass itn (see k_minres), from ||R2||^2 and, with
+// Scalar recurrence of MINRES pass itn >= 1 (see k_minres), from ||R2||^2 and, with
 // `lanczos`, the partials <R1, R2> and <Y, R2> of its product; ks is the state
 // that pass itn - 1 left.  Every block runs it on the same reduced values in
 // the same order; the lead thread stores the next state.
@@ -208,7 +208,7 @@ struct MinresCoef {
 __device__ __forceinline__ MinresCoef minres_scalars(int itn, bool lanczos, double nrm2, double r12, double yr2,
                                                      const double (&ks)[7], double* next, bool lead) {
   MinresCoef q;
-  const double beta = itn >= 1 ? sqrt(fmax(nrm2, 0.0)) : 0.0;
+  const double beta = sqrt(fmax(nrm2, 0.0));
   double oldb = 0.0, alfa_prev = 0.0, dbar = 0.0, epsln = 0.0, phibar = beta, cs = -1.0, sn = 0.0;
   if (itn >= 2) {
     oldb = ks[0];
@@ -240,7 +240,7 @@ __device__ __forceinline__ MinresCoef minres_scalars(int itn, bool lanczos, doub
   const double s = beta > kTinyNorm ? 1.0 / beta : 0.0;
   const double c1 = (itn >= 2 && oldb > kTinyNorm) ? beta / oldb : 0.0;
   const double alfa = lanczos ? s * (s * yr2 - c1 * r12) : 0.0;
-  if (lead && itn >= 1) {
+  if (lead) {
     next[0] = beta;
     next[1] = alfa;
     next[2] = dbar;

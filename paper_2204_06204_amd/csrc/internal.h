@@ -248,12 +248,11 @@ hipError_t launch_resid_diag(fbto_grid_s* g, const T* rho, const T* u, const T* 
 template <typename T>
 hipError_t launch_apply_cg(fbto_grid_s* g, const T* rho, const T* p, T* s, int nrhs, int step, hipStream_t st,
                            int* nb_out);
-// y = K u with the partials of r.u and y.u: the product of Lanczos iteration
-// `step` (one RHS).  r is u itself: r.u is also left as the norm of iteration
-// step - 1.
+// y = K u with the partials of u.u and y.u: the first product of a Krylov step,
+// of Lanczos iteration `step` (one RHS).  u.u is also left as the norm of
+// iteration step - 1.
 template <typename T>
-hipError_t launch_apply_lanczos(fbto_grid_s* g, const T* rho, const T* u, const T* r, T* y, int step, hipStream_t st,
-                                int* nb_out);
+hipError_t launch_apply_lanczos(fbto_grid_s* g, const T* rho, const T* u, T* y, int step, hipStream_t st, int* nb_out);
 // One fused CG step k (voxel grids): vector update of step k from `in`, stored
 // into `out`, and out.s = K p of step k + 1 with its partials.  x_updates: 1:
 // out.x = in.x + alpha_k p_k; 0: no x is read or written; 2: in.x lacks step
@@ -390,8 +389,7 @@ template <typename T>
 hipError_t plane_apply_cg(fbto_grid_s* g, const T* rho, const T* p, const T* invD, T* s, int nrhs, int step,
                           hipStream_t st, int* nb_out);
 template <typename T>
-hipError_t plane_apply_lanczos(fbto_grid_s* g, const T* rho, const T* u, const T* r, T* y, int step, hipStream_t st,
-                               int* nb_out);
+hipError_t plane_apply_lanczos(fbto_grid_s* g, const T* rho, const T* u, T* y, int step, hipStream_t st, int* nb_out);
 template <typename T>
 hipError_t plane_diag(fbto_grid_s* g, const T* rho, T* invD, hipStream_t st);
 template <typename T>

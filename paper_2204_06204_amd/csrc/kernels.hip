@@ -95,8 +95,8 @@ static int flat_grid(int64_t n) {
 //          with the partials of r.z
 //   CG     y = s = K p with the partials of p.s and s.D^-1 s (the product of
 //          the first CG step)
-//   LZ     y = K u with the partials of r.u and y.u (the product of a Lanczos
-//          step of the Krylov update)
+//   LZ     y = K u with the partials of u.u and y.u (the first product of the
+//          Krylov update)
 //   CGF    one fused CG step: the vector update of step k is done where each
 //          node is staged (r' = r - alpha s, p' = D^-1 r' + beta p,
 //          x' = x + alpha p), the owner of the node stores x', r', p' into the
@@ -150,7 +150,6 @@ struct ApplyArgs {
   int dn_out;          // RESID: 1 or 3 values per node
   double ke_diag;      // diagonal entry of KE (with z)
   const T* dinv;
-  const T* r;          // LZ: the vector paired with u in the first partial
   const uint8_t* mask; // bits 0-2: fixed DOFs of the node; bit 3: the node has a spring
   Modal<T> km;
   Simp sp;
@@ -854,16 +853,15 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
   T rq[2][NR][3];  // its unmasked input value
   T dq[2][DN];     // CGF: its D^-1
   T rho_next;
-  // residual, CG and Lanczos modes: values of the own node read only at its
-  // output (RESID: f; CG: D^-1; LZ: r), loaded one layer ahead.  FP64 loads them at the output instead: the queue would not
-  // fit its registers.
-  constexpr bool kOwnQ = sizeof(T) == 4 && (MODE == MODE_RESID || MODE == MODE_CG || MODE == MODE_LZ);
+  // residual and CG modes: values of the own node read only at its output
+  // (RESID: f; CG: D^-1), loaded one layer ahead.  FP64 loads them at the output
+  // instead: the queue would not fit its registers.
+  constexpr bool kOwnQ = sizeof(T) == 4 && (MODE == MODE_RESID || MODE == MODE_CG);
   T oq[2][NR][3];
-  __amdgpu_buffer_rsrc_t rs_f[NR], rs_cr[NR], rs_y[NR], rs_z[NR];
+  __amdgpu_buffer_rsrc_t rs_f[NR], rs_y[NR], rs_z[NR];
 #pragma unroll
   for (int r = 0; r < NR; ++r) {
     rs_f[r] = vres(A.f, r);
-    rs_cr[r] = vres(A.r, r);
     rs_y[r] = vres(A.y, r);
     rs_z[r] = vres(A.z, r);
   }
@@ -875,13 +873,11 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
     for (int r = 0; r < NR; ++r) {
       if constexpr (MODE == MODE_RESID) {
         bload3(rs_f[r], o3, so3, q[r]);
-      } else if constexpr (MODE == MODE_CG) {
+      } else {
         T d[DN];
         load_d(ok ? vwd : kOOR, ok ? splane(k) : 0u, o3, so3, d);
 #pragma unroll
         for (int c = 0; c < DN; ++c) q[r][c] = d[c];
-      } else {
-        bload3(rs_cr[r], o3, so3, q[r]);
       }
     }
   };
@@ -1071,7 +1067,7 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
         } else {
           bstore3(rs_y[r], o3, so3, acc);
           if constexpr (MODE == MODE_CG || MODE == MODE_LZ) {
-            T q3[3];  // CG: D^-1; LZ: the paired vector
+            T q3[3];  // CG: D^-1
             if constexpr (MODE == MODE_CG) {
               T d[DN];
               if constexpr (kOwnQ) {
@@ -1082,23 +1078,18 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
               }
 #pragma unroll
               for (int c = 0; c < 3; ++c) q3[c] = dof_d(d, m, c);
-            } else if constexpr (kOwnQ) {
-#pragma unroll
-              for (int c = 0; c < 3; ++c) q3[c] = oq[P][r][c];
-            } else {
-              bload3(rs_cr[r], o3, so3, q3);
             }
-            double yu = 0.0, ru = 0.0;
+            double yu = 0.0, uu = 0.0;
             T ss = (T)0;
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
               yu += (double)acc[c] * (double)pv[c];
               if constexpr (MODE == MODE_CG) ss += acc[c] * (q3[c] * acc[c]);
-              else ru += (double)q3[c] * (double)pv[c];
+              else uu += (double)pv[c] * (double)pv[c];
             }
             part[4 * r + 1] += own_only(yu);  // p.s / y.u
             if constexpr (MODE == MODE_CG) tpart[r][2] += own_t(ss);  // s.D^-1 s
-            else part[4 * r] += own_only(ru);                         // r.u
+            else part[4 * r] += own_only(uu);                         // u.u
           }
           if constexpr (MODE == MODE_CGF || MODE == MODE_MRF) {
             double yu = 0.0;
@@ -1136,7 +1127,7 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
     // CG: step k's product -> set k & 1; CGF: step k + 1's -> set (k + 1) & 1;
     // LZ: iteration k's
     const int par = (MODE == MODE_CGF ? A.step + 1 : A.step) & 1;
-    // CG: p.s, s.D^-1 s   CGF: also r.z (, r.r)   LZ: y.u, r.u
+    // CG: p.s, s.D^-1 s   CGF: also r.z (, r.r)   LZ: y.u, u.u
     constexpr int NV = MODE == MODE_CGF ? (RR ? 4 : 3) : 2;
     double* dst[NV * NR];
     double v[NV * NR];
@@ -1161,9 +1152,9 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
       }
     }
     write_parts<NV * NR, 0u>(v, dst, lb);
-    // LZ: the paired vector is u itself, so r.u is its norm's square too (which
-    // had a launch of its own: Alg. 3 iteration at 128x64x64 FP32 469.9 -> 464.8 us,
-    // plane 576x192 FP64 280.6 -> 276.6 us)
+    // LZ: u.u is the norm's square of iteration `step` - 1 too (which had a launch of
+    // its own: Alg. 3 iteration at 128x64x64 FP32 469.9 -> 464.8 us, plane 576x192
+    // FP64 280.6 -> 276.6 us)
     if constexpr (MODE == MODE_LZ)
       if (tid == 0) pslot(parts, P_KRN0 + (par ^ 1), 0, kMaxP)[lb] = v[1];
   }
@@ -1660,13 +1651,12 @@ hipError_t launch_apply_cg(fbto_grid_s* g, const T* rho, const T* p, T* s, int n
 }
 
 template <typename T>
-hipError_t launch_apply_lanczos(fbto_grid_s* g, const T* rho, const T* u, const T* r, T* y, int step, hipStream_t st,
+hipError_t launch_apply_lanczos(fbto_grid_s* g, const T* rho, const T* u, T* y, int step, hipStream_t st,
                                 int* nb_out) {
-  if (g->dim == 2) return plane_apply_lanczos<T>(g, rho, u, r, y, step, st, nb_out);
+  if (g->dim == 2) return plane_apply_lanczos<T>(g, rho, u, y, step, st, nb_out);
   ApplyArgs<T> A{};
   A.rho = rho;
   A.u = u;
-  A.r = r;
   A.y = y;
   A.step = step;
   return launch_apply_mode<T, MODE_LZ>(g, A, 1, st, nb_out);
@@ -3595,8 +3585,7 @@ hipError_t launch_opt_finish(fbto_grid_s* g, int nrhs, int nb_dot, int nb_lo, in
   template hipError_t launch_resid_diag<T>(fbto_grid_s*, const T*, const T*, const T*, T*, T*, int,    \
                                            hipStream_t, int*);                                         \
   template hipError_t launch_apply_cg<T>(fbto_grid_s*, const T*, const T*, T*, int, int, hipStream_t, int*); \
-  template hipError_t launch_apply_lanczos<T>(fbto_grid_s*, const T*, const T*, const T*, T*, int,     \
-                                              hipStream_t, int*);                                      \
+  template hipError_t launch_apply_lanczos<T>(fbto_grid_s*, const T*, const T*, T*, int, hipStream_t, int*); \
   template hipError_t launch_cg_step<T>(fbto_grid_s*, const T*, T*, T*, const T*, T*, const T*, const T*, int, int, \
                                         bool, const CgCnt&, double, hipStream_t, int*);                \
   template hipError_t launch_cg_sens<T>(fbto_grid_s*, const T*, const CgSet<T>&, T*, const T*, T*, const T*, int, \

@@ -40,7 +40,6 @@ struct PlaneArgs {
   const T* invD;       // CG: the preconditioner
   T* invD_out;         // RESID (optional): form the Jacobi diagonal and store its inverse, and z = D^-1 r
   T* z;                // RESID, with invD_out
-  const T* r;          // LZ: the vector paired with u in the first partial
   const uint8_t* mask; // bit c: DOF c of the node fixed
   Q4<T> ke;
   double ke_diag;
@@ -149,7 +148,7 @@ __global__ void __launch_bounds__(kPlaneBlock) k_plane_apply(PlaneArgs<T> A, int
           part[4 * r + 2] += (double)fv * (double)fv;
           part[4 * r + 3] += (double)rv * (double)zv;
         }
-      } else {  // PL_CG: p.s, s.D^-1 s; PL_LZ: y.u, r.u
+      } else {  // PL_CG: p.s, s.D^-1 s; PL_LZ: y.u, u.u
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
           A.y[o + c] = acc[r][c];
@@ -157,7 +156,7 @@ __global__ void __launch_bounds__(kPlaneBlock) k_plane_apply(PlaneArgs<T> A, int
           if constexpr (MODE == PL_CG)
             part[2 * r + 1] += (double)acc[r][c] * (double)(A.invD[2 * (int64_t)n + c] * acc[r][c]);
           else
-            part[2 * r + 1] += (double)A.r[o + c] * (double)pv[c];
+            part[2 * r + 1] += (double)pv[c] * (double)pv[c];
         }
       }
     }
@@ -171,7 +170,7 @@ __global__ void __launch_bounds__(kPlaneBlock) k_plane_apply(PlaneArgs<T> A, int
       dst[2 * r + 1] = pslot2(A.P, (MODE == PL_CG ? P_EP0 : P_RZ0) + par, rhs0 + r, A.maxp);
     }
     write_parts<2 * NR, 0u>(part, dst, blockIdx.x);
-    // LZ: the paired vector is u itself, so r.u is its norm's square too
+    // LZ: u.u is the norm's square of iteration `step` - 1 too
     if constexpr (MODE == PL_LZ)
       if (threadIdx.x == 0) pslot2(A.P, P_KRN0 + (par ^ 1), 0, A.maxp)[blockIdx.x] = part[1];
   }
@@ -630,12 +629,10 @@ hipError_t plane_apply_cg(fbto_grid_s* g, const T* rho, const T* p, const T* inv
 }
 
 template <typename T>
-hipError_t plane_apply_lanczos(fbto_grid_s* g, const T* rho, const T* u, const T* r, T* y, int step, hipStream_t st,
-                               int* nb_out) {
+hipError_t plane_apply_lanczos(fbto_grid_s* g, const T* rho, const T* u, T* y, int step, hipStream_t st, int* nb_out) {
   PlaneArgs<T> A = plane_args<T>(g);
   A.rho = rho;
   A.u = u;
-  A.r = r;
   A.y = y;
   A.step = step;
   return plane_launch<T, PL_LZ>(g, A, 1, st, nb_out);
@@ -726,8 +723,7 @@ hipError_t plane_hs(fbto_grid_s* g, T* Hsi, hipStream_t st) {
                                      hipStream_t, int*);                                                     \
   template hipError_t plane_apply_cg<T>(fbto_grid_s*, const T*, const T*, const T*, T*, int, int, hipStream_t, \
                                         int*);                                                               \
-  template hipError_t plane_apply_lanczos<T>(fbto_grid_s*, const T*, const T*, const T*, T*, int, hipStream_t, \
-                                             int*);                                                          \
+  template hipError_t plane_apply_lanczos<T>(fbto_grid_s*, const T*, const T*, T*, int, hipStream_t, int*);   \
   template hipError_t plane_minres_fused<T>(fbto_grid_s*, const T*, int, const T*, const T*, const T*, T*,   \
                                             const T*, T*, T*, T*, int, int, double, hipStream_t, int*);      \
   template hipError_t plane_diag<T>(fbto_grid_s*, const T*, T*, hipStream_t);                                \
