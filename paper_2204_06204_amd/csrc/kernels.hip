@@ -288,9 +288,9 @@ __device__ __forceinline__ void layer_product(const T (&Flo)[4][3], const T (&Fu
   face_values(lo, out);
 }
 
-template <typename T, int NR>
+template <typename T>
 struct ApplyStage {
-  T v[2][NR][3];
+  T v[2][3];
   unsigned m[2];
 };
 
@@ -419,9 +419,9 @@ __device__ __forceinline__ T wave_uniform(T v) {
 // Waves per SIMD the register allocation of a z-march variant must allow:
 // three for the single-RHS FP32 fused steps (at most 168 VGPRs), which run
 // many blocks per CU on large grids; the others are left to the compiler.
-template <typename T, int NR, int MODE>
+template <typename T, int MODE>
 constexpr int apply_min_waves() {
-  return (sizeof(T) == 4 && NR == 1 && (MODE == MODE_CGF || MODE == MODE_MRF)) ? 3 : 1;
+  return (sizeof(T) == 4 && (MODE == MODE_CGF || MODE == MODE_MRF)) ? 3 : 1;
 }
 
 // RR (fused CG step): form r.r for the tolerance test; solves of a fixed
@@ -439,8 +439,8 @@ constexpr int apply_min_waves() {
 // p_{k+2} goes to, before storing it: two steps read x, p_k and write x once,
 // where an update per step reads and writes x twice (the same operations in
 // the same order, half a vector less per step on average).
-template <typename T, int NR, int MODE, bool RR = true, int DN = 1, int XU = 1>
-__global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_per_eu(apply_min_waves<T, NR, MODE>())))
+template <typename T, int MODE, bool RR = true, int DN = 1, int XU = 1>
+__global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_per_eu(apply_min_waves<T, MODE>())))
     k_apply(ApplyArgs<T> A) {
   extern __shared__ __align__(16) unsigned char apply_smem[];
   const int b = blockIdx.x;
@@ -459,9 +459,9 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
   // a node's three values and a thread's nine corner values lie together:
   // odd strides of 3 and 9 values (no bank conflicts), few wide LDS
   // instructions, and immediate offsets instead of an address each
-  T* nodes = reinterpret_cast<T*>(apply_smem);   // [2][NR][NS][3]
-  T* corners = nodes + 2 * NR * 3 * NS;         // [2][NR][TS][9]
-  T* dcorn = corners + 2 * NR * 9 * TS;          // [2][TS] density sums of the diagonal
+  T* nodes = reinterpret_cast<T*>(apply_smem);   // [2][NS][3]
+  T* corners = nodes + 2 * 3 * NS;              // [2][TS][9]
+  T* dcorn = corners + 2 * 9 * TS;              // [2][TS] density sums of the diagonal
 
   // Thread (tx, ty) of the tile computes element column (x0 + tx, y0 + ty)
   // for tx < BX, ty < BY and stages node (x0 + tx, y0 + ty).  In the node
@@ -522,7 +522,7 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
   const int64_t pbase = (int64_t)ez0 * plane;               // first node of plane ez0
   const int64_t vbase = (int64_t)rhs0 * G.ndof + 3 * pbase;  // its first value in RHS rhs0
   auto rsrc = [](const void* p) { return zrsrc(p); };
-  auto vres = [&](const T* v, int r = 0) { return rsrc(v ? v + vbase + (int64_t)r * G.ndof : v); };  // [nrhs][3N]
+  auto vres = [&](const T* v) { return rsrc(v ? v + vbase : v); };  // [nrhs][3N]
   auto dres = [&](const T* v, int dn) { return rsrc(v ? v + dn * pbase : v); };  // [N][dn]
   // An access takes the byte offset of the lane's node column in its plane
   // (computed once; kOOR where the lane has none) and the plane's byte offset
@@ -553,46 +553,38 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
 
   // Planes past the slab's last one (kend) are staged but never read; their
   // loads are out of range.
-  __amdgpu_buffer_rsrc_t rs_u[NR];
-#pragma unroll
-  for (int r = 0; r < NR; ++r) rs_u[r] = vres(A.u, r);
-  auto issue = [&](int k, ApplyStage<T, NR>& S) {
+  const __amdgpu_buffer_rsrc_t rs_u = vres(A.u);
+  auto issue = [&](int k, ApplyStage<T>& S) {
     const bool kv = k >= 0 && k <= kend && k <= G.nz;  // planes the block reads
     const uint32_t so1 = kv ? splane(k) : 0u, so3 = (uint32_t)(3 * sizeof(T)) * so1;
 #pragma unroll
     for (int sl = 0; sl < kSlots; ++sl) {
       const uint32_t o1 = kv ? (sl ? vx1 : vc1) : kOOR, o3 = kv ? (sl ? vx3 : vc3) : kOOR;
       S.m[sl] = bmask(o1, so1);
-#pragma unroll
-      for (int r = 0; r < NR; ++r) bload3(rs_u[r], o3, so3, S.v[sl][r]);
+      bload3(rs_u, o3, so3, S.v[sl]);
     }
   };
-  auto stage = [&](const ApplyStage<T, NR>& S, int buf) {
-    T* nb = nodes + buf * (NR * 3 * NS);
+  auto stage = [&](const ApplyStage<T>& S, int buf) {
+    T* nb = nodes + buf * (3 * NS);
 #pragma unroll
     for (int sl = 0; sl < kSlots; ++sl) {
       if (sl == 1 && !has_extra) continue;  // no far node: nothing staged
 #pragma unroll
-      for (int r = 0; r < NR; ++r)
-#pragma unroll
-        for (int c = 0; c < 3; ++c) nb[(r * NS + li[sl]) * 3 + c] = zmasked(S.m[sl], c, S.v[sl][r][c]);
+      for (int c = 0; c < 3; ++c) nb[3 * li[sl] + c] = zmasked(S.m[sl], c, S.v[sl][c]);
     }
   };
   // the lower-left node of the thread's element (node 0's for threads
   // without an element, whose face values nothing reads: their reads stay
   // inside the plane)
   const int lf = 3 * (elem_t ? li[0] : 0);
-  auto read_face = [&](int buf, T (&F)[NR][4][3]) {
-    const T* nb = nodes + buf * (NR * 3 * NS) + lf;
+  auto read_face = [&](int buf, T (&F)[4][3]) {
+    const T* nb = nodes + buf * (3 * NS) + lf;
+    T u4[4][3];
 #pragma unroll
-    for (int r = 0; r < NR; ++r) {
-      T u4[4][3];
+    for (int a = 0; a < 4; ++a)
 #pragma unroll
-      for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int c = 0; c < 3; ++c) u4[a][c] = nb[3 * (r * NS + (a >> 1) * NW) + 3 * (a & 1) + c];
-      face_modes(u4, F[r]);
-    }
+      for (int c = 0; c < 3; ++c) u4[a][c] = nb[3 * (a >> 1) * NW + 3 * (a & 1) + c];
+    face_modes(u4, F);
   };
   // The density of the next layer is loaded raw and turned into s_e only
   // when it is used: consuming a load right after it was issued would make
@@ -610,18 +602,14 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
     return el ? simp_s<T>(rv, A.sp) : (T)0;
   };
 
-  static_assert(MODE != MODE_CGF || NR == 1, "the fused CG step handles one RHS per launch");
-  static_assert(MODE != MODE_MRF || NR == 1, "the fused MINRES step handles one RHS per launch");
-  constexpr int NP = MODE == MODE_APPLY ? 1 : 4 * NR;  // partial values per block
+  constexpr int NP = MODE == MODE_APPLY ? 1 : 4;  // partial values per block
   double part[NP];
   // The thread's own sums of non-negative terms (r.r, r.z = sum r^2 / d,
   // f.f) and max|r| over its owned nodes, at most 3 (dz + 1) terms per RHS,
   // accumulate in T and join the FP64 partials before the block reduction;
   // sums with terms of either sign (p.s) stay FP64 throughout.
   //   RESID: r.r, max|r|, f.f, r.z   CGF: r.z, r.r   CG, CGF: s.D^-1 s (2)
-  T tpart[NR][4];
-#pragma unroll
-  for (int r = 0; r < NR; ++r) tpart[r][0] = tpart[r][1] = tpart[r][2] = tpart[r][3] = (T)0;
+  T tpart[4] = {(T)0, (T)0, (T)0, (T)0};
 #pragma unroll
   for (int i = 0; i < NP; ++i) part[i] = 0.0;
 
@@ -714,8 +702,8 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
       if constexpr (RR) rr += rn[c] * rn[c];
     }
     const bool owner = writer && own_plane;
-    tpart[0][0] += owner ? rz : (T)0;                    // r.z
-    if constexpr (RR) tpart[0][1] += owner ? rr : (T)0;  // r.r
+    tpart[0] += owner ? rz : (T)0;                    // r.z
+    if constexpr (RR) tpart[1] += owner ? rr : (T)0;  // r.r
     if constexpr (XU >= 1) bstore3(rs_xo, o3, so3, xn);
     bstore3(rs_ro, o3, so3, rn);
     bstore3(rs_po, o3, so3, pn);
@@ -836,49 +824,38 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
       q[i] = v;
     }
   }
-  ApplyStage<T, NR> S[2];
+  ApplyStage<T> S[2];
   FusedStage<T, DN> SF;
   MinresStage<T> SM;
-  T F[2][NR][4][3];
-  T carry[NR][4][3];
+  T F[2][4][3];
+  T carry[4][3];
 #pragma unroll
-  for (int r = 0; r < NR; ++r)
+  for (int q = 0; q < 4; ++q)
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-      for (int c = 0; c < 3; ++c) carry[r][q][c] = (T)0;
+    for (int c = 0; c < 3; ++c) carry[q][c] = (T)0;
 
   // prologue: planes ez0, ez0 + 1 staged (and, unfused, plane ez0 + 2 in flight)
   unsigned mq[2];  // mask of the own node, by parity of the plane from ez0
-  T rq[2][NR][3];  // its unmasked input value
+  T rq[2][3];  // its unmasked input value
   T dq[2][DN];     // CGF: its D^-1
   T rho_next;
   // residual and CG modes: values of the own node read only at its output
   // (RESID: f; CG: D^-1), loaded one layer ahead.  FP64 loads them at the output
   // instead: the queue would not fit its registers.
   constexpr bool kOwnQ = sizeof(T) == 4 && (MODE == MODE_RESID || MODE == MODE_CG);
-  T oq[2][NR][3];
-  __amdgpu_buffer_rsrc_t rs_f[NR], rs_y[NR], rs_z[NR];
-#pragma unroll
-  for (int r = 0; r < NR; ++r) {
-    rs_f[r] = vres(A.f, r);
-    rs_y[r] = vres(A.y, r);
-    rs_z[r] = vres(A.z, r);
-  }
+  T oq[2][3];
+  const __amdgpu_buffer_rsrc_t rs_f = vres(A.f), rs_y = vres(A.y), rs_z = vres(A.z);
   const __amdgpu_buffer_rsrc_t rs_do = dres(A.dinv_out, A.dn_out);
-  auto load_own = [&](int k, T (&q)[NR][3]) {
+  auto load_own = [&](int k, T (&q)[3]) {
     const bool ok = k >= k0 && k < kend;  // planes this block outputs
     const uint32_t o3 = ok ? vw3 : kOOR, so3 = ok ? s3(k) : 0u;
+    if constexpr (MODE == MODE_RESID) {
+      bload3(rs_f, o3, so3, q);
+    } else {
+      T d[DN];
+      load_d(ok ? vwd : kOOR, ok ? splane(k) : 0u, o3, so3, d);
 #pragma unroll
-    for (int r = 0; r < NR; ++r) {
-      if constexpr (MODE == MODE_RESID) {
-        bload3(rs_f[r], o3, so3, q[r]);
-      } else {
-        T d[DN];
-        load_d(ok ? vwd : kOOR, ok ? splane(k) : 0u, o3, so3, d);
-#pragma unroll
-        for (int c = 0; c < DN; ++c) q[r][c] = d[c];
-      }
+      for (int c = 0; c < DN; ++c) q[c] = d[c];
     }
   };
   if constexpr (MODE == MODE_CGF) {
@@ -887,9 +864,9 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
     rho_next = load_rho(ez0);
     issue_f(ez0 + 1, SF1);
     cg_prologue();
-    stage_f(SF, ez0 & 1, ez0, rq[0][0], dq[0]);
+    stage_f(SF, ez0 & 1, ez0, rq[0], dq[0]);
     mq[0] = SF.m;
-    stage_f(SF1, (ez0 + 1) & 1, ez0 + 1, rq[1][0], dq[1]);
+    stage_f(SF1, (ez0 + 1) & 1, ez0 + 1, rq[1], dq[1]);
     mq[1] = SF1.m;
   } else if constexpr (MODE == MODE_MRF) {
     MinresStage<T> SM1;
@@ -897,9 +874,9 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
     rho_next = load_rho(ez0);
     issue_m(ez0 + 1, SM1);
     mrf_prologue();
-    stage_m(SM, ez0 & 1, ez0, rq[0][0]);
+    stage_m(SM, ez0 & 1, ez0, rq[0]);
     mq[0] = SM.m;
-    stage_m(SM1, (ez0 + 1) & 1, ez0 + 1, rq[1][0]);
+    stage_m(SM1, (ez0 + 1) & 1, ez0 + 1, rq[1]);
     mq[1] = SM1.m;
   } else {
     issue(ez0, S[0]);
@@ -909,12 +886,10 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
     mq[0] = S[0].m[0];
     mq[1] = S[1].m[0];
 #pragma unroll
-    for (int r = 0; r < NR; ++r)
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        rq[0][r][c] = S[0].v[0][r][c];
-        rq[1][r][c] = S[1].v[0][r][c];
-      }
+    for (int c = 0; c < 3; ++c) {
+      rq[0][c] = S[0].v[0][c];
+      rq[1][c] = S[1].v[0][c];
+    }
     // the density first, then the next plane: as in every layer, so that
     // the wait for the density leaves the plane's loads in flight
     rho_next = load_rho(ez0);
@@ -948,39 +923,33 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
     s_below = s;
     read_face((ez + 1) & 1, F[P ^ 1]);
     const bool emit = ez >= k0;  // uniform over the block
-    T out[NR][4][3];
-#pragma unroll
-    for (int r = 0; r < NR; ++r) layer_product(F[P][r], F[P ^ 1][r], s, km, carry[r], out[r]);
+    T out[4][3];
+    layer_product(F[P], F[P ^ 1], s, km, carry, out);
     const int cb = ez & 1;
     if (emit && live) {
 #pragma unroll
-      for (int r = 0; r < NR; ++r)
+      for (int a = 1; a < 4; ++a)
 #pragma unroll
-        for (int a = 1; a < 4; ++a)
-#pragma unroll
-          for (int c = 0; c < 3; ++c)
-            corners[((cb * NR + r) * TS + tid) * 9 + (a - 1) * 3 + c] = out[r][a][c];
+        for (int c = 0; c < 3; ++c) corners[(cb * TS + tid) * 9 + (a - 1) * 3 + c] = out[a][c];
       if constexpr (MODE == MODE_RESID) {
         if (A.z) dcorn[cb * TS + tid] = dcol;
       }
     }
     // the staged plane's values of the own node: into the slot that this
     // layer's output leaves
-    T nq[NR][3], nd[DN];
+    T nq[3], nd[DN];
     unsigned nm;
     if constexpr (MODE == MODE_CGF) {
-      stage_f(SF, ez & 1, ez + 2, nq[0], nd);
+      stage_f(SF, ez & 1, ez + 2, nq, nd);
       nm = SF.m;
     } else if constexpr (MODE == MODE_MRF) {
-      stage_m(SM, ez & 1, ez + 2, nq[0]);
+      stage_m(SM, ez & 1, ez + 2, nq);
       nm = SM.m;
     } else {
       stage(S[P], ez & 1);
       nm = S[P].m[0];
 #pragma unroll
-      for (int r = 0; r < NR; ++r)
-#pragma unroll
-        for (int c = 0; c < 3; ++c) nq[r][c] = S[P].v[0][r][c];
+      for (int c = 0; c < 3; ++c) nq[c] = S[P].v[0][c];
     }
     __syncthreads();
     {
@@ -989,128 +958,124 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
       const bool wr = emit && writer;
       const uint32_t o3 = emit ? vw3 : kOOR, so3 = emit ? s3(ez) : 0u;
       const unsigned m = wr ? mq[P] : 0u;
+      const T* cr = corners + cb * 9 * TS;
+      T acc[3], pv[3];
 #pragma unroll
-      for (int r = 0; r < NR; ++r) {
-        const T* cr = corners + (cb * NR + r) * 9 * TS;
-        T acc[3], pv[3];
+      for (int c = 0; c < 3; ++c) {
+        acc[c] = ((out[0][c] + cr[cr1 + c]) + cr[crb + c]) + cr[crbb + c];
+        pv[c] = rq[P][c];  // the input value at this node, as staged
+      }
+      if (m) {  // springs, then identity rows of fixed DOFs (rare nodes)
+        const int n = gcol[0] + ez * plane;
+        if (m & 8u) {
+          for (int sI = 0; sI < A.nspring; ++sI) {
+            const int64_t d = A.sdof[sI] - (int64_t)3 * n;
 #pragma unroll
-        for (int c = 0; c < 3; ++c) {
-          acc[c] = ((out[r][0][c] + cr[cr1 + c]) + cr[crb + c]) + cr[crbb + c];
-          pv[c] = rq[P][r][c];  // the input value at this node, as staged
+            for (int c = 0; c < 3; ++c)
+              if (d == c) acc[c] += A.sk[sI] * pv[c];
+          }
         }
-        if (m) {  // springs, then identity rows of fixed DOFs (rare nodes)
-          const int n = gcol[0] + ez * plane;
-          if (m & 8u) {
-            for (int sI = 0; sI < A.nspring; ++sI) {
-              const int64_t d = A.sdof[sI] - (int64_t)3 * n;
 #pragma unroll
-              for (int c = 0; c < 3; ++c)
-                if (d == c) acc[c] += A.sk[sI] * pv[c];
-            }
-          }
+        for (int c = 0; c < 3; ++c)
+          if ((m >> c) & 1u) acc[c] = pv[c];
+      }
+      // partial sums count owned nodes only (a select: values of a thread
+      // without an owned node may be anything, NaN included)
+      auto own_only = [wr](double v) { return wr ? v : 0.0; };
+      auto own_t = [wr](T v) { return wr ? v : (T)0; };
+      if constexpr (MODE == MODE_RESID) {
+        T fv[3], rv[3], zv[3] = {(T)0, (T)0, (T)0};
+        if constexpr (kOwnQ) {
 #pragma unroll
-          for (int c = 0; c < 3; ++c)
-            if ((m >> c) & 1u) acc[c] = pv[c];
-        }
-        // partial sums count owned nodes only (a select: values of a thread
-        // without an owned node may be anything, NaN included)
-        auto own_only = [wr](double v) { return wr ? v : 0.0; };
-        auto own_t = [wr](T v) { return wr ? v : (T)0; };
-        if constexpr (MODE == MODE_RESID) {
-          T fv[3], rv[3], zv[3] = {(T)0, (T)0, (T)0};
-          if constexpr (kOwnQ) {
-#pragma unroll
-            for (int c = 0; c < 3; ++c) fv[c] = oq[P][r][c];
-          } else {
-            bload3(rs_f[r], o3, so3, fv);
-          }
-#pragma unroll
-          for (int c = 0; c < 3; ++c) rv[c] = fv[c] - acc[c];
-          if (A.z) {  // the start of a CG solve (uniform)
-            // Jacobi diagonal: ke_diag * sum of s over the node's 8 elements,
-            // one value (and one division) for the node's three DOFs
-            const T d0 = (T)A.ke_diag * (((dcol + dcorn[cb * TS + tl1]) + dcorn[cb * TS + tlb]) + dcorn[cb * TS + tlbb]);
-            const T dinv0 = d0 > (T)0 ? (T)1 / d0 : (T)0;
-            T d[3] = {dinv0, dinv0, dinv0};
-            if (m) {  // springs and fixed DOFs (rare nodes)
-#pragma unroll
-              for (int c = 0; c < 3; ++c) {
-                T dc = d0;
-                if (m & 8u)
-                  for (int sI = 0; sI < A.nspring; ++sI)
-                    if (A.sdof[sI] == (int64_t)(3 * (gcol[0] + ez * plane) + c)) dc += A.sk[sI];
-                if ((m >> c) & 1u) dc = (T)1;
-                d[c] = dc > (T)0 ? (T)1 / dc : (T)0;
-              }
-            }
-#pragma unroll
-            for (int c = 0; c < 3; ++c) zv[c] = d[c] * rv[c];
-            bstore3(rs_z[r], o3, so3, zv);
-            if (A.dinv_out && rhs0 == 0) {  // the same for every RHS
-              if (A.dn_out == 1) zstore1<T>(rs_do, emit ? vwd : kOOR, emit ? sd(ez) : 0u, dinv0);
-              else bstore3(rs_do, o3, so3, d);
-            }
-          }
-          bstore3(rs_y[r], A.y ? o3 : kOOR, so3, rv);
-          T rr = (T)0, rm = (T)0, ff = (T)0, rz = (T)0;
-#pragma unroll
-          for (int c = 0; c < 3; ++c) {
-            rr += rv[c] * rv[c];
-            rm = fmax(rm, fabs(rv[c]));
-            ff += fv[c] * fv[c];
-            rz += rv[c] * zv[c];
-          }
-          tpart[r][0] += own_t(rr);
-          tpart[r][1] = fmax(tpart[r][1], own_t(rm));
-          tpart[r][2] += own_t(ff);
-          tpart[r][3] += own_t(rz);
+          for (int c = 0; c < 3; ++c) fv[c] = oq[P][c];
         } else {
-          bstore3(rs_y[r], o3, so3, acc);
-          if constexpr (MODE == MODE_CG || MODE == MODE_LZ) {
-            T q3[3];  // CG: D^-1
-            if constexpr (MODE == MODE_CG) {
-              T d[DN];
-              if constexpr (kOwnQ) {
+          bload3(rs_f, o3, so3, fv);
+        }
 #pragma unroll
-                for (int c = 0; c < DN; ++c) d[c] = oq[P][r][c];
-              } else {
-                load_d(emit ? vwd : kOOR, emit ? splane(ez) : 0u, o3, so3, d);
-              }
-#pragma unroll
-              for (int c = 0; c < 3; ++c) q3[c] = dof_d(d, m, c);
-            }
-            double yu = 0.0, uu = 0.0;
-            T ss = (T)0;
+        for (int c = 0; c < 3; ++c) rv[c] = fv[c] - acc[c];
+        if (A.z) {  // the start of a CG solve (uniform)
+          // Jacobi diagonal: ke_diag * sum of s over the node's 8 elements,
+          // one value (and one division) for the node's three DOFs
+          const T d0 = (T)A.ke_diag * (((dcol + dcorn[cb * TS + tl1]) + dcorn[cb * TS + tlb]) + dcorn[cb * TS + tlbb]);
+          const T dinv0 = d0 > (T)0 ? (T)1 / d0 : (T)0;
+          T d[3] = {dinv0, dinv0, dinv0};
+          if (m) {  // springs and fixed DOFs (rare nodes)
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
-              yu += (double)acc[c] * (double)pv[c];
-              if constexpr (MODE == MODE_CG) ss += acc[c] * (q3[c] * acc[c]);
-              else uu += (double)pv[c] * (double)pv[c];
+              T dc = d0;
+              if (m & 8u)
+                for (int sI = 0; sI < A.nspring; ++sI)
+                  if (A.sdof[sI] == (int64_t)(3 * (gcol[0] + ez * plane) + c)) dc += A.sk[sI];
+              if ((m >> c) & 1u) dc = (T)1;
+              d[c] = dc > (T)0 ? (T)1 / dc : (T)0;
             }
-            part[4 * r + 1] += own_only(yu);  // p.s / y.u
-            if constexpr (MODE == MODE_CG) tpart[r][2] += own_t(ss);  // s.D^-1 s
-            else part[4 * r] += own_only(uu);                         // u.u
           }
-          if constexpr (MODE == MODE_CGF || MODE == MODE_MRF) {
-            double yu = 0.0;
 #pragma unroll
-            for (int c = 0; c < 3; ++c) yu += (double)acc[c] * (double)pv[c];
-            part[1] += own_only(yu);  // p'.s' / <K y, y>
+          for (int c = 0; c < 3; ++c) zv[c] = d[c] * rv[c];
+          bstore3(rs_z, o3, so3, zv);
+          if (A.dinv_out && rhs0 == 0) {  // the same for every RHS
+            if (A.dn_out == 1) zstore1<T>(rs_do, emit ? vwd : kOOR, emit ? sd(ez) : 0u, dinv0);
+            else bstore3(rs_do, o3, so3, d);
           }
-          if constexpr (MODE == MODE_CGF) {
-            T ss = (T)0;
+        }
+        bstore3(rs_y, A.y ? o3 : kOOR, so3, rv);
+        T rr = (T)0, rm = (T)0, ff = (T)0, rz = (T)0;
 #pragma unroll
-            for (int c = 0; c < 3; ++c) ss += acc[c] * (dof_d(dq[P], m, c) * acc[c]);
-            tpart[0][2] += own_t(ss);  // s'.D^-1 s'
+        for (int c = 0; c < 3; ++c) {
+          rr += rv[c] * rv[c];
+          rm = fmax(rm, fabs(rv[c]));
+          ff += fv[c] * fv[c];
+          rz += rv[c] * zv[c];
+        }
+        tpart[0] += own_t(rr);
+        tpart[1] = fmax(tpart[1], own_t(rm));
+        tpart[2] += own_t(ff);
+        tpart[3] += own_t(rz);
+      } else {
+        bstore3(rs_y, o3, so3, acc);
+        if constexpr (MODE == MODE_CG || MODE == MODE_LZ) {
+          T q3[3];  // CG: D^-1
+          if constexpr (MODE == MODE_CG) {
+            T d[DN];
+            if constexpr (kOwnQ) {
+#pragma unroll
+              for (int c = 0; c < DN; ++c) d[c] = oq[P][c];
+            } else {
+              load_d(emit ? vwd : kOOR, emit ? splane(ez) : 0u, o3, so3, d);
+            }
+#pragma unroll
+            for (int c = 0; c < 3; ++c) q3[c] = dof_d(d, m, c);
           }
+          double yu = 0.0, uu = 0.0;
+          T ss = (T)0;
+#pragma unroll
+          for (int c = 0; c < 3; ++c) {
+            yu += (double)acc[c] * (double)pv[c];
+            if constexpr (MODE == MODE_CG) ss += acc[c] * (q3[c] * acc[c]);
+            else uu += (double)pv[c] * (double)pv[c];
+          }
+          part[1] += own_only(yu);  // p.s / y.u
+          if constexpr (MODE == MODE_CG) tpart[2] += own_t(ss);  // s.D^-1 s
+          else part[0] += own_only(uu);                         // u.u
+        }
+        if constexpr (MODE == MODE_CGF || MODE == MODE_MRF) {
+          double yu = 0.0;
+#pragma unroll
+          for (int c = 0; c < 3; ++c) yu += (double)acc[c] * (double)pv[c];
+          part[1] += own_only(yu);  // p'.s' / <K y, y>
+        }
+        if constexpr (MODE == MODE_CGF) {
+          T ss = (T)0;
+#pragma unroll
+          for (int c = 0; c < 3; ++c) ss += acc[c] * (dof_d(dq[P], m, c) * acc[c]);
+          tpart[2] += own_t(ss);  // s'.D^-1 s'
         }
       }
     }
     mq[P] = nm;
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-#pragma unroll
-      for (int r = 0; r < NR; ++r) rq[P][r][c] = nq[r][c];
+      rq[P][c] = nq[c];
     }
     if constexpr (MODE == MODE_CGF) {
 #pragma unroll
@@ -1129,29 +1094,26 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
     const int par = (MODE == MODE_CGF ? A.step + 1 : A.step) & 1;
     // CG: p.s, s.D^-1 s   CGF: also r.z (, r.r)   LZ: y.u, u.u
     constexpr int NV = MODE == MODE_CGF ? (RR ? 4 : 3) : 2;
-    double* dst[NV * NR];
-    double v[NV * NR];
-#pragma unroll
-    for (int r = 0; r < NR; ++r) {
-      dst[NV * r + 0] = pslot(parts, P_PQ0 + par, r, kMaxP);
-      v[NV * r + 0] = part[4 * r + 1];
-      if constexpr (MODE == MODE_LZ) {
-        dst[NV * r + 1] = pslot(parts, P_RZ0 + par, r, kMaxP);
-        v[NV * r + 1] = part[4 * r];
-      } else {
-        dst[NV * r + 1] = pslot(parts, P_EP0 + par, r, kMaxP);
-        v[NV * r + 1] = (double)tpart[r][2];
-      }
-      if constexpr (MODE == MODE_CGF) {
-        dst[NV * r + 2] = pslot(parts, P_RZ0 + par, r, kMaxP);
-        v[NV * r + 2] = (double)tpart[r][0];
-        if constexpr (RR) {
-          dst[NV * r + 3] = pslot(parts, P_RN0 + par, r, kMaxP);
-          v[NV * r + 3] = (double)tpart[r][1];
-        }
+    double* dst[NV];
+    double v[NV];
+    dst[0] = pslot(parts, P_PQ0 + par, 0, kMaxP);
+    v[0] = part[1];
+    if constexpr (MODE == MODE_LZ) {
+      dst[1] = pslot(parts, P_RZ0 + par, 0, kMaxP);
+      v[1] = part[0];
+    } else {
+      dst[1] = pslot(parts, P_EP0 + par, 0, kMaxP);
+      v[1] = (double)tpart[2];
+    }
+    if constexpr (MODE == MODE_CGF) {
+      dst[2] = pslot(parts, P_RZ0 + par, 0, kMaxP);
+      v[2] = (double)tpart[0];
+      if constexpr (RR) {
+        dst[3] = pslot(parts, P_RN0 + par, 0, kMaxP);
+        v[3] = (double)tpart[1];
       }
     }
-    write_parts<NV * NR, 0u>(v, dst, lb);
+    write_parts<NV, 0u>(v, dst, lb);
     // LZ: u.u is the norm's square of iteration `step` - 1 too (which had a launch of
     // its own: Alg. 3 iteration at 128x64x64 FP32 469.9 -> 464.8 us, plane 576x192
     // FP64 280.6 -> 276.6 us)
@@ -1171,16 +1133,13 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
     if (!A.parts) return;
     if (lb == 0 && tid == 0) {   // a new solve starts from this residual
       Scalars* sc = const_cast<Scalars*>(A.sc);
-      for (int r = 0; r < NR; ++r) {
-        sc->done[rhs0 + r] = 0.0;
-        sc->status[rhs0 + r] = 0.0;
-        sc->steps[rhs0 + r] = 0.0;
-      }
+      sc->done[rhs0] = 0.0;
+      sc->status[rhs0] = 0.0;
+      sc->steps[rhs0] = 0.0;
     }
-    static_assert(NR == 1, "one RHS per launch");
     double v[4];
     double* dst[4];
-    for (int i = 0; i < 4; ++i) v[i] = (double)tpart[0][i];
+    for (int i = 0; i < 4; ++i) v[i] = (double)tpart[i];
     dst[0] = pslot(parts, P_RNF, 0, kMaxP);
     dst[1] = pslot(parts, P_RIF, 0, kMaxP);
     dst[2] = pslot(parts, P_FN, 0, kMaxP);
@@ -1398,11 +1357,11 @@ static size_t sens_lds_bytes(int bx, int by) {
   return sizeof(T) * (size_t)(2 * 3 * (bx + 1) * (by + 1));
 }
 
-template <typename T, int NR, int MODE>
+template <typename T, int MODE>
 static size_t apply_lds_bytes(int bx, int by) {
   const size_t ns = (size_t)(bx + 1) * (by + 1);                      // nodes per plane
   const size_t ts = node_layout<MODE>() ? ns : (size_t)bx * by;      // corner slots
-  return sizeof(T) * (2 * NR * 3 * ns + 2 * NR * 9 * ts + 2 * ts);
+  return sizeof(T) * (2 * 3 * ns + 2 * 9 * ts + 2 * ts);
 }
 
 // The z-march addresses each vector from the block's first plane with
@@ -1431,7 +1390,7 @@ bool apply_offsets_fit(const Geo& G, int dz, size_t value_bytes) {
 // filled), 12x428x428 54 and 56 (0.58), 469x10x469 60 and 58 (0.75).  And fewer
 // planes than the thinnest slab: 1048x1050x2 165 and 125 us, 396x397x14 53 and
 // 48.
-template <typename T, int NR, int MODE>
+template <typename T, int MODE>
 static TileChoice choose_large_tile(const Geo& G, int nrhs, int n_cu, int lds_per_cu) {
   constexpr int kMinDz = 16;
   static const int shapes[][2] = {{27, 8}, {31, 7}, {35, 6}, {24, 9}, {20, 11}, {18, 12}};
@@ -1441,12 +1400,12 @@ static TileChoice choose_large_tile(const Geo& G, int nrhs, int n_cu, int lds_pe
   for (const auto& sh : shapes) {
     const int bx = sh[0], by = sh[1], threads = zmarch_threads<MODE>(bx, by);
     const int tiles_x = (G.nxn + bx - 2) / (bx - 1), tiles_y = (G.nyn + by - 2) / (by - 1);
-    const size_t need = apply_lds_bytes<T, NR, MODE>(bx, by);
+    const size_t need = apply_lds_bytes<T, MODE>(bx, by);
     if (need > kApplyMaxLds) continue;
     for (int cap = 2; cap <= 3; ++cap) {
       const size_t lds = std::max(need, (size_t)lds_for_block_cap(lds_per_cu, cap));
       int occ = 0;
-      const hipError_t oe = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_apply<T, NR, MODE>, threads, lds);
+      const hipError_t oe = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_apply<T, MODE>, threads, lds);
       if (oe != hipSuccess || occ < cap || lds > kApplyMaxLds) continue;
       for (int dz = kMinDz; dz <= std::min(49, G.nzn); ++dz) {
         const int slabs = (G.nzn + dz - 1) / dz;
@@ -1486,14 +1445,14 @@ static double layer_cost(double w) {
 // width (8x8x65000, FP32 MINRES pass: 195 us with 22 columns, 170 with 10).  Before, a layer cost
 // max(w, 8) in every kernel: K u at 256x128x128 48 -> 39.6 us; FP64 CG step at
 // 64x32x32 13.9 -> 13.1 us, at 180x90x90 87 -> 79 us.
-template <typename T, int NR, int MODE>
+template <typename T, int MODE>
 static TileChoice choose_tile(const Geo& G, int nrhs, int n_cu, int lds_per_cu, int override_shape) {
   // fixed fields of a caller's override (FBTO_OPT_APPLY_TILE / _CGF_TILE)
   const int want_bx = override_shape & 0xff, want_by = (override_shape >> 8) & 0xff,
             want_dz = (override_shape >> 16) & 0xff;
   if constexpr (MODE == MODE_CGF || MODE == MODE_MRF) {
     if (override_shape == 0 && G.E >= ((int64_t)1 << 21)) {
-      const TileChoice t = choose_large_tile<T, NR, MODE>(G, nrhs, n_cu, lds_per_cu);
+      const TileChoice t = choose_large_tile<T, MODE>(G, nrhs, n_cu, lds_per_cu);
       if (t.nblocks) return t;
     }
   }
@@ -1507,7 +1466,7 @@ static TileChoice choose_tile(const Geo& G, int nrhs, int n_cu, int lds_per_cu, 
       // at most four waves: every layer ends at a block-wide barrier, and
       // blocks of up to one wave per SIMD measured fastest
       if (ts < 128 || ts > 256) continue;
-      const size_t lds = MODE == MODE_SENSF ? sens_lds_bytes<T>(bx, by) : apply_lds_bytes<T, NR, MODE>(bx, by);
+      const size_t lds = MODE == MODE_SENSF ? sens_lds_bytes<T>(bx, by) : apply_lds_bytes<T, MODE>(bx, by);
       if (lds > kApplyMaxLds) continue;
       const int waves = (ts + 63) / 64;
       int occ = 0;
@@ -1515,7 +1474,7 @@ static TileChoice choose_tile(const Geo& G, int nrhs, int n_cu, int lds_per_cu, 
       if constexpr (MODE == MODE_SENSF)
         oe = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_cg_sens<T>, 64 * waves, lds);
       else
-        oe = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_apply<T, NR, MODE>, 64 * waves, lds);
+        oe = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_apply<T, MODE>, 64 * waves, lds);
       if (oe != hipSuccess || occ < 1) continue;
       const int tiles_x = (G.nxn + bx - 2) / (bx - 1);
       const int tiles_y = (G.nyn + by - 2) / (by - 1);
@@ -1544,11 +1503,11 @@ static TileChoice choose_tile(const Geo& G, int nrhs, int n_cu, int lds_per_cu, 
   return best;
 }
 
-template <typename T, int NR, int MODE, bool RR = true, int DN = 1, int XU = 1>
+template <typename T, int MODE, bool RR = true, int DN = 1, int XU = 1>
 static hipError_t launch_apply_t(fbto_grid_s* g, const ApplyArgs<T>& A0, int nrhs, hipStream_t st, int* nb_out) {
   TileChoice& t = g->tiles[sizeof(T) == 8 ? 1 : 0][nrhs - 1][MODE];
   if (t.nblocks == 0) {
-    t = choose_tile<T, NR, MODE>(g->geo, nrhs, g->n_cu, g->lds_per_cu, g->tile_override[MODE == MODE_CGF ? 1 : 0]);
+    t = choose_tile<T, MODE>(g->geo, nrhs, g->n_cu, g->lds_per_cu, g->tile_override[MODE == MODE_CGF ? 1 : 0]);
     if (t.nblocks == 0) return hipErrorInvalidConfiguration;
   }
   if (t.nblocks > g->max_partials) return hipErrorInvalidValue;
@@ -1566,10 +1525,10 @@ static hipError_t launch_apply_t(fbto_grid_s* g, const ApplyArgs<T>& A0, int nrh
   A.inv_ty = inv_small(t.tiles_y);
   A.inv_tw = 1.0f / (float)(node_layout<MODE>() ? t.bx + 1 : t.bx);
   const int grid = A.per_xcd * 8;
-  size_t lds = apply_lds_bytes<T, NR, MODE>(t.bx, t.by);
+  size_t lds = apply_lds_bytes<T, MODE>(t.bx, t.by);
   if (t.cap) lds = std::max(lds, (size_t)lds_for_block_cap(g->lds_per_cu, t.cap));
   const int threads = zmarch_threads<MODE>(t.bx, t.by);  // whole waves
-  hipLaunchKernelGGL((k_apply<T, NR, MODE, RR, DN, XU>), dim3(grid, nrhs), dim3(threads), lds, st, A);
+  hipLaunchKernelGGL((k_apply<T, MODE, RR, DN, XU>), dim3(grid, nrhs), dim3(threads), lds, st, A);
   return hipGetLastError();
 }
 
@@ -1589,7 +1548,7 @@ static hipError_t launch_apply_mode(fbto_grid_s* g, ApplyArgs<T> A, int nrhs, hi
   // one launch: on small grids a launch per load case left most CUs idle.
   // Three loads at 97x53x41, FP32: a CG step of all three 39 -> 18 us.
   if (g->max_partials != kApplyMaxBlocks || nrhs < 1 || nrhs > 4) return hipErrorInvalidValue;
-  return launch_apply_t<T, 1, MODE, RR, DN, XU>(g, A, nrhs, st, nb_out);
+  return launch_apply_t<T, MODE, RR, DN, XU>(g, A, nrhs, st, nb_out);
 }
 
 int apply_max_blocks(const Geo&, int) { return kApplyMaxBlocks; }
@@ -1667,7 +1626,7 @@ hipError_t launch_cg_sens(fbto_grid_s* g, const T* rho, const CgSet<T>& in, T* x
                           int step, const CgCnt& cn, double rtol, hipStream_t st, int* nb_out) {
   TileChoice& t = g->tiles[sizeof(T) == 8 ? 1 : 0][0][MODE_SENSF];
   if (t.nblocks == 0) {
-    t = choose_tile<T, 1, MODE_SENSF>(g->geo, 1, g->n_cu, g->lds_per_cu, g->tile_override[0]);
+    t = choose_tile<T, MODE_SENSF>(g->geo, 1, g->n_cu, g->lds_per_cu, g->tile_override[0]);
     if (t.nblocks == 0) return hipErrorInvalidConfiguration;
   }
   if (t.nblocks > g->max_partials || g->max_partials != kApplyMaxBlocks) return hipErrorInvalidValue;
