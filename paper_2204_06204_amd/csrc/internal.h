@@ -305,7 +305,7 @@ struct OuterRec {
 // The plain-sum filter of the element gradient ge fused with the design
 // step y = x - half_alpha (H ge - mean), leaving the projection's seed
 // partials (their count in *nb_seed).  The mean comes from nb_sum partials
-// in slot GSUM.  hipErrorNotSupported where the filter is not a z-march
+// in slot GSUM.  hipErrorNotSupported where the filter is not k_filter_z
 // (plane grids, stencils wider than 3): the caller then filters and steps
 // apart.  rec (may be null): the parts of outer-iteration records it writes too.
 template <typename T>
@@ -404,7 +404,7 @@ hipError_t plane_minres_fused(fbto_grid_s* g, const T* rho, int itn, const T* Y,
                               const T* W, T* W2, T* x, T* Ynext, int n_apply, int n_kr, double damp, hipStream_t st,
                               int* nb_out);
 // One vector pass of the Krylov step (MINRES recurrence), iteration `itn`
-// of 0 .. last (see k_minres); returns the block count of its partials.
+// of 1 .. last (see k_minres); returns the block count of its partials.
 template <typename T>
 hipError_t launch_minres(fbto_grid_s* g, int itn, int last, const T* Y, T* R1, const T* R2, T* W2, const T* W,
                          T* x, int n_apply, int n_prev, double damp, hipStream_t st, int* nb_out);

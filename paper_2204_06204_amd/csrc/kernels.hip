@@ -105,7 +105,6 @@ static int flat_grid(int64_t n) {
 //          of a tile are read by its neighbours while their owner writes the
 //          update.  On large grids the iterate is updated every second step,
 //          by two directions at once (XU).
-// ===========================================================================
 //   MRF    the fused MINRES step of the Krylov low-level step (one RHS):
 //          the vector pass of iteration t (see k_minres) done where each
 //          node is staged, and iteration t + 1's product K y of the new
@@ -118,6 +117,7 @@ static int flat_grid(int64_t n) {
 //          write W, W2 and x, where a direction per pass takes ten accesses.
 //          FP32 256x128x128 118 -> 105 us per Krylov degree, 128x64x64 21.5 ->
 //          20.3 us; FP64 233 -> 208 and 31.7 -> 29.5 us.
+// ===========================================================================
 enum { MODE_APPLY = 0, MODE_RESID = 1, MODE_CG = 2, MODE_CGF = 3, MODE_SENSF = 4, MODE_MRF = 5, MODE_LZ = 6 };
 static_assert(MODE_LZ < kApplyModes, "a tile choice per mode");
 constexpr int kApplyMaxThreads = 512;
@@ -395,8 +395,6 @@ __device__ __forceinline__ T zmasked(unsigned m, int c, T v) {
   }
 }
 
-// A value that is the same in every lane of the wave, kept in a scalar
-// register (FP32; FP64 values stay in vector registers).
 // Wave priority around the plane loads of a z-march layer (FP32 only): the
 // loads then go out ahead of the element products of the other waves on the
 // SIMD.  Measured: FP32 fused steps 1.5-2.5% and the FP32 apply up to 2%
@@ -410,6 +408,8 @@ __device__ __forceinline__ void loads_priority(bool raise) {
   }
 }
 
+// A value that is the same in every lane of the wave, kept in a scalar
+// register (FP32; FP64 values stay in vector registers).
 template <typename T>
 __device__ __forceinline__ T wave_uniform(T v) {
   if constexpr (sizeof(T) == 4) return __builtin_bit_cast(T, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v)));
@@ -417,8 +417,9 @@ __device__ __forceinline__ T wave_uniform(T v) {
 }
 
 // Waves per SIMD the register allocation of a z-march variant must allow:
-// three for the single-RHS FP32 fused steps (at most 168 VGPRs), which run
-// many blocks per CU on large grids; the others are left to the compiler.
+// three for the FP32 fused steps (at most 168 VGPRs; they take 114 to 135),
+// which run many blocks per CU on large grids; the others are left to the
+// compiler.
 template <typename T, int MODE>
 constexpr int apply_min_waves() {
   return (sizeof(T) == 4 && (MODE == MODE_CGF || MODE == MODE_MRF)) ? 3 : 1;
@@ -427,18 +428,12 @@ constexpr int apply_min_waves() {
 // RR (fused CG step): form r.r for the tolerance test; solves of a fixed
 // step count (rtol = 0) read no r.r and run the variant without it.
 // DN (CG, CGF): values of the inverse diagonal per node.
-// XU (fused CG and MINRES steps): updates of the iterate.  1: x += alpha_k p_k.  0: none, it
-// is left to the next step; 2: x += alpha_{k-1} p_{k-1} + alpha_k p_k, with
-// p_{k-1} read from the buffer that p_{k+1} goes to, before it is stored.  The
-// operations and their order are the same; two steps read x and p_{k-1} and
-// write x once instead of reading and writing x twice, half a vector less per
-// step.
-// DN (CG, CGF): values of the inverse diagonal per node.
-// XUP (fused CG step): update the iterate.  A step without it leaves
-// x += alpha_k p_k to the next one, which reads p_k from the buffer that its own
-// p_{k+2} goes to, before storing it: two steps read x, p_k and write x once,
-// where an update per step reads and writes x twice (the same operations in
-// the same order, half a vector less per step on average).
+// XU (fused CG and MINRES steps): updates of the iterate.  1: x += alpha_k p_k;
+// 0: none, it is left to the next step; 2: x += alpha_{k-1} p_{k-1} + alpha_k
+// p_k, with p_{k-1} read from the buffer that p_{k+1} goes to, before it is
+// stored.  The operations and their order are the same; two steps read x and
+// p_{k-1} and write x once instead of reading and writing x twice, half a vector
+// less per step.
 template <typename T, int MODE, bool RR = true, int DN = 1, int XU = 1>
 __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_per_eu(apply_min_waves<T, MODE>())))
     k_apply(ApplyArgs<T> A) {
@@ -528,11 +523,12 @@ __global__ void __launch_bounds__(kApplyMaxThreads) __attribute__((amdgpu_waves_
   // (computed once; kOOR where the lane has none) and the plane's byte offset
   // in a scalar register: no vector arithmetic per access.
   // The small grids are bound by the instructions they issue: with this, the
-  // node and corner layouts above and one select per partial a layer of K u
-  // takes 240 vector instructions instead of 280 (160 of them the product)
-  // and the FP32 fused step 260 instead of 320, in 129 registers instead of
-  // 156.  K u at 256x128x128 51.5 -> 49.0 us; FP32 outer iteration 208 -> 199
-  // us at 128x64x64 and 120 -> 116 us at 64x32x32; FP64 336 -> 325 us.
+  // node and corner layouts above and one select per partial an FP32 layer of
+  // K u went from 270 to 237 vector instructions and one of the fused step from
+  // 310 to 267, in 129 registers instead of 156 (215, 250 to 257 and 114 to 121
+  // now, with the element product by strain groups).  K u at 256x128x128 51.5 ->
+  // 49.0 us; FP32 outer iteration 208 -> 199 us at 128x64x64 and 120 -> 116 us at
+  // 64x32x32; FP64 336 -> 325 us.
   const uint32_t vc1 = gcol[0] >= 0 ? (uint32_t)gcol[0] : kOOR;  // mask bytes
   const uint32_t vc3 = gcol[0] >= 0 ? (uint32_t)(3 * sizeof(T)) * (uint32_t)gcol[0] : kOOR;
   const uint32_t vx1 = has_extra && gcol[1] >= 0 ? (uint32_t)gcol[1] : kOOR;  // the far node
@@ -1669,10 +1665,14 @@ hipError_t launch_cg_sens(fbto_grid_s* g, const T* rho, const CgSet<T>& in, T* x
 }
 
 // Grids whose iterate is updated every second step: 2^19 elements and more,
-// without springs.  On smaller ones the steps are bound by latency, and two
-// kernels in turn measured slower than one (16x8x8 FP64 iteration 85.8 against
-// 84.0 us); four-load 384x192x192 iteration 13.47 -> 13.19 ms with it,
-// 128x64x64 FP64 308 -> 303 us.
+// without springs (CG).  Single and paired, in us per step:
+//   FP32 CG   64x32x32 8.43, 8.42   64^3 12.6, 12.3   128x64x64 16.9, 16.4   128^3 41.3, 39.8
+//   FP64 CG   64x32x32 10.4, 10.3   64^3 17.9, 17.4   128x64x64 26.4, 25.4   128^3 112, 106
+//   FP32 MRF  64x32x32 9.45, 9.27   64^3 14.0, 13.4   128x64x64 19.8, 18.1   128^3 48.9, 44.5
+//   FP64 MRF  64x32x32 11.1, 10.5   64^3 19.9, 18.8   128x64x64 29.4, 26.8   128^3 130, 110
+// Two kernels in turn cost nothing that these show; where the rule's line lies
+// every one of them gains 3% or more.  Below 2^16 elements CG gains nothing (-1 to
+// +2%), and a whole 16x8x8 FP64 iteration measured 2% slower.
 bool cg_pairs_updates(const fbto_grid_s* g) { return minres_pairs_updates(g) && g->n_springs == 0; }
 bool minres_pairs_updates(const fbto_grid_s* g) { return g->dim == 3 && g->geo.E >= ((int64_t)1 << 19); }
 
@@ -1788,10 +1788,13 @@ hipError_t launch_diag(fbto_grid_s* g, const T* rho, T* invD, hipStream_t st) {
 // itself, not a recurrence for it, so the residual follows f - K x as closely
 // as the textbook's.  Against the recurrence of Chronopoulos and Gear
 // (w = K z, s = w + beta s) a step carries one vector less (nine accesses
-// instead of eleven) and its FP32 iterates are 3-10 times closer to FP64's
-// after 8 and 24 steps (48x24x24 grids, CPU emulation).  The scalars are
-// reduced from the partials in every block's prologue; convergence and
-// breakdown are decided identically in every block.
+// instead of eleven).  beta's numerator is a difference of two sums, which loses
+// digits where the residual falls fast; the error against FP64 is no larger for
+// it (FP32 solves from zero to 24 steps on six grids, 8 to 16 inputs each: 0.94
+// to 1.00 times that of the other recurrence, geometric means; whole outer
+// iterations 0.92 to 1.06 times, within their spread).  The scalars are reduced
+// from the partials in every block's prologue; convergence and breakdown are
+// decided identically in every block.
 // ===========================================================================
 
 // One vector update, step k (plane grids; also the last step of a solve
@@ -1918,7 +1921,7 @@ __global__ void __launch_bounds__(kVecBlock)
 // waves meet at each barrier).
 constexpr int kFinishThreads = 256;
 
-// Reduce the final residual norms into the scalars (slots RN1, RI1 with n_r
+// Reduce the final residual norms into the scalars (slots RNF, RIF with n_r
 // partials, f.f from FN); with `info`, also write the outer-iteration record
 // (compliance from DOT, projection results, gradient mean).
 template <int NR>
@@ -2098,18 +2101,19 @@ hipError_t launch_relax_update(fbto_grid_s* g, T* u, const T* r, const T* invD, 
 // Krylov step of Alg. 3 (Eq. LSP, beta = 1): the new iterate minimises the
 // residual over u + span{r, K r, ..., K^D r}.  It is computed by the MINRES
 // recurrence (Lanczos vectors and Givens rotations, as in Paige and
-// Saunders), D + 1 iterations from u.  Iteration itn (1 .. D + 1) is one
-// CG-mode apply Y = K R2 (partials <R1, R2>, <Y, R2>) and one pass of this
-// kernel, which
+// Saunders), D + 1 iterations from u.  Iteration itn (1 .. D + 1) is a product
+// Y = K R2 (partials <R1, R2>, <Y, R2>) and a vector pass, which
 //   - reduces beta = ||R2|| (the previous pass's partials) and, from the
-//     apply's partials, alpha = <v, K v - (beta/oldb) R1> with v = R2/beta;
+//     product's partials, alpha = <v, K v - (beta/oldb) R1> with v = R2/beta;
 //   - finishes iteration itn - 1: its Givens rotation needs beta, then
 //     w = (v' - oldeps w'' - delta w') / gamma, x += damp * phi * w, where
 //     v' = R1 / oldb is that iteration's Lanczos vector;
 //   - forms the next Lanczos vector y = K v - (beta/oldb) R1 - (alpha/beta) R2
 //     into R1's buffer and leaves ||y||^2 as partials.
-// The first product (LZ mode) leaves ||R2||^2 of R2 = f - K u; pass D + 2 only
-// finishes iteration D + 1.  Every block runs the scalar recurrence on the same
+// The first product (LZ mode) leaves ||R2||^2 of R2 = f - K u.  The vector passes
+// of iterations 1 .. D are fused with the next product (k_apply's MRF mode,
+// k_plane_minres); this kernel is that of iteration D + 1 and pass D + 2, which
+// only finishes that iteration.  Every block runs the scalar recurrence on the same
 // reduced values in the same order; block 0 keeps its state for the next
 // pass.  The caller rotates the buffers: R1 <- R2, R2 <- the buffer y went
 // to, W <- the buffer w went to (W2), W2 <- W.  `damp` scales the step
@@ -2426,13 +2430,6 @@ __global__ void __launch_bounds__(kVecBlock)
   }
 }
 
-// Density filter for R <= 1: a block owns 64 x 4 element columns and four
-// layers and stages them with their halo in LDS, every load issued up front
-// (one memory latency per block, 2.3 loads per output); a thread then sums the
-// windows of its column's four outputs.  Read by each thread from memory, the
-// window took 13.5 loads per output (27 transposed, with Hsi), and the final
-// projection pass clamped each of them.  Out-of-grid neighbours are 0 (the
-// stencil is truncated at the boundary).
 // The evaluation of one search pass at lam for one entry: f(lam) and the linear
 // piece of f just right (+) and just left (-) of lam, f(l) = C - l nA (an
 // entry adds its bound to C where it is clamped, else its value to C and one
@@ -2479,6 +2476,13 @@ __device__ __forceinline__ void step_parts(double (&v3)[3], double (&ev)[kEval],
   write_parts<3 + kEval, kSeedEvalMax, NTHR>(w, dst, block, lds);
 }
 
+// Density filter for R <= 1: a block owns 64 x 4 element columns and four
+// layers and stages them with their halo in LDS, every load issued up front
+// (one memory latency per block, 2.3 loads per output); a thread then sums the
+// windows of its column's four outputs.  Read by each thread from memory, the
+// window took 13.5 loads per output (27 transposed, with Hsi), and the final
+// projection pass clamped each of them.  Out-of-grid neighbours are 0 (the
+// stencil is truncated at the boundary).
 constexpr int kFiltBX = 64, kFiltBY = 4, kFiltDZ = 4;
 
 // The gradient step fused into the plain-sum filter (the transposed filter
@@ -2933,9 +2937,9 @@ hipError_t launch_filter(fbto_grid_s* g, int kind, const T* in, T* out, int want
   return hipGetLastError();
 }
 
-// Whether the grid's filter runs as the z-march filter (voxel grid, stencil
-// of radius R <= 1, its tiles within the partial slots): the variants fused
-// with the step and with the final projection pass need it.
+// Whether the grid's filter is k_filter_z (voxel grid, stencil of radius R <= 1,
+// its tiles within the partial slots): the variants fused with the step and with
+// the final projection pass need it.
 bool zmarch_filter(const fbto_grid_s* g) {
   if (g->dim == 2) return false;
   const double r = g->desc.filter_radius;
