@@ -576,7 +576,7 @@ def main():
     bytes64 = 2 * ndof * 8 + E * 8
     bytes_fused = fused_step_bytes(ndof, E)
     achieved = bytes_fused / t_fused / 1e9
-    traffic = measured_traffic(("k_apply<float, 1, 3, false, 1, 0>", "k_apply<float, 1, 3, false, 1, 2>"),
+    traffic = measured_traffic(("k_apply<float, 3, false, 1, 0>", "k_apply<float, 3, false, 1, 2>"),
                                "outer_step_pmc.json")
     # algorithmic bytes of one outer iteration (FP32, m inner steps), kernel by kernel
     m = p.inner_steps
@@ -645,7 +645,7 @@ def main():
         "final_state": {"fp32": st32, "fp64": st64},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
-                     "kernel": "k_apply<float, 1, CGF> (fused Jacobi-PCG step, 7 of the 8 steps of an "
+                     "kernel": "k_apply<float, CGF> (fused Jacobi-PCG step, 7 of the 8 steps of an "
                                "outer iteration), algorithmic bytes 7.5*3N*4 + 5N + E*4 = "
                                f"{bytes_fused} per launch, {t_fused * 1e6:.2f} us per launch"},
         "fused_step_sizes": fsizes,
