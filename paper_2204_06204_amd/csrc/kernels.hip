@@ -2277,7 +2277,23 @@ __global__ void __launch_bounds__(kVecBlock)
 // The same for grids that fill few of the tiles' elements (see sens_staged): one
 // element per thread in the order of their numbers, its eight nodes gathered
 // through the caches.  No thread is idle on any grid, but a node is read eight
-// times.  Same operations in the same order as k_sens.
+// times.  Same operations in the same order as k_sens.  In FP64 lam is tested
+// once more, which it always passes: the branch keeps its loads behind u's share
+// of the product (2x1024x1024 47 us, without the branch 55; FP32 33.0 and 32.3).
+template <typename T>
+__device__ __forceinline__ void gather_elem(const Geo& G, const T* v, const uint8_t* mask, int ex, int ey, int ez,
+                                            T (&ue)[8][3]) {
+#pragma unroll
+  for (int a = 0; a < 8; ++a) {
+    const int n = ex + (a & 1) + G.nxn * (ey + ((a >> 1) & 1) + G.nyn * (ez + (a >> 2)));
+    const unsigned m = mask[n];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      const T x = v[3 * n + c];  // 3 N < 2^31
+      ue[a][c] = ((m >> c) & 1u) ? (T)0 : x;
+    }
+  }
+}
 template <typename T, bool LAM>
 __global__ void __launch_bounds__(kVecBlock)
     k_sens_gather(Geo G, const T* rho, const T* u, const T* lam, int nrhs, T* dobj, const uint8_t* mask, Modal<T> km,
@@ -2290,20 +2306,15 @@ __global__ void __launch_bounds__(kVecBlock)
   const int ey = row - ez * G.ny;
   double acc = 0.0;
   for (int R = 0; R < nrhs; ++R) {
-    T ue[8][3], le[8][3];
-#pragma unroll
-    for (int a = 0; a < 8; ++a) {
-      const int n = ex + (a & 1) + G.nxn * (ey + ((a >> 1) & 1) + G.nyn * (ez + (a >> 2)));
-      const unsigned m = mask[n];
-      const int64_t o = R * G.ndof + 3 * (int64_t)n;
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        ue[a][c] = zmasked(m, c, u[o + c]);
-        if constexpr (LAM) le[a][c] = zmasked(m, c, lam[o + c]);
-      }
+    T ue[8][3];
+    gather_elem<T>(G, u + R * G.ndof, mask, ex, ey, ez, ue);
+    if (LAM && (sizeof(T) == 4 || lam)) {
+      T le[8][3];
+      gather_elem<T>(G, lam + R * G.ndof, mask, ex, ey, ez, le);
+      acc += elem_bilinear<T>(le, ue, km);
+    } else {
+      acc += elem_bilinear<T>(ue, ue, km);
     }
-    if constexpr (LAM) acc += elem_bilinear<T>(le, ue, km);
-    else acc += elem_bilinear<T>(ue, ue, km);
   }
   double val = -(double)simp_ds<T>(rho[e], sp) * acc;
   if (Hsi) val *= (double)Hsi[e];
@@ -2312,15 +2323,15 @@ __global__ void __launch_bounds__(kVecBlock)
 
 // Share of the LDS tiles that a grid's elements have to fill for the staged
 // kernel to be chosen: below it, its idle threads cost more than the repeated
-// reads.  Staged against gathered, 2.2M elements: with all of the tile filled
-// (1024x1024x2) 0.83 of the time in FP32 and 0.61 in FP64, with lam 0.65 and
-// 0.54; with 0.87 to 0.93 of it (56, 60 x 195^2, 30x270x270) 1.05-0.97, 0.86-
-// 0.74, 0.79-0.74, 0.78-0.66; with 0.69 to 0.74 (22, 24, 48 x N^2) 1.22-1.16,
-// 0.93-0.90, 0.94-0.88, 0.86-0.83; with 0.56 (18, 36 x N^2) 1.46, 1.11, 1.12,
-// 1.03; with 1/32 (1x1483x1483) 19, 14, 16, 13.
+// reads.  Staged against gathered on 2.2M elements, FP32, FP64, FP32 with lam, FP64
+// with lam: all of the tiles filled (1024x1024x2) 0.83, 0.61, 0.65, 0.62 of the
+// time; 0.87 to 0.93 of them (56, 60 x N^2, 30x270x270) 1.05-0.97, 0.86-0.74,
+// 0.79-0.74, 0.89-0.75; 0.69 to 0.74 (22, 24, 48 x N^2) 1.22-1.16, 0.93-0.90,
+// 0.94-0.88, 0.98-0.94; 0.62 (20x330x330) 1.32, 1.03, 1.01, 1.09; 0.56 (18, 36 x
+// N^2) 1.46, 1.11, 1.12, 1.17; 1/32 (1x1483x1483) 19, 14, 16, 13.
 template <typename T, bool LAM>
 static bool sens_staged(const Geo& G, const dim3& grid) {
-  constexpr double min_fill = sizeof(T) == 4 ? (LAM ? 0.72 : 0.9) : (LAM ? 0.56 : 0.72);
+  constexpr double min_fill = sizeof(T) == 4 ? (LAM ? 0.72 : 0.9) : (LAM ? 0.68 : 0.72);
   return (double)G.E >= min_fill * kVecBlock * ((double)grid.x * grid.y * grid.z);
 }
 
